@@ -1602,8 +1602,7 @@ void launch_mfma_dw(const Problem &p, bool block_ap, const void *X, const void *
     if (partials) {
         ProfScope ps(PK_REDUCE, st);
         const uint32_t n_per = (uint32_t)(p.g / 32);
-        if (ds != nullptr) launch_reduce_partials(a.part_ds, ds, s, (size_t)p.O * p.G, n_per, false, st);
-        if (dz != nullptr) launch_reduce_partials(a.part_dz, dz, s, (size_t)p.O * p.G, n_per, true, st);
+        if (ds != nullptr || dz != nullptr) launch_reduce_partials(a.part_ds, a.part_dz, ds, dz, s, (size_t)p.O * p.G, n_per, st);
     }
 }
 

@@ -42,8 +42,9 @@ void launch_unpack_work(const Problem &p, const void *work, const void *clampbit
                         uint8_t *clamped, float *zbar, hipStream_t st);
 void launch_unpack(const Problem &p, const void *Wpacked, const void *zpacked, int32_t *codes, int32_t *zcodes, hipStream_t st);
 void launch_init_minmax(const Problem &p, const void *W, float *s, float *z, hipStream_t st);
-void launch_reduce_partials(const float *part, float *out, const float *s, size_t n_out, uint32_t n_per, bool scale_by_s,
-                            hipStream_t st);
+// ds / dz (each may be NULL) of n_out groups from n_per consecutive partials each; dz is scaled by -s.
+void launch_reduce_partials(const float *part_ds, const float *part_dz, float *ds, float *dz, const float *s, size_t n_out,
+                            uint32_t n_per, hipStream_t st);
 
 // ---- gemm_mfma.hip (bf16 activations) -----------------------------------------------------------
 // Scratch of the GEMM launches that cut the tiles of a partly filled last round along K: one buffer of fp32 accumulator

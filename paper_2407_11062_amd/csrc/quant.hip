@@ -396,17 +396,26 @@ __global__ __launch_bounds__(256) void k_init_minmax_wave(const InitBatch b, flo
     }
 }
 
-// out[o,j] = sum of the n_per consecutive per-32-column partials of group j, in index order;
-// `scale_by_s` multiplies by -s[o,j] (turns a sum of clamped dWhat into dz).
-__global__ __launch_bounds__(256) void k_reduce_partials(const float *__restrict__ part, float *__restrict__ out,
-                                                         const float *__restrict__ s, uint32_t n_out, uint32_t n_per,
-                                                         int scale_by_s)
+// Groups wider than a dW tile: ds / dz of group t from its n_per consecutive per-32-column partials, in one launch
+// (blockIdx.y: 0 = ds, 1 = dz).  LPG lanes share a group: each adds every LPG-th partial, an xor butterfly adds the lanes:
+// a fixed order.  One thread per group walking its partials alone left the chip with a few hundred wavefronts of serial,
+// uncoalesced loads (18 us per output at 4096 groups of 128 partials, 36 us for ds and dz; now 6 us for both).
+// `dz` (blockIdx.y = 1) is multiplied by -s[t]: the sum of the clamped dWhat becomes the gradient of the zero point.
+template <int LPG>
+__global__ __launch_bounds__(256) void k_reduce_partials(const float *__restrict__ part_ds, const float *__restrict__ part_dz,
+                                                         float *__restrict__ ds, float *__restrict__ dz,
+                                                         const float *__restrict__ s, uint32_t n_out, uint32_t n_per)
 {
-    const uint32_t t = blockIdx.x * 256u + threadIdx.x;
-    if (t >= n_out) return;
+    const bool is_dz = blockIdx.y != 0;
+    const float *__restrict__ part = is_dz ? part_dz : part_ds;
+    float *__restrict__ out = is_dz ? dz : ds;
+    const uint32_t t = blockIdx.x * (256u / LPG) + threadIdx.x / LPG, l = threadIdx.x % LPG;
+    if (out == nullptr || t >= n_out) return;         // LPG divides the wavefront: the lanes of a group leave together
     float acc = 0.0f;
-    for (uint32_t k = 0; k < n_per; ++k) acc += part[(size_t)t * n_per + k];
-    out[t] = scale_by_s ? -s[t] * acc : acc;
+    for (uint32_t k = l; k < n_per; k += LPG) acc += part[(size_t)t * n_per + k];
+#pragma unroll
+    for (int m = LPG / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m);
+    if (l == 0) out[t] = is_dz ? -s[t] * acc : acc;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -559,10 +568,14 @@ void launch_init_minmax(const Problem &p, const void *W, float *s, float *z, hip
     launch_init_minmax_batch(&j, 1, st);
 }
 
-void launch_reduce_partials(const float *part, float *out, const float *s, size_t n_out, uint32_t n_per, bool scale_by_s,
-                            hipStream_t st)
+void launch_reduce_partials(const float *part_ds, const float *part_dz, float *ds, float *dz, const float *s, size_t n_out,
+                            uint32_t n_per, hipStream_t st)
 {
-    k_reduce_partials<<<dim3(blocks_for(n_out)), dim3(256), 0, st>>>(part, out, s, (uint32_t)n_out, n_per, scale_by_s ? 1 : 0);
+    const uint32_t n = (uint32_t)n_out;
+    // a wavefront per group as soon as a group has more partials than half of one; few partials: several groups per wavefront
+#define EQAT_RED(L) k_reduce_partials<L><<<dim3(blocks_for(n_out, 256 / L), 2), dim3(256), 0, st>>>(part_ds, part_dz, ds, dz, s, n, n_per)
+    if (n_per > 32) EQAT_RED(64); else if (n_per > 8) EQAT_RED(16); else EQAT_RED(4);
+#undef EQAT_RED
 }
 
 }  // namespace eqat

@@ -194,6 +194,15 @@ def test_block_ap_bf16(tag, T, I, O, bits, g, wdt):
     check_block_ap(X, W, s, z, dY, bits, g, TOL[torch.bfloat16])
 
 
+@pytest.mark.parametrize("I,g", [(768, 96), (512, 256), (576, 288), (1024, 1024), (1056, -1), (3200, -1)],
+                         ids=lambda v: str(v))
+def test_groups_wider_than_a_tile_sum_their_partials(I, g):
+    # 3, 8, 9, 32, 33 and 100 partials of 32 columns per group: the edges of the three ways the lanes share a group
+    X, W, s, z, dY = make_case(("partials", I, g), 72, I, 40, 2, g, torch.bfloat16, torch.bfloat16)
+    check_block_ap(X, W, s, z, dY, 2, g, TOL[torch.bfloat16])
+    check_e2e_trained_z(X, W, s, z, dY, 2, g, TOL[torch.bfloat16], synth.seed_of("partials", I, g))
+
+
 # More output tiles than the chip holds workgroups: every workgroup of the fwd / dX kernel then walks several tiles with
 # its K loop running through the tile boundaries.  Ragged in every dimension, K-tile counts 5 (odd: one padding K tile
 # per output tile) and 6; the third case walks with the small (128 x 128) tile (144 big tiles = 576 small ones).
