@@ -183,9 +183,9 @@ eqat_status eqat_unpack(const eqat_desc *d, const uint8_t *Wpacked, const uint8_
 
 /*
  * E2E-QP forward (Sec. 3.3): What = (w_q - z) * s from the packed codes, Y = X * What^T.
- * With bf16 activations and at most 16 tokens (T * I * 2 <= 64 KiB) this is one memory-bound
- * matrix-vector kernel that reads the packed arrays as they are and uses no workspace (the
- * decode-time case of the paper's App. "Speedup with BitBLAS"); otherwise the tiled MFMA GEMM.
+ * With bf16 activations and up to a few dozen tokens (16 with any group that is 32, 64 or a multiple of 128 or T * I * 2
+ * <= 64 KiB, 32 or 64 depending on the size) this is one memory-bound kernel that reads the packed arrays as they are and
+ * uses no workspace (the decode-time case of the paper's App. "Speedup with BitBLAS"); otherwise the tiled MFMA GEMM.
  */
 eqat_status eqat_qlinear_fwd(const eqat_desc *d, const void *X, const uint8_t *Wpacked, const float *s,
                              const uint8_t *zpacked, void *Y, void *ws, size_t ws_bytes, void *stream);

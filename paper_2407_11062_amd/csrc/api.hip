@@ -270,6 +270,13 @@ eqat_status eqat_unpack(const eqat_desc *d, const uint8_t *Wpacked, const uint8_
 
 }  // extern "C"
 
+// Forward on codes in the working layout: the tile kernel, or for a few dozen tokens the one made for them.
+static void fwd_on_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, const eqat::SkScratch &sk, hipStream_t st)
+{
+    if (eqat::gemv_work_applies(p)) { ProfScope ps(eqat::PK_GEMV, st); eqat::launch_gemv_work(p, X, codes, sz, Y, st); }
+    else { ProfScope ps(eqat::PK_GEMM_FWD, st); eqat::launch_mfma_fwd(p, X, codes, sz, Y, sk, st); }
+}
+
 // keep: the workspace has the layout of the backward pass and is left holding what Eq.(1) produced (codes, clamp
 // bit-plane, (s, zbar) pairs), so that a backward call on the same (W, s, z) need not run Eq.(1) again.
 static eqat_status fq_fwd_any(const eqat_desc *d, const void *X, const void *W, const float *s, const float *z, void *Y,
@@ -288,7 +295,7 @@ static eqat_status fq_fwd_any(const eqat_desc *d, const void *X, const void *W, 
     if (p.act_bf16) {
         const eqat::SkScratch sk = sk_of(l, w8);
         if (!kept) { ProfScope ps(eqat::PK_QUANTIZE, st); eqat::launch_quantize(p, W, s, z, w8 + l.codes, keep ? w8 + l.clamp : nullptr, w8 + l.sz, nullptr, false, sk.counters, (uint32_t)(l.sk_ctr_bytes / 4), st); }
-        if (p.T > 0) { ProfScope ps(eqat::PK_GEMM_FWD, st); eqat::launch_mfma_fwd(p, X, w8 + l.codes, w8 + l.sz, Y, sk, st); }
+        if (p.T > 0) fwd_on_work(p, X, w8 + l.codes, w8 + l.sz, Y, sk, st);
     } else {
         { ProfScope ps(eqat::PK_F32, st); eqat::launch_f32_fwd(p, false, X, W, s, z, Y, st); }
     }
@@ -374,7 +381,7 @@ struct QOperands { const void *codes; const void *sz; eqat::SkScratch sk; float 
 static eqat_status qlinear_fwd_run(const Problem &p, const void *X, const float *s, const QOperands &q, void *Y, hipStream_t st)
 {
     if (p.T == 0) return launch_status();
-    if (p.act_bf16) { ProfScope ps(eqat::PK_GEMM_FWD, st); eqat::launch_mfma_fwd(p, X, q.codes, q.sz, Y, q.sk, st); }
+    if (p.act_bf16) fwd_on_work(p, X, q.codes, q.sz, Y, q.sk, st);
     else { ProfScope ps(eqat::PK_F32, st); eqat::launch_f32_fwd(p, true, X, q.codes, s, q.sz, Y, st); }
     return launch_status();
 }
@@ -425,7 +432,7 @@ static eqat_status qlinear_fwd_any(const eqat_desc *d, const void *X, const uint
     if (p.T == 0 && !keep) return EQAT_OK;
     hipStream_t st = (hipStream_t)stream;
     char *w8 = (char *)ws;
-    if (!keep && eqat::gemv_applies(p)) { // a few tokens: one HBM-bound kernel on the caller's own packed arrays
+    if (!keep && eqat::gemv_applies(p)) { // up to a few dozen tokens: one kernel on the caller's own packed arrays
         ProfScope ps(eqat::PK_GEMV, st);
         eqat::launch_gemv(p, X, Wpacked, s, zpacked, zfloat, Y, st);
         return launch_status();

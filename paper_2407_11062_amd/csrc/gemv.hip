@@ -1,5 +1,5 @@
 // E2E-QP forward for a handful of tokens (decode-time matrix-vector product, App. "Speedup with BitBLAS" of the paper
-// measures this shape of work):  Y[t,o] = sum_i X[t,i] * (w_q[o,i] - z[o,j]) * s[o,j],  T <= 16.
+// measures this shape of work):  Y[t,o] = sum_i X[t,i] * (w_q[o,i] - z[o,j]) * s[o,j],  T <= 64.
 //
 // HBM-bound: every weight is read once, N/8 bytes, straight from the dense packed stream of the C ABI (no re-layout
 // pass, which would triple the traffic).  One workgroup owns 16 output rows; its 4 waves split the input dimension
@@ -8,15 +8,19 @@
 // per 32-code segment (WhatTable, shared with the GEMM producer) turns codes into bf16 at about one VALU
 // instruction per weight and the multiply-adds cost nothing.
 //
-// Order of the contraction index.  A lane holds one 32-code segment of one row and feeds 8 of its codes to each of 4
-// MFMAs.  In the dense 2- and 4-bit streams, (word >> shift) & 0x03030303 / 0x0F0F0F0F leaves four codes that are 4
-// (resp. 2) apart, not consecutive, in the four bytes of a register.  MFMA does not care in which order k runs as long
-// as both operands agree, so the token rows are staged in LDS once per workgroup in exactly that order (slot_code()).
-// The dense 3-bit stream has no byte alignment at all; its codes are extracted one by one (slower, still correct).
+// Order of the contraction index.  A lane holds one 32-code segment of one row and feeds 8 consecutive codes of it to each
+// of 4 MFMAs.  In the dense 2-bit stream, (word >> 2 k) & 0x03030303 leaves the codes k, k + 4, k + 8, k + 12 of the word
+// in the four bytes of a register, and the table turns them into two registers, the pairs (k, k + 4) and (k + 8, k + 12):
+// the four first pairs are the first eight codes of the word in the order 0 4 1 5 2 6 3 7, the four second pairs the other
+// eight in the same order.  MFMA does not care in which order k runs as long as both operands agree, so the token rows
+// are staged in LDS with every eight values in that order (slot_code()), a permutation inside 16 bytes.  4-bit codes come
+// out of their converts in any order wanted, and the dense 3-bit stream, which has no byte alignment at all, is extracted
+// code by code: both keep the natural order.
 #include "common.h"
 #include "kernels.h"
 
 #include <algorithm>
+#include <atomic>
 
 namespace eqat {
 
@@ -25,16 +29,14 @@ namespace {
 // code index (0..31, within a segment) that sits in contraction slot m (0..7) of MFMA t (0..3) of the lane owning the segment
 template <int BITS> __host__ __device__ constexpr int slot_code(int t, int m)
 {
-    if (BITS == 2) return 16 * (t / 2) + 4 * (m % 4) + (2 * (t % 2) + m / 4);
-    if (BITS == 4) return 8 * t + 2 * (m % 4) + m / 4;
+    if (BITS == 2) return 8 * t + 4 * (m % 2) + m / 2;
     return 8 * t + m;
 }
 
 // inverse of slot_code: position (8 t + m) of code c in the slot order of its segment
 template <int BITS> __host__ __device__ constexpr int code_slot(int c)
 {
-    if (BITS == 2) { const int wd = c / 16, k = c % 16, p = k % 4, q = k / 4; return 8 * (2 * wd + p / 2) + 4 * (p % 2) + q; }
-    if (BITS == 4) { const int t = c / 8, k = c % 8, p = k % 2, q = k / 2; return 8 * t + 4 * p + q; }
+    if (BITS == 2) { const int k = c % 8; return c - k + 2 * (k % 4) + k / 4; }
     return c;
 }
 
@@ -52,23 +54,31 @@ static_assert(slot_maps_are_inverse<2>() && slot_maps_are_inverse<3>() && slot_m
 template <int BITS, int T4>
 __device__ __forceinline__ bf16x8 eight_of(const WhatTable<BITS> &tab, const CodeWords<BITS> &c)
 {
-    uint32_t t0, t1;
+    uintx4 u;
     if constexpr (BITS == 2) {
         const uint32_t w = c.w[T4 / 2];
-        t0 = (w >> (2 * (2 * (T4 % 2) + 0))) & 0x03030303u;
-        t1 = (w >> (2 * (2 * (T4 % 2) + 1))) & 0x03030303u;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            uint32_t d0, d1;                       // the lookup of a word is shared by its two MFMAs
+            tab.four((w >> (2 * k)) & 0x03030303u, d0, d1);
+            u[k] = T4 % 2 ? d1 : d0;
+        }
     } else if constexpr (BITS == 4) {
-        const uint32_t w = c.w[T4];
-        t0 = w & 0x0F0F0F0Fu;
-        t1 = (w >> 4) & 0x0F0F0F0Fu;
+        const uint32_t even = c.w[T4] & 0x0F0F0F0Fu, odd = (c.w[T4] >> 4) & 0x0F0F0F0Fu;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            bf16x2 p;
+            p[0] = (bf16_t)__builtin_fmaf(byte_to_float(even, k), tab.s, tab.b);
+            p[1] = (bf16_t)__builtin_fmaf(byte_to_float(odd, k), tab.s, tab.b);
+            u[k] = __builtin_bit_cast(uint32_t, p);
+        }
     } else {
-        t0 = code_at<3, 8 * T4 + 0>(c) | (code_at<3, 8 * T4 + 1>(c) << 8) | (code_at<3, 8 * T4 + 2>(c) << 16) | (code_at<3, 8 * T4 + 3>(c) << 24);
-        t1 = code_at<3, 8 * T4 + 4>(c) | (code_at<3, 8 * T4 + 5>(c) << 8) | (code_at<3, 8 * T4 + 6>(c) << 16) | (code_at<3, 8 * T4 + 7>(c) << 24);
+        const uint32_t t0 = code_at<3, 8 * T4 + 0>(c) | (code_at<3, 8 * T4 + 1>(c) << 8) | (code_at<3, 8 * T4 + 2>(c) << 16) | (code_at<3, 8 * T4 + 3>(c) << 24);
+        const uint32_t t1 = code_at<3, 8 * T4 + 4>(c) | (code_at<3, 8 * T4 + 5>(c) << 8) | (code_at<3, 8 * T4 + 6>(c) << 16) | (code_at<3, 8 * T4 + 7>(c) << 24);
+        uint32_t d0, d1;
+        tab.four(t0, d0, d1); u[0] = d0; u[1] = d1;
+        tab.four(t1, d0, d1); u[2] = d0; u[3] = d1;
     }
-    uintx4 u;
-    uint32_t d0, d1;
-    tab.four(t0, d0, d1); u[0] = d0; u[1] = d1;
-    tab.four(t1, d0, d1); u[2] = d0; u[3] = d1;
     return __builtin_bit_cast(bf16x8, u);
 }
 
@@ -77,7 +87,7 @@ struct GemvArgs {
     int T, I, O, G, g;
     uint32_t spg_magic;            // ceil(2^32 / (g/32)): group of segment sg = mulhi(sg, spg_magic), exact for sg * (g/32) < 2^32
     uint32_t w_row_bytes, z_row_words;
-    uint32_t w_bytes, s_bytes, z_bytes;
+    uint32_t x_bytes, w_bytes, s_bytes, z_bytes;
 };
 
 constexpr int kGemvRows = 16;      // output rows per workgroup (the M of the MFMA)
@@ -333,32 +343,322 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
     }
 }
 
+// More tokens (up to 64) than the kernels above stage at once.  The tokens a wave needs are those of its own run only, so
+// nothing is shared between the waves of a workgroup: each streams its piece of the token rows through a small patch of
+// LDS of its own, SUB segments of every lane group at a time, with the next piece already on its way into registers, and
+// the main loop has no barrier.  Runs are half as long as above (RS = 4 segments, 512 inputs per wave and trip): the waves
+// of a long row spread more evenly, and NB blocks of 16 tokens weigh more per run.  LDS rows are 16 bytes longer than
+// their data (the 8 lanes served together read 8 rows) and the four 16-byte chunks of a segment are XOR-permuted with the
+// lane group.
+// What bounds it: up to 16 tokens the loads of codes in flight (as above); beyond that the tokens, which every workgroup
+// of RB 16-row blocks reads out of L2 once.  Neighbouring lanes fetch neighbouring 16-byte chunks (a segment per lane, 64
+// bytes apart, ran at 16 bytes per clock and compute unit: 11008 x 4096, 64 tokens 57 -> 37 us), and two row blocks share
+// the tokens when that still leaves a workgroup for every compute unit (O >= 8192; 64 tokens, 28672 x 8192: 138 -> 96 us,
+// 8192 x 28672: 130 -> 80 us; with fewer rows one block is faster: 4096 x 11008 17 instead of 23 us at 24 tokens).
+// Measured against what these sizes took before (codes re-laid, then a 128 x 128-tile GEMM on a few compute units):
+// 8 tokens, 3 bit: 13824 x 5120 68 -> 23 us; 8 tokens, 4 bit: 4096 x 11008 127 -> 14 us; 32 tokens, 2 bit: 4096 x 4096
+// 46 -> 10 us, 28672 x 8192 109 -> 52 us; 64 tokens, 2 bit: 4096 x 4096 46 -> 16 us, 28672 x 8192 110 -> 96 us.
+// Where the weights come from: the caller's dense stream with packed or with float zero points, or the working layout with
+// (s, z) pairs that a kept workspace or a prepared layer holds.  The contraction runs in the same order for all three, so
+// the forward of a layer is bitwise the same whichever of them a call has.
+constexpr int kPackedZ = 0, kFloatZ = 1, kWorking = 2;
+
+// eight consecutive values in slot order
+template <int BITS> __device__ __forceinline__ bf16x8 slots_of(bf16x8 v)
+{
+    bf16x8 w;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) w[m] = v[slot_code<BITS>(0, m)];
+    return w;
+}
+
+constexpr int kWideRS = 4;              // segments per lane and run
+template <int NB> constexpr int kWideSub = NB >= 4 ? 1 : 2;
+template <int NB> constexpr int kWideRowBytes = 4 * kWideSub<NB> * 64 + 16;
+template <int NB> constexpr int kWideWaveBytes = NB * 16 * kWideRowBytes<NB>;
+
+template <int BITS, int SRC, int NG, int NB, int RB>
+__global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs a)
+{
+    constexpr int RS = kWideRS, SUB = kWideSub<NB>, ROWB = kWideRowBytes<NB>, WPS = SRC == kWorking ? WorkCodes<BITS>::kWords : BITS, CW = RS * WPS / 4, XC = NB * SUB * 4;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_waves = (int)(blockDim.x >> 6);
+    const int r = lane & 15, kq = lane >> 4;
+    const int n_segs = a.I >> 5, n_runs = (n_segs + 4 * RS - 1) / (4 * RS);
+    const int o0 = blockIdx.x * (RB * kGemvRows) + r;                        // this lane's row of block 0
+    unsigned char *const patch = smem_raw + wave * kWideWaveBytes<NB>;
+
+    const __amdgpu_buffer_rsrc_t rX = make_rsrc(a.X, a.x_bytes);
+    const __amdgpu_buffer_rsrc_t rW = make_rsrc(a.Wp, a.w_bytes);
+    const __amdgpu_buffer_rsrc_t rS = make_rsrc(a.s, a.s_bytes);
+    const __amdgpu_buffer_rsrc_t rZ = make_rsrc(SRC == kFloatZ ? (const void *)a.zf : (const void *)a.zp, a.z_bytes);
+
+    // Piece `sub` of run `sc`: 16-byte chunk i of this lane is number (lane + 64 i) of [token][lane group][SUB][4], so that
+    // neighbouring lanes read neighbouring chunks; tokens and segments past the end come as zeros.
+    uintx4 xr[XC];
+    auto fetch_tokens = [&](int sc, int sub) {
+#pragma unroll
+        for (int i = 0; i < XC; ++i) {
+            const int e = lane + 64 * i, n = e / (16 * SUB), part = (e / 4) % (4 * SUB);
+            const int seg = (sc * 4 + part / SUB) * RS + sub * SUB + part % SUB;
+            const uint32_t off = (n < a.T && seg < n_segs) ? ((uint32_t)n * (uint32_t)a.I + (uint32_t)(seg * 32 + (e % 4) * 8)) * 2u : kOobOffset;
+            const intx4 v = buf_load16(rX, off);
+            xr[i] = uintx4{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
+        }
+    };
+    auto stage_tokens = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_wave_barrier();              // LDS accesses of a wave complete in order
+#pragma unroll
+        for (int i = 0; i < XC; ++i) {
+            const int e = lane + 64 * i, n = e / (16 * SUB), part = (e / 4) % (4 * SUB);
+            *reinterpret_cast<bf16x8 *>(patch + n * ROWB + part * 64 + (((e % 4) ^ (part / SUB)) * 16)) = slots_of<BITS>(__builtin_bit_cast(bf16x8, xr[i]));
+        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+    };
+
+    floatx4 acc[RB][NB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[rb][b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+
+    if (wave < n_runs) fetch_tokens(wave, 0);
+    for (int sc = wave; sc < n_runs; sc += n_waves) {
+        // codes, step sizes and zero points of the run
+        const int seg0 = (sc * 4 + kq) * RS;
+        const uint32_t j0 = NG > 1 ? (uint32_t)(seg0 / RS) * NG : __umulhi((uint32_t)seg0, a.spg_magic);
+        uintx4 cq[RB][CW];
+        float sq[RB][NG], zq[RB][NG];
+        uint32_t zw[RB][2];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const int o = o0 + rb * kGemvRows;
+            const bool ok = o < a.O && seg0 < n_segs;
+            const uint32_t base = (uint32_t)o * a.w_row_bytes + (uint32_t)seg0 * (4u * WPS);
+#pragma unroll
+            for (int q = 0; q < CW; ++q) {
+                const intx4 v = buf_load16(rW, ok ? base + 16u * q : kOobOffset);
+                cq[rb][q] = uintx4{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
+            }
+            const uint32_t gi = ok ? ((uint32_t)o * (uint32_t)a.G + j0) * 4u : kOobOffset;
+            auto wide = [&](__amdgpu_buffer_rsrc_t rr, float (&dst)[NG]) {
+                if constexpr (NG == 4) {
+                    const intx4 v = buf_load16(rr, gi);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) dst[k] = __int_as_float(v[k]);
+                } else if constexpr (NG == 2) {
+                    const intx2 v = buf_load8(rr, gi);
+                    dst[0] = __int_as_float(v[0]); dst[1] = __int_as_float(v[1]);
+                } else {
+                    dst[0] = __int_as_float(buf_load4(rr, gi));
+                }
+            };
+            if constexpr (SRC == kWorking) {
+#pragma unroll
+                for (int k = 0; k < NG; ++k) {
+                    const intx2 v = buf_load8(rS, ok ? ((uint32_t)o * (uint32_t)a.G + j0 + k) * 8u : kOobOffset);
+                    sq[rb][k] = __int_as_float(v[0]); zq[rb][k] = __int_as_float(v[1]);
+                }
+            } else {
+                wide(rS, sq[rb]);
+            }
+            if constexpr (SRC == kFloatZ) {
+                wide(rZ, zq[rb]);
+            } else if constexpr (SRC == kPackedZ) {
+                const uint32_t wi = (j0 * BITS) >> 5;
+                zw[rb][0] = (uint32_t)buf_load4(rZ, ok ? ((uint32_t)o * a.z_row_words + wi) * 4u : kOobOffset);
+                zw[rb][1] = (BITS == 3) ? (uint32_t)buf_load4(rZ, ok ? ((uint32_t)o * a.z_row_words + wi + 1u) * 4u : kOobOffset) : 0u;
+            }
+        }
+        WhatTable<BITS> tab[RB];
+#pragma unroll
+        for (int sub = 0; sub < RS / SUB; ++sub) {
+            stage_tokens();
+            if (sub + 1 < RS / SUB) fetch_tokens(sc, sub + 1);
+            else fetch_tokens(sc + n_waves, 0);       // past the last run: all out of range
+#pragma unroll
+            for (int k = 0; k < SUB; ++k) {
+                const int u = sub * SUB + k;
+                constexpr int kSegsPerGroup = RS / NG;
+                bf16x8 w[RB][4];
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    if (u % kSegsPerGroup == 0) {
+                        const int gsel = u / kSegsPerGroup;
+                        float zv;
+                        if constexpr (SRC != kPackedZ) zv = zq[rb][gsel];
+                        else zv = (float)((uint32_t)((((uint64_t)zw[rb][0] | ((uint64_t)zw[rb][1] << 32)) >> ((j0 * BITS) & 31u)) >> (gsel * BITS)) & ((1u << BITS) - 1u));
+                        // a segment past the end of the row shares its loads with the next row: its weights are forced to zero
+                        tab[rb].build(seg0 + u < n_segs ? sq[rb][gsel] : 0.0f, zv);
+                    } else if (seg0 + u >= n_segs) {
+                        tab[rb].build(0.0f, 0.0f);
+                    }
+                    if constexpr (SRC == kWorking) {
+                        WorkCodes<BITS> cw;
+#pragma unroll
+                        for (int j = 0; j < WPS; ++j) cw.w[j] = cq[rb][(u * WPS + j) / 4][(u * WPS + j) % 4];
+                        w[rb][0] = slots_of<BITS>(tab[rb].template eight<0>(cw)); w[rb][1] = slots_of<BITS>(tab[rb].template eight<1>(cw));
+                        w[rb][2] = slots_of<BITS>(tab[rb].template eight<2>(cw)); w[rb][3] = slots_of<BITS>(tab[rb].template eight<3>(cw));
+                    } else {
+                        CodeWords<BITS> cw;
+#pragma unroll
+                        for (int j = 0; j < WPS; ++j) cw.w[j] = cq[rb][(u * WPS + j) / 4][(u * WPS + j) % 4];
+                        w[rb][0] = eight_of<BITS, 0>(tab[rb], cw); w[rb][1] = eight_of<BITS, 1>(tab[rb], cw);
+                        w[rb][2] = eight_of<BITS, 2>(tab[rb], cw); w[rb][3] = eight_of<BITS, 3>(tab[rb], cw);
+                    }
+                }
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const unsigned char *const row = patch + (b * 16 + r) * ROWB + (kq * SUB + k) * 64;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const bf16x8 x = *reinterpret_cast<const bf16x8 *>(row + ((t ^ kq) * 16));
+#pragma unroll
+                        for (int rb = 0; rb < RB; ++rb) acc[rb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[rb][t], x, acc[rb][b], 0, 0, 0);
+                    }
+                }
+            }
+        }
+    }
+
+    // ---- sum the waves' partial tiles (wave order) and store: consecutive outputs of a token from consecutive lanes ----
+    constexpr int ROWS = RB * kGemvRows;
+    __syncthreads();
+    float *const red = reinterpret_cast<float *>(smem_raw);                  // [waves][tokens][rows]
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) red[((wave * NB + b) * 16 + r) * ROWS + rb * kGemvRows + 4 * kq + i] = acc[rb][b][i];
+    __syncthreads();
+    for (int e = tid; e < a.T * ROWS; e += 64 * n_waves) {
+        const int n = e / ROWS, oo = blockIdx.x * ROWS + e % ROWS;
+        if (oo >= a.O) continue;
+        float v = 0.0f;
+        for (int w = 0; w < n_waves; ++w) v += red[(w * NB * 16 + n) * ROWS + e % ROWS];
+        a.Y[(size_t)n * a.O + oo] = (bf16_t)v;
+    }
+}
+
 }  // namespace
+
+// all token rows staged in LDS at once (k_gemv_run, k_gemv_any)
+static bool gemv_tokens_fit(const Problem &p) { return p.T <= 16 && (size_t)p.T * p.I * 2 <= 64 * 1024; }
+// Waves per row block of k_gemv_run: one per run of 1024 inputs when four would leave the chip short of waves.
+static int gemv_run_waves(const Problem &p)
+{
+    const int n_blocks = (int)((p.O + kGemvRows - 1) / kGemvRows), n_runs = (int)((p.I / 32 + 31) / 32);
+    const bool more = n_runs > kGemvWaves && n_blocks * kGemvWaves < 16 * 256;
+    return more ? std::min(n_runs, kGemvMaxWaves) : kGemvWaves;
+}
+// groups per run of k_gemv_wide (128 inputs of a lane); 0 = a group size it does not take
+static int wide_groups(const Problem &p) { return p.g == 32 ? 4 : p.g == 64 ? 2 : p.g % 128 == 0 ? 1 : 0; }
+
+// k_gemv_wide although the tokens would fit: from 8 tokens on the per-token rows of k_gemv_run, a multiple of 64 bytes apart, collide
+// on the LDS banks (16 tokens of 4096 inputs, 11008 rows: 12 instead of 18 us, 2 bit; at 4 tokens k_gemv_run is the faster
+// one, 10 against 12 us), and when the code lines that its waves hold half read (up to 28 waves per compute unit, 64 lanes
+// x 8 segments each) exceed the 4 MB L2 of an XCD by half, every line is fetched more than once (4 bit, 28672 x 8192, one
+// token: 90 against 51 us; 13824 x 5120, 4.4 MB: 18 against 24 us).
+static bool wide_is_faster(const Problem &p)
+{
+    if (wide_groups(p) == 0) return false;
+    const int64_t waves = std::min<int64_t>((p.O + kGemvRows - 1) / kGemvRows * gemv_run_waves(p), 28 * 256);
+    return p.T >= 8 || waves * (64 * 8 * 4 * p.bits) / 8 > (int64_t)6 << 20;
+}
+
+// 17 to 64 tokens, on every forward entry point alike (bitwise equal results).  The largest matrices are left to the tile
+// kernel above 32 tokens: 28672 x 8192, 48 tokens: 78 us against 88, 13824 x 5120: 50 against 39.
+bool gemv_work_applies(const Problem &p)
+{
+    return p.act_bf16 && wide_groups(p) != 0 && p.T > 16 && (p.T <= 32 || (p.T <= 64 && p.O * p.I <= (int64_t)1 << 27));
+}
 
 bool gemv_applies(const Problem &p)
 {
-    return p.act_bf16 && p.T >= 1 && p.T <= 16 && (size_t)p.T * p.I * 2 <= 64 * 1024;
+    return p.act_bf16 && p.T >= 1 && (gemv_tokens_fit(p) || (p.T <= 16 && wide_groups(p) != 0) || gemv_work_applies(p));
+}
+
+template <int BITS, int SRC, int NG, int NB, int RB>
+static void launch_wide_t(const GemvArgs &a, hipStream_t st)
+{
+    auto kern = k_gemv_wide<BITS, SRC, NG, NB, RB>;
+    const int n_runs = (a.I / 32 + 4 * kWideRS - 1) / (4 * kWideRS), trips = (n_runs + kGemvMaxWaves - 1) / kGemvMaxWaves;
+    const int waves = (n_runs + trips - 1) / trips;
+    const size_t smem = (size_t)waves * kWideWaveBytes<NB>;      // at least the 1 KB per wave and token block of the final sum
+    static_assert(kWideWaveBytes<NB> >= NB * RB * 1024 && kGemvMaxWaves * kWideWaveBytes<NB> <= 160 * 1024, "LDS of the final sum, of one CU");
+    // more dynamic LDS than the default limit: allowed once per instantiation and device
+    static std::atomic<uint64_t> allowed{0};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev > 63) dev = 0;
+    if (!((allowed.load(std::memory_order_relaxed) >> dev) & 1u)) {
+        (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kGemvMaxWaves * kWideWaveBytes<NB>);
+        allowed.fetch_or((uint64_t)1 << dev, std::memory_order_relaxed);
+    }
+    kern<<<dim3((unsigned)((a.O + RB * kGemvRows - 1) / (RB * kGemvRows))), dim3(64 * waves), smem, st>>>(a);
+}
+template <int BITS, int SRC>
+static void launch_wide_z(int ng, const GemvArgs &a, hipStream_t st)
+{
+    const bool two = a.O >= 2 * kGemvRows * 256;
+#define EQAT_WIDE_NB(NG)                                                                          \
+    do {                                                                                          \
+        if (a.T <= 16) launch_wide_t<BITS, SRC, NG, 1, 1>(a, st);                                 \
+        else if (a.T <= 32 && !two) launch_wide_t<BITS, SRC, NG, 2, 1>(a, st);                 \
+        else if (a.T <= 32) launch_wide_t<BITS, SRC, NG, 2, 2>(a, st);                         \
+        else if (!two) launch_wide_t<BITS, SRC, NG, 4, 1>(a, st);                              \
+        else launch_wide_t<BITS, SRC, NG, 4, 2>(a, st);                                        \
+    } while (0)
+    if (ng == 4) EQAT_WIDE_NB(4); else if (ng == 2) EQAT_WIDE_NB(2); else EQAT_WIDE_NB(1);
+#undef EQAT_WIDE_NB
+}
+template <int SRC> static void launch_wide(const Problem &p, const GemvArgs &a, hipStream_t st)
+{
+    const int ng = wide_groups(p);
+    if (p.bits == 2) launch_wide_z<2, SRC>(ng, a, st); else if (p.bits == 3) launch_wide_z<3, SRC>(ng, a, st); else launch_wide_z<4, SRC>(ng, a, st);
+}
+
+static GemvArgs gemv_args(const Problem &p, const void *X, const void *codes, const void *s, void *Y)
+{
+    GemvArgs a{};
+    a.X = (const bf16_t *)X; a.Wp = (const uint32_t *)codes; a.s = (const float *)s; a.Y = (bf16_t *)Y;
+    a.T = (int)p.T; a.I = (int)p.I; a.O = (int)p.O; a.G = (int)p.G; a.g = (int)p.g;
+    a.spg_magic = (p.g == 32) ? 0u : (uint32_t)((((uint64_t)1 << 32) + (uint64_t)(p.g / 32) - 1) / (uint64_t)(p.g / 32));
+    a.x_bytes = (uint32_t)(p.T * p.I * 2);
+    return a;
+}
+
+void launch_gemv_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, hipStream_t st)
+{
+    GemvArgs a = gemv_args(p, X, codes, sz, Y);
+    a.w_row_bytes = (uint32_t)(work_code_bytes(p) / p.O);
+    a.w_bytes = (uint32_t)work_code_bytes(p);
+    a.s_bytes = (uint32_t)(p.O * p.G * 8);
+    launch_wide<kWorking>(p, a, st);
 }
 
 void launch_gemv(const Problem &p, const void *X, const void *Wpacked, const float *s, const void *zpacked,
                  const float *zfloat, void *Y, hipStream_t st)
 {
-    GemvArgs a{};
-    a.X = (const bf16_t *)X; a.Wp = (const uint32_t *)Wpacked; a.s = s; a.zp = (const uint32_t *)zpacked; a.zf = zfloat;
-    a.Y = (bf16_t *)Y;
-    a.T = (int)p.T; a.I = (int)p.I; a.O = (int)p.O; a.G = (int)p.G; a.g = (int)p.g;
-    a.spg_magic = (p.g == 32) ? 0u : (uint32_t)((((uint64_t)1 << 32) + (uint64_t)(p.g / 32) - 1) / (uint64_t)(p.g / 32));
+    GemvArgs a = gemv_args(p, X, Wpacked, s, Y);
+    a.zp = (const uint32_t *)zpacked; a.zf = zfloat;
     a.w_row_bytes = (uint32_t)(p.I * p.bits / 8);
     a.z_row_words = (uint32_t)((p.G * p.bits + 31) / 32);
     a.w_bytes = (uint32_t)(p.O * p.I * p.bits / 8);
     a.s_bytes = (uint32_t)(p.O * p.G * 4);
     a.z_bytes = zfloat != nullptr ? a.s_bytes : (uint32_t)(p.O * a.z_row_words * 4);
+    if (!gemv_tokens_fit(p) || wide_is_faster(p)) {
+        if (zfloat != nullptr) launch_wide<kFloatZ>(p, a, st); else launch_wide<kPackedZ>(p, a, st);
+        return;
+    }
     // groups per run of 256 inputs; 0 = a group size the run kernel does not take
     const int ng = p.g == 32 ? 8 : p.g == 64 ? 4 : p.g == 128 ? 2 : (p.g % 256 == 0 ? 1 : 0);
     // a wave per run of 1024 inputs when four waves per row block would leave the chip short of waves (see k_gemv_run)
-    const int n_blocks = (int)((p.O + kGemvRows - 1) / kGemvRows), n_runs = (int)((p.I / 32 + 31) / 32);
-    const bool more_waves = ng != 0 && n_runs > kGemvWaves && n_blocks * kGemvWaves < 16 * 256;
-    const int waves = more_waves ? std::min(n_runs, kGemvMaxWaves) : kGemvWaves;
+    const int n_blocks = (int)((p.O + kGemvRows - 1) / kGemvRows), waves = ng != 0 ? gemv_run_waves(p) : kGemvWaves;
+    const bool more_waves = waves != kGemvWaves;
     const size_t red_bytes = (size_t)waves * 16 * 16 * 4;
     const size_t smem = (size_t)p.T * p.I * 2 > red_bytes ? (size_t)p.T * p.I * 2 : red_bytes;
     const dim3 grid((unsigned)n_blocks), block(64 * waves);

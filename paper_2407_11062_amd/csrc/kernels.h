@@ -71,6 +71,9 @@ bool dw_needs_partials(const Problem &p);
 
 // ---- gemv.hip (E2E-QP forward for a few tokens, straight from the dense packed stream) -----------
 bool gemv_applies(const Problem &p);
+// The same on the working layout and the (s, z) pairs, bitwise the same results: calls that hold those take it where this applies.
+bool gemv_work_applies(const Problem &p);
+void launch_gemv_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, hipStream_t st);
 // exactly one of zpacked / zfloat is not NULL
 void launch_gemv(const Problem &p, const void *X, const void *Wpacked, const float *s, const void *zpacked,
                  const float *zfloat, void *Y, hipStream_t st);

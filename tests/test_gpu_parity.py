@@ -733,3 +733,44 @@ def test_stacked_linears_equal_their_parts():
     # and against the oracle on the stack itself
     ref = oracle.fq_linear_bwd(None, npf(Wc), sc.cpu().numpy(), zc.cpu().numpy(), npf(dYc), bits, g, want=("dX",))
     assert relerr(out["dX"], ref["dX"]) <= TOL[torch.bfloat16]
+
+
+# ---------------------------------------------------------------- forward for 8 to 64 tokens
+# ends of the 16-token blocks, last runs of 512 inputs that are cut short (and shorter than a lane group), more runs than
+# waves, one and two row blocks per workgroup with a ragged last one, token rows that do not fit LDS at once
+WIDE_CASES = [
+    ("w0", 8, 4096, 40, 2, 64),
+    ("w1", 16, 1056, 24, 3, 32),
+    ("w2", 9, 5120, 48, 3, 128),
+    ("w3", 17, 544, 40, 4, 32),
+    ("w4", 32, 640, 8200, 2, 128),
+    ("w5", 33, 1152, 24, 4, -1),
+    ("w6", 64, 320, 8216, 3, 64),
+    ("w7", 64, 4736, 56, 2, 64),
+    ("w8", 1, 8192, 24576, 4, 128),
+]
+
+
+@pytest.mark.parametrize("tag,T,I,O,bits,g", WIDE_CASES)
+def test_forward_of_a_few_dozen_tokens(tag, T, I, O, bits, g):
+    X, W, s, z, dY = make_case(tag, T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
+    Xd, Wd, sd, zd = dev(X), dev(W), dev(s), dev(z)
+    Wp, zp = eq.eqat_pack(Wd, sd, zd, bits, g)
+    Wpn, zpn = Wp.cpu().numpy(), zp.cpu().numpy()
+    ref = oracle.qlinear_fwd(npf(X), Wpn, s.numpy(), zpn, bits, g)
+    Y = eq.eqat_qlinear_fwd(Xd, Wp, sd, zp, bits, g)
+    # What, a bf16 rounding of 2^-9, enters every product, and Y is rounded once more: well inside the path's bar
+    assert relerr(Y, ref) <= TOL[torch.bfloat16]
+    zf = z + synth.uniform(tuple(z.shape), -0.6, 0.6, synth.seed_of(tag, "zf"))
+    Yz = eq.eqat_qlinear_fwd_z(Xd, Wp, sd, dev(zf.contiguous()), bits, g)
+    assert relerr(Yz, oracle.qlinear_fwd_z(npf(X), Wpn, s.numpy(), zf.numpy(), bits, g)) <= TOL[torch.bfloat16]
+    if T > 16:       # every forward entry point takes the same route: bitwise
+        assert torch.equal(Y, eq.eqat_fq_linear_fwd(Xd, Wd, sd, zd, bits, g))
+        prepared = eq.eqat_qlinear_prepare(Wp, zp, I, bits, g)
+        assert torch.equal(Y, eq.eqat_qlinear_fwd_prepared(Xd, prepared, sd, O, bits, g))
+        assert torch.equal(Yz, eq.eqat_qlinear_fwd_prepared(Xd, prepared, sd, O, bits, g, z=dev(zf.contiguous())))
+    Xb = Xd.clone()
+    Xb[T // 2] = float("inf")
+    Yb = eq.eqat_qlinear_fwd(Xb, Wp, sd, zp, bits, g)
+    keep = [t for t in range(T) if t != T // 2]
+    assert torch.equal(Yb[keep], Y[keep])
