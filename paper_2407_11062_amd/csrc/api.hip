@@ -274,6 +274,7 @@ eqat_status eqat_unpack(const eqat_desc *d, const uint8_t *Wpacked, const uint8_
 static void fwd_on_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, const eqat::SkScratch &sk, hipStream_t st)
 {
     if (eqat::gemv_work_applies(p)) { ProfScope ps(eqat::PK_GEMV, st); eqat::launch_gemv_work(p, X, codes, sz, Y, st); }
+    else if (eqat::mid_applies(p)) { ProfScope ps(eqat::PK_GEMM_FWD, st); eqat::launch_mid_work(p, X, codes, sz, Y, st); }
     else { ProfScope ps(eqat::PK_GEMM_FWD, st); eqat::launch_mfma_fwd(p, X, codes, sz, Y, sk, st); }
 }
 
@@ -435,6 +436,11 @@ static eqat_status qlinear_fwd_any(const eqat_desc *d, const void *X, const uint
     if (!keep && eqat::gemv_applies(p)) { // up to a few dozen tokens: one kernel on the caller's own packed arrays
         ProfScope ps(eqat::PK_GEMV, st);
         eqat::launch_gemv(p, X, Wpacked, s, zpacked, zfloat, Y, st);
+        return launch_status();
+    }
+    if (!keep && eqat::mid_applies(p)) {
+        ProfScope ps(eqat::PK_GEMM_FWD, st);
+        eqat::launch_mid(p, X, Wpacked, s, zpacked, zfloat, Y, st);
         return launch_status();
     }
     const eqat::SkScratch sk = sk_of(l, w8);

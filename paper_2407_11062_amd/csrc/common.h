@@ -177,4 +177,54 @@ template <int BITS> struct WhatTable {
 __device__ __forceinline__ float to_float(float v) { return v; }
 __device__ __forceinline__ float to_float(bf16_t v) { return (float)v; }
 
+template <int V> struct IC { static constexpr int value = V; };       // an index as a type
+
+// ---- direct-to-LDS loads ------------------------------------------------------------------------------------
+// 16 bytes per lane from a buffer straight into LDS: lane j's bytes land at lds_wave_base + 16 j; a voffset beyond the
+// buffer writes zeros.  Issued as inline assembly on purpose: the compiler models the builtin form as a store to LDS and,
+// not being able to tell it apart from the transpose reads of the other buffer, waits for vmcnt(0) before the next LDS
+// read, which puts the whole fetch latency on the critical path of every K tile.  Nothing tracks these loads, so every
+// consumer sits behind an explicit "s_waitcnt vmcnt(0)" + barrier (the one in the main loop, and the one after it).
+struct RawRsrc { intx4 w; };
+__device__ __forceinline__ RawRsrc make_raw_rsrc(const void *p, uint32_t bytes)
+{
+    const uint64_t a = (uint64_t)p;
+    RawRsrc r;
+    r.w[0] = (int)(uint32_t)a; r.w[1] = (int)(uint32_t)((a >> 32) & 0xFFFFu); r.w[2] = (int)bytes; r.w[3] = 0x00020000;
+    return r;
+}
+// The LDS destination is a 32-bit LDS address that the caller has built from wave-uniform scalars (so that M0 costs
+// one scalar instruction instead of a 64-bit pointer computation and a v_readfirstlane per load).
+__device__ __forceinline__ uint32_t lds_addr_of(const void *p)
+{
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
+}
+__device__ __forceinline__ void load_to_lds16_at(const RawRsrc &r, uint32_t lds_addr_uniform, uint32_t voffset)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :: "s"(lds_addr_uniform), "v"(voffset), "s"(r.w) : "memory", "m0");
+}
+
+// the same with 4 bytes per lane: lane j's word lands at lds_wave_base + 4 j
+__device__ __forceinline__ void load_to_lds4_at(const RawRsrc &r, uint32_t lds_addr_uniform, uint32_t voffset)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                 :: "s"(lds_addr_uniform), "v"(voffset), "s"(r.w) : "memory", "m0");
+}
+
+// Workgroup barrier behind "everything I issued has completed".  The wait is the builtin, not assembly text, so that the
+// compiler's own wait-count bookkeeping knows that its register loads are complete here and inserts no further vmcnt
+// wait while the (untracked) direct-to-LDS loads of the next tile are in flight: such a wait counts ALL outstanding
+// loads and would stall on the tile fetch.  The empty asm statements keep the compiler from moving LDS accesses across.
+__device__ __forceinline__ void wait_all_and_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070);       // vmcnt(0) lgkmcnt(0); expcnt field at its maximum = no wait
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// s_waitcnt operand: "at most N vector-memory operations still outstanding, all LDS operations complete".
+constexpr int waitcnt_vm_lgkm0(int n) { return (n & 15) | 0x70 | ((n >> 4) << 14); }
+
 }  // namespace eqat

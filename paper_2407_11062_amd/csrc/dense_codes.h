@@ -1,0 +1,86 @@
+// Codes of the dense stream as MFMA operands: what the forward kernels that read the caller's packed arrays share.
+#pragma once
+#include "common.h"
+
+namespace eqat {
+
+// code index (0..31, within a segment) that sits in contraction slot m (0..7) of MFMA t (0..3) of the lane owning the segment
+template <int BITS> __host__ __device__ constexpr int slot_code(int t, int m)
+{
+    if (BITS == 2) return 8 * t + 4 * (m % 2) + m / 2;
+    return 8 * t + m;
+}
+
+// inverse of slot_code: position (8 t + m) of code c in the slot order of its segment
+template <int BITS> __host__ __device__ constexpr int code_slot(int c)
+{
+    if (BITS == 2) { const int k = c % 8; return c - k + 2 * (k % 4) + k / 4; }
+    return c;
+}
+
+template <int BITS> constexpr bool slot_maps_are_inverse()
+{
+    for (int c = 0; c < 32; ++c) {
+        const int sl = code_slot<BITS>(c);
+        if (sl < 0 || sl >= 32 || slot_code<BITS>(sl / 8, sl % 8) != c) return false;
+    }
+    return true;
+}
+static_assert(slot_maps_are_inverse<2>() && slot_maps_are_inverse<3>() && slot_maps_are_inverse<4>(), "slot order");
+
+// the 8 weights of MFMA t of a segment, in slot order
+template <int BITS, int T4>
+__device__ __forceinline__ bf16x8 eight_of(const WhatTable<BITS> &tab, const CodeWords<BITS> &c)
+{
+    uintx4 u;
+    if constexpr (BITS == 2) {
+        const uint32_t w = c.w[T4 / 2];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            uint32_t d0, d1;                       // the lookup of a word is shared by its two MFMAs
+            tab.four((w >> (2 * k)) & 0x03030303u, d0, d1);
+            u[k] = T4 % 2 ? d1 : d0;
+        }
+    } else if constexpr (BITS == 4) {
+        const uint32_t even = c.w[T4] & 0x0F0F0F0Fu, odd = (c.w[T4] >> 4) & 0x0F0F0F0Fu;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            bf16x2 p;
+            p[0] = (bf16_t)__builtin_fmaf(byte_to_float(even, k), tab.s, tab.b);
+            p[1] = (bf16_t)__builtin_fmaf(byte_to_float(odd, k), tab.s, tab.b);
+            u[k] = __builtin_bit_cast(uint32_t, p);
+        }
+    } else {
+        const uint32_t t0 = code_at<3, 8 * T4 + 0>(c) | (code_at<3, 8 * T4 + 1>(c) << 8) | (code_at<3, 8 * T4 + 2>(c) << 16) | (code_at<3, 8 * T4 + 3>(c) << 24);
+        const uint32_t t1 = code_at<3, 8 * T4 + 4>(c) | (code_at<3, 8 * T4 + 5>(c) << 8) | (code_at<3, 8 * T4 + 6>(c) << 16) | (code_at<3, 8 * T4 + 7>(c) << 24);
+        uint32_t d0, d1;
+        tab.four(t0, d0, d1); u[0] = d0; u[1] = d1;
+        tab.four(t1, d0, d1); u[2] = d0; u[3] = d1;
+    }
+    return __builtin_bit_cast(bf16x8, u);
+}
+
+// Where the weights come from: the caller's dense stream with packed or with float zero points, or the working layout with
+// (s, z) pairs that a kept workspace or a prepared layer holds.  The contraction runs in the same order for all three, so
+// the forward of a layer is bitwise the same whichever of them a call has.
+constexpr int kPackedZ = 0, kFloatZ = 1, kWorking = 2;
+
+// eight consecutive values in slot order
+template <int BITS> __device__ __forceinline__ bf16x8 slots_of(bf16x8 v)
+{
+    bf16x8 w;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) w[m] = v[slot_code<BITS>(0, m)];
+    return w;
+}
+
+// slot order back to eight consecutive values
+template <int BITS> __device__ __forceinline__ bf16x8 unslot_of(bf16x8 v)
+{
+    bf16x8 w;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) w[c] = v[code_slot<BITS>(c)];
+    return w;
+}
+
+}  // namespace eqat

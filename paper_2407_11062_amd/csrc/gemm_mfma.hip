@@ -176,7 +176,6 @@ __device__ __forceinline__ bool sk_item(const SkPlan &sk, int nb, int tiles_m, i
 // waits for its stores to complete, the workgroup meets, then one thread signals.
 constexpr int kAuxDeviceScope = 16;      // "sc1" of the raw buffer intrinsics on gfx940 and later
 constexpr int kSkSpinLimit = 1 << 22;    // polls of ~1 us: a bound that is never reached, so that no wave can spin for ever
-__device__ __forceinline__ void wait_all_and_barrier();
 // register r of block (i, j), whichever way a kernel keeps its accumulators
 template <int MI, int NI> __device__ __forceinline__ float acc_get(const floatx16 (&acc)[MI][NI], int i, int j, int r) { return acc[i][j][r]; }
 template <int MI, int NI> __device__ __forceinline__ float acc_get(const floatx4 (&acc)[MI][NI][4], int i, int j, int r) { return acc[i][j][r >> 2][r & 3]; }
@@ -287,7 +286,6 @@ struct GemmQArgs {
     SkPlan sk;             // which tiles, or parts of tiles, a workgroup computes
 };
 
-template <int V> struct IC { static constexpr int value = V; };
 // f(IC<0>{}), f(IC<1>{}), ..., f(IC<N - 1>{}): a loop whose index is a compile-time constant inside the body
 template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F &&f)
 {
@@ -312,43 +310,6 @@ __device__ __forceinline__ bf16x8 frag_kc_swz(const bf16_t *tile, int row0, int 
 {
     const int r = row0 + (lane & 31);
     return *reinterpret_cast<const bf16x8 *>(tile + r * 64 + kc_swz(r, kk * 2 + (lane >> 5)) * 8);
-}
-
-// 16 bytes per lane from a buffer straight into LDS: lane j's bytes land at lds_wave_base + 16 j; a voffset beyond the
-// buffer writes zeros.  Issued as inline assembly on purpose: the compiler models the builtin form as a store to LDS and,
-// not being able to tell it apart from the transpose reads of the other buffer, waits for vmcnt(0) before the next LDS
-// read, which puts the whole fetch latency on the critical path of every K tile.  Nothing tracks these loads, so every
-// consumer sits behind an explicit "s_waitcnt vmcnt(0)" + barrier (the one in the main loop, and the one after it).
-struct RawRsrc { intx4 w; };
-__device__ __forceinline__ RawRsrc make_raw_rsrc(const void *p, uint32_t bytes)
-{
-    const uint64_t a = (uint64_t)p;
-    RawRsrc r;
-    r.w[0] = (int)(uint32_t)a; r.w[1] = (int)(uint32_t)((a >> 32) & 0xFFFFu); r.w[2] = (int)bytes; r.w[3] = 0x00020000;
-    return r;
-}
-// The LDS destination is a 32-bit LDS address that the caller has built from wave-uniform scalars (so that M0 costs
-// one scalar instruction instead of a 64-bit pointer computation and a v_readfirstlane per load).
-__device__ __forceinline__ uint32_t lds_addr_of(const void *p)
-{
-    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
-}
-__device__ __forceinline__ void load_to_lds16_at(const RawRsrc &r, uint32_t lds_addr_uniform, uint32_t voffset)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :: "s"(lds_addr_uniform), "v"(voffset), "s"(r.w) : "memory", "m0");
-}
-
-// Workgroup barrier behind "everything I issued has completed".  The wait is the builtin, not assembly text, so that the
-// compiler's own wait-count bookkeeping knows that its register loads are complete here and inserts no further vmcnt
-// wait while the (untracked) direct-to-LDS loads of the next tile are in flight: such a wait counts ALL outstanding
-// loads and would stall on the tile fetch.  The empty asm statements keep the compiler from moving LDS accesses across.
-__device__ __forceinline__ void wait_all_and_barrier()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0x0070);       // vmcnt(0) lgkmcnt(0); expcnt field at its maximum = no wait
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
 }
 
 // Software pipeline of the main loop (one workgroup, K tile kt, LDS buffer kt & 1):
@@ -855,8 +816,6 @@ struct KmLoader {
     }
 };
 
-// s_waitcnt operand: "at most N vector-memory operations still outstanding, all LDS operations complete".
-constexpr int waitcnt_vm_lgkm0(int n) { return (n & 15) | 0x70 | ((n >> 4) << 14); }
 
 // CUT: the grid is as large as the chip holds at once and a workgroup works through the items that a.sk deals it: whole
 // tiles, and parts (along T) of tiles that it shares with others (see SkPlan; the accumulators of the parts meet in

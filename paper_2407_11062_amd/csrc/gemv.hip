@@ -17,6 +17,7 @@
 // out of their converts in any order wanted, and the dense 3-bit stream, which has no byte alignment at all, is extracted
 // code by code: both keep the natural order.
 #include "common.h"
+#include "dense_codes.h"
 #include "kernels.h"
 
 #include <algorithm>
@@ -25,62 +26,6 @@
 namespace eqat {
 
 namespace {
-
-// code index (0..31, within a segment) that sits in contraction slot m (0..7) of MFMA t (0..3) of the lane owning the segment
-template <int BITS> __host__ __device__ constexpr int slot_code(int t, int m)
-{
-    if (BITS == 2) return 8 * t + 4 * (m % 2) + m / 2;
-    return 8 * t + m;
-}
-
-// inverse of slot_code: position (8 t + m) of code c in the slot order of its segment
-template <int BITS> __host__ __device__ constexpr int code_slot(int c)
-{
-    if (BITS == 2) { const int k = c % 8; return c - k + 2 * (k % 4) + k / 4; }
-    return c;
-}
-
-template <int BITS> constexpr bool slot_maps_are_inverse()
-{
-    for (int c = 0; c < 32; ++c) {
-        const int sl = code_slot<BITS>(c);
-        if (sl < 0 || sl >= 32 || slot_code<BITS>(sl / 8, sl % 8) != c) return false;
-    }
-    return true;
-}
-static_assert(slot_maps_are_inverse<2>() && slot_maps_are_inverse<3>() && slot_maps_are_inverse<4>(), "slot order");
-
-// the 8 weights of MFMA t of a segment, in slot order
-template <int BITS, int T4>
-__device__ __forceinline__ bf16x8 eight_of(const WhatTable<BITS> &tab, const CodeWords<BITS> &c)
-{
-    uintx4 u;
-    if constexpr (BITS == 2) {
-        const uint32_t w = c.w[T4 / 2];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            uint32_t d0, d1;                       // the lookup of a word is shared by its two MFMAs
-            tab.four((w >> (2 * k)) & 0x03030303u, d0, d1);
-            u[k] = T4 % 2 ? d1 : d0;
-        }
-    } else if constexpr (BITS == 4) {
-        const uint32_t even = c.w[T4] & 0x0F0F0F0Fu, odd = (c.w[T4] >> 4) & 0x0F0F0F0Fu;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            bf16x2 p;
-            p[0] = (bf16_t)__builtin_fmaf(byte_to_float(even, k), tab.s, tab.b);
-            p[1] = (bf16_t)__builtin_fmaf(byte_to_float(odd, k), tab.s, tab.b);
-            u[k] = __builtin_bit_cast(uint32_t, p);
-        }
-    } else {
-        const uint32_t t0 = code_at<3, 8 * T4 + 0>(c) | (code_at<3, 8 * T4 + 1>(c) << 8) | (code_at<3, 8 * T4 + 2>(c) << 16) | (code_at<3, 8 * T4 + 3>(c) << 24);
-        const uint32_t t1 = code_at<3, 8 * T4 + 4>(c) | (code_at<3, 8 * T4 + 5>(c) << 8) | (code_at<3, 8 * T4 + 6>(c) << 16) | (code_at<3, 8 * T4 + 7>(c) << 24);
-        uint32_t d0, d1;
-        tab.four(t0, d0, d1); u[0] = d0; u[1] = d1;
-        tab.four(t1, d0, d1); u[2] = d0; u[3] = d1;
-    }
-    return __builtin_bit_cast(bf16x8, u);
-}
 
 struct GemvArgs {
     const bf16_t *X; const uint32_t *Wp; const float *s; const uint32_t *zp; const float *zf; bf16_t *Y;
@@ -358,20 +303,6 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
 // Measured against what these sizes took before (codes re-laid, then a 128 x 128-tile GEMM on a few compute units):
 // 8 tokens, 3 bit: 13824 x 5120 68 -> 23 us; 8 tokens, 4 bit: 4096 x 11008 127 -> 14 us; 32 tokens, 2 bit: 4096 x 4096
 // 46 -> 10 us, 28672 x 8192 109 -> 52 us; 64 tokens, 2 bit: 4096 x 4096 46 -> 16 us, 28672 x 8192 110 -> 96 us.
-// Where the weights come from: the caller's dense stream with packed or with float zero points, or the working layout with
-// (s, z) pairs that a kept workspace or a prepared layer holds.  The contraction runs in the same order for all three, so
-// the forward of a layer is bitwise the same whichever of them a call has.
-constexpr int kPackedZ = 0, kFloatZ = 1, kWorking = 2;
-
-// eight consecutive values in slot order
-template <int BITS> __device__ __forceinline__ bf16x8 slots_of(bf16x8 v)
-{
-    bf16x8 w;
-#pragma unroll
-    for (int m = 0; m < 8; ++m) w[m] = v[slot_code<BITS>(0, m)];
-    return w;
-}
-
 constexpr int kWideRS = 4;              // segments per lane and run
 template <int NB> constexpr int kWideSub = NB >= 4 ? 1 : 2;
 template <int NB> constexpr int kWideRowBytes = 4 * kWideSub<NB> * 64 + 16;
@@ -556,7 +487,11 @@ static int gemv_run_waves(const Problem &p)
     return more ? std::min(n_runs, kGemvMaxWaves) : kGemvWaves;
 }
 // groups per run of k_gemv_wide (128 inputs of a lane); 0 = a group size it does not take
-static int wide_groups(const Problem &p) { return p.g == 32 ? 4 : p.g == 64 ? 2 : p.g % 128 == 0 ? 1 : 0; }
+static int wide_groups(const Problem &p)
+{
+    if (p.g > 64 && !group_by_magic(p)) return 0;
+    return p.g == 32 ? 4 : p.g == 64 ? 2 : p.g % 128 == 0 ? 1 : 0;
+}
 
 // k_gemv_wide although the tokens would fit: from 8 tokens on the per-token rows of k_gemv_run, a multiple of 64 bytes apart, collide
 // on the LDS banks (16 tokens of 4096 inputs, 11008 rows: 12 instead of 18 us, 2 bit; at 4 tokens k_gemv_run is the faster
@@ -570,11 +505,13 @@ static bool wide_is_faster(const Problem &p)
     return p.T >= 8 || waves * (64 * 8 * 4 * p.bits) / 8 > (int64_t)6 << 20;
 }
 
-// 17 to 64 tokens, on every forward entry point alike (bitwise equal results).  The largest matrices are left to the tile
-// kernel above 32 tokens: 28672 x 8192, 48 tokens: 78 us against 88, 13824 x 5120: 50 against 39.
+// 17 to 64 tokens, on every forward entry point alike (bitwise equal results).  Above 32 tokens k_gemm_mid is the faster one
+// where the rows fill the chip and the contraction is short.  This kernel takes about 8 us and 0.5 us per million weights
+// there: 4096 x 4096 16 us against 25, 4096 x 11008 32 against 58; 13824 x 5120 40 against 30, 28672 x 8192 96 against 60.
 bool gemv_work_applies(const Problem &p)
 {
-    return p.act_bf16 && wide_groups(p) != 0 && p.T > 16 && (p.T <= 32 || (p.T <= 64 && p.O * p.I <= (int64_t)1 << 27));
+    if (!p.act_bf16 || wide_groups(p) == 0 || p.T <= 16 || p.T > 64) return false;
+    return p.T <= 32 || 8.0 + 0.5e-6 * (double)(p.O * p.I) <= mid_us(p);
 }
 
 bool gemv_applies(const Problem &p)

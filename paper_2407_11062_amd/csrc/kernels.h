@@ -78,6 +78,18 @@ void launch_gemv_work(const Problem &p, const void *X, const void *codes, const 
 void launch_gemv(const Problem &p, const void *X, const void *Wpacked, const float *s, const void *zpacked,
                  const float *zfloat, void *Y, hipStream_t st);
 
+// whether mulhi(segment, ceil(2^32 / (g / 32))) is the group of every segment of a row
+inline bool group_by_magic(const Problem &p) { return (p.I / 32) * (p.g / 32) < ((int64_t)1 << 32); }
+
+// ---- gemm_mid.hip (forward for some dozens to about a thousand tokens) --------------------------------------------
+bool mid_applies(const Problem &p);
+double mid_us(const Problem &p);                  // what it takes, as the rules of dispatch estimate it
+// from the caller's dense stream (exactly one of zpacked / zfloat is not NULL), or from the working layout and (s, z) pairs:
+// bitwise the same results
+void launch_mid(const Problem &p, const void *X, const void *Wpacked, const float *s, const void *zpacked, const float *zfloat,
+                void *Y, hipStream_t st);
+void launch_mid_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, hipStream_t st);
+
 // ---- train_step.hip (Block-AP step glue: reconstruction loss, AdamW over {W, s, z}) --------------------
 size_t recon_loss_ws_bytes();
 // loss[0] = mean (Y - Yref)^2, dY (may be NULL) = 2 (Y - Yref) / n; `partial` = recon_loss_ws_bytes() of scratch.

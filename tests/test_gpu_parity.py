@@ -751,6 +751,22 @@ WIDE_CASES = [
 ]
 
 
+# k_gemm_mid: one K step and a piece of one, ragged last token tiles of 64 and 96 and weight tiles, a row that ends inside a
+# 16-byte chunk of 3-bit codes, groups of 32, groups wider than a K step and not dividing it, packed zero points that
+# straddle words, two rounds of workgroups, group sizes k_gemv_wide does not take
+WIDE_CASES += [
+    ("m0", 65, 256, 136, 2, 64),
+    ("m1", 100, 1056, 200, 3, 32),
+    ("m2", 333, 544, 264, 4, 32),
+    ("m3", 70, 1440, 72, 2, 288),
+    ("m4", 129, 1152, 1000, 3, -1),
+    ("m5", 97, 352, 24584, 2, 32),
+    ("m6", 289, 3200, 11016, 4, 128),
+    ("m7", 48, 288, 2056, 3, 96),
+    ("m8", 600, 32, 40, 4, 32),
+]
+
+
 @pytest.mark.parametrize("tag,T,I,O,bits,g", WIDE_CASES)
 def test_forward_of_a_few_dozen_tokens(tag, T, I, O, bits, g):
     X, W, s, z, dY = make_case(tag, T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
