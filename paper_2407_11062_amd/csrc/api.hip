@@ -369,7 +369,7 @@ static eqat_status fq_bwd_any(const eqat_desc *d, const void *X, const void *W, 
                                  (float *)(w8 + l.part), sk, st);
     } else {
         ProfScope ps(eqat::PK_F32, st);
-        if (dX != nullptr && p.T > 0) eqat::launch_f32_dx(p, false, dY, W, s, z, dX, st);
+        if (dX != nullptr && p.T > 0) eqat::launch_f32_dx(p, false, dY, W, s, z, (float *)(w8 + l.dwhat), dX, st);
         if (want_w) eqat::launch_f32_dw(p, true, X, dY, W, s, z, (float *)(w8 + l.dwhat), dW, ds, dz, st);
     }
     return launch_status();
@@ -396,7 +396,7 @@ static eqat_status qlinear_bwd_run(const Problem &p, const void *X, const float 
         if (want_g) eqat::launch_mfma_dw(p, false, X, dY, nullptr, q.codes, nullptr, q.sz, s, nullptr, ds, dz, q.part, q.sk, st);
     } else {
         ProfScope ps(eqat::PK_F32, st);
-        if (dX != nullptr && p.T > 0) eqat::launch_f32_dx(p, true, dY, q.codes, s, q.sz, dX, st);
+        if (dX != nullptr && p.T > 0) eqat::launch_f32_dx(p, true, dY, q.codes, s, q.sz, q.dwhat, dX, st);
         if (want_g) eqat::launch_f32_dw(p, false, X, dY, q.codes, s, q.sz, q.dwhat, nullptr, ds, dz, st);
     }
     return launch_status();

@@ -1,96 +1,179 @@
-// fp32-activation path: plain LDS-tiled FMA kernels.  It exists for the small all-fp32 configuration
-// (parity to 1e-5); throughput is not its purpose.  Every quantisation decision here uses the exact
-// binary32 quotient.
+// fp32-activation path (parity to 1e-5): every product and sum in binary32, on v_mfma_f32_32x32x2_f32, and every
+// quantisation decision from the exact binary32 quotient.
+//
+// The problems are small (a 512 x 512 linear at 256 tokens is 128 tiles of 32 x 32), so what bounds them is latency: the
+// waves of a workgroup share one output tile and split the contraction in blocks of 32, operands come from global memory
+// straight into MFMA registers without LDS or a barrier, and the waves' sums meet in LDS once, in wave order.  (Before:
+// 64 x 64 tiles of scalar FMAs walked by one workgroup each, 32 of them, with an element-wise bounds check, and an epilogue of
+// one thread per group: 74 + 76 + 34 + 75 us for forward, dX, dWhat and epilogue of that linear; now 9 + 11 + 5 + 5.  2048 tokens, 2048 x 2048:
+// 1589 -> 655 us for all.)  The error against 64 bits halves: eight or four short chains of sums in the place of one long one.
+// K order: lane half h of block k0 holds k0 + 16 h + e, e = 0 .. 15, for both operands; product e multiplies k0 + e and
+// k0 + 16 + e.
 #include "common.h"
 #include "kernels.h"
 
 namespace eqat {
 
-// ---- element accessors (return 0 outside the matrix) ----------------------------------------------
-struct PlainF32 {          // M[r][c], row-major, ld = columns
-    const float *p; int rows, cols;
-    __device__ __forceinline__ float at(int r, int c) const { return (r < rows && c < cols) ? p[(size_t)r * cols + c] : 0.0f; }
+// ---- operands: 16 consecutive contraction indices k .. k + 15 of row (or column) m; zeros outside the matrix -----------
+struct RowMajorF32 {       // element (m, k) = p[m][k]
+    const float *p; int rows, cols; uint32_t bytes;
+    __device__ __forceinline__ void load(int m, int k, float (&v)[16]) const
+    {
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(p, bytes);
+        if (k + 16 <= cols) {
+            const uint32_t off = m < rows ? ((uint32_t)m * (uint32_t)cols + (uint32_t)k) * 4u : kOobOffset;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const intx4 u = buf_load16(rs, off + 16u * q);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * q + e] = __int_as_float(u[e]);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                v[e] = __int_as_float(buf_load4(rs, m < rows && k + e < cols ? ((uint32_t)m * (uint32_t)cols + (uint32_t)(k + e)) * 4u : kOobOffset));
+        }
+    }
+};
+struct ColMajorF32 {       // element (m, k) = p[k][m].  Plain loads: What of a large bf16 matrix may exceed 2 GiB here
+    const float *p; int rows, cols;                      // rows: extent of k
+    __device__ __forceinline__ void load(int m, int k, float (&v)[16]) const
+    {
+        if (m < cols && k + 16 <= rows) {
+            const float *const q = p + (size_t)k * cols + m;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = q[(size_t)e * cols];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = m < cols && k + e < rows ? p[(size_t)(k + e) * cols + m] : 0.0f;
+        }
+    }
 };
 
 template <typename WT> struct FakeQuantW {   // What[o][i] from W, s, z  (Eqs.(1),(2))
     const WT *W; const float *s, *z; int O, I, g, G; float qmax;
-    __device__ __forceinline__ float at(int o, int i) const
+    __device__ __forceinline__ float what(float w, float sv, float zb) const
     {
-        if (o >= O || i >= I) return 0.0f;
-        const int j = i / g;
-        const float sv = s[(size_t)o * G + j], zb = zbar_of(z[(size_t)o * G + j], qmax);
-        const float r = __builtin_rintf(to_float(W[(size_t)o * I + i]) / sv);
+        const float r = __builtin_rintf(w / sv);
         const float q = __builtin_fminf(__builtin_fmaxf(r + zb, 0.0f), qmax);
         return (q - zb) * sv;
+    }
+    __device__ __forceinline__ void row(int o, int i, float (&v)[16]) const     // What[o][i .. i + 15], one group
+    {
+        if (o >= O || i >= I) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = 0.0f;
+            return;
+        }
+        const size_t gi = (size_t)o * G + i / g;
+        const float sv = s[gi], zb = zbar_of(z[gi], qmax);
+        WT w[16];
+        __builtin_memcpy(w, __builtin_assume_aligned(W + (size_t)o * I + i, 16), sizeof(w));
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = what(to_float(w[e]), sv, zb);
     }
 };
 
 template <int BITS> struct PackedW {         // What[o][i] from packed codes and (s, z) pairs  (Eq.(2))
     const uint32_t *codes; const floatx2 *sz; int O, I, g, G;
-    __device__ __forceinline__ float at(int o, int i) const
+    __device__ __forceinline__ void row(int o, int i, float (&v)[16]) const     // i a multiple of 16
     {
-        if (o >= O || i >= I) return 0.0f;
+        if (o >= O || i >= I) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = 0.0f;
+            return;
+        }
         const floatx2 p = sz[(size_t)o * G + i / g];
         const uint32_t *seg = codes + ((size_t)o * I + (i & ~31)) / 32 * BITS;
-        return ((float)code_at_rt<BITS>(seg, i & 31) - p[1]) * p[0];
+        const int h = (i >> 4) & 1;
+        uint64_t bits = BITS == 2 ? seg[h] : BITS == 3 ? ((uint64_t)seg[h] | ((uint64_t)seg[h + 1] << 32)) >> (16 * h)
+                                                       : (uint64_t)seg[2 * h] | ((uint64_t)seg[2 * h + 1] << 32);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = ((float)((uint32_t)(bits >> (BITS * e)) & ((1u << BITS) - 1u)) - p[1]) * p[0];
     }
 };
+template <typename W> struct WeightRows {    // element (m, k) = What[m][k]
+    W w;
+    __device__ __forceinline__ void load(int m, int k, float (&v)[16]) const { w.row(m, k, v); }
+};
 
-// C[m][n] = sum_k A(m,k) * B(k,n);  A is read through (TRANS_A ? a.at(k,m) : a.at(m,k)),
-// B through (TRANS_B ? b.at(n,k) : b.at(k,n)).  64x64 tile, 16x16 threads, 4x4 outputs per thread.
-template <typename AccA, typename AccB, bool TRANS_A, bool TRANS_B>
-__global__ __launch_bounds__(256) void k_f32_gemm(AccA a, AccB b, float *__restrict__ C, int M, int N, int K)
+// dX contracts over the rows of What: a lane would meet another (s, z) with every element, and every tile of tokens would
+// divide again (2048 x 2048 x 2048: 820 us).  It reads the plain matrix that this kernel leaves in the scratch that
+// dWhat takes afterwards (4 + 190 us), 16 weights per thread.
+template <typename W> __global__ __launch_bounds__(256) void k_f32_what(W w, float *__restrict__ out)
 {
-    __shared__ float As[16][64 + 1];
-    __shared__ float Bs[16][64 + 1];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        for (int e = threadIdx.x; e < 16 * 64; e += 256) {
-            // consecutive threads walk the contiguous axis of each operand
-            int kk, mm;
-            if (TRANS_A) { mm = e & 63; kk = e >> 6; } else { kk = e & 15; mm = e >> 4; }
-            As[kk][mm] = (k0 + kk < K) ? (TRANS_A ? a.at(k0 + kk, m0 + mm) : a.at(m0 + mm, k0 + kk)) : 0.0f;
-            int kb, nn;
-            if (TRANS_B) { kb = e & 15; nn = e >> 4; } else { nn = e & 63; kb = e >> 6; }
-            Bs[kb][nn] = (k0 + kb < K) ? (TRANS_B ? b.at(n0 + nn, k0 + kb) : b.at(k0 + kb, n0 + nn)) : 0.0f;
-        }
-        __syncthreads();
+    const int per_row = w.I / 16;
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= (int64_t)w.O * per_row) return;
+    const int o = (int)(e / per_row), i = (int)(e - (int64_t)o * per_row) * 16;
+    float v[16];
+    w.row(o, i, v);
+    floatx4 *const dst = reinterpret_cast<floatx4 *>(out + (size_t)o * w.I + i);
 #pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float av[4], bv[4];
+    for (int q = 0; q < 4; ++q) dst[q] = floatx4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+}
+
+// C[m][n] = sum_k A(m,k) * B(n,k).  A wave's tile is 32 MB x 32 NB; the NW waves of a workgroup take every NW-th block of
+// 32 of the contraction.
+template <typename OpA, typename OpB, int MB, int NB, int NW>
+__global__ __launch_bounds__(64 * NW) void k_f32_gemm(OpA a, OpB b, float *__restrict__ C, int M, int N, int K)
+{
+    __shared__ float red[NW][32][33];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31, h = lane >> 5;
+    const int m0 = blockIdx.y * (32 * MB), n0 = blockIdx.x * (32 * NB);
+    floatx16 acc[MB][NB];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { av[i] = As[kk][ty * 4 + i]; bv[i] = Bs[kk][tx * 4 + i]; }
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fmaf(av[i], bv[j], acc[i][j]);
-        }
-        __syncthreads();
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+    for (int k0 = wave * 32; k0 < K; k0 += 32 * NW) {
+        float va[MB][16], vb[NB][16];
+#pragma unroll
+        for (int i = 0; i < MB; ++i) a.load(m0 + 32 * i + r, k0 + 16 * h, va[i]);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) b.load(n0 + 32 * j + r, k0 + 16 * h, vb[j]);
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i][e], vb[j][e], acc[i][j], 0, 0, 0);
     }
+    // acc[..][e] of a lane: row 8 (e / 4) + 4 h + e % 4, column r of the block
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-            if (m < M && n < N) C[(size_t)m * N + n] = acc[i][j];
+        for (int j = 0; j < NB; ++j) {
+            if (i + j > 0) __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 16; ++e) red[wave][8 * (e >> 2) + 4 * h + (e & 3)][r] = acc[i][j][e];
+            __syncthreads();
+            for (int e = threadIdx.x; e < 1024; e += 64 * NW) {
+                const int m = e >> 5, n = e & 31;
+                float v = 0.0f;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) v += red[w][m][n];
+                if (m0 + 32 * i + m < M && n0 + 32 * j + n < N) C[(size_t)(m0 + 32 * i + m) * N + n0 + 32 * j + n] = v;
+            }
         }
 }
 
-// Per-group epilogue of the Block-AP backward (Eqs.(3)-(5)): one thread per (o, j).
+// Per-group epilogue of the Block-AP backward (Eqs.(3)-(5)): 32 lanes per group (o, j), consecutive in-features on
+// consecutive lanes.
 template <typename WT>
 __global__ __launch_bounds__(256) void k_f32_epilogue_block_ap(const float *__restrict__ dwhat, const WT *__restrict__ W,
                                                                const float *__restrict__ s, const float *__restrict__ z,
                                                                WT *__restrict__ dW, float *__restrict__ ds, float *__restrict__ dz,
                                                                int O, int I, int g, int G, float qmax)
 {
-    const int t = blockIdx.x * 256 + threadIdx.x;
+    const int t = blockIdx.x * 8 + (threadIdx.x >> 5);
     if (t >= O * G) return;
     const int o = t / G, j = t - o * G;
     const float sv = s[t], zb = zbar_of(z[t], qmax);
     float gs = 0.0f, gz = 0.0f;
-    for (int i = j * g; i < (j + 1) * g; ++i) {
+    for (int i = j * g + (threadIdx.x & 31); i < (j + 1) * g; i += 32) {
         const size_t e = (size_t)o * I + i;
         const float d = dwhat[e];
         const float tq = to_float(W[e]) / sv;
@@ -103,6 +186,8 @@ __global__ __launch_bounds__(256) void k_f32_epilogue_block_ap(const float *__re
         gs = __builtin_fmaf(d, cs, gs);
         if (dW != nullptr) dW[e] = (WT)(d * cw);
     }
+    for (int k = 16; k >= 1; k >>= 1) { gs += __shfl_xor(gs, k, 32); gz += __shfl_xor(gz, k, 32); }
+    if ((threadIdx.x & 31) != 0) return;
     if (ds != nullptr) ds[t] = gs;
     if (dz != nullptr) dz[t] = -sv * gz;
 }
@@ -112,60 +197,69 @@ __global__ __launch_bounds__(256) void k_f32_epilogue_e2e(const float *__restric
                                                           const floatx2 *__restrict__ sz, float *__restrict__ ds,
                                                           float *__restrict__ dz, int O, int I, int g, int G)
 {
-    const int t = blockIdx.x * 256 + threadIdx.x;
+    const int t = blockIdx.x * 8 + (threadIdx.x >> 5);
     if (t >= O * G) return;
     const int o = t / G, j = t - o * G;
     const float zq = sz[t][1];
     float gs = 0.0f, gz = 0.0f;
-    for (int i = j * g; i < (j + 1) * g; ++i) {
+    for (int i = j * g + (threadIdx.x & 31); i < (j + 1) * g; i += 32) {
         const size_t e = (size_t)o * I + i;
         const uint32_t *seg = codes + (e & ~(size_t)31) / 32 * BITS;
         gs = __builtin_fmaf(dwhat[e], (float)code_at_rt<BITS>(seg, i & 31) - zq, gs);
         gz += dwhat[e];
     }
+    for (int k = 16; k >= 1; k >>= 1) { gs += __shfl_xor(gs, k, 32); gz += __shfl_xor(gz, k, 32); }
+    if ((threadIdx.x & 31) != 0) return;
     if (ds != nullptr) ds[t] = gs;
     if (dz != nullptr) dz[t] = -sz[t][0] * gz;
 }
 
 // ---- host ------------------------------------------------------------------------------------------
-template <typename AccA, typename AccB, bool TA, bool TB>
-static void gemm(AccA a, AccB b, float *C, int M, int N, int K, hipStream_t st)
+template <typename OpA, typename OpB>
+static void gemm(OpA a, OpB b, float *C, int M, int N, int K, hipStream_t st)
 {
     if (M <= 0 || N <= 0) return;
-    const dim3 grid((N + 63) / 64, (M + 63) / 64), block(256);
-    k_f32_gemm<AccA, AccB, TA, TB><<<grid, block, 0, st>>>(a, b, C, M, N, K);
+    // 64 x 64 per wave reads half as much per product; 32 x 32 until that still gives every compute unit a workgroup
+    const int64_t big = ((M + 63) / 64) * (int64_t)((N + 63) / 64);
+    if (big >= 256) k_f32_gemm<OpA, OpB, 2, 2, 4><<<dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, st>>>(a, b, C, M, N, K);
+    else k_f32_gemm<OpA, OpB, 1, 1, 8><<<dim3((N + 31) / 32, (M + 31) / 32), dim3(512), 0, st>>>(a, b, C, M, N, K);
 }
+static RowMajorF32 rows_of(const void *p, int rows, int cols) { return RowMajorF32{(const float *)p, rows, cols, (uint32_t)((size_t)rows * cols * 4)}; }
+static ColMajorF32 cols_of(const void *p, int rows, int cols) { return ColMajorF32{(const float *)p, rows, cols}; }
 
-template <bool DX, typename AccW>
-static void fwd_or_dx(const Problem &p, const void *A, AccW w, void *out, hipStream_t st)
+// scratch NULL: the forward
+template <typename AccW>
+static void fwd_or_dx(const Problem &p, const void *A, AccW w, void *out, float *scratch, hipStream_t st)
 {
-    if (!DX) gemm<PlainF32, AccW, false, true>(PlainF32{(const float *)A, (int)p.T, (int)p.I}, w, (float *)out, (int)p.T, (int)p.O, (int)p.I, st);
-    else     gemm<PlainF32, AccW, false, false>(PlainF32{(const float *)A, (int)p.T, (int)p.O}, w, (float *)out, (int)p.T, (int)p.I, (int)p.O, st);
+    const int T = (int)p.T, I = (int)p.I, O = (int)p.O;
+    if (scratch == nullptr) { gemm(rows_of(A, T, I), WeightRows<AccW>{w}, (float *)out, T, O, I, st); return; }
+    k_f32_what<AccW><<<dim3((unsigned)(((int64_t)O * (I / 16) + 255) / 256)), dim3(256), 0, st>>>(w, scratch);
+    gemm(rows_of(A, T, O), ColMajorF32{scratch, O, I}, (float *)out, T, I, O, st);
 }
 
-template <bool DX>
-static void dispatch_w(const Problem &p, bool packed, const void *A, const void *Wc, const float *s, const void *zsz, void *out, hipStream_t st)
+static void dispatch_w(const Problem &p, bool packed, const void *A, const void *Wc, const float *s, const void *zsz, void *out,
+                       float *scratch, hipStream_t st)
 {
     const int O = (int)p.O, I = (int)p.I, g = (int)p.g, G = (int)p.G;
     if (packed) {
         const uint32_t *c = (const uint32_t *)Wc; const floatx2 *sz = (const floatx2 *)zsz;
-        if (p.bits == 2) fwd_or_dx<DX>(p, A, PackedW<2>{c, sz, O, I, g, G}, out, st);
-        else if (p.bits == 3) fwd_or_dx<DX>(p, A, PackedW<3>{c, sz, O, I, g, G}, out, st);
-        else fwd_or_dx<DX>(p, A, PackedW<4>{c, sz, O, I, g, G}, out, st);
+        if (p.bits == 2) fwd_or_dx(p, A, PackedW<2>{c, sz, O, I, g, G}, out, scratch, st);
+        else if (p.bits == 3) fwd_or_dx(p, A, PackedW<3>{c, sz, O, I, g, G}, out, scratch, st);
+        else fwd_or_dx(p, A, PackedW<4>{c, sz, O, I, g, G}, out, scratch, st);
     } else {
         const float qmax = (float)((1 << p.bits) - 1);
-        if (p.w_bf16) fwd_or_dx<DX>(p, A, FakeQuantW<bf16_t>{(const bf16_t *)Wc, s, (const float *)zsz, O, I, g, G, qmax}, out, st);
-        else fwd_or_dx<DX>(p, A, FakeQuantW<float>{(const float *)Wc, s, (const float *)zsz, O, I, g, G, qmax}, out, st);
+        if (p.w_bf16) fwd_or_dx(p, A, FakeQuantW<bf16_t>{(const bf16_t *)Wc, s, (const float *)zsz, O, I, g, G, qmax}, out, scratch, st);
+        else fwd_or_dx(p, A, FakeQuantW<float>{(const float *)Wc, s, (const float *)zsz, O, I, g, G, qmax}, out, scratch, st);
     }
 }
 
 void launch_f32_fwd(const Problem &p, bool packed, const void *X, const void *Wc, const float *s, const void *zsz, void *Y, hipStream_t st)
 {
-    dispatch_w<false>(p, packed, X, Wc, s, zsz, Y, st);
+    dispatch_w(p, packed, X, Wc, s, zsz, Y, nullptr, st);
 }
-void launch_f32_dx(const Problem &p, bool packed, const void *dY, const void *Wc, const float *s, const void *zsz, void *dX, hipStream_t st)
+void launch_f32_dx(const Problem &p, bool packed, const void *dY, const void *Wc, const float *s, const void *zsz, float *what, void *dX, hipStream_t st)
 {
-    dispatch_w<true>(p, packed, dY, Wc, s, zsz, dX, st);
+    dispatch_w(p, packed, dY, Wc, s, zsz, dX, what, st);
 }
 
 void launch_f32_dw(const Problem &p, bool block_ap, const void *X, const void *dY, const void *Wc, const float *s,
@@ -173,8 +267,8 @@ void launch_f32_dw(const Problem &p, bool block_ap, const void *X, const void *d
 {
     const int O = (int)p.O, I = (int)p.I, g = (int)p.g, G = (int)p.G, T = (int)p.T;
     // dWhat[o][i] = sum_t dY[t][o] * X[t][i]
-    gemm<PlainF32, PlainF32, true, false>(PlainF32{(const float *)dY, T, O}, PlainF32{(const float *)X, T, I}, dwhat, O, I, T, st);
-    const dim3 grid((unsigned)(((size_t)O * G + 255) / 256)), block(256);
+    gemm(cols_of(dY, T, O), cols_of(X, T, I), dwhat, O, I, T, st);
+    const dim3 grid((unsigned)(((size_t)O * G + 7) / 8)), block(256);
     if (block_ap) {
         const float qmax = (float)((1 << p.bits) - 1);
         if (p.w_bf16) k_f32_epilogue_block_ap<bf16_t><<<grid, block, 0, st>>>(dwhat, (const bf16_t *)Wc, s, (const float *)zsz, (bf16_t *)dW, ds, dz, O, I, g, G, qmax);

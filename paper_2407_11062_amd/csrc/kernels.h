@@ -105,11 +105,12 @@ struct AdamGroup {                      // one parameter tensor; p == NULL: abse
 // One launch over three parameter groups (weights, step sizes, zero points); step counts from 1.
 void launch_adamw(const AdamGroup *groups, float beta1, float beta2, float eps, int step, hipStream_t st);
 
-// ---- gemm_f32.hip (fp32 activations; simple tiled FMA kernels, exact division everywhere) --------
+// ---- gemm_f32.hip (fp32 activations; binary32 products and sums, exact division everywhere) --------
 void launch_f32_fwd(const Problem &p, bool packed, const void *X, const void *W_or_codes, const float *s, const void *z_or_sz,
                     void *Y, hipStream_t st);
+// `what` is scratch for O*I floats (dWhat's)
 void launch_f32_dx(const Problem &p, bool packed, const void *dY, const void *W_or_codes, const float *s, const void *z_or_sz,
-                   void *dX, hipStream_t st);
+                   float *what, void *dX, hipStream_t st);
 // dWhat[O,I] fp32 = dY^T X into `dwhat` (scratch O*I floats), then the per-group epilogue.
 void launch_f32_dw(const Problem &p, bool block_ap, const void *X, const void *dY, const void *W_or_codes, const float *s,
                    const void *z_or_sz, float *dwhat, void *dW, float *ds, float *dz, hipStream_t st);

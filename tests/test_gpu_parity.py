@@ -790,3 +790,18 @@ def test_forward_of_a_few_dozen_tokens(tag, T, I, O, bits, g):
     Yb = eq.eqat_qlinear_fwd(Xb, Wp, sd, zp, bits, g)
     keep = [t for t in range(T) if t != T // 2]
     assert torch.equal(Yb[keep], Y[keep])
+
+
+# fp32 activations: 32 x 32 tiles with ragged edges and contraction ends (tokens, O and I as the contraction, O odd so that rows
+# are only 4-byte aligned), fewer contraction blocks than waves, 64 x 64 tiles with ragged last ones, groups wider than a block
+@pytest.mark.parametrize("tag,T,I,O,bits,g,wdt", [
+    ("f0", 1, 32, 1, 2, 32, torch.float32),
+    ("f1", 33, 288, 65, 3, 96, torch.bfloat16),
+    ("f2", 1037, 1056, 1043, 4, 32, torch.float32),
+    ("f3", 95, 640, 2040, 2, -1, torch.bfloat16),
+])
+def test_fp32_activation_path_at_its_edges(tag, T, I, O, bits, g, wdt):
+    X, W, s, z, dY = make_case(tag, T, I, O, bits, g, torch.float32, wdt)
+    check_block_ap(X, W, s, z, dY, bits, g, TOL[torch.float32] if wdt == torch.float32 else TOL[torch.bfloat16])
+    check_e2e(X, W, s, z, dY, bits, g, TOL[torch.float32])
+    check_e2e_trained_z(X, W, s, z, dY, bits, g, TOL[torch.float32], synth.seed_of(tag, "zdrift"))
