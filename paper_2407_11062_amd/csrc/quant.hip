@@ -110,9 +110,12 @@ constexpr size_t kPackLargeChunks = (size_t)1 << 24;     // 8-weight chunks: 134
 template <typename WT, int BITS, bool CLAMPBITS, bool WORK, int U = kQuantUnroll>
 __global__ __launch_bounds__(256) void k_quantize(const QuantizeBatch batch)
 {
-    const int slot = batch_slot(batch.first, blockIdx.x);
+    // Packing walks its matrices from the last weight to the first: the pass that comes before it (min/max, an optimizer
+    // step) leaves the end of W in the 256 MB memory-side cache, not the beginning.
+    const uint32_t bid = WORK ? blockIdx.x : gridDim.x - 1u - blockIdx.x;
+    const int slot = batch_slot(batch.first, bid);
     const QuantizeArgs &a = batch.a[slot];
-    const uint32_t block = blockIdx.x - batch.first[slot];
+    const uint32_t block = bid - batch.first[slot];
     if (a.zero_words != nullptr) clear_words(a.zero_words, a.n_zero, block, batch.first[slot + 1] - batch.first[slot]);
     if (block >= a.n_quant_blocks) {
         const uint32_t t = (block - a.n_quant_blocks) * 256u + threadIdx.x;
