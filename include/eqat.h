@@ -183,9 +183,10 @@ eqat_status eqat_unpack(const eqat_desc *d, const uint8_t *Wpacked, const uint8_
 
 /*
  * E2E-QP forward (Sec. 3.3): What = (w_q - z) * s from the packed codes, Y = X * What^T.
- * With bf16 activations and up to a few dozen tokens (16 with any group that is 32, 64 or a multiple of 128 or T * I * 2
- * <= 64 KiB, 32 or 64 depending on the size) this is one memory-bound kernel that reads the packed arrays as they are and
- * uses no workspace (the decode-time case of the paper's App. "Speedup with BitBLAS"); otherwise the tiled MFMA GEMM.
+ * With bf16 activations the packed arrays are read as they are, by one kernel and without the workspace, up to some hundred
+ * tokens: up to 16 (any group that is 32, 64 or a multiple of 128, else while T * I * 2 <= 64 KiB) and for some dozens by a
+ * memory-bound matrix-vector kernel (the decode-time case of the paper's App. "Speedup with BitBLAS"), beyond by a GEMM
+ * made for few tiles, where it is the faster one; otherwise the codes are re-laid and the tiled MFMA GEMM runs.
  */
 eqat_status eqat_qlinear_fwd(const eqat_desc *d, const void *X, const uint8_t *Wpacked, const float *s,
                              const uint8_t *zpacked, void *Y, void *ws, size_t ws_bytes, void *stream);
@@ -202,7 +203,8 @@ eqat_status eqat_qlinear_bwd(const eqat_desc *d, const void *X, const uint8_t *W
 /*
  * The E2E-QP pair for a training step that runs forward and backward on unchanged (Wpacked, s, zpacked): the forward
  * leaves the codes in the library's working layout and the (s, z) pairs in the workspace, the backward uses them.
- * Both take a workspace of EQAT_OP_Q_BWD size; the forward always runs the tiled GEMM (no few-token kernel).
+ * Both take a workspace of EQAT_OP_Q_BWD size; the forward never takes the
+ * kernel for up to 16 tokens.
  * Precondition of _bwd_kept (not checked): `ws` untouched since eqat_qlinear_fwd_keep ran on the same descriptor (any
  * token count), Wpacked, s and zpacked.  Results are bitwise those of eqat_qlinear_fwd (more than 16 tokens) /
  * eqat_qlinear_bwd.
@@ -227,7 +229,8 @@ eqat_status eqat_qlinear_bwd_kept(const eqat_desc *d, const void *X, const uint8
  *                          float array z [O,G] given, as eqat_qlinear_fwd_z / eqat_qlinear_bwd_z.  z NULL: the zero
  *                          points the layer was prepared with.  dz = -s * group-sum (dY^T X) may be asked for either way.
  *                          Workspace of EQAT_OP_QP_FWD / EQAT_OP_QP_BWD size (the pairs; no room for codes).
- *                          The tiled GEMM always runs (no few-token kernel).  The prepared layer is only read, except for
+ *                          The kernel for up to 16 tokens is not taken (there the results agree to
+ *                          rounding).  The prepared layer is only read, except for
  *                          a few counters inside it that a launch uses and leaves at zero: calls on the same prepared
  *                          layer must not overlap in time (different streams need their own copy).
  *   eqat_qlinear_fwd_prepared_keep / eqat_qlinear_bwd_prepared_kept

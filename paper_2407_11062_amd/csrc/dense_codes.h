@@ -28,6 +28,20 @@ template <int BITS> constexpr bool slot_maps_are_inverse()
 }
 static_assert(slot_maps_are_inverse<2>() && slot_maps_are_inverse<3>() && slot_maps_are_inverse<4>(), "slot order");
 
+// twelve bits, i.e. four codes, of a 3-bit segment from bit BIT on
+template <int BIT> __device__ __forceinline__ uint32_t twelve_at(const CodeWords<3> &c)
+{
+    constexpr int wi = BIT / 32, sh = BIT % 32;
+    if constexpr (sh <= 20) return (c.w[wi] >> sh) & 0xFFFu;
+    else return __builtin_amdgcn_alignbit(c.w[wi + 1], c.w[wi], sh) & 0xFFFu;
+}
+// four 3-bit codes to the four bytes of a register
+__device__ __forceinline__ uint32_t spread_3bit(uint32_t x)
+{
+    const uint32_t pairs = (x | (x << 10)) & 0x003F003Fu;
+    return (pairs | (pairs << 5)) & 0x07070707u;
+}
+
 // the 8 weights of MFMA t of a segment, in slot order
 template <int BITS, int T4>
 __device__ __forceinline__ bf16x8 eight_of(const WhatTable<BITS> &tab, const CodeWords<BITS> &c)
@@ -51,8 +65,9 @@ __device__ __forceinline__ bf16x8 eight_of(const WhatTable<BITS> &tab, const Cod
             u[k] = __builtin_bit_cast(uint32_t, p);
         }
     } else {
-        const uint32_t t0 = code_at<3, 8 * T4 + 0>(c) | (code_at<3, 8 * T4 + 1>(c) << 8) | (code_at<3, 8 * T4 + 2>(c) << 16) | (code_at<3, 8 * T4 + 3>(c) << 24);
-        const uint32_t t1 = code_at<3, 8 * T4 + 4>(c) | (code_at<3, 8 * T4 + 5>(c) << 8) | (code_at<3, 8 * T4 + 6>(c) << 16) | (code_at<3, 8 * T4 + 7>(c) << 24);
+        // four codes are 12 bits: pairs to the halves of a register, then codes to its bytes, five instructions in the place of
+        // a field extract and an insert per code (one token, 3 bit: 5120 x 13824 18.3 -> 15.6 us, 28672 x 8192 31 -> 27 us)
+        const uint32_t t0 = spread_3bit(twelve_at<24 * T4>(c)), t1 = spread_3bit(twelve_at<24 * T4 + 12>(c));
         uint32_t d0, d1;
         tab.four(t0, d0, d1); u[0] = d0; u[1] = d1;
         tab.four(t1, d0, d1); u[2] = d0; u[3] = d1;

@@ -14,8 +14,8 @@
 // the four first pairs are the first eight codes of the word in the order 0 4 1 5 2 6 3 7, the four second pairs the other
 // eight in the same order.  MFMA does not care in which order k runs as long as both operands agree, so the token rows
 // are staged in LDS with every eight values in that order (slot_code()), a permutation inside 16 bytes.  4-bit codes come
-// out of their converts in any order wanted, and the dense 3-bit stream, which has no byte alignment at all, is extracted
-// code by code: both keep the natural order.
+// out of their converts in any order wanted, and the dense 3-bit stream, which has no byte alignment at all, is taken twelve
+// bits at a time (spread_3bit): both keep the natural order.
 #include "common.h"
 #include "dense_codes.h"
 #include "kernels.h"
@@ -290,9 +290,9 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
 
 // More tokens (up to 64) than the kernels above stage at once.  The tokens a wave needs are those of its own run only, so
 // nothing is shared between the waves of a workgroup: each streams its piece of the token rows through a small patch of
-// LDS of its own, SUB segments of every lane group at a time, with the next piece already on its way into registers, and
-// the main loop has no barrier.  Runs are half as long as above (RS = 4 segments, 512 inputs per wave and trip): the waves
-// of a long row spread more evenly, and NB blocks of 16 tokens weigh more per run.  LDS rows are 16 bytes longer than
+// LDS of its own, SUB segments of every lane group at a time (the whole run with up to 8 tokens), with the next piece already
+// on its way into registers, and the main loop has no barrier.  Runs are half as long as above (RS = 4 segments, 512 inputs per wave and trip): the waves
+// of a long row spread more evenly, and the tokens weigh more per run.  LDS rows are 16 bytes longer than
 // their data (the 8 lanes served together read 8 rows) and the four 16-byte chunks of a segment are XOR-permuted with the
 // lane group.
 // What bounds it: up to 16 tokens the loads of codes in flight (as above); beyond that the tokens, which every workgroup
@@ -301,24 +301,24 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
 // the tokens when that still leaves a workgroup for every compute unit (O >= 8192; 64 tokens, 28672 x 8192: 138 -> 96 us,
 // 8192 x 28672: 130 -> 80 us; with fewer rows one block is faster: 4096 x 11008 17 instead of 23 us at 24 tokens).
 // Measured against what these sizes took before (codes re-laid, then a 128 x 128-tile GEMM on a few compute units):
-// 8 tokens, 3 bit: 13824 x 5120 68 -> 23 us; 8 tokens, 4 bit: 4096 x 11008 127 -> 14 us; 32 tokens, 2 bit: 4096 x 4096
+// 8 tokens, 3 bit: 13824 x 5120 68 -> 16 us; 8 tokens, 4 bit: 4096 x 11008 127 -> 14 us; 32 tokens, 2 bit: 4096 x 4096
 // 46 -> 10 us, 28672 x 8192 109 -> 52 us; 64 tokens, 2 bit: 4096 x 4096 46 -> 16 us, 28672 x 8192 110 -> 96 us.
 constexpr int kWideRS = 4;              // segments per lane and run
-template <int NB> constexpr int kWideSub = NB >= 4 ? 1 : 2;
-template <int NB> constexpr int kWideRowBytes = 4 * kWideSub<NB> * 64 + 16;
-template <int NB> constexpr int kWideWaveBytes = NB * 16 * kWideRowBytes<NB>;
+template <int TR> constexpr int kWideSub = TR >= 64 ? 1 : TR >= 16 ? 2 : 4;              // TR: token rows of the patch
+template <int TR> constexpr int kWideRowBytes = 4 * kWideSub<TR> * 64 + 16;
+template <int TR> constexpr int kWideWaveBytes = TR * kWideRowBytes<TR>;
 
-template <int BITS, int SRC, int NG, int NB, int RB>
+template <int BITS, int SRC, int NG, int TR, int RB>
 __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs a)
 {
-    constexpr int RS = kWideRS, SUB = kWideSub<NB>, ROWB = kWideRowBytes<NB>, WPS = SRC == kWorking ? WorkCodes<BITS>::kWords : BITS, CW = RS * WPS / 4, XC = NB * SUB * 4;
+    constexpr int RS = kWideRS, SUB = kWideSub<TR>, ROWB = kWideRowBytes<TR>, NB = (TR + 15) / 16, WPS = SRC == kWorking ? WorkCodes<BITS>::kWords : BITS, CW = RS * WPS / 4, XC = TR * SUB / 4;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_waves = (int)(blockDim.x >> 6);
     const int r = lane & 15, kq = lane >> 4;
     const int n_segs = a.I >> 5, n_runs = (n_segs + 4 * RS - 1) / (4 * RS);
     const int o0 = blockIdx.x * (RB * kGemvRows) + r;                        // this lane's row of block 0
-    unsigned char *const patch = smem_raw + wave * kWideWaveBytes<NB>;
+    unsigned char *const patch = smem_raw + wave * kWideWaveBytes<TR>;
 
     const __amdgpu_buffer_rsrc_t rX = make_rsrc(a.X, a.x_bytes);
     const __amdgpu_buffer_rsrc_t rW = make_rsrc(a.Wp, a.w_bytes);
@@ -356,14 +356,11 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[rb][b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 
-    if (wave < n_runs) fetch_tokens(wave, 0);
-    for (int sc = wave; sc < n_runs; sc += n_waves) {
-        // codes, step sizes and zero points of the run
+    // codes, step sizes and zero points of run `sc`; past the last run all out of range
+    struct Run { uintx4 cq[RB][CW]; float sq[RB][NG], zq[RB][NG]; uint32_t zw[RB][2]; };
+    auto fetch_run = [&](int sc, Run &into) {
         const int seg0 = (sc * 4 + kq) * RS;
         const uint32_t j0 = NG > 1 ? (uint32_t)(seg0 / RS) * NG : __umulhi((uint32_t)seg0, a.spg_magic);
-        uintx4 cq[RB][CW];
-        float sq[RB][NG], zq[RB][NG];
-        uint32_t zw[RB][2];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             const int o = o0 + rb * kGemvRows;
@@ -372,7 +369,7 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
 #pragma unroll
             for (int q = 0; q < CW; ++q) {
                 const intx4 v = buf_load16(rW, ok ? base + 16u * q : kOobOffset);
-                cq[rb][q] = uintx4{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
+                into.cq[rb][q] = uintx4{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
             }
             const uint32_t gi = ok ? ((uint32_t)o * (uint32_t)a.G + j0) * 4u : kOobOffset;
             auto wide = [&](__amdgpu_buffer_rsrc_t rr, float (&dst)[NG]) {
@@ -391,19 +388,31 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
 #pragma unroll
                 for (int k = 0; k < NG; ++k) {
                     const intx2 v = buf_load8(rS, ok ? ((uint32_t)o * (uint32_t)a.G + j0 + k) * 8u : kOobOffset);
-                    sq[rb][k] = __int_as_float(v[0]); zq[rb][k] = __int_as_float(v[1]);
+                    into.sq[rb][k] = __int_as_float(v[0]); into.zq[rb][k] = __int_as_float(v[1]);
                 }
             } else {
-                wide(rS, sq[rb]);
+                wide(rS, into.sq[rb]);
             }
             if constexpr (SRC == kFloatZ) {
-                wide(rZ, zq[rb]);
+                wide(rZ, into.zq[rb]);
             } else if constexpr (SRC == kPackedZ) {
                 const uint32_t wi = (j0 * BITS) >> 5;
-                zw[rb][0] = (uint32_t)buf_load4(rZ, ok ? ((uint32_t)o * a.z_row_words + wi) * 4u : kOobOffset);
-                zw[rb][1] = (BITS == 3) ? (uint32_t)buf_load4(rZ, ok ? ((uint32_t)o * a.z_row_words + wi + 1u) * 4u : kOobOffset) : 0u;
+                into.zw[rb][0] = (uint32_t)buf_load4(rZ, ok ? ((uint32_t)o * a.z_row_words + wi) * 4u : kOobOffset);
+                into.zw[rb][1] = (BITS == 3) ? (uint32_t)buf_load4(rZ, ok ? ((uint32_t)o * a.z_row_words + wi + 1u) * 4u : kOobOffset) : 0u;
             }
         }
+    };
+
+    // Fetched a run ahead where that costs no waves: 2-bit codes and few tokens (13824 x 5120, 8 tokens 17 -> 12 us; 4 bit or 16
+    // tokens 5-15 % slower).
+    constexpr bool AHEAD = TR == 8 && BITS == 2;
+    Run run, next;
+    if constexpr (AHEAD) fetch_run(wave, next);
+    if (wave < n_runs) fetch_tokens(wave, 0);
+    for (int sc = wave; sc < n_runs; sc += n_waves) {
+        const int seg0 = (sc * 4 + kq) * RS;
+        const uint32_t j0 = NG > 1 ? (uint32_t)(seg0 / RS) * NG : __umulhi((uint32_t)seg0, a.spg_magic);
+        if constexpr (AHEAD) { run = next; fetch_run(sc + n_waves, next); } else fetch_run(sc, run);
         WhatTable<BITS> tab[RB];
 #pragma unroll
         for (int sub = 0; sub < RS / SUB; ++sub) {
@@ -420,30 +429,30 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
                     if (u % kSegsPerGroup == 0) {
                         const int gsel = u / kSegsPerGroup;
                         float zv;
-                        if constexpr (SRC != kPackedZ) zv = zq[rb][gsel];
-                        else zv = (float)((uint32_t)((((uint64_t)zw[rb][0] | ((uint64_t)zw[rb][1] << 32)) >> ((j0 * BITS) & 31u)) >> (gsel * BITS)) & ((1u << BITS) - 1u));
+                        if constexpr (SRC != kPackedZ) zv = run.zq[rb][gsel];
+                        else zv = (float)((uint32_t)((((uint64_t)run.zw[rb][0] | ((uint64_t)run.zw[rb][1] << 32)) >> ((j0 * BITS) & 31u)) >> (gsel * BITS)) & ((1u << BITS) - 1u));
                         // a segment past the end of the row shares its loads with the next row: its weights are forced to zero
-                        tab[rb].build(seg0 + u < n_segs ? sq[rb][gsel] : 0.0f, zv);
+                        tab[rb].build(seg0 + u < n_segs ? run.sq[rb][gsel] : 0.0f, zv);
                     } else if (seg0 + u >= n_segs) {
                         tab[rb].build(0.0f, 0.0f);
                     }
                     if constexpr (SRC == kWorking) {
                         WorkCodes<BITS> cw;
 #pragma unroll
-                        for (int j = 0; j < WPS; ++j) cw.w[j] = cq[rb][(u * WPS + j) / 4][(u * WPS + j) % 4];
+                        for (int j = 0; j < WPS; ++j) cw.w[j] = run.cq[rb][(u * WPS + j) / 4][(u * WPS + j) % 4];
                         w[rb][0] = slots_of<BITS>(tab[rb].template eight<0>(cw)); w[rb][1] = slots_of<BITS>(tab[rb].template eight<1>(cw));
                         w[rb][2] = slots_of<BITS>(tab[rb].template eight<2>(cw)); w[rb][3] = slots_of<BITS>(tab[rb].template eight<3>(cw));
                     } else {
                         CodeWords<BITS> cw;
 #pragma unroll
-                        for (int j = 0; j < WPS; ++j) cw.w[j] = cq[rb][(u * WPS + j) / 4][(u * WPS + j) % 4];
+                        for (int j = 0; j < WPS; ++j) cw.w[j] = run.cq[rb][(u * WPS + j) / 4][(u * WPS + j) % 4];
                         w[rb][0] = eight_of<BITS, 0>(tab[rb], cw); w[rb][1] = eight_of<BITS, 1>(tab[rb], cw);
                         w[rb][2] = eight_of<BITS, 2>(tab[rb], cw); w[rb][3] = eight_of<BITS, 3>(tab[rb], cw);
                     }
                 }
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    const unsigned char *const row = patch + (b * 16 + r) * ROWB + (kq * SUB + k) * 64;
+                    const unsigned char *const row = patch + (TR == 8 ? r & 7 : b * 16 + r) * ROWB + (kq * SUB + k) * 64;
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
                         const bf16x8 x = *reinterpret_cast<const bf16x8 *>(row + ((t ^ kq) * 16));
@@ -519,20 +528,20 @@ bool gemv_applies(const Problem &p)
     return p.act_bf16 && p.T >= 1 && (gemv_tokens_fit(p) || (p.T <= 16 && wide_groups(p) != 0) || gemv_work_applies(p));
 }
 
-template <int BITS, int SRC, int NG, int NB, int RB>
+template <int BITS, int SRC, int NG, int TR, int RB>
 static void launch_wide_t(const GemvArgs &a, hipStream_t st)
 {
-    auto kern = k_gemv_wide<BITS, SRC, NG, NB, RB>;
+    auto kern = k_gemv_wide<BITS, SRC, NG, TR, RB>;
     const int n_runs = (a.I / 32 + 4 * kWideRS - 1) / (4 * kWideRS), trips = (n_runs + kGemvMaxWaves - 1) / kGemvMaxWaves;
     const int waves = (n_runs + trips - 1) / trips;
-    const size_t smem = (size_t)waves * kWideWaveBytes<NB>;      // at least the 1 KB per wave and token block of the final sum
-    static_assert(kWideWaveBytes<NB> >= NB * RB * 1024 && kGemvMaxWaves * kWideWaveBytes<NB> <= 160 * 1024, "LDS of the final sum, of one CU");
+    const size_t smem = (size_t)waves * kWideWaveBytes<TR>;      // at least the 1 KB per wave and token block of the final sum
+    static_assert(kWideWaveBytes<TR> >= (TR + 15) / 16 * RB * 1024 && kGemvMaxWaves * kWideWaveBytes<TR> <= 160 * 1024, "LDS of the final sum, of one CU");
     // more dynamic LDS than the default limit: allowed once per instantiation and device
     static std::atomic<uint64_t> allowed{0};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev > 63) dev = 0;
     if (!((allowed.load(std::memory_order_relaxed) >> dev) & 1u)) {
-        (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kGemvMaxWaves * kWideWaveBytes<NB>);
+        (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kGemvMaxWaves * kWideWaveBytes<TR>);
         allowed.fetch_or((uint64_t)1 << dev, std::memory_order_relaxed);
     }
     kern<<<dim3((unsigned)((a.O + RB * kGemvRows - 1) / (RB * kGemvRows))), dim3(64 * waves), smem, st>>>(a);
@@ -543,11 +552,12 @@ static void launch_wide_z(int ng, const GemvArgs &a, hipStream_t st)
     const bool two = a.O >= 2 * kGemvRows * 256;
 #define EQAT_WIDE_NB(NG)                                                                          \
     do {                                                                                          \
-        if (a.T <= 16) launch_wide_t<BITS, SRC, NG, 1, 1>(a, st);                                 \
-        else if (a.T <= 32 && !two) launch_wide_t<BITS, SRC, NG, 2, 1>(a, st);                 \
-        else if (a.T <= 32) launch_wide_t<BITS, SRC, NG, 2, 2>(a, st);                         \
-        else if (!two) launch_wide_t<BITS, SRC, NG, 4, 1>(a, st);                              \
-        else launch_wide_t<BITS, SRC, NG, 4, 2>(a, st);                                        \
+        if (a.T <= 8) launch_wide_t<BITS, SRC, NG, 8, 1>(a, st);                                  \
+        else if (a.T <= 16) launch_wide_t<BITS, SRC, NG, 16, 1>(a, st);                           \
+        else if (a.T <= 32 && !two) launch_wide_t<BITS, SRC, NG, 32, 1>(a, st);                 \
+        else if (a.T <= 32) launch_wide_t<BITS, SRC, NG, 32, 2>(a, st);                         \
+        else if (!two) launch_wide_t<BITS, SRC, NG, 64, 1>(a, st);                              \
+        else launch_wide_t<BITS, SRC, NG, 64, 2>(a, st);                                        \
     } while (0)
     if (ng == 4) EQAT_WIDE_NB(4); else if (ng == 2) EQAT_WIDE_NB(2); else EQAT_WIDE_NB(1);
 #undef EQAT_WIDE_NB

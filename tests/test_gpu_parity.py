@@ -748,6 +748,7 @@ WIDE_CASES = [
     ("w6", 64, 320, 8216, 3, 64),
     ("w7", 64, 4736, 56, 2, 64),
     ("w8", 1, 8192, 24576, 4, 128),
+    ("w9", 5, 8192, 40, 3, 64),
 ]
 
 
