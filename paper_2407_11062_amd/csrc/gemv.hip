@@ -252,8 +252,11 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
             if (u % kSegsPerGroup == 0) {
                 const int gsel = u / kSegsPerGroup;                                   // compile time after unrolling
                 const float sv = sq[gsel / 4][gsel % 4];
-                const float zv = FLOATZ ? zq[gsel / 4][gsel % 4] : (float)((uint32_t)(zbits >> (gsel * BITS)) & ((1u << BITS) - 1u));
-                // a segment past the end of the row shares its loads with the next row: its weights are forced to zero
+                float zv;
+                if constexpr (FLOATZ) zv = seg_ok ? zq[gsel / 4][gsel % 4] : 0.0f;
+                else zv = (float)((uint32_t)(zbits >> (gsel * BITS)) & ((1u << BITS) - 1u));
+                // a segment past the end of the row shares its loads with the next row: its weights are forced to zero, by
+                // the step size and, as a float zero point may be infinite or NaN there, by that too
                 tab.build(seg_ok ? sv : 0.0f, zv);
             }
             CodeWords<BITS> cw;
@@ -429,9 +432,9 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
                     if (u % kSegsPerGroup == 0) {
                         const int gsel = u / kSegsPerGroup;
                         float zv;
-                        if constexpr (SRC != kPackedZ) zv = run.zq[rb][gsel];
+                        if constexpr (SRC != kPackedZ) zv = seg0 + u < n_segs ? run.zq[rb][gsel] : 0.0f;
                         else zv = (float)((uint32_t)((((uint64_t)run.zw[rb][0] | ((uint64_t)run.zw[rb][1] << 32)) >> ((j0 * BITS) & 31u)) >> (gsel * BITS)) & ((1u << BITS) - 1u));
-                        // a segment past the end of the row shares its loads with the next row: its weights are forced to zero
+                        // a segment past the end of the row shares its loads with the next row: its weights are forced to zero (see k_gemv_run)
                         tab[rb].build(seg0 + u < n_segs ? run.sq[rb][gsel] : 0.0f, zv);
                     } else if (seg0 + u >= n_segs) {
                         tab[rb].build(0.0f, 0.0f);

@@ -793,6 +793,30 @@ def test_forward_of_a_few_dozen_tokens(tag, T, I, O, bits, g):
     assert torch.equal(Yb[keep], Y[keep])
 
 
+# Rows that end inside a run (I % 128, I % 256 != 0): the step sizes and zero points of a run are fetched with one wide load,
+# which then reaches into the next row.  Its weights are zeroed through the step size, but 0 * inf is NaN: a float zero point
+# of the next row must not get there either.  k_gemv_run, k_gemv_any, k_gemv_wide at its four token counts, k_gemm_mid, tiles.
+@pytest.mark.parametrize("T,I,O,bits,g", [
+    (1, 1120, 24, 2, 32), (4, 1120, 24, 3, 32), (7, 1088, 24, 4, 64), (2, 1152, 24, 2, 128), (3, 1440, 24, 2, 96),
+    (8, 1120, 24, 2, 32), (12, 1088, 24, 3, 64), (24, 1120, 24, 2, 32), (40, 1088, 24, 4, 64), (64, 1120, 40, 3, 32),
+    (70, 4384, 5000, 2, 32), (300, 352, 40, 2, 32),
+])
+def test_a_non_finite_zero_point_stays_in_its_row(T, I, O, bits, g):
+    X, W, s, z, dY = make_case(("zleak", T, I), T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
+    Xd, sd = dev(X), dev(s)
+    Wp, zp = eq.eqat_pack(dev(W), sd, dev(z), bits, g)
+    prepared = eq.eqat_qlinear_prepare(Wp, zp, I, bits, g)
+    bad = [1, O // 2, O - 1]
+    keep = [o for o in range(O) if o not in bad]
+    zb = z.clone()
+    zb[1], zb[O // 2], zb[O - 1] = float("inf"), float("nan"), float("-inf")
+    for fwd in (lambda zz: eq.eqat_qlinear_fwd_z(Xd, Wp, sd, zz, bits, g),
+                lambda zz: eq.eqat_qlinear_fwd_prepared(Xd, prepared, sd, O, bits, g, z=zz)):
+        Y, Yb = fwd(dev(z)), fwd(dev(zb))
+        assert torch.equal(Yb[:, keep], Y[:, keep])
+        assert not torch.isfinite(Yb[:, bad].float()).any()
+
+
 # fp32 activations: 32 x 32 tiles with ragged edges and contraction ends (tokens, O and I as the contraction, O odd so that rows
 # are only 4-byte aligned), fewer contraction blocks than waves, 64 x 64 tiles with ragged last ones, groups wider than a block
 @pytest.mark.parametrize("tag,T,I,O,bits,g,wdt", [
