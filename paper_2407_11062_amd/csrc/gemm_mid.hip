@@ -274,9 +274,11 @@ double launch_us(const Problem &p, int bm)
     return (double)rounds * (6.0 + (double)((p.I + kMidBK - 1) / kMidBK) * (bm == 64 ? 1.2 : 1.45));
 }
 
+int token_tile(const Problem &p) { return launch_us(p, 96) < launch_us(p, 64) ? 96 : 64; }
+
 template <int SRC> void launch_src(const Problem &p, const MidArgs &a, hipStream_t st)
 {
-    const bool tall = launch_us(p, 96) < launch_us(p, 64);
+    const bool tall = token_tile(p) == 96;
 #define EQAT_MID(B) do { if (tall) launch_t<B, SRC, 96>(a, st); else launch_t<B, SRC, 64>(a, st); } while (0)
     if (p.bits == 2) EQAT_MID(2); else if (p.bits == 3) EQAT_MID(3); else EQAT_MID(4);
 #undef EQAT_MID
@@ -293,6 +295,8 @@ MidArgs mid_args(const Problem &p, const void *X, const void *codes, const void 
 }
 
 }  // namespace
+
+FwdRoute mid_route(const Problem &p) { return FwdRoute{FWD_MID, token_tile(p), kMidBN}; }
 
 double mid_us(const Problem &p) { return std::min(launch_us(p, 96), launch_us(p, 64)); }
 

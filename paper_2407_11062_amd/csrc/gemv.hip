@@ -576,6 +576,16 @@ bool gemv_applies(const Problem &p)
     return p.act_bf16 && p.T >= 1 && (gemv_tokens_fit(p) || (p.T <= 16 && wide_groups(p) != 0) || gemv_work_applies(p));
 }
 
+// groups per run of k_gemv_run (256 inputs of a lane); 0 = a group size it does not take
+static int run_groups(const Problem &p) { return p.g == 32 ? 8 : p.g == 64 ? 4 : p.g == 128 ? 2 : p.g % 256 == 0 ? 1 : 0; }
+
+FwdRoute gemv_route(const Problem &p)
+{
+    if (gemv_tokens_fit(p) && !wide_is_faster(p)) return FwdRoute{run_groups(p) != 0 ? FWD_GEMV_RUN : FWD_GEMV_ANY, 16, kGemvRows};
+    const int tokens = p.T <= 8 ? 8 : p.T <= 16 ? 16 : p.T <= 32 ? 32 : 64;
+    return FwdRoute{FWD_GEMV_WIDE, tokens, tokens >= 32 && p.O >= 2 * kGemvRows * 256 ? 2 * kGemvRows : kGemvRows};
+}
+
 template <int BITS, int SRC, int NG, int TR, int RB>
 static void launch_wide_t(const GemvArgs &a, hipStream_t st)
 {
@@ -595,17 +605,17 @@ static void launch_wide_t(const GemvArgs &a, hipStream_t st)
     kern<<<dim3((unsigned)((a.O + RB * kGemvRows - 1) / (RB * kGemvRows))), dim3(64 * waves), smem, st>>>(a);
 }
 template <int BITS, int SRC>
-static void launch_wide_z(int ng, const GemvArgs &a, hipStream_t st)
+static void launch_wide_z(int ng, const FwdRoute &way, const GemvArgs &a, hipStream_t st)
 {
-    const bool two = a.O >= 2 * kGemvRows * 256;
+    const bool two = way.rows != kGemvRows;
 #define EQAT_WIDE_NB(NG)                                                                          \
     do {                                                                                          \
-        if (a.T <= 8) launch_wide_t<BITS, SRC, NG, 8, 1>(a, st);                                  \
-        else if (a.T <= 16) launch_wide_t<BITS, SRC, NG, 16, 1>(a, st);                           \
-        else if (a.T <= 32 && !two) launch_wide_t<BITS, SRC, NG, 32, 1>(a, st);                 \
-        else if (a.T <= 32) launch_wide_t<BITS, SRC, NG, 32, 2>(a, st);                         \
-        else if (!two) launch_wide_t<BITS, SRC, NG, 64, 1>(a, st);                              \
-        else launch_wide_t<BITS, SRC, NG, 64, 2>(a, st);                                        \
+        if (way.tokens == 8) launch_wide_t<BITS, SRC, NG, 8, 1>(a, st);                           \
+        else if (way.tokens == 16) launch_wide_t<BITS, SRC, NG, 16, 1>(a, st);                    \
+        else if (way.tokens == 32 && !two) launch_wide_t<BITS, SRC, NG, 32, 1>(a, st);            \
+        else if (way.tokens == 32) launch_wide_t<BITS, SRC, NG, 32, 2>(a, st);                    \
+        else if (!two) launch_wide_t<BITS, SRC, NG, 64, 1>(a, st);                                \
+        else launch_wide_t<BITS, SRC, NG, 64, 2>(a, st);                                          \
     } while (0)
     if (ng == 4) EQAT_WIDE_NB(4); else if (ng == 2) EQAT_WIDE_NB(2); else EQAT_WIDE_NB(1);
 #undef EQAT_WIDE_NB
@@ -613,7 +623,10 @@ static void launch_wide_z(int ng, const GemvArgs &a, hipStream_t st)
 template <int SRC> static void launch_wide(const Problem &p, const GemvArgs &a, hipStream_t st)
 {
     const int ng = wide_groups(p);
-    if (p.bits == 2) launch_wide_z<2, SRC>(ng, a, st); else if (p.bits == 3) launch_wide_z<3, SRC>(ng, a, st); else launch_wide_z<4, SRC>(ng, a, st);
+    const FwdRoute way = gemv_route(p);
+    if (p.bits == 2) launch_wide_z<2, SRC>(ng, way, a, st);
+    else if (p.bits == 3) launch_wide_z<3, SRC>(ng, way, a, st);
+    else launch_wide_z<4, SRC>(ng, way, a, st);
 }
 
 static GemvArgs gemv_args(const Problem &p, const void *X, const void *codes, const void *s, void *Y)
@@ -645,12 +658,11 @@ void launch_gemv(const Problem &p, const void *X, const void *Wpacked, const flo
     a.w_bytes = (uint32_t)(p.O * p.I * p.bits / 8);
     a.s_bytes = (uint32_t)(p.O * p.G * 4);
     a.z_bytes = zfloat != nullptr ? a.s_bytes : (uint32_t)(p.O * a.z_row_words * 4);
-    if (!gemv_tokens_fit(p) || wide_is_faster(p)) {
+    if (gemv_route(p).kernel == FWD_GEMV_WIDE) {
         if (zfloat != nullptr) launch_wide<kFloatZ>(p, a, st); else launch_wide<kPackedZ>(p, a, st);
         return;
     }
-    // groups per run of 256 inputs; 0 = a group size the run kernel does not take
-    const int ng = p.g == 32 ? 8 : p.g == 64 ? 4 : p.g == 128 ? 2 : (p.g % 256 == 0 ? 1 : 0);
+    const int ng = run_groups(p);
     // a wave per run of 1024 inputs when four waves per row block would leave the chip short of waves (see k_gemv_run)
     const int n_blocks = (int)((p.O + kGemvRows - 1) / kGemvRows), waves = ng != 0 ? gemv_run_waves(p) : kGemvWaves;
     const bool more_waves = waves != kGemvWaves;

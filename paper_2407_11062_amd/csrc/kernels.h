@@ -69,8 +69,14 @@ void launch_mfma_dw(const Problem &p, bool block_ap, const void *X, const void *
                     const SkScratch &sk, hipStream_t st);
 bool dw_needs_partials(const Problem &p);
 
+// The kernel that a forward with bf16 activations takes, and the piece of the output that a workgroup of it computes (0: the
+// tile kernel plans that by itself).
+enum FwdKernel { FWD_GEMV_ANY, FWD_GEMV_RUN, FWD_GEMV_WIDE, FWD_MID, FWD_TILES };
+struct FwdRoute { FwdKernel kernel; int tokens, rows; };
+
 // ---- gemv.hip (E2E-QP forward for a few tokens, straight from the dense packed stream) -----------
 bool gemv_applies(const Problem &p);
+FwdRoute gemv_route(const Problem &p);            // where one of the two predicates holds
 // The same on the working layout and the (s, z) pairs, bitwise the same results: calls that hold those take it where this applies.
 bool gemv_work_applies(const Problem &p);
 void launch_gemv_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, hipStream_t st);
@@ -83,6 +89,7 @@ inline bool group_by_magic(const Problem &p) { return (p.I / 32) * (p.g / 32) < 
 
 // ---- gemm_mid.hip (forward for some dozens to about a thousand tokens) --------------------------------------------
 bool mid_applies(const Problem &p);
+FwdRoute mid_route(const Problem &p);
 double mid_us(const Problem &p);                  // what it takes, as the rules of dispatch estimate it
 // from the caller's dense stream (exactly one of zpacked / zfloat is not NULL), or from the working layout and (s, z) pairs:
 // bitwise the same results

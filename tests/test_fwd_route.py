@@ -1,0 +1,54 @@
+"""Which kernel a forward takes, asked on the host (`eqat_fwd_route`, no GPU): the lines of the dispatch rules, and that a
+call's kernel does not depend on the entry point from 17 tokens on (the results of all of them are bitwise equal there)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_2407_11062_amd as eq
+
+ANY, RUN, WIDE, MID, TILES = range(5)
+
+
+def route(T, I, O, bits, g, packed=True, act=eq.BF16):
+    out = (ctypes.c_int32 * 3)()
+    d = eq.make_desc(T, I, O, bits, g, act, eq.BF16)
+    rc = eq.lib().eqat_fwd_route(ctypes.byref(d), int(packed), out)
+    assert rc == 0, eq.lib().eqat_status_string(rc)
+    return tuple(out)
+
+
+def test_group_sizes_and_token_counts_choose_the_matrix_vector_kernel():
+    assert route(1, 4096, 4096, 2, 64)[0] == RUN and route(1, 4096, 4096, 2, -1)[0] == RUN
+    assert route(1, 4800, 4096, 2, 96)[0] == ANY and route(1, 1152, 4096, 2, 384)[0] == ANY
+    assert route(12, 4096, 4096, 2, 64) == (WIDE, 16, 16) and route(8, 4096, 4096, 2, 64) == (WIDE, 8, 16)
+    assert route(4, 28672, 8192, 2, 64)[0] == WIDE                # the token rows exceed the LDS of k_gemv_run
+    assert route(17, 4096, 8176, 3, 64) == (WIDE, 32, 16) and route(17, 4096, 8192, 3, 64) == (WIDE, 32, 32)
+    assert route(64, 4096, 8176, 3, 64) == (WIDE, 64, 16) and route(64, 8192, 8192, 3, 64) == (WIDE, 64, 32)
+    assert route(8192, 4096, 4096, 2, 64) == (TILES, 0, 0)
+
+
+def test_the_entry_point_does_not_matter_from_17_tokens_on():
+    rng = np.random.default_rng(7)
+    seen = set()
+    for _ in range(3000):
+        T, I, O = int(np.exp(rng.uniform(np.log(17), np.log(3000)))), 32 * int(rng.integers(1, 400)), 8 * int(rng.integers(1, 3000))
+        g = int(rng.choice([32, I]))
+        bits = int(rng.integers(2, 5))
+        a, b = route(T, I, O, bits, g, True), route(T, I, O, bits, g, False)
+        assert a == b, (T, I, O, bits, g, a, b)
+        seen.add(a[:2])
+    assert seen >= {(WIDE, 32), (WIDE, 64), (MID, 64), (MID, 96), (TILES, 0)}
+    for T in range(1, 17):                                        # fewer: only the packed arrays have a kernel of their own
+        assert route(T, 4096, 4096, 2, 64, False)[0] == TILES
+
+
+def test_bad_arguments():
+    L = eq.lib()
+    out = (ctypes.c_int32 * 3)()
+    ok = eq.make_desc(4, 512, 512, 2, 32, eq.BF16, eq.BF16)
+    assert L.eqat_fwd_route(ctypes.byref(ok), 1, out) == 0
+    assert L.eqat_fwd_route(ctypes.byref(ok), 1, None) != 0 and L.eqat_fwd_route(None, 1, out) != 0
+    for bad in (eq.make_desc(0, 512, 512, 2, 32, eq.BF16, eq.BF16), eq.make_desc(4, 512, 512, 2, 32, eq.F32, eq.F32),
+                eq.make_desc(4, 512, 512, 5, 32, eq.BF16, eq.BF16), eq.make_desc(4, 500, 512, 2, 32, eq.BF16, eq.BF16)):
+        assert L.eqat_fwd_route(ctypes.byref(bad), 1, out) != 0
