@@ -550,16 +550,21 @@ static int wide_groups(const Problem &p)
     return p.g == 32 ? 4 : p.g == 64 ? 2 : p.g % 128 == 0 ? 1 : 0;
 }
 
-// k_gemv_wide although the tokens would fit: from 8 tokens on the per-token rows of k_gemv_run, a multiple of 64 bytes apart, collide
-// on the LDS banks (16 tokens of 4096 inputs, 11008 rows: 12 instead of 18 us, 2 bit; at 4 tokens k_gemv_run is the faster
-// one, 10 against 12 us), and when the code lines that its waves hold half read (up to 28 waves per compute unit, 64 lanes
-// x 8 segments each) exceed the 4 MB L2 of an XCD by half, every line is fetched more than once (4 bit, 28672 x 8192, one
-// token: 90 against 51 us; 13824 x 5120, 4.4 MB: 18 against 24 us).
+// k_gemv_wide although the tokens would fit.
+// From 7 tokens on: k_gemv_run stages all token rows, 56 KB at 7 tokens of 4096 inputs, which leaves two workgroups per compute
+// unit, and rows a multiple of 64 bytes apart collide on the LDS banks.  7 tokens: faster or equal at every size, width and
+// group measured (one group per row: 11008 x 4096, 2 bit 15.1 -> 8.9 us, 3 bit 17.9 -> 11.6; 16384 x 2048, 4 bit 10.8 -> 8.8);
+// at 5 and 6 k_gemv_run is up to 19 and 8 % the faster one (3 bit).
+// Fewer tokens, 4-bit codes, more than 6144 waves (24 per compute unit; k_gemv_run<4> holds 20 to 28): a second round, and half
+// read lines of codes that leave the L2 in between.  28672 x 8192, one token 71 -> 39 us, 28672 x 4096 26 -> 23.  With one
+// group per run k_gemv_run needs fewer registers and has its 28 waves: one or two tokens of rows that its four waves walk in
+// one trip are faster there (28672 x 4096: 20 us against 22, 40000 x 4096 27 against 30; 28672 x 4608, two trips: 24, 22).
 static bool wide_is_faster(const Problem &p)
 {
     if (wide_groups(p) == 0) return false;
-    const int64_t waves = std::min<int64_t>((p.O + kGemvRows - 1) / kGemvRows * gemv_run_waves(p), 28 * 256);
-    return p.T >= 8 || waves * (64 * 8 * 4 * p.bits) / 8 > (int64_t)6 << 20;
+    if (p.T >= 7) return true;
+    if (p.bits != 4 || (p.O + kGemvRows - 1) / kGemvRows * gemv_run_waves(p) <= 24 * 256) return false;
+    return !(p.g % 256 == 0 && p.T <= 2 && p.I > 2048 && p.I <= 4096);
 }
 
 // 17 to 64 tokens, on every forward entry point alike (bitwise equal results).  Above 32 tokens k_gemm_mid is the faster one

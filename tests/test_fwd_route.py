@@ -28,6 +28,20 @@ def test_group_sizes_and_token_counts_choose_the_matrix_vector_kernel():
     assert route(8192, 4096, 4096, 2, 64) == (TILES, 0, 0)
 
 
+def test_few_tokens_take_the_faster_of_the_two_matrix_vector_kernels():
+    # 3-bit codes, 7 tokens, one group per row: k_gemv_wide; 4-bit codes of many rows, too, but one or two tokens of at most
+    # four runs of 1024 inputs with one group per run
+    assert route(6, 4096, 11008, 3, -1)[0] == RUN and route(7, 4096, 11008, 3, -1) == (WIDE, 8, 16)
+    for g in (256, 512, -1):
+        for T in (1, 2):
+            assert route(T, 4096, 28672, 4, g)[0] == RUN and route(T, 4608, 28672, 4, 512)[0] == WIDE, (T, g)
+        assert route(3, 4096, 28672, 4, g)[0] == WIDE, g
+    assert route(1, 4096, 28672, 4, 128)[0] == WIDE and route(1, 8192, 24576, 4, 128)[0] == RUN
+    assert route(1, 8192, 24592, 4, 128)[0] == WIDE and route(1, 8192, 28672, 3, 128)[0] == RUN
+    # the token rows of up to 16 tokens in the LDS of k_gemv_run: 64 KB at most
+    assert route(6, 5440, 4096, 2, 64)[0] == RUN and route(6, 5504, 4096, 2, 64)[0] == WIDE
+
+
 def test_the_entry_point_does_not_matter_from_17_tokens_on():
     rng = np.random.default_rng(7)
     seen = set()
