@@ -311,11 +311,6 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, 1>(tab, cw), b1, acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, 2>(tab, cw), b2, acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, 3>(tab, cw), b3, acc, 0, 0, 0);
-            // 3-bit codes with float zero points: the compiler spreads codes of later segments early and needs 71 registers
-            // where the one-by-one extraction before it had 66, i.e. 6 waves per SIMD instead of 7, and the 7168 waves of
-            // 28672 rows take a second round.  Segment by segment (one token, g = 64: 28672 x 8192 45 -> 30 us, one by one 35;
-            // 28672 x 4096 24.6 -> 16.5, 19.5; 4096 x 11008, g = 128 11.5 -> 10.1, 10.8).
-            if constexpr (BITS == 3 && FLOATZ) __builtin_amdgcn_sched_barrier(0);
         }
     }
 

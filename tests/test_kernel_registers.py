@@ -47,8 +47,3 @@ def run_kernel(waves, bits, floatz, ng, mw):
 def test_matrix_vector_kernel_of_2_bit_codes_keeps_eight_waves(waves_per_simd, floatz, ng):
     # four waves for each 16 of 28672 rows are 7168: one round of 256 compute units takes 7 waves per SIMD
     assert run_kernel(waves_per_simd, 2, floatz, ng, 0) == 8
-
-
-@pytest.mark.parametrize("ng", [1, 2, 4])
-def test_matrix_vector_kernel_of_3_bit_codes_and_float_zero_points_keeps_seven_waves(waves_per_simd, ng):
-    assert run_kernel(waves_per_simd, 3, 1, ng, 0) >= 7
