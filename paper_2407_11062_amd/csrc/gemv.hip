@@ -8,14 +8,12 @@
 // per 32-code segment (WhatTable, shared with the GEMM producer) turns codes into bf16 at about one VALU
 // instruction per weight and the multiply-adds cost nothing.
 //
-// Order of the contraction index.  A lane holds one 32-code segment of one row and feeds 8 codes of it to each of 4 MFMAs.
-// In the dense 2-bit stream, (word >> 2 k) & 0x03030303 leaves the codes k, k + 4, k + 8, k + 12 of the word in the four
-// bytes of a register, and the table turns them into two registers, the pairs (k, k + 4) and (k + 8, k + 12).  MFMA does not
-// care in which order k runs as long as both operands agree, so the token rows are staged in LDS in the order in which the
-// codes come.  Up to 16 tokens staged at once (k_gemv_run, k_gemv_any) a MFMA takes the two lookups of two neighbouring k
-// (run_slot_code()).  k_gemv_wide takes the four first pairs, which are the first eight codes of the word in the order
-// 0 4 1 5 2 6 3 7, and then the four second pairs, the other eight in the same order (slot_code()): a permutation inside
-// 16 bytes, which it can apply to the values that it streams, and to the working layout.  4-bit codes come
+// Order of the contraction index.  A lane holds one 32-code segment of one row and feeds 8 consecutive codes of it to each
+// of 4 MFMAs.  In the dense 2-bit stream, (word >> 2 k) & 0x03030303 leaves the codes k, k + 4, k + 8, k + 12 of the word
+// in the four bytes of a register, and the table turns them into two registers, the pairs (k, k + 4) and (k + 8, k + 12):
+// the four first pairs are the first eight codes of the word in the order 0 4 1 5 2 6 3 7, the four second pairs the other
+// eight in the same order.  MFMA does not care in which order k runs as long as both operands agree, so the token rows
+// are staged in LDS with every eight values in that order (slot_code()), a permutation inside 16 bytes.  4-bit codes come
 // out of their converts in any order wanted, and the dense 3-bit stream, which has no byte alignment at all, is taken twelve
 // bits at a time (spread_3bit): both keep the natural order.
 #include "common.h"
@@ -36,44 +34,6 @@ struct GemvArgs {
     uint32_t w_row_bytes, z_row_words;
     uint32_t x_bytes, w_bytes, s_bytes, z_bytes;
 };
-
-// Slot order of the two kernels below: with 2-bit codes a MFMA consumes both halves of what its own two lookups give.  The
-// order of k_gemv_wide (slot_code) shares every lookup between two MFMAs, which keeps eight weights alive across the first
-// product: 76 registers instead of 56 in k_gemv_run<2, false, 4, false>, 6 waves per SIMD instead of 8, and the 7168 waves
-// of 28672 rows no longer run in one round (one token: 28672 x 8192 26.7 us against 23.1, 28672 x 4096 15.1 against 13.4).
-template <int BITS> __host__ __device__ constexpr int run_slot_code(int t, int m)
-{
-    return BITS == 2 ? 16 * (t / 2) + 4 * (m % 4) + (2 * (t % 2) + m / 4) : slot_code<BITS>(t, m);
-}
-template <int BITS> __host__ __device__ constexpr int run_code_slot(int c)
-{
-    if (BITS != 2) return code_slot<BITS>(c);
-    const int wd = c / 16, k = c % 16, p = k % 4, q = k / 4;
-    return 8 * (2 * wd + p / 2) + 4 * (p % 2) + q;
-}
-template <int BITS> constexpr bool run_slot_maps_are_inverse()
-{
-    for (int c = 0; c < 32; ++c) {
-        const int sl = run_code_slot<BITS>(c);
-        if (sl < 0 || sl >= 32 || run_slot_code<BITS>(sl / 8, sl % 8) != c) return false;
-    }
-    return true;
-}
-static_assert(run_slot_maps_are_inverse<2>() && run_slot_maps_are_inverse<3>() && run_slot_maps_are_inverse<4>(), "slot order");
-template <int BITS, int T4>
-__device__ __forceinline__ bf16x8 run_eight_of(const WhatTable<BITS> &tab, const CodeWords<BITS> &c)
-{
-    if constexpr (BITS == 2) {
-        const uint32_t w = c.w[T4 / 2];
-        uintx4 u;
-        uint32_t d0, d1;
-        tab.four((w >> (4 * (T4 % 2))) & 0x03030303u, d0, d1); u[0] = d0; u[1] = d1;
-        tab.four((w >> (4 * (T4 % 2) + 2)) & 0x03030303u, d0, d1); u[2] = d0; u[3] = d1;
-        return __builtin_bit_cast(bf16x8, u);
-    } else {
-        return eight_of<BITS, T4>(tab, c);
-    }
-}
 
 constexpr int kGemvRows = 16;      // output rows per workgroup (the M of the MFMA)
 constexpr int kGemvWaves = 4;      // waves per workgroup, splitting the input dimension
@@ -102,7 +62,7 @@ __global__ __launch_bounds__(64 * kGemvWaves) void k_gemv_any(const GemvArgs a)
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const bf16x8 *>(src + 8 * q);
 #pragma unroll
-        for (int c = 0; c < 32; ++c) dst[run_code_slot<BITS>(c)] = v[c / 8][c % 8];
+        for (int c = 0; c < 32; ++c) dst[code_slot<BITS>(c)] = v[c / 8][c % 8];
     }
     __syncthreads();
 
@@ -166,10 +126,10 @@ __global__ __launch_bounds__(64 * kGemvWaves) void k_gemv_any(const GemvArgs a)
                 }
                 WhatTable<BITS> tab;
                 tab.build(sv[u][rb], zv[u][rb]);
-                acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, 0>(tab, cw[u][rb]), b0, acc[rb], 0, 0, 0);
-                acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, 1>(tab, cw[u][rb]), b1, acc[rb], 0, 0, 0);
-                acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, 2>(tab, cw[u][rb]), b2, acc[rb], 0, 0, 0);
-                acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, 3>(tab, cw[u][rb]), b3, acc[rb], 0, 0, 0);
+                acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 0>(tab, cw[u][rb]), b0, acc[rb], 0, 0, 0);
+                acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 1>(tab, cw[u][rb]), b1, acc[rb], 0, 0, 0);
+                acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 2>(tab, cw[u][rb]), b2, acc[rb], 0, 0, 0);
+                acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 3>(tab, cw[u][rb]), b3, acc[rb], 0, 0, 0);
             }
         }
     }
@@ -270,7 +230,7 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const bf16x8 *>(src + 8 * q);
 #pragma unroll
-        for (int c = 0; c < 32; ++c) dst[run_code_slot<BITS>(c)] = v[c / 8][c % 8];
+        for (int c = 0; c < 32; ++c) dst[code_slot<BITS>(c)] = v[c / 8][c % 8];
     }
     __syncthreads();
 
@@ -307,10 +267,10 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
             const bf16x8 b1 = *reinterpret_cast<const bf16x8 *>(xrow + 8);
             const bf16x8 b2 = *reinterpret_cast<const bf16x8 *>(xrow + 16);
             const bf16x8 b3 = *reinterpret_cast<const bf16x8 *>(xrow + 24);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, 0>(tab, cw), b0, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, 1>(tab, cw), b1, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, 2>(tab, cw), b2, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, 3>(tab, cw), b3, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 0>(tab, cw), b0, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 1>(tab, cw), b1, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 2>(tab, cw), b2, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 3>(tab, cw), b3, acc, 0, 0, 0);
         }
     }
 
