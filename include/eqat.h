@@ -351,12 +351,12 @@ eqat_status eqat_plan_item(const eqat_desc *d, int gemm, int block, int j, int32
 
 /*
  * Test aid (host only, nothing is launched): the kernel that a forward of this descriptor (bf16 activations, tokens >= 1)
- * takes, from the packed arrays as they are (from_packed != 0: eqat_qlinear_fwd, eqat_qlinear_fwd_z) or from codes in the
- * working layout (0: every other forward).  route[3] = { 0 matrix-vector, any group; 1 matrix-vector; 2 matrix-vector with
- * streamed tokens; 3 GEMM for few tiles; 4 tiled GEMM,  tokens and  rows that a workgroup computes (0 for 4) }.  Lets a test
- * assert that its sizes reach the kernel it is about.
+ * takes, from the packed arrays as they are (source 1: eqat_qlinear_fwd, 2: eqat_qlinear_fwd_z) or from codes in the working
+ * layout (0: every other forward).  route[3] = { 0 matrix-vector, any group; 1 matrix-vector; 2 matrix-vector with streamed
+ * tokens; 3 GEMM for few tiles; 4 tiled GEMM; 5 matrix-vector, segment by segment,  tokens,  rows that a workgroup computes
+ * (0 for 4) }.  Lets a test assert that its sizes reach the kernel it is about.
  */
-eqat_status eqat_fwd_route(const eqat_desc *d, int from_packed, int32_t *route);
+eqat_status eqat_fwd_route(const eqat_desc *d, int source, int32_t *route);
 
 /*
  * Optional per-kernel timing (measurement aid, not part of the paper's method).

@@ -272,9 +272,9 @@ eqat_status eqat_unpack(const eqat_desc *d, const uint8_t *Wpacked, const uint8_
 
 // Which kernel computes a forward, from the caller's packed arrays as they are (eqat_qlinear_fwd, _z) or from codes in the
 // working layout (all others).
-static eqat::FwdRoute fwd_route(const Problem &p, bool from_packed)
+static eqat::FwdRoute fwd_route(const Problem &p, bool from_packed, bool floatz)
 {
-    if (from_packed ? eqat::gemv_applies(p) : eqat::gemv_work_applies(p)) return eqat::gemv_route(p);
+    if (from_packed ? eqat::gemv_applies(p) : eqat::gemv_work_applies(p)) return eqat::gemv_route(p, floatz);
     if (eqat::mid_applies(p)) return eqat::mid_route(p);
     return eqat::FwdRoute{eqat::FWD_TILES, 0, 0};
 }
@@ -282,7 +282,7 @@ static eqat::FwdRoute fwd_route(const Problem &p, bool from_packed)
 // Forward on codes in the working layout.
 static void fwd_on_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, const eqat::SkScratch &sk, hipStream_t st)
 {
-    const eqat::FwdKernel kernel = fwd_route(p, false).kernel;
+    const eqat::FwdKernel kernel = fwd_route(p, false, false).kernel;
     if (kernel == eqat::FWD_GEMV_WIDE) { ProfScope ps(eqat::PK_GEMV, st); eqat::launch_gemv_work(p, X, codes, sz, Y, st); }
     else if (kernel == eqat::FWD_MID) { ProfScope ps(eqat::PK_GEMM_FWD, st); eqat::launch_mid_work(p, X, codes, sz, Y, st); }
     else { ProfScope ps(eqat::PK_GEMM_FWD, st); eqat::launch_mfma_fwd(p, X, codes, sz, Y, sk, st); }
@@ -444,7 +444,7 @@ static eqat_status qlinear_fwd_any(const eqat_desc *d, const void *X, const uint
     hipStream_t st = (hipStream_t)stream;
     char *w8 = (char *)ws;
     // the caller's own packed arrays, one kernel
-    const eqat::FwdKernel kernel = !keep && p.act_bf16 ? fwd_route(p, true).kernel : eqat::FWD_TILES;
+    const eqat::FwdKernel kernel = !keep && p.act_bf16 ? fwd_route(p, true, zfloat != nullptr).kernel : eqat::FWD_TILES;
     if (kernel == eqat::FWD_MID) {
         ProfScope ps(eqat::PK_GEMM_FWD, st);
         eqat::launch_mid(p, X, Wpacked, s, zpacked, zfloat, Y, st);
@@ -607,14 +607,14 @@ eqat_status eqat_plan_item(const eqat_desc *d, int gemm, int block, int j, int32
 }
 
 // Test aid (host only): which kernel a forward takes.
-eqat_status eqat_fwd_route(const eqat_desc *d, int from_packed, int32_t *route)
+eqat_status eqat_fwd_route(const eqat_desc *d, int source, int32_t *route)
 {
     Problem p;
     if (eqat_status e = check_desc(d, true, &p)) return e;
     if (route == nullptr) return EQAT_ERR_NULL;
     if (!p.act_bf16) return EQAT_ERR_DTYPE;                          // the fp32 path has one forward kernel
     if (p.T < 1) return EQAT_ERR_SHAPE;
-    const eqat::FwdRoute way = fwd_route(p, from_packed != 0);
+    const eqat::FwdRoute way = fwd_route(p, source != 0, source == 2);
     route[0] = way.kernel; route[1] = way.tokens; route[2] = way.rows;
     return EQAT_OK;
 }

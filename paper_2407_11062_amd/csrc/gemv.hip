@@ -164,7 +164,10 @@ __global__ __launch_bounds__(64 * kGemvWaves) void k_gemv_any(const GemvArgs a)
 // matrices with few row blocks (less than 16 waves per compute unit with four) that puts every load of the launch in
 // flight at once (measured 4-7 % faster at 5120 x 5120, 13824 x 5120 and 8192 x 8192); with many row blocks the chip is
 // full anyway and the fixed-size version, whose loops the compiler knows, is the faster one.
-template <int BITS, bool FLOATZ, int NG, bool MW>
+// SEG: segment by segment.  Left to itself the compiler runs ahead over the eight segments of a run, spreading codes and
+// converting weights long before their MFMAs: the quicker order for small matrices, but the more registers and the waves
+// drift further apart, so that half-read lines of codes leave the L2.  See by_segments().
+template <int BITS, bool FLOATZ, int NG, bool MW, bool SEG>
 __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv_run(const GemvArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -271,6 +274,7 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 1>(tab, cw), b1, acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 2>(tab, cw), b2, acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 3>(tab, cw), b3, acc, 0, 0, 0);
+            if constexpr (SEG) __builtin_amdgcn_sched_barrier(0);
         }
     }
 
@@ -539,9 +543,24 @@ bool gemv_applies(const Problem &p)
 // groups per run of k_gemv_run (256 inputs of a lane); 0 = a group size it does not take
 static int run_groups(const Problem &p) { return p.g == 32 ? 8 : p.g == 64 ? 4 : p.g == 128 ? 2 : p.g % 256 == 0 ? 1 : 0; }
 
-FwdRoute gemv_route(const Problem &p)
+// Forms of k_gemv_run that exist segment by segment, too, and when they are taken: more than 2^25 weights (the chip full of
+// waves; fewer: up to 8 % slower, 0.3 us).  One token, without -> with: 2 bit, g = 64: 28672 x 8192 26.7 -> 23.6 us,
+// 28672 x 4096 15.1 -> 13.4, 8192 x 8192 9.6 -> 9.3 (from 3 tokens on +-5 %, not taken); float zero points: 3 bit, g = 64
+// 28672 x 8192 45 -> 30, 11008 x 4096 10.5 -> 9.6; 4 bit, g = 64 24000 x 8192 60 -> 34, g = 32 8192 x 28672 65 -> 45.
+template <int BITS, bool FLOATZ, int NG> constexpr bool kHasSegments = BITS == 2 ? NG == 4 : FLOATZ && NG >= (BITS == 3 ? 2 : 4);
+static bool by_segments(const Problem &p, bool floatz)
 {
-    if (gemv_tokens_fit(p) && !wide_is_faster(p)) return FwdRoute{run_groups(p) != 0 ? FWD_GEMV_RUN : FWD_GEMV_ANY, 16, kGemvRows};
+    if (p.O * p.I <= (int64_t)1 << 25) return false;
+    const int ng = run_groups(p);
+    return p.bits == 2 ? ng == 4 && p.T <= 2 : floatz && ng >= (p.bits == 3 ? 2 : 4);
+}
+
+FwdRoute gemv_route(const Problem &p, bool floatz)
+{
+    if (gemv_tokens_fit(p) && !wide_is_faster(p)) {
+        const FwdKernel kernel = run_groups(p) == 0 ? FWD_GEMV_ANY : by_segments(p, floatz) ? FWD_GEMV_SEGMENTS : FWD_GEMV_RUN;
+        return FwdRoute{kernel, 16, kGemvRows};
+    }
     const int tokens = p.T <= 8 ? 8 : p.T <= 16 ? 16 : p.T <= 32 ? 32 : 64;
     return FwdRoute{FWD_GEMV_WIDE, tokens, tokens >= 32 && p.O >= 2 * kGemvRows * 256 ? 2 * kGemvRows : kGemvRows};
 }
@@ -583,7 +602,7 @@ static void launch_wide_z(int ng, const FwdRoute &way, const GemvArgs &a, hipStr
 template <int SRC> static void launch_wide(const Problem &p, const GemvArgs &a, hipStream_t st)
 {
     const int ng = wide_groups(p);
-    const FwdRoute way = gemv_route(p);
+    const FwdRoute way = gemv_route(p, false);
     if (p.bits == 2) launch_wide_z<2, SRC>(ng, way, a, st);
     else if (p.bits == 3) launch_wide_z<3, SRC>(ng, way, a, st);
     else launch_wide_z<4, SRC>(ng, way, a, st);
@@ -618,7 +637,8 @@ void launch_gemv(const Problem &p, const void *X, const void *Wpacked, const flo
     a.w_bytes = (uint32_t)(p.O * p.I * p.bits / 8);
     a.s_bytes = (uint32_t)(p.O * p.G * 4);
     a.z_bytes = zfloat != nullptr ? a.s_bytes : (uint32_t)(p.O * a.z_row_words * 4);
-    if (gemv_route(p).kernel == FWD_GEMV_WIDE) {
+    const FwdKernel kernel = gemv_route(p, zfloat != nullptr).kernel;
+    if (kernel == FWD_GEMV_WIDE) {
         if (zfloat != nullptr) launch_wide<kFloatZ>(p, a, st); else launch_wide<kPackedZ>(p, a, st);
         return;
     }
@@ -632,12 +652,18 @@ void launch_gemv(const Problem &p, const void *X, const void *Wpacked, const flo
     if (ng == 1) {          // magic for "group of segment": exact for segment * (g/32) < 2^32
         a.spg_magic = (uint32_t)((((uint64_t)1 << 32) + (uint64_t)(p.g / 32) - 1) / (uint64_t)(p.g / 32));
     }
+    const bool seg = kernel == FWD_GEMV_SEGMENTS;
+#define EQAT_GEMV_SEG(B, FZ, N, MW)                                                               \
+    do {                                                                                          \
+        if (seg && kHasSegments<B, FZ, N>) k_gemv_run<B, FZ, N, MW, kHasSegments<B, FZ, N>><<<grid, block, smem, st>>>(a); \
+        else k_gemv_run<B, FZ, N, MW, false><<<grid, block, smem, st>>>(a);                        \
+    } while (0)
 #define EQAT_GEMV_NG(B, FZ, MW)                                                                   \
     do {                                                                                          \
-        if (ng == 8) k_gemv_run<B, FZ, 8, MW><<<grid, block, smem, st>>>(a);                       \
-        else if (ng == 4) k_gemv_run<B, FZ, 4, MW><<<grid, block, smem, st>>>(a);                  \
-        else if (ng == 2) k_gemv_run<B, FZ, 2, MW><<<grid, block, smem, st>>>(a);                  \
-        else k_gemv_run<B, FZ, 1, MW><<<grid, block, smem, st>>>(a);                               \
+        if (ng == 8) EQAT_GEMV_SEG(B, FZ, 8, MW);                                                  \
+        else if (ng == 4) EQAT_GEMV_SEG(B, FZ, 4, MW);                                             \
+        else if (ng == 2) EQAT_GEMV_SEG(B, FZ, 2, MW);                                             \
+        else EQAT_GEMV_SEG(B, FZ, 1, MW);                                                          \
     } while (0)
 #define EQAT_GEMV_RUN(B, FZ)                                                                      \
     do {                                                                                          \
@@ -649,6 +675,7 @@ void launch_gemv(const Problem &p, const void *X, const void *Wpacked, const flo
     if (p.bits == 2) EQAT_GEMV(2); else if (p.bits == 3) EQAT_GEMV(3); else EQAT_GEMV(4);
 #undef EQAT_GEMV_RUN
 #undef EQAT_GEMV_NG
+#undef EQAT_GEMV_SEG
 #undef EQAT_GEMV
 }
 

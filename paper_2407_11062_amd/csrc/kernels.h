@@ -71,12 +71,12 @@ bool dw_needs_partials(const Problem &p);
 
 // The kernel that a forward with bf16 activations takes, and the piece of the output that a workgroup of it computes (0: the
 // tile kernel plans that by itself).
-enum FwdKernel { FWD_GEMV_ANY, FWD_GEMV_RUN, FWD_GEMV_WIDE, FWD_MID, FWD_TILES };
+enum FwdKernel { FWD_GEMV_ANY, FWD_GEMV_RUN, FWD_GEMV_WIDE, FWD_MID, FWD_TILES, FWD_GEMV_SEGMENTS };
 struct FwdRoute { FwdKernel kernel; int tokens, rows; };
 
 // ---- gemv.hip (E2E-QP forward for a few tokens, straight from the dense packed stream) -----------
 bool gemv_applies(const Problem &p);
-FwdRoute gemv_route(const Problem &p);            // where one of the two predicates holds
+FwdRoute gemv_route(const Problem &p, bool floatz);         // where one of the two predicates holds
 // The same on the working layout and the (s, z) pairs, bitwise the same results: calls that hold those take it where this applies.
 bool gemv_work_applies(const Problem &p);
 void launch_gemv_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, hipStream_t st);

@@ -7,13 +7,14 @@ import pytest
 
 import paper_2407_11062_amd as eq
 
-ANY, RUN, WIDE, MID, TILES = range(5)
+ANY, RUN, WIDE, MID, TILES, SEGMENTS = range(6)
+WORK, PACKED, FLOATZ = range(3)
 
 
-def route(T, I, O, bits, g, packed=True, act=eq.BF16):
+def route(T, I, O, bits, g, source=PACKED, act=eq.BF16):
     out = (ctypes.c_int32 * 3)()
     d = eq.make_desc(T, I, O, bits, g, act, eq.BF16)
-    rc = eq.lib().eqat_fwd_route(ctypes.byref(d), int(packed), out)
+    rc = eq.lib().eqat_fwd_route(ctypes.byref(d), source, out)
     assert rc == 0, eq.lib().eqat_status_string(rc)
     return tuple(out)
 
@@ -42,6 +43,16 @@ def test_few_tokens_take_the_faster_of_the_two_matrix_vector_kernels():
     assert route(6, 5440, 4096, 2, 64)[0] == RUN and route(6, 5504, 4096, 2, 64)[0] == WIDE
 
 
+def test_large_matrices_go_segment_by_segment_where_that_is_faster():
+    large, small = (4096, 8208), (4096, 8192)                     # just above and at 2^25 weights
+    for bits, g, source in ((2, 64, PACKED), (2, 64, FLOATZ), (3, 32, FLOATZ), (3, 128, FLOATZ), (4, 32, FLOATZ), (4, 64, FLOATZ)):
+        assert route(1, *large, bits, g, source)[0] == SEGMENTS and route(1, *small, bits, g, source)[0] == RUN, (bits, g, source)
+    for bits, g, source in ((2, 32, PACKED), (2, 128, FLOATZ), (3, 64, PACKED), (3, 256, FLOATZ), (4, 64, PACKED), (4, 128, FLOATZ)):
+        assert route(1, *large, bits, g, source)[0] == RUN, (bits, g, source)
+    assert route(2, *large, 2, 64)[0] == SEGMENTS and route(3, *large, 2, 64)[0] == RUN
+    assert route(6, *large, 3, 64, FLOATZ)[0] == SEGMENTS and route(7, *large, 3, 64, FLOATZ)[0] == WIDE
+
+
 def test_the_entry_point_does_not_matter_from_17_tokens_on():
     rng = np.random.default_rng(7)
     seen = set()
@@ -49,12 +60,12 @@ def test_the_entry_point_does_not_matter_from_17_tokens_on():
         T, I, O = int(np.exp(rng.uniform(np.log(17), np.log(3000)))), 32 * int(rng.integers(1, 400)), 8 * int(rng.integers(1, 3000))
         g = int(rng.choice([32, I]))
         bits = int(rng.integers(2, 5))
-        a, b = route(T, I, O, bits, g, True), route(T, I, O, bits, g, False)
-        assert a == b, (T, I, O, bits, g, a, b)
+        a, b, c = (route(T, I, O, bits, g, source) for source in (WORK, PACKED, FLOATZ))
+        assert a == b == c, (T, I, O, bits, g, a, b, c)
         seen.add(a[:2])
     assert seen >= {(WIDE, 32), (WIDE, 64), (MID, 64), (MID, 96), (TILES, 0)}
     for T in range(1, 17):                                        # fewer: only the packed arrays have a kernel of their own
-        assert route(T, 4096, 4096, 2, 64, False)[0] == TILES
+        assert route(T, 4096, 4096, 2, 64, WORK)[0] == TILES
 
 
 def test_bad_arguments():

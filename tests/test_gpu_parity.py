@@ -645,6 +645,10 @@ GEMV_CASES = [
     ("v10", 1, 11008, 40, 3, 128),
     ("v11", 3, 8192, 32, 4, 64),
     ("v12", 1, 28672, 24, 2, 64),
+    # more than 2^25 weights: segment by segment (packed and float zero points; float only), four waves and one per run
+    ("v13", 2, 3968, 8488, 2, 64),
+    ("v14", 1, 5440, 6184, 3, 64),
+    ("v15", 3, 3968, 8488, 4, 32),
 ]
 
 
