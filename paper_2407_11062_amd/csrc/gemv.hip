@@ -545,14 +545,14 @@ static int run_groups(const Problem &p) { return p.g == 32 ? 8 : p.g == 64 ? 4 :
 
 // Forms of k_gemv_run that exist segment by segment, too, and when they are taken: more than 2^25 weights (the chip full of
 // waves; fewer: up to 8 % slower, 0.3 us).  One token, without -> with: 2 bit, g = 64: 28672 x 8192 26.7 -> 23.6 us,
-// 28672 x 4096 15.1 -> 13.4, 8192 x 8192 9.6 -> 9.3 (from 3 tokens on +-5 %, not taken); float zero points: 3 bit, g = 64
+// 28672 x 4096 15.1 -> 13.4, 8192 x 8192 9.6 -> 9.3 (from 3 tokens on +-5 %, not taken); float zero points: 2 bit, g = 32 28672 x 8192 29.9 -> 28.2; 3 bit, g = 64
 // 28672 x 8192 45 -> 30, 11008 x 4096 10.5 -> 9.6; 4 bit, g = 64 24000 x 8192 60 -> 34, g = 32 8192 x 28672 65 -> 45.
-template <int BITS, bool FLOATZ, int NG> constexpr bool kHasSegments = BITS == 2 ? NG == 4 : FLOATZ && NG >= (BITS == 3 ? 2 : 4);
+template <int BITS, bool FLOATZ, int NG> constexpr bool kHasSegments = BITS == 2 ? NG == 4 || (FLOATZ && NG == 8) : FLOATZ && NG >= (BITS == 3 ? 2 : 4);
 static bool by_segments(const Problem &p, bool floatz)
 {
     if (p.O * p.I <= (int64_t)1 << 25) return false;
     const int ng = run_groups(p);
-    return p.bits == 2 ? ng == 4 && p.T <= 2 : floatz && ng >= (p.bits == 3 ? 2 : 4);
+    return p.bits == 2 ? (ng == 4 || (floatz && ng == 8)) && p.T <= 2 : floatz && ng >= (p.bits == 3 ? 2 : 4);
 }
 
 FwdRoute gemv_route(const Problem &p, bool floatz)

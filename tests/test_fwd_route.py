@@ -45,7 +45,7 @@ def test_few_tokens_take_the_faster_of_the_two_matrix_vector_kernels():
 
 def test_large_matrices_go_segment_by_segment_where_that_is_faster():
     large, small = (4096, 8208), (4096, 8192)                     # just above and at 2^25 weights
-    for bits, g, source in ((2, 64, PACKED), (2, 64, FLOATZ), (3, 32, FLOATZ), (3, 128, FLOATZ), (4, 32, FLOATZ), (4, 64, FLOATZ)):
+    for bits, g, source in ((2, 64, PACKED), (2, 64, FLOATZ), (2, 32, FLOATZ), (3, 32, FLOATZ), (3, 128, FLOATZ), (4, 32, FLOATZ), (4, 64, FLOATZ)):
         assert route(1, *large, bits, g, source)[0] == SEGMENTS and route(1, *small, bits, g, source)[0] == RUN, (bits, g, source)
     for bits, g, source in ((2, 32, PACKED), (2, 128, FLOATZ), (3, 64, PACKED), (3, 256, FLOATZ), (4, 64, PACKED), (4, 128, FLOATZ)):
         assert route(1, *large, bits, g, source)[0] == RUN, (bits, g, source)
