@@ -164,10 +164,32 @@ __global__ __launch_bounds__(64 * kGemvWaves) void k_gemv_any(const GemvArgs a)
 // matrices with few row blocks (less than 16 waves per compute unit with four) that puts every load of the launch in
 // flight at once (measured 4-7 % faster at 5120 x 5120, 13824 x 5120 and 8192 x 8192); with many row blocks the chip is
 // full anyway and the fixed-size version, whose loops the compiler knows, is the faster one.
-// SEG: segment by segment.  Left to itself the compiler runs ahead over the eight segments of a run, spreading codes and
-// converting weights long before their MFMAs: the quicker order for small matrices, but the more registers and the waves
-// drift further apart, so that half-read lines of codes leave the L2.  See by_segments().
-template <int BITS, bool FLOATZ, int NG, bool MW, bool SEG>
+// FORM.  kFree: left to itself the compiler runs ahead over the eight segments of a run, spreading codes and converting weights
+// long before their MFMAs: the quicker order for small matrices, but the more registers and the waves drift further apart, so
+// that half-read lines of codes leave the L2.  kSegments: one segment after the other.  kPairs (2 bit): another slot order, in
+// which a MFMA consumes both halves of what its own two lookups give; no eight weights live across a MFMA and 60 registers in
+// the place of 80, eight waves per SIMD, but the token rows take a 2-byte scatter that collides on the LDS banks (with more
+// than one token 3 to 30 % slower).  See run_form().
+enum RunForm { kFree, kSegments, kPairs };
+template <int BITS, int FORM> __host__ __device__ constexpr int run_code_slot(int c)
+{
+    if (FORM != kPairs) return code_slot<BITS>(c);
+    const int wd = c / 16, k = c % 16, p = k % 4, q = k / 4;        // 2 bit: codes 4 q + p of a word come out of shift 2 p
+    return 8 * (2 * wd + p / 2) + 4 * (p % 2) + q;
+}
+template <int BITS, int FORM, int T4>
+__device__ __forceinline__ bf16x8 run_eight_of(const WhatTable<BITS> &tab, const CodeWords<BITS> &c)
+{
+    if constexpr (FORM != kPairs) return eight_of<BITS, T4>(tab, c);
+    const uint32_t w = c.w[T4 / 2];
+    uintx4 u;
+    uint32_t d0, d1;
+    tab.four((w >> (4 * (T4 % 2))) & 0x03030303u, d0, d1); u[0] = d0; u[1] = d1;
+    tab.four((w >> (4 * (T4 % 2) + 2)) & 0x03030303u, d0, d1); u[2] = d0; u[3] = d1;
+    return __builtin_bit_cast(bf16x8, u);
+}
+
+template <int BITS, bool FLOATZ, int NG, bool MW, int FORM>
 __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv_run(const GemvArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -233,7 +255,7 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const bf16x8 *>(src + 8 * q);
 #pragma unroll
-        for (int c = 0; c < 32; ++c) dst[code_slot<BITS>(c)] = v[c / 8][c % 8];
+        for (int c = 0; c < 32; ++c) dst[run_code_slot<BITS, FORM>(c)] = v[c / 8][c % 8];
     }
     __syncthreads();
 
@@ -270,11 +292,11 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
             const bf16x8 b1 = *reinterpret_cast<const bf16x8 *>(xrow + 8);
             const bf16x8 b2 = *reinterpret_cast<const bf16x8 *>(xrow + 16);
             const bf16x8 b3 = *reinterpret_cast<const bf16x8 *>(xrow + 24);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 0>(tab, cw), b0, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 1>(tab, cw), b1, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 2>(tab, cw), b2, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(eight_of<BITS, 3>(tab, cw), b3, acc, 0, 0, 0);
-            if constexpr (SEG) __builtin_amdgcn_sched_barrier(0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, FORM, 0>(tab, cw), b0, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, FORM, 1>(tab, cw), b1, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, FORM, 2>(tab, cw), b2, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, FORM, 3>(tab, cw), b3, acc, 0, 0, 0);
+            if constexpr (FORM == kSegments) __builtin_amdgcn_sched_barrier(0);
         }
     }
 
@@ -543,22 +565,27 @@ bool gemv_applies(const Problem &p)
 // groups per run of k_gemv_run (256 inputs of a lane); 0 = a group size it does not take
 static int run_groups(const Problem &p) { return p.g == 32 ? 8 : p.g == 64 ? 4 : p.g == 128 ? 2 : p.g % 256 == 0 ? 1 : 0; }
 
-// Forms of k_gemv_run that exist segment by segment, too, and when they are taken: more than 2^25 weights (the chip full of
-// waves; fewer: up to 8 % slower, 0.3 us).  One token, without -> with: 2 bit, g = 64: 28672 x 8192 26.7 -> 23.6 us,
-// 28672 x 4096 15.1 -> 13.4, 8192 x 8192 9.6 -> 9.3 (from 3 tokens on +-5 %, not taken); float zero points: 2 bit, g = 32 28672 x 8192 29.9 -> 28.2; 3 bit, g = 64
-// 28672 x 8192 45 -> 30, 11008 x 4096 10.5 -> 9.6; 4 bit, g = 64 24000 x 8192 60 -> 34, g = 32 8192 x 28672 65 -> 45.
+// Forms of k_gemv_run that exist beside the free one, and when they are taken: more than 2^25 weights (the chip full of waves;
+// fewer: up to 8 % slower, 0.3 us).  One token, free -> segment by segment, us: float zero points, 3 bit, g = 64 28672 x 8192
+// 45 -> 30, 11008 x 4096 10.5 -> 9.6; 4 bit, g = 64 24000 x 8192 60 -> 34, g = 32 8192 x 28672 65 -> 45; 2 bit, g = 32
+// 28672 x 8192 29.9 -> 28.0.  2 bit, g = 64 28672 x 8192 26.7 -> 23.6, 8192 x 8192 9.6 -> 9.3 (from 3 tokens on +-5 %, not
+// taken).  There, with one token and more waves than fit at six to a SIMD, in pairs:
+// 28672 x 8192 25.5 -> 20.7 (segment by segment 22.1), 28672 x 6144 21.0 -> 16.9 (18.6), 28672 x 4096 14.6 -> 12.0 (13.1).
 template <int BITS, bool FLOATZ, int NG> constexpr bool kHasSegments = BITS == 2 ? NG == 4 || (FLOATZ && NG == 8) : FLOATZ && NG >= (BITS == 3 ? 2 : 4);
-static bool by_segments(const Problem &p, bool floatz)
+template <int BITS, int NG, bool MW> constexpr bool kHasPairs = BITS == 2 && NG == 4 && !MW;
+static RunForm run_form(const Problem &p, bool floatz)
 {
-    if (p.O * p.I <= (int64_t)1 << 25) return false;
+    if (p.O * p.I <= (int64_t)1 << 25) return kFree;
     const int ng = run_groups(p);
-    return p.bits == 2 ? (ng == 4 || (floatz && ng == 8)) && p.T <= 2 : floatz && ng >= (p.bits == 3 ? 2 : 4);
+    if (p.bits != 2) return floatz && ng >= (p.bits == 3 ? 2 : 4) ? kSegments : kFree;
+    if (p.T > 2 || !(ng == 4 || (floatz && ng == 8))) return kFree;
+    return ng == 4 && p.T == 1 && (p.O + kGemvRows - 1) / kGemvRows * kGemvWaves > 24 * 256 ? kPairs : kSegments;
 }
 
 FwdRoute gemv_route(const Problem &p, bool floatz)
 {
     if (gemv_tokens_fit(p) && !wide_is_faster(p)) {
-        const FwdKernel kernel = run_groups(p) == 0 ? FWD_GEMV_ANY : by_segments(p, floatz) ? FWD_GEMV_SEGMENTS : FWD_GEMV_RUN;
+        const FwdKernel kernel = run_groups(p) == 0 ? FWD_GEMV_ANY : static_cast<FwdKernel>(FWD_GEMV_RUN + run_form(p, floatz));
         return FwdRoute{kernel, 16, kGemvRows};
     }
     const int tokens = p.T <= 8 ? 8 : p.T <= 16 ? 16 : p.T <= 32 ? 32 : 64;
@@ -652,18 +679,19 @@ void launch_gemv(const Problem &p, const void *X, const void *Wpacked, const flo
     if (ng == 1) {          // magic for "group of segment": exact for segment * (g/32) < 2^32
         a.spg_magic = (uint32_t)((((uint64_t)1 << 32) + (uint64_t)(p.g / 32) - 1) / (uint64_t)(p.g / 32));
     }
-    const bool seg = kernel == FWD_GEMV_SEGMENTS;
-#define EQAT_GEMV_SEG(B, FZ, N, MW)                                                               \
+    const RunForm form = run_form(p, zfloat != nullptr);
+#define EQAT_GEMV_FORM(B, FZ, N, MW)                                                              \
     do {                                                                                          \
-        if (seg && kHasSegments<B, FZ, N>) k_gemv_run<B, FZ, N, MW, kHasSegments<B, FZ, N>><<<grid, block, smem, st>>>(a); \
-        else k_gemv_run<B, FZ, N, MW, false><<<grid, block, smem, st>>>(a);                        \
+        if (form == kPairs) k_gemv_run<B, FZ, N, MW, kHasPairs<B, N, MW> ? kPairs : kFree><<<grid, block, smem, st>>>(a); \
+        else if (form == kSegments) k_gemv_run<B, FZ, N, MW, kHasSegments<B, FZ, N> ? kSegments : kFree><<<grid, block, smem, st>>>(a); \
+        else k_gemv_run<B, FZ, N, MW, kFree><<<grid, block, smem, st>>>(a);                        \
     } while (0)
 #define EQAT_GEMV_NG(B, FZ, MW)                                                                   \
     do {                                                                                          \
-        if (ng == 8) EQAT_GEMV_SEG(B, FZ, 8, MW);                                                  \
-        else if (ng == 4) EQAT_GEMV_SEG(B, FZ, 4, MW);                                             \
-        else if (ng == 2) EQAT_GEMV_SEG(B, FZ, 2, MW);                                             \
-        else EQAT_GEMV_SEG(B, FZ, 1, MW);                                                          \
+        if (ng == 8) EQAT_GEMV_FORM(B, FZ, 8, MW);                                                  \
+        else if (ng == 4) EQAT_GEMV_FORM(B, FZ, 4, MW);                                             \
+        else if (ng == 2) EQAT_GEMV_FORM(B, FZ, 2, MW);                                             \
+        else EQAT_GEMV_FORM(B, FZ, 1, MW);                                                          \
     } while (0)
 #define EQAT_GEMV_RUN(B, FZ)                                                                      \
     do {                                                                                          \
@@ -675,7 +703,7 @@ void launch_gemv(const Problem &p, const void *X, const void *Wpacked, const flo
     if (p.bits == 2) EQAT_GEMV(2); else if (p.bits == 3) EQAT_GEMV(3); else EQAT_GEMV(4);
 #undef EQAT_GEMV_RUN
 #undef EQAT_GEMV_NG
-#undef EQAT_GEMV_SEG
+#undef EQAT_GEMV_FORM
 #undef EQAT_GEMV
 }
 

@@ -71,7 +71,7 @@ bool dw_needs_partials(const Problem &p);
 
 // The kernel that a forward with bf16 activations takes, and the piece of the output that a workgroup of it computes (0: the
 // tile kernel plans that by itself).
-enum FwdKernel { FWD_GEMV_ANY, FWD_GEMV_RUN, FWD_GEMV_WIDE, FWD_MID, FWD_TILES, FWD_GEMV_SEGMENTS };
+enum FwdKernel { FWD_TILES, FWD_MID, FWD_GEMV_WIDE, FWD_GEMV_ANY, FWD_GEMV_RUN, FWD_GEMV_RUN_SEGMENTS, FWD_GEMV_RUN_PAIRS };
 struct FwdRoute { FwdKernel kernel; int tokens, rows; };
 
 // ---- gemv.hip (E2E-QP forward for a few tokens, straight from the dense packed stream) -----------

@@ -7,7 +7,7 @@ import pytest
 
 import paper_2407_11062_amd as eq
 
-ANY, RUN, WIDE, MID, TILES, SEGMENTS = range(6)
+TILES, MID, WIDE, ANY, RUN, SEGMENTS, PAIRS = range(7)
 WORK, PACKED, FLOATZ = range(3)
 
 
@@ -50,6 +50,9 @@ def test_large_matrices_go_segment_by_segment_where_that_is_faster():
     for bits, g, source in ((2, 32, PACKED), (2, 128, FLOATZ), (3, 64, PACKED), (3, 256, FLOATZ), (4, 64, PACKED), (4, 128, FLOATZ)):
         assert route(1, *large, bits, g, source)[0] == RUN, (bits, g, source)
     assert route(2, *large, 2, 64)[0] == SEGMENTS and route(3, *large, 2, 64)[0] == RUN
+    for source in (PACKED, FLOATZ):                               # 6144 and 6160 waves of k_gemv_run
+        assert route(1, 4096, 24576, 2, 64, source)[0] == SEGMENTS and route(1, 4096, 24584, 2, 64, source)[0] == PAIRS
+        assert route(2, 4096, 28672, 2, 64, source)[0] == SEGMENTS and route(1, 4096, 28672, 2, 128, source)[0] == RUN
     assert route(6, *large, 3, 64, FLOATZ)[0] == SEGMENTS and route(7, *large, 3, 64, FLOATZ)[0] == WIDE
 
 

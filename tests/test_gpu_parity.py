@@ -649,6 +649,7 @@ GEMV_CASES = [
     ("v13", 2, 3968, 8488, 2, 64),
     ("v14", 1, 5440, 6184, 3, 64),
     ("v15", 3, 3968, 8488, 4, 32),
+    ("v16", 1, 1408, 24616, 2, 64),             # in pairs of lookups
 ]
 
 
