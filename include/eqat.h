@@ -353,8 +353,9 @@ eqat_status eqat_plan_item(const eqat_desc *d, int gemm, int block, int j, int32
  * Test aid (host only, nothing is launched): the kernel that a forward of this descriptor (bf16 activations, tokens >= 1)
  * takes, from the packed arrays as they are (source 1: eqat_qlinear_fwd, 2: eqat_qlinear_fwd_z) or from codes in the working
  * layout (0: every other forward).  route[3] = { 0 tiled GEMM; 1 GEMM for few tiles; 2 matrix-vector with streamed
- * tokens; 3 matrix-vector, any group; 4 matrix-vector, 5 the same segment by segment, 6 the same in pairs of lookups,
- * tokens,  rows that a workgroup computes (0 for the tiled GEMM) }.  Lets a test assert that its sizes reach the kernel it is about.
+ * tokens; 3 matrix-vector, any group; 4 matrix-vector, 5 the same segment by segment, 6 the same in pairs of lookups;
+ * 7 a re-layout of the codes, then 1,  tokens,  rows that a workgroup computes (0 for the tiled GEMM) }.  Lets a test
+ * assert that its sizes reach the kernel it is about.
  */
 eqat_status eqat_fwd_route(const eqat_desc *d, int source, int32_t *route);
 

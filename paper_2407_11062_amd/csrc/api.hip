@@ -275,7 +275,7 @@ eqat_status eqat_unpack(const eqat_desc *d, const uint8_t *Wpacked, const uint8_
 static eqat::FwdRoute fwd_route(const Problem &p, bool from_packed, bool floatz)
 {
     if (from_packed ? eqat::gemv_applies(p) : eqat::gemv_work_applies(p)) return eqat::gemv_route(p, floatz);
-    if (eqat::mid_applies(p)) return eqat::mid_route(p);
+    if (eqat::mid_applies(p)) return eqat::mid_route(p, from_packed);
     return eqat::FwdRoute{eqat::FWD_TILES, 0, 0};
 }
 
@@ -443,14 +443,14 @@ static eqat_status qlinear_fwd_any(const eqat_desc *d, const void *X, const uint
     if (p.T == 0 && !keep) return EQAT_OK;
     hipStream_t st = (hipStream_t)stream;
     char *w8 = (char *)ws;
-    // the caller's own packed arrays, one kernel
+    // the caller's own packed arrays, one kernel; else re-laid first
     const eqat::FwdKernel kernel = !keep && p.act_bf16 ? fwd_route(p, true, zfloat != nullptr).kernel : eqat::FWD_TILES;
     if (kernel == eqat::FWD_MID) {
         ProfScope ps(eqat::PK_GEMM_FWD, st);
         eqat::launch_mid(p, X, Wpacked, s, zpacked, zfloat, Y, st);
         return launch_status();
     }
-    if (kernel != eqat::FWD_TILES) {
+    if (kernel != eqat::FWD_TILES && kernel != eqat::FWD_RELAY_MID) {
         ProfScope ps(eqat::PK_GEMV, st);
         eqat::launch_gemv(p, X, Wpacked, s, zpacked, zfloat, Y, st);
         return launch_status();

@@ -268,10 +268,10 @@ template <int BITS, int SRC, int BM> void launch_t(MidArgs a, hipStream_t st)
 
 // What a launch with token tiles of `bm` takes, in us: rounds of workgroups (one per compute unit), each 6 us and 1.2 (64
 // tokens) or 1.45 (96) us per 256-wide K step; fitted at 4096, 8192 and 11008 inputs.
+int64_t rounds_of(const Problem &p, int bm) { return (((p.T + bm - 1) / bm) * ((p.O + kMidBN - 1) / kMidBN) + 255) / 256; }
 double launch_us(const Problem &p, int bm)
 {
-    const int64_t tiles = ((p.T + bm - 1) / bm) * ((p.O + kMidBN - 1) / kMidBN), rounds = (tiles + 255) / 256;
-    return (double)rounds * (6.0 + (double)((p.I + kMidBK - 1) / kMidBK) * (bm == 64 ? 1.2 : 1.45));
+    return (double)rounds_of(p, bm) * (6.0 + (double)((p.I + kMidBK - 1) / kMidBK) * (bm == 64 ? 1.2 : 1.45));
 }
 
 int token_tile(const Problem &p) { return launch_us(p, 96) < launch_us(p, 64) ? 96 : 64; }
@@ -296,7 +296,16 @@ MidArgs mid_args(const Problem &p, const void *X, const void *codes, const void 
 
 }  // namespace
 
-FwdRoute mid_route(const Problem &p) { return FwdRoute{FWD_MID, token_tile(p), kMidBN}; }
+// From 3-bit codes as packed, which have no byte alignment, a K step takes 0.45 us longer than from the working layout.  With two
+// rounds of workgroups and three token tiles or more that is more than the re-layout costs, and even the 128 x 128 tiles
+// behind a re-layout are faster then (g = 128, us, as packed / tiles / re-laid: 1300 tokens, 4096 x 11008 198 / 181 / 167;
+// 384 tokens, 11008 x 8192 148 / 136 / 122; 640 tokens, 8192 x 5120 95 / 90 / 83).  With two token tiles every weight is
+// rebuilt twice only: 160 tokens, 28672 x 4096 76 as packed, 81 re-laid.
+FwdRoute mid_route(const Problem &p, bool from_packed)
+{
+    const int tokens = token_tile(p);
+    return FwdRoute{from_packed && p.bits == 3 && p.T > 2 * tokens && rounds_of(p, tokens) > 1 ? FWD_RELAY_MID : FWD_MID, tokens, kMidBN};
+}
 
 double mid_us(const Problem &p) { return std::min(launch_us(p, 96), launch_us(p, 64)); }
 

@@ -71,7 +71,8 @@ bool dw_needs_partials(const Problem &p);
 
 // The kernel that a forward with bf16 activations takes, and the piece of the output that a workgroup of it computes (0: the
 // tile kernel plans that by itself).
-enum FwdKernel { FWD_TILES, FWD_MID, FWD_GEMV_WIDE, FWD_GEMV_ANY, FWD_GEMV_RUN, FWD_GEMV_RUN_SEGMENTS, FWD_GEMV_RUN_PAIRS };
+enum FwdKernel { FWD_TILES, FWD_MID, FWD_GEMV_WIDE, FWD_GEMV_ANY, FWD_GEMV_RUN, FWD_GEMV_RUN_SEGMENTS, FWD_GEMV_RUN_PAIRS,
+                 FWD_RELAY_MID /* the codes re-laid, then FWD_MID from the working layout */ };
 struct FwdRoute { FwdKernel kernel; int tokens, rows; };
 
 // ---- gemv.hip (E2E-QP forward for a few tokens, straight from the dense packed stream) -----------
@@ -89,7 +90,7 @@ inline bool group_by_magic(const Problem &p) { return (p.I / 32) * (p.g / 32) < 
 
 // ---- gemm_mid.hip (forward for some dozens to about a thousand tokens) --------------------------------------------
 bool mid_applies(const Problem &p);
-FwdRoute mid_route(const Problem &p);
+FwdRoute mid_route(const Problem &p, bool from_packed);
 double mid_us(const Problem &p);                  // what it takes, as the rules of dispatch estimate it
 // from the caller's dense stream (exactly one of zpacked / zfloat is not NULL), or from the working layout and (s, z) pairs:
 // bitwise the same results
