@@ -57,7 +57,7 @@ def test_large_matrices_go_segment_by_segment_where_that_is_faster():
 
 
 def test_3_bit_codes_are_relaid_where_two_rounds_rebuild_them():
-    for T, I, O in ((1300, 11008, 4096), (384, 8192, 11008), (385, 3520, 8200)):
+    for T, I, O in ((1300, 11008, 4096), (384, 8192, 11008), (450, 3520, 8200)):
         assert route(T, I, O, 3, 32) == route(T, I, O, 3, 32, FLOATZ) == (RELAY_MID, 96, 128), (T, I, O)
         assert route(T, I, O, 2, 32) == route(T, I, O, 4, 32) == route(T, I, O, 3, 32, WORK) == (MID, 96, 128)
     assert route(333, 4096, 4096, 3, 128)[0] == MID and route(192, 4096, 28672, 3, 128) == (MID, 96, 128)

@@ -770,7 +770,7 @@ WIDE_CASES += [
     ("m6", 289, 3200, 11016, 4, 128),
     ("m7", 48, 288, 2056, 3, 96),
     ("m8", 600, 32, 40, 4, 32),
-    ("m9", 385, 3520, 8200, 3, 32),             # two rounds: 3-bit codes are re-laid first
+    ("m9", 450, 3520, 8200, 3, 32),             # two rounds: 3-bit codes are re-laid first
 ]
 
 
