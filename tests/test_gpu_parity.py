@@ -830,6 +830,13 @@ def test_a_non_finite_zero_point_stays_in_its_row(T, I, O, bits, g):
     ("f1", 33, 288, 65, 3, 96, torch.bfloat16),
     ("f2", 1037, 1056, 1043, 4, 32, torch.float32),
     ("f3", 95, 640, 2040, 2, -1, torch.bfloat16),
+    # contractions of one block (a tile per wave, side by side along either dimension) and of two; at most 32 output features
+    ("f4", 31, 2080, 1043, 3, 32, torch.float32),
+    ("f5", 20, 1056, 2051, 4, 96, torch.bfloat16),
+    ("f6", 40, 2080, 1043, 2, 32, torch.float32),
+    ("f7", 1037, 32, 1043, 2, 32, torch.float32),
+    ("f8", 95, 640, 31, 3, 64, torch.float32),
+    ("f9", 129, 96, 32, 4, 32, torch.bfloat16),
 ])
 def test_fp32_activation_path_at_its_edges(tag, T, I, O, bits, g, wdt):
     X, W, s, z, dY = make_case(tag, T, I, O, bits, g, torch.float32, wdt)
