@@ -151,14 +151,15 @@ template <typename W> __global__ __launch_bounds__(256) void k_f32_dx_short(cons
     }
 }
 
-// C[m][n] = sum_k A(m,k) * B(n,k).  A wave's tile is 32 MB x 32 NB; the NW waves of a workgroup take every NW-th block of
-// 32 of the contraction.
-template <typename OpA, typename OpB, int MB, int NB, int NW>
-__global__ __launch_bounds__(64 * NW) void k_f32_gemm(OpA a, OpB b, float *__restrict__ C, int M, int N, int K)
+// C[m][n] = sum_k A(m,k) * B(n,k).  A wave's tile is 32 MB x 32 NB.  SPLIT: the NW waves of a workgroup share a tile and take
+// every NW-th block of 32 of the contraction; else each has a tile of its own, side by side along M (along_m) or N.
+template <typename OpA, typename OpB, int MB, int NB, int NW, bool SPLIT>
+__global__ __launch_bounds__(64 * NW) void k_f32_gemm(OpA a, OpB b, float *__restrict__ C, int M, int N, int K, bool along_m)
 {
-    __shared__ float red[NW][32][33];
+    __shared__ float red[SPLIT ? NW : 1][32][33];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31, h = lane >> 5;
-    const int m0 = blockIdx.y * (32 * MB), n0 = blockIdx.x * (32 * NB);
+    const int m0 = (!SPLIT && along_m ? blockIdx.y * NW + wave : blockIdx.y) * (32 * MB);
+    const int n0 = (!SPLIT && !along_m ? blockIdx.x * NW + wave : blockIdx.x) * (32 * NB);
     floatx16 acc[MB][NB];
 #pragma unroll
     for (int i = 0; i < MB; ++i)
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(64 * NW) void k_f32_gemm(OpA a, OpB b, float *__res
         for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-    for (int k0 = wave * 32; k0 < K; k0 += 32 * NW) {
+    for (int k0 = SPLIT ? wave * 32 : 0; k0 < K; k0 += SPLIT ? 32 * NW : 32) {
         float va[MB][16], vb[NB][16];
 #pragma unroll
         for (int i = 0; i < MB; ++i) a.load(m0 + 32 * i + r, k0 + 16 * h, va[i]);
@@ -180,6 +181,18 @@ __global__ __launch_bounds__(64 * NW) void k_f32_gemm(OpA a, OpB b, float *__res
                 for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i][e], vb[j][e], acc[i][j], 0, 0, 0);
     }
     // acc[..][e] of a lane: row 8 (e / 4) + 4 h + e % 4, column r of the block
+    if constexpr (!SPLIT) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int m = m0 + 32 * i + 8 * (e >> 2) + 4 * h + (e & 3), n = n0 + 32 * j + r;
+                    if (m < M && n < N) C[(size_t)m * N + n] = acc[i][j][e];
+                }
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -257,10 +270,22 @@ template <typename OpA, typename OpB>
 static void gemm(OpA a, OpB b, float *C, int M, int N, int K, hipStream_t st)
 {
     if (M <= 0 || N <= 0) return;
-    // 64 x 64 per wave reads half as much per product; 32 x 32 until that still gives every compute unit a workgroup
+    // 64 x 64 per wave reads half as much per product; 32 x 32 until that still gives every compute unit a workgroup.  A contraction
+    // shorter than the waves' share leaves waves idle that only wait for the sums: with one block of 32 every wave takes a
+    // tile of its own (2048 x 2048, 4 bit, g = 32, one token: dWhat and its sums 49 -> 29 us), with two a workgroup has two
+    // waves (33 tokens: 48 -> 38; with 256 tiles to go around four are 6 % faster, with three blocks 20 %).
     const int64_t big = ((M + 63) / 64) * (int64_t)((N + 63) / 64);
-    if (big >= 256) k_f32_gemm<OpA, OpB, 2, 2, 4><<<dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, st>>>(a, b, C, M, N, K);
-    else k_f32_gemm<OpA, OpB, 1, 1, 8><<<dim3((N + 31) / 32, (M + 31) / 32), dim3(512), 0, st>>>(a, b, C, M, N, K);
+    const int blocks = (K + 31) / 32;
+    const bool along_m = M >= N;
+    auto go = [&](auto kernel, int side, int waves, bool split) {
+        const int wm = !split && along_m ? waves : 1, wn = !split && !along_m ? waves : 1;
+        const dim3 grid((N + side * wn - 1) / (side * wn), (M + side * wm - 1) / (side * wm));
+        kernel<<<grid, dim3(64 * waves), 0, st>>>(a, b, C, M, N, K, along_m);
+    };
+    if (big < 256) go(k_f32_gemm<OpA, OpB, 1, 1, 8, true>, 32, 8, true);
+    else if (blocks <= 1) go(k_f32_gemm<OpA, OpB, 2, 2, 4, false>, 64, 4, false);
+    else if (blocks == 2 && big >= 512) go(k_f32_gemm<OpA, OpB, 2, 2, 2, true>, 64, 2, true);
+    else go(k_f32_gemm<OpA, OpB, 2, 2, 4, true>, 64, 4, true);
 }
 static RowMajorF32 rows_of(const void *p, int rows, int cols) { return RowMajorF32{(const float *)p, rows, cols, (uint32_t)((size_t)rows * cols * 4)}; }
 static ColMajorF32 cols_of(const void *p, int rows, int cols) { return ColMajorF32{(const float *)p, rows, cols}; }
