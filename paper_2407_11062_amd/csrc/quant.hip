@@ -111,8 +111,10 @@ template <typename WT, int BITS, bool CLAMPBITS, bool WORK, int U = kQuantUnroll
 __global__ __launch_bounds__(256) void k_quantize(const QuantizeBatch batch)
 {
     // Packing walks its matrices from the last weight to the first: the pass that comes before it (min/max, an optimizer
-    // step) leaves the end of W in the 256 MB memory-side cache, not the beginning.
-    const uint32_t bid = WORK ? blockIdx.x : gridDim.x - 1u - blockIdx.x;
+    // step) leaves the end of W in the 256 MB memory-side cache, not the beginning.  Eight blocks at a time, so that every
+    // weight stays with the XCD, and the L2, that it was on (min/max + pack of 4096 x 1024 in fp32: 13.2 -> 12.0 us; front to back 12.0).
+    const uint32_t whole = gridDim.x & ~7u;
+    const uint32_t bid = WORK || blockIdx.x >= whole ? blockIdx.x : whole - 8u - (blockIdx.x & ~7u) + (blockIdx.x & 7u);
     const int slot = batch_slot(batch.first, bid);
     const QuantizeArgs &a = batch.a[slot];
     const uint32_t block = bid - batch.first[slot];
