@@ -614,11 +614,14 @@ template <int BITS, int SRC>
 static void launch_wide_z(int ng, const FwdRoute &way, const GemvArgs &a, hipStream_t st)
 {
     const bool two = way.rows != kGemvRows;
+    // the working layout comes here from 17 tokens on
 #define EQAT_WIDE_NB(NG)                                                                          \
     do {                                                                                          \
-        if (way.tokens == 8) launch_wide_t<BITS, SRC, NG, 8, 1>(a, st);                           \
-        else if (way.tokens == 16) launch_wide_t<BITS, SRC, NG, 16, 1>(a, st);                    \
-        else if (way.tokens == 32 && !two) launch_wide_t<BITS, SRC, NG, 32, 1>(a, st);            \
+        if constexpr (SRC != kWorking) {                                                          \
+            if (way.tokens == 8) { launch_wide_t<BITS, SRC, NG, 8, 1>(a, st); break; }            \
+            if (way.tokens == 16) { launch_wide_t<BITS, SRC, NG, 16, 1>(a, st); break; }          \
+        }                                                                                         \
+        if (way.tokens == 32 && !two) launch_wide_t<BITS, SRC, NG, 32, 1>(a, st);            \
         else if (way.tokens == 32) launch_wide_t<BITS, SRC, NG, 32, 2>(a, st);                    \
         else if (!two) launch_wide_t<BITS, SRC, NG, 64, 1>(a, st);                                \
         else launch_wide_t<BITS, SRC, NG, 64, 2>(a, st);                                          \
