@@ -135,9 +135,17 @@ def _p(t):
     return t.data_ptr()
 
 
+try:
+    _raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+except AttributeError:                               # not public: a torch without them has the Stream object
+    def _raw_stream(device):
+        return torch.cuda.current_stream(device).cuda_stream
+    _device = torch.cuda.current_device
+
+
 def _stream():
     """Handle of torch's current stream on the current device."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_device())
 
 
 def _check(fn, status):

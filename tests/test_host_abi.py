@@ -261,3 +261,20 @@ def test_binding_fails_loudly_without_the_library(monkeypatch, tmp_path):
     monkeypatch.setattr(eq, "LIB_PATH", str(tmp_path / "libeqat.so"))
     with pytest.raises(RuntimeError, match="no fallback"):
         eq.lib()
+
+
+def test_binding_finds_the_current_stream_without_torchs_private_calls(monkeypatch):
+    import importlib.util
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.delattr(torch._C, "_cuda_getDevice", raising=False)
+    spec = importlib.util.spec_from_file_location("eqat_binding_copy", eq.__file__)
+    copy = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(copy)
+
+    class Stream:
+        def __init__(self, device):
+            self.cuda_stream = 0x1000 + device
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
+    monkeypatch.setattr(copy, "_device", lambda: 3)
+    assert copy._stream() == 0x1003
