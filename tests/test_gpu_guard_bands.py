@@ -15,6 +15,7 @@ import torch
 
 import paper_2407_11062_amd as eq
 from paper_2407_11062_amd import synth
+from test_fwd_route import MID, PAIRS, RELAY_MID, WIDE, route
 
 pytestmark = pytest.mark.gpu
 GUARD = 4096
@@ -56,11 +57,19 @@ CASES = [
     ("cut_tiles", 4400, 512, 4104, 2, 64, torch.bfloat16, torch.bfloat16),
     ("walk_odd_k", 4400, 320, 4104, 2, 64, torch.bfloat16, torch.bfloat16),
     ("split_dw_tiles", 2100, 4352, 4104, 3, 64, torch.bfloat16, torch.bfloat16),     # 289 dW tiles, 33 K tiles: split along the tokens
+    ("wide", 40, 1088, 72, 2, 64, torch.bfloat16, torch.bfloat16),                  # the forward on k_gemv_wide ...
+    ("mid_64", 100, 1056, 200, 3, 32, torch.bfloat16, torch.bfloat16),              # ... k_gemm_mid, 64- and 96-token tiles
+    ("mid_96", 381, 1056, 5480, 4, 32, torch.bfloat16, torch.bfloat16),
+    ("mid_relaid", 450, 3520, 8200, 3, 32, torch.bfloat16, torch.bfloat16),         # ... behind a re-layout of the codes
+    ("fp32_short", 40, 1056, 31, 4, 32, torch.float32, torch.float32),
+    ("fp32_tile_per_wave", 20, 2080, 1043, 2, 32, torch.float32, torch.float32),
 ]
+FWD_ROUTES = {"wide": (WIDE, 64, 16), "mid_64": (MID, 64, 128), "mid_96": (MID, 96, 128), "mid_relaid": (RELAY_MID, 96, 128)}
 
 
 @pytest.mark.parametrize("tag,T,I,O,bits,g,act,wdt", CASES)
 def test_nothing_is_written_outside_outputs_and_workspaces(tag, T, I, O, bits, g, act, wdt):
+    assert tag not in FWD_ROUTES or route(T, I, O, bits, g) == FWD_ROUTES[tag]
     G = 1 if g == -1 else I // g
     gd = Guarded()
     W = gd.new((O, I), wdt, synth.normal((O, I), 0.02, synth.seed_of("guard", tag, "W"), wdt).cuda())
@@ -131,8 +140,10 @@ def test_nothing_is_written_outside_outputs_and_workspaces(tag, T, I, O, bits, g
     gd.check("eqat_block_ap_update")
 
 
-@pytest.mark.parametrize("T,I,O,bits,g", [(1, 4096, 136, 2, 64), (5, 1184, 72, 3, 32), (16, 2048, 24, 4, 128), (3, 576, 40, 2, 96)])
+@pytest.mark.parametrize("T,I,O,bits,g", [(1, 4096, 136, 2, 64), (5, 1184, 72, 3, 32), (16, 2048, 24, 4, 128), (3, 576, 40, 2, 96),
+                                          (1, 1408, 24616, 2, 64), (8, 2080, 72, 4, 32), (24, 1056, 8208, 4, 32)])
 def test_few_token_forward_stays_inside_y(T, I, O, bits, g):
+    assert O < 24000 or route(T, I, O, bits, g)[0] == PAIRS
     gd = Guarded()
     gen = torch.Generator(device="cuda"); gen.manual_seed(T * 1000 + O)
     Wp = torch.randint(0, 256, (O, I * bits // 8), dtype=torch.uint8, device="cuda", generator=gen)

@@ -12,6 +12,7 @@ import torch
 import oracle
 import paper_2407_11062_amd as eq
 from paper_2407_11062_amd import synth
+from test_fwd_route import ANY, FLOATZ, MID, PACKED, PAIRS, RELAY_MID, RUN, SEGMENTS, TILES, WIDE, WORK, route
 
 pytestmark = pytest.mark.gpu
 
@@ -277,13 +278,16 @@ def test_cut_tiles_are_deterministic_and_ignore_what_the_workspace_held(case):
             assert torch.equal(out[k], outs[0][1][k]), k
 
 
+@pytest.mark.parametrize("T", [40, 300])
 @pytest.mark.parametrize("I,O", [(352, 200), (320, 192), (96, 72)])
-def test_a_non_finite_token_does_not_leak_into_its_neighbour(I, O):
+def test_a_non_finite_token_does_not_leak_into_its_neighbour(I, O, T):
     """K tiles are 64 wide and two are multiplied per trip: with a contraction length that is not a multiple of 128 the
     last K tile (and a padding tile) reach past the end of an activation row, i.e. into the next row.  The weights there
     are zero, but 0 * Inf is NaN: the chunks past K must not be loaded at all.  Row 7 of X and of dY carries Inf and
-    NaN; every other row of Y (fwd, K = I) and of dX (K = O) must come out as without them."""
-    T, bits, g = 40, 2, 32
+    NaN; every other row of Y (fwd, K = I) and of dX (K = O) must come out as without them.  The forward of 40 tokens takes
+    k_gemv_wide (runs of 512 inputs, cut short here) or k_gemm_mid, that of 300 and both dX the tile kernel."""
+    bits, g = 2, 32
+    assert route(T, I, O, bits, g)[0] == (TILES if T == 300 else MID if I == 96 else WIDE)
     X, W, s, z, dY = make_case(("leak", I, O), T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
     Xd, Wd, sd, zd, dYd = dev(X), dev(W), dev(s), dev(z), dev(dY)
     Y0 = eq.eqat_fq_linear_fwd(Xd, Wd, sd, zd, bits, g)
@@ -638,7 +642,8 @@ GEMV_CASES = [
     ("v5", 3, 384, 40, 2, -1),             # one group per row
     ("v6", 1, 96, 8, 3, 96),               # a single, partly filled chunk; one 8-row block
     ("v7", 4, 2048, 264, 4, 32),
-    ("v8", 7, 160, 24, 3, 32),
+    ("v8", 7, 160, 24, 3, 32),                  # k_gemv_wide
+    ("v17", 6, 160, 24, 3, 32),
     # a row gets one wave per 1024 inputs, up to 16: five waves, eleven (the last run ragged), eight with 4-bit codes,
     # and more runs than waves (two trips for some waves: the down projection of the 70B block)
     ("v9", 2, 5120, 48, 2, 64),
@@ -653,8 +658,14 @@ GEMV_CASES = [
 ]
 
 
+# kernels with packed and with float zero points where they are not the plain k_gemv_run
+GEMV_KERNELS = {"v4": (WIDE, WIDE), "v5": (ANY, ANY), "v6": (ANY, ANY), "v8": (WIDE, WIDE), "v13": (SEGMENTS, SEGMENTS),
+                "v14": (RUN, SEGMENTS), "v15": (RUN, SEGMENTS), "v16": (PAIRS, PAIRS)}
+
+
 @pytest.mark.parametrize("tag,T,I,O,bits,g", GEMV_CASES)
 def test_e2e_qp_forward_few_tokens(tag, T, I, O, bits, g):
+    assert (route(T, I, O, bits, g, PACKED)[0], route(T, I, O, bits, g, FLOATZ)[0]) == GEMV_KERNELS.get(tag, (RUN, RUN))
     X, W, s, z, dY = make_case(tag, T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
     qmax = 2 ** bits - 1
     z = z.clamp(0, qmax)
@@ -677,16 +688,20 @@ def test_e2e_qp_forward_few_tokens(tag, T, I, O, bits, g):
         assert relerr(Yk, npf(Y[T - 1:T]).astype(np.float64)) <= 1e-2
 
 
-def test_few_token_kernel_and_gemm_agree_across_the_switch():
-    # 16 tokens run the matrix-vector kernel, 17 the tiled GEMM: the first 16 rows must agree to bf16 accuracy
-    X, W, s, z, dY = make_case("switch", 17, 512, 64, 2, 64, torch.bfloat16, torch.bfloat16)
+@pytest.mark.parametrize("I,gemm", [(512, TILES), (2048, MID)])
+@pytest.mark.parametrize("T,few", [(4, RUN), (16, WIDE), (17, WIDE)])
+def test_few_token_kernel_and_gemm_agree_across_the_switch(T, few, I, gemm):
+    # the first tokens of a call of 72, which runs a GEMM (the tiles or k_gemm_mid), and alone, where they take one of the two
+    # matrix-vector kernels: equal to bf16 accuracy
+    assert route(T, I, 64, 2, 64)[0] == few and route(72, I, 64, 2, 64)[0] == gemm
+    X, W, s, z, dY = make_case(("switch", I), 72, I, 64, 2, 64, torch.bfloat16, torch.bfloat16)
     z = z.clamp(0, 3)
     sd = dev(s)
     Wp, zp = eq.eqat_pack(dev(W), sd, dev(z), 2, 64)
     Xd = dev(X)
-    Y17 = eq.eqat_qlinear_fwd(Xd, Wp, sd, zp, 2, 64)
-    Y16 = eq.eqat_qlinear_fwd(Xd[:16].contiguous(), Wp, sd, zp, 2, 64)
-    assert relerr(Y16, npf(Y17[:16]).astype(np.float64)) <= 1e-2
+    Yall = eq.eqat_qlinear_fwd(Xd, Wp, sd, zp, 2, 64)
+    Yfew = eq.eqat_qlinear_fwd(Xd[:T].contiguous(), Wp, sd, zp, 2, 64)
+    assert relerr(Yfew, npf(Yall[:T]).astype(np.float64)) <= 1e-2
 
 
 # ---------------------------------------------------------------- the rest of the paper's (N, g) grid; stacked linears
@@ -706,9 +721,11 @@ def test_grid_rest_block_ap_and_e2e(bits, g):
 
 def test_stacked_linears_equal_their_parts():
     """q|k|v (or gate|up) share their input; groups run along the input dimension, so the three weight matrices stacked
-    along the output dimension are ONE quantized linear whose every per-row result is that of the part it came from."""
+    along the output dimension are ONE quantized linear whose every per-row result is that of the part it came from:
+    bitwise where stack and parts take the same kernel with the same split of the contraction, as here (whole tiles)."""
     bits, g, T, I = 2, 64, 300, 256
     parts = [("q", 264), ("k", 40), ("v", 40)]
+    assert all(route(T, I, O, bits, g, WORK)[0] == TILES for O in (264, 40, 344))
     Xs = synth.normal((T, I), 1.0, synth.seed_of("stack", "X"), torch.bfloat16)
     Ws, ss, zs, dYs = [], [], [], []
     for name, O in parts:
@@ -740,42 +757,75 @@ def test_stacked_linears_equal_their_parts():
     assert relerr(out["dX"], ref["dX"]) <= TOL[torch.bfloat16]
 
 
+@pytest.mark.parametrize("T,I,outs,part,stack", [(48, 1024, (4096, 1024, 1024), WIDE, MID), (333, 1056, (5480, 2760, 2760), MID, TILES)])
+def test_stacked_linears_agree_with_their_parts_where_the_kernel_changes(T, I, outs, part, stack):
+    """The kernel of a forward depends on the number of output rows, and with it the order of the sums: a stack then agrees
+    with its parts to rounding, and both with the oracle."""
+    bits, g = 2, 32
+    assert route(T, I, outs[0], bits, g)[0] == part and route(T, I, sum(outs), bits, g)[0] == stack
+    X = synth.normal((T, I), 1.0, synth.seed_of("stackx", T), torch.bfloat16)
+    Xd, refs, Ys, Wps, zps, ss = dev(X), [], [], [], [], []
+    for k, O in enumerate(outs):
+        _, W, s, z, _ = make_case(("stackx", T, k), 1, I, O, bits, g, torch.bfloat16, torch.bfloat16)
+        Wp, zp = eq.eqat_pack(dev(W), dev(s), dev(z), bits, g)
+        refs.append(oracle.qlinear_fwd(npf(X), Wp.cpu().numpy(), s.numpy(), zp.cpu().numpy(), bits, g))
+        Ys.append(eq.eqat_qlinear_fwd(Xd, Wp, dev(s), zp, bits, g))
+        Wps.append(Wp), zps.append(zp), ss.append(dev(s))
+    Y = eq.eqat_qlinear_fwd(Xd, torch.cat(Wps), torch.cat(ss), torch.cat(zps), bits, g)
+    ref = np.concatenate(refs, axis=1)
+    assert relerr(Y, ref) <= TOL[torch.bfloat16] and relerr(torch.cat(Ys, dim=1), ref) <= TOL[torch.bfloat16]
+    # the two differ by the rounding of Y to bf16 (2^-8 of an element at most) and by that of binary32 sums
+    assert relerr(Y, npf(torch.cat(Ys, dim=1)).astype(np.float64)) <= 1e-2
+
+
 # ---------------------------------------------------------------- forward for 8 to 64 tokens
-# ends of the 16-token blocks, last runs of 512 inputs that are cut short (and shorter than a lane group), more runs than
-# waves, one and two row blocks per workgroup with a ragged last one, token rows that do not fit LDS at once
+# k_gemv_wide: ends of the 16-token blocks, last runs of 512 inputs that are cut short (and shorter than a lane group), more runs
+# than waves, one and two row blocks per workgroup with a ragged last one, token rows that do not fit LDS at once, 4-bit codes
+# of many rows
 WIDE_CASES = [
-    ("w0", 8, 4096, 40, 2, 64),
-    ("w1", 16, 1056, 24, 3, 32),
-    ("w2", 9, 5120, 48, 3, 128),
-    ("w3", 17, 544, 40, 4, 32),
-    ("w4", 32, 640, 8200, 2, 128),
-    ("w5", 33, 1152, 24, 4, -1),
-    ("w6", 64, 320, 8216, 3, 64),
-    ("w7", 64, 4736, 56, 2, 64),
-    ("w8", 1, 8192, 24576, 4, 128),
-    ("w9", 5, 8192, 40, 3, 64),
+    ("w0", 8, 4096, 40, 2, 64, (WIDE, 8, 16)),
+    ("w1", 16, 1056, 24, 3, 32, (WIDE, 16, 16)),
+    ("w2", 9, 5120, 48, 3, 128, (WIDE, 16, 16)),
+    ("w3", 17, 544, 40, 4, 32, (WIDE, 32, 16)),
+    ("w4", 32, 640, 8200, 2, 128, (WIDE, 32, 32)),
+    ("w5", 33, 1152, 24, 4, -1, (WIDE, 64, 16)),
+    ("w6", 64, 4096, 8216, 3, 64, (WIDE, 64, 32)),
+    ("w7", 64, 4736, 56, 2, 64, (WIDE, 64, 16)),
+    ("w8", 1, 8192, 24592, 4, 128, (WIDE, 8, 16)),
+    ("w9", 5, 8192, 40, 3, 64, (WIDE, 8, 16)),
+    ("w10", 8, 2080, 72, 4, 32, (WIDE, 8, 16)),
+    ("w11", 24, 1056, 8208, 4, 32, (WIDE, 32, 32)),
+    ("w12", 64, 4128, 8216, 2, 32, (WIDE, 64, 32)),
 ]
-
-
-# k_gemm_mid: one K step and a piece of one, ragged last token tiles of 64 and 96 and weight tiles, a row that ends inside a
-# 16-byte chunk of 3-bit codes, groups of 32, groups wider than a K step and not dividing it, packed zero points that
-# straddle words, two rounds of workgroups, group sizes k_gemv_wide does not take
+# k_gemm_mid: few K steps and a piece of one, ragged last token tiles of 64 and 96 and weight tiles at every width of codes, a row
+# that ends inside a 16-byte chunk of 3-bit codes, groups of 32, groups wider than a K step and not dividing it, packed zero
+# points that straddle words, two rounds of workgroups, group sizes k_gemv_wide does not take
 WIDE_CASES += [
-    ("m0", 65, 256, 136, 2, 64),
-    ("m1", 100, 1056, 200, 3, 32),
-    ("m2", 333, 544, 264, 4, 32),
-    ("m3", 70, 1440, 72, 2, 288),
-    ("m4", 129, 1152, 1000, 3, -1),
-    ("m5", 97, 352, 24584, 2, 32),
-    ("m6", 289, 3200, 11016, 4, 128),
-    ("m7", 48, 288, 2056, 3, 96),
-    ("m8", 600, 32, 40, 4, 32),
-    ("m9", 450, 3520, 8200, 3, 32),             # two rounds: 3-bit codes are re-laid first
+    ("m1", 100, 1056, 200, 3, 32, (MID, 64, 128)),
+    ("m3", 70, 1440, 72, 2, 288, (MID, 64, 128)),
+    ("m4", 129, 1152, 1000, 3, -1, (MID, 64, 128)),
+    ("m6", 289, 3200, 11016, 4, 128, (MID, 64, 128)),
+    ("m7", 48, 288, 2056, 3, 96, (MID, 64, 128)),
+    ("m9", 450, 3520, 8200, 3, 32, (RELAY_MID, 96, 128)),       # 3-bit codes are re-laid first
+    ("m10", 381, 1056, 5480, 4, 32, (MID, 96, 128)),
+    ("m11", 381, 1056, 5480, 2, 32, (MID, 96, 128)),
+    ("m12", 381, 1056, 5480, 3, 96, (MID, 96, 128)),
+    ("m13", 70, 1056, 136, 4, 32, (MID, 64, 128)),
+]
+# sizes beside these, which k_gemm_mid's rule leaves to others
+WIDE_CASES += [
+    ("m0", 65, 256, 136, 2, 64, (TILES, 0, 0)),
+    ("m2", 333, 544, 264, 4, 32, (TILES, 0, 0)),
+    ("m5", 97, 352, 24584, 2, 32, (TILES, 0, 0)),
+    ("m8", 600, 32, 40, 4, 32, (TILES, 0, 0)),
+    ("n6", 64, 320, 8216, 3, 64, (MID, 64, 128)),
+    ("n8", 1, 8192, 24576, 4, 128, (RUN, 16, 16)),
 ]
 
 
-@pytest.mark.parametrize("tag,T,I,O,bits,g", WIDE_CASES)
-def test_forward_of_a_few_dozen_tokens(tag, T, I, O, bits, g):
+@pytest.mark.parametrize("tag,T,I,O,bits,g,way", WIDE_CASES)
+def test_forward_of_a_few_dozen_tokens(tag, T, I, O, bits, g, way):
+    assert route(T, I, O, bits, g, PACKED) == route(T, I, O, bits, g, FLOATZ) == way
     X, W, s, z, dY = make_case(tag, T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
     Xd, Wd, sd, zd = dev(X), dev(W), dev(s), dev(z)
     Wp, zp = eq.eqat_pack(Wd, sd, zd, bits, g)
