@@ -183,10 +183,11 @@ eqat_status eqat_unpack(const eqat_desc *d, const uint8_t *Wpacked, const uint8_
 
 /*
  * E2E-QP forward (Sec. 3.3): What = (w_q - z) * s from the packed codes, Y = X * What^T.
- * With bf16 activations the packed arrays are read as they are, by one kernel and without the workspace, up to some hundred
- * tokens: up to 16 (any group that is 32, 64 or a multiple of 128, else while T * I * 2 <= 64 KiB) and for some dozens by a
- * memory-bound matrix-vector kernel (the decode-time case of the paper's App. "Speedup with BitBLAS"), beyond by a GEMM
- * made for few tiles, where it is the faster one; otherwise the codes are re-laid and the tiled MFMA GEMM runs.
+ * With bf16 activations the packed arrays are read as they are, by one kernel and without the workspace: up to 16 tokens
+ * (any group that is 32, 64 or a multiple of 128, else while T * I * 2 <= 64 KiB) and for some dozens by a memory-bound
+ * matrix-vector kernel (the decode-time case of the paper's App. "Speedup with BitBLAS"), beyond by a GEMM made for few
+ * output tiles, where it is the faster one (3-bit codes of three or more token tiles in two rounds of workgroups are
+ * re-laid first); otherwise the codes are re-laid and the tiled MFMA GEMM runs.  eqat_fwd_route tells which.
  */
 eqat_status eqat_qlinear_fwd(const eqat_desc *d, const void *X, const uint8_t *Wpacked, const float *s,
                              const uint8_t *zpacked, void *Y, void *ws, size_t ws_bytes, void *stream);

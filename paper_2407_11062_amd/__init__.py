@@ -123,9 +123,9 @@ def _tdt(code: int):
     return torch.bfloat16 if code == BF16 else torch.float32
 
 
-# The short calls (one token, small linears) are bound by what happens here, not by the kernel: 8.7 us per call with a
-# Stream object, a descriptor and a c_void_p per argument made each time, against 3.6 us for a 4096 x 4096 matrix-vector
-# product on the GPU.  Pointers therefore travel as plain integers (the argument types convert them), the raw stream handle
+# The short calls (one token, small linears) would be bound by what happens here, not by the kernel: 8.7 us per call with a
+# Stream object, a descriptor and a c_void_p per argument made each time, against 4.6 us for a 4096 x 4096 matrix-vector
+# product on the GPU; 5.5 us as it is.  Pointers therefore travel as plain integers (the argument types convert them), the raw stream handle
 # is asked for directly, and descriptors of equal contents are made once.
 def _p(t):
     if t is None:

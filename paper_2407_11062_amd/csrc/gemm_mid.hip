@@ -1,5 +1,5 @@
-// Forward for some dozens to about a thousand tokens (prompt processing, short training batches):
-// Y[T,O] = X[T,I] * What[O,I]^T.
+// Forward for few output tiles (prompt processing, short training batches: more than 32 tokens, at most 512 tiles of 128 x 128
+// and two rounds of workgroups here, see mid_applies): Y[T,O] = X[T,I] * What[O,I]^T.
 //
 // The 256 x 256 and 128 x 128 tile kernels have too few tiles here (333 tokens x 4096 rows: 96 on 256 compute units) and
 // every workgroup walks the whole contraction: 64 K tiles of 0.55 us whatever the fill.  This kernel puts the spare
@@ -312,7 +312,9 @@ double mid_us(const Problem &p) { return std::min(launch_us(p, 96), launch_us(p,
 // Against the 128 x 128-tile kernel, which takes 0.55 us per 64-wide K tile while a compute unit has one tile at most and
 // 0.9 or more beyond that (11008 x 4096: 256 tokens, 172 tiles: 43 us there, 46-49 here in two rounds; 288 tokens, 258
 // tiles: 61 and 47; 400 tokens: 63 and 57).  More than two rounds here, or more than two tiles per compute unit there: the
-// 256 x 256 tiles are the better kernel (11008 x 4096, 515 tokens: 68 us in tiles, 84 here).
+// 256 x 256 tiles are the better kernel (11008 x 4096, 515 tokens: 68 us in tiles, 84 here).  The GEMMs alone are compared:
+// a forward from the packed arrays saves the re-layout as well and would gain a little earlier, but every forward entry point
+// shares the rule, so that their results stay bitwise equal.
 bool mid_applies(const Problem &p)
 {
     if (!p.act_bf16 || !group_by_magic(p) || p.T <= 32) return false;

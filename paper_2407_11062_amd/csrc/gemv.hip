@@ -13,7 +13,8 @@
 // in the four bytes of a register, and the table turns them into two registers, the pairs (k, k + 4) and (k + 8, k + 12):
 // the four first pairs are the first eight codes of the word in the order 0 4 1 5 2 6 3 7, the four second pairs the other
 // eight in the same order.  MFMA does not care in which order k runs as long as both operands agree, so the token rows
-// are staged in LDS with every eight values in that order (slot_code()), a permutation inside 16 bytes.  4-bit codes come
+// are staged in LDS with every eight values in that order (slot_code()), a permutation inside 16 bytes; k_gemv_run has
+// another order beside it (kPairs).  4-bit codes come
 // out of their converts in any order wanted, and the dense 3-bit stream, which has no byte alignment at all, is taken twelve
 // bits at a time (spread_3bit): both keep the natural order.
 #include "common.h"

@@ -88,7 +88,7 @@ void launch_gemv(const Problem &p, const void *X, const void *Wpacked, const flo
 // whether mulhi(segment, ceil(2^32 / (g / 32))) is the group of every segment of a row
 inline bool group_by_magic(const Problem &p) { return (p.I / 32) * (p.g / 32) < ((int64_t)1 << 32); }
 
-// ---- gemm_mid.hip (forward for some dozens to about a thousand tokens) --------------------------------------------
+// ---- gemm_mid.hip (forward for few output tiles) --------------------------------------------
 bool mid_applies(const Problem &p);
 FwdRoute mid_route(const Problem &p, bool from_packed);
 double mid_us(const Problem &p);                  // what it takes, as the rules of dispatch estimate it

@@ -3,6 +3,8 @@
   python -m paper_2407_11062_amd.profsum trace   <prefix>_kernel_stats.csv  <out.txt>  "<command that was profiled>" [bench.json]
   python -m paper_2407_11062_amd.profsum traffic <out.json> <workload> <fetch.csv> <write.csv> <copy_fetch.csv> <copy_write.csv> <copy_bytes>
 
+  python -m paper_2407_11062_amd.profsum launches <out.txt> "<heading>" <passes> <prefix>_kernel_trace.csv
+
   python -m paper_2407_11062_amd.profsum counters <out.txt> "<command that was profiled>" <counter_collection.csv> [more.csv ...]
 
 `trace`   one line per kernel (calls, total and average duration, share) from `rocprofv3 --kernel-trace --stats`,
@@ -13,6 +15,9 @@
 `traffic-rows` the same two counters for every library kernel of a run with launches of several sizes (the benchmark's
           rows): one line per kernel and grid size (work-items of the launch), so that each matrix shape stands alone.
           python -m paper_2407_11062_amd.profsum traffic-rows <out.txt> "<command>" <fetch.csv> <write.csv> <copy_fetch.csv> <copy_write.csv> <copy_bytes>
+`launches` appends one section: a line per library kernel and launch shape (workgroups, their size), with the number of launches,
+          the median and the shortest, from the kernel trace of a run of `passes` passes over some calls; launches that are
+          no multiple of the passes belong to the preparation and are left out.
 `counters` mean reading per launch of every counter in the given `rocprofv3 --pmc` CSV files, per library kernel, plus
           the MFMA pipe's share of the busy cycles where both counters are present.
 """
@@ -151,6 +156,24 @@ def counters(out_txt, command, *csvs) -> None:
     print(open(out_txt).read())
 
 
+def launches(out_txt: str, heading: str, passes: str, trace_csv: str) -> None:
+    times = collections.OrderedDict()
+    for r in csv.DictReader(open(trace_csv)):
+        if "eqat" not in r["Kernel_Name"]:
+            continue
+        name = r["Kernel_Name"].replace("void ", "").replace("eqat::", "").replace("(anonymous namespace)::", "").split("(")[0]
+        shape = tuple(int(r[k]) for k in ("Grid_Size_X", "Grid_Size_Y", "Workgroup_Size_X"))
+        times.setdefault((name, shape), []).append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
+    with open(out_txt, "a") as f:
+        f.write("\n%s\n" % heading)
+        for (name, (gx, gy, wx)), v in times.items():
+            if len(v) % int(passes) != 0:
+                continue
+            v.sort()
+            f.write("  %-60s workgroups %6d x %3d of %4d  launches %3d  median %8.2f us  min %8.2f us\n"
+                    % (name[:60], gx // wx, gy, wx, len(v), v[len(v) // 2], v[0]))
+
+
 def main(argv):
     if len(argv) >= 4 and argv[0] == "trace":
         trace(*argv[1:5])
@@ -158,6 +181,8 @@ def main(argv):
         traffic(*argv[1:])
     elif len(argv) == 8 and argv[0] == "traffic-rows":
         traffic_rows(*argv[1:])
+    elif len(argv) == 5 and argv[0] == "launches":
+        launches(*argv[1:])
     elif len(argv) >= 4 and argv[0] == "counters":
         counters(*argv[1:])
     else:
