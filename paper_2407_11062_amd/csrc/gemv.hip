@@ -333,6 +333,9 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
 // Measured against what these sizes took before (codes re-laid, then a 128 x 128-tile GEMM on a few compute units):
 // 8 tokens, 3 bit: 13824 x 5120 68 -> 16 us; 8 tokens, 4 bit: 4096 x 11008 127 -> 14 us; 32 tokens, 2 bit: 4096 x 4096
 // 46 -> 10 us, 28672 x 8192 109 -> 52 us; 64 tokens, 2 bit: 4096 x 4096 46 -> 16 us, 28672 x 8192 110 -> 96 us.
+// Groups of 32 with two row blocks (four step sizes and zero points per run and block) spill 100 to 180 bytes a lane and are
+// the slower for it, but not slower than what they replace: 32 tokens, 28672 x 8192, 2 bit: g = 128 105 -> 53 us, g = 32
+// 128 -> 89; 8192 x 8192, 4 bit: 96 -> 21, 100 -> 34.
 constexpr int kWideRS = 4;              // segments per lane and run
 template <int TR> constexpr int kWideSub = TR >= 64 ? 1 : TR >= 16 ? 2 : 4;              // TR: token rows of the patch
 template <int TR> constexpr int kWideRowBytes = 4 * kWideSub<TR> * 64 + 16;
@@ -566,21 +569,25 @@ bool gemv_applies(const Problem &p)
 // groups per run of k_gemv_run (256 inputs of a lane); 0 = a group size it does not take
 static int run_groups(const Problem &p) { return p.g == 32 ? 8 : p.g == 64 ? 4 : p.g == 128 ? 2 : p.g % 256 == 0 ? 1 : 0; }
 
-// Forms of k_gemv_run that exist beside the free one, and when they are taken: more than 2^25 weights (the chip full of waves;
-// fewer: up to 8 % slower, 0.3 us).  One token, free -> segment by segment, us: float zero points, 3 bit, g = 64 28672 x 8192
-// 45 -> 30, 11008 x 4096 10.5 -> 9.6; 4 bit, g = 64 24000 x 8192 60 -> 34, g = 32 8192 x 28672 65 -> 45; 2 bit, g = 32
-// 28672 x 8192 29.9 -> 28.0.  2 bit, g = 64 28672 x 8192 26.7 -> 23.6, 8192 x 8192 9.6 -> 9.3 (from 3 tokens on +-5 %, not
-// taken).  There, with one token and more waves than fit at six to a SIMD, in pairs:
-// 28672 x 8192 25.5 -> 20.7 (segment by segment 22.1), 28672 x 6144 21.0 -> 16.9 (18.6), 28672 x 4096 14.6 -> 12.0 (13.1).
+// Forms of k_gemv_run that exist beside the free one, and when they are taken.
+// kSegments: more than 2^25 weights (the chip full of waves; fewer: up to 8 % slower, 0.3 us).  One token, free -> segment by
+// segment, us: float zero points, 3 bit, g = 64 28672 x 8192 45 -> 30, 11008 x 4096 10.5 -> 9.6; 4 bit, g = 64 24000 x 8192
+// 60 -> 34, g = 32 8192 x 28672 65 -> 45; 2 bit, g = 32 28672 x 8192 29.9 -> 28.0.  2 bit, g = 64 28672 x 8192 26.7 -> 23.6,
+// 8192 x 8192 9.6 -> 9.3 (from 3 tokens on +-5 %, not taken).
+// kPairs: 2 bit, g = 64, more waves than fit at six to a SIMD, and one token, or 8 KB of tokens, to scatter (from four tokens on
+// only if all waves fit at eight: 40000 x 512, 6 tokens 8.4 us free, 9.8 in pairs).  One token: 28672 x 8192 25.5 -> 20.7
+// (segment by segment 22.1), 28672 x 6144 21.0 -> 16.9 (18.6), 28672 x 4096 14.6 -> 12.0 (13.1); two: 60000 x 1024 12.5 -> 11.1
+// (free); four: 28672 x 512 6.8 -> 5.7 (free).
 template <int BITS, bool FLOATZ, int NG> constexpr bool kHasSegments = BITS == 2 ? NG == 4 || (FLOATZ && NG == 8) : FLOATZ && NG >= (BITS == 3 ? 2 : 4);
 template <int BITS, int NG, bool MW> constexpr bool kHasPairs = BITS == 2 && NG == 4 && !MW;
 static RunForm run_form(const Problem &p, bool floatz)
 {
-    if (p.O * p.I <= (int64_t)1 << 25) return kFree;
     const int ng = run_groups(p);
+    const int64_t waves = (p.O + kGemvRows - 1) / kGemvRows * kGemvWaves;
+    if (p.bits == 2 && ng == 4 && waves > 24 * 256 && (p.T == 1 || (p.T * p.I <= 4096 && (p.T <= 3 || waves <= 32 * 256)))) return kPairs;
+    if (p.O * p.I <= (int64_t)1 << 25) return kFree;
     if (p.bits != 2) return floatz && ng >= (p.bits == 3 ? 2 : 4) ? kSegments : kFree;
-    if (p.T > 2 || !(ng == 4 || (floatz && ng == 8))) return kFree;
-    return ng == 4 && p.T == 1 && (p.O + kGemvRows - 1) / kGemvRows * kGemvWaves > 24 * 256 ? kPairs : kSegments;
+    return p.T <= 2 && (ng == 4 || (floatz && ng == 8)) ? kSegments : kFree;
 }
 
 FwdRoute gemv_route(const Problem &p, bool floatz)

@@ -50,6 +50,10 @@ def test_large_matrices_go_segment_by_segment_where_that_is_faster():
     for bits, g, source in ((2, 32, PACKED), (2, 128, FLOATZ), (3, 64, PACKED), (3, 256, FLOATZ), (4, 64, PACKED), (4, 128, FLOATZ)):
         assert route(1, *large, bits, g, source)[0] == RUN, (bits, g, source)
     assert route(2, *large, 2, 64)[0] == SEGMENTS and route(3, *large, 2, 64)[0] == RUN
+    assert route(2, 2048, 24584, 2, 64)[0] == PAIRS and route(2, 2048, 24576, 2, 64)[0] == SEGMENTS
+    assert route(2, 2112, 24584, 2, 64)[0] == SEGMENTS and route(3, 1344, 60000, 2, 64)[0] == PAIRS
+    assert route(1, 512, 60000, 2, 64)[0] == PAIRS and route(4, 1024, 60000, 2, 64)[0] == RUN
+    assert route(4, 1024, 32768, 2, 64)[0] == PAIRS and route(4, 1024, 32776, 2, 64)[0] == RUN
     for source in (PACKED, FLOATZ):                               # 6144 and 6160 waves of k_gemv_run
         assert route(1, 4096, 24576, 2, 64, source)[0] == SEGMENTS and route(1, 4096, 24584, 2, 64, source)[0] == PAIRS
         assert route(2, 4096, 28672, 2, 64, source)[0] == SEGMENTS and route(1, 4096, 28672, 2, 128, source)[0] == RUN

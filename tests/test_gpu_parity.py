@@ -655,12 +655,13 @@ GEMV_CASES = [
     ("v14", 1, 5440, 6184, 3, 64),
     ("v15", 3, 3968, 8488, 4, 32),
     ("v16", 1, 1408, 24616, 2, 64),             # in pairs of lookups
+    ("v18", 3, 320, 24584, 2, 64),
 ]
 
 
 # kernels with packed and with float zero points where they are not the plain k_gemv_run
 GEMV_KERNELS = {"v4": (WIDE, WIDE), "v5": (ANY, ANY), "v6": (ANY, ANY), "v8": (WIDE, WIDE), "v13": (SEGMENTS, SEGMENTS),
-                "v14": (RUN, SEGMENTS), "v15": (RUN, SEGMENTS), "v16": (PAIRS, PAIRS)}
+                "v14": (RUN, SEGMENTS), "v15": (RUN, SEGMENTS), "v16": (PAIRS, PAIRS), "v18": (PAIRS, PAIRS)}
 
 
 @pytest.mark.parametrize("tag,T,I,O,bits,g", GEMV_CASES)
