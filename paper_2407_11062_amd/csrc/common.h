@@ -157,6 +157,10 @@ template <int BITS> struct WhatTable {
             d0 = __builtin_amdgcn_perm(y, x, 0x05010400u);     // x0 y0 x1 y1
             d1 = __builtin_amdgcn_perm(y, x, 0x07030602u);     // x2 y2 x3 y3
         } else {
+            // The masked word stays as it is: folded into a bit-field extract per code, every convert (v_cvt_f32_ubyte0..3, one
+            // instruction per code) would need an extract in front: 127 -> 107 arithmetic instructions per K tile of the tile kernels,
+            // and k_gemm_mid, which is bound by them, 31 -> 28 us (333 tokens, 4096 x 4096) and 74 -> 66 us (4096 x 11008).
+            asm("" : "+v"(t));
             bf16x2 p01, p23;
             p01[0] = (bf16_t)__builtin_fmaf(byte_to_float(t, 0), s, b); p01[1] = (bf16_t)__builtin_fmaf(byte_to_float(t, 1), s, b);
             p23[0] = (bf16_t)__builtin_fmaf(byte_to_float(t, 2), s, b); p23[1] = (bf16_t)__builtin_fmaf(byte_to_float(t, 3), s, b);

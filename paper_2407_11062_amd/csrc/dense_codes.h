@@ -56,7 +56,9 @@ __device__ __forceinline__ bf16x8 eight_of(const WhatTable<BITS> &tab, const Cod
             u[k] = T4 % 2 ? d1 : d0;
         }
     } else if constexpr (BITS == 4) {
-        const uint32_t even = c.w[T4] & 0x0F0F0F0Fu, odd = (c.w[T4] >> 4) & 0x0F0F0F0Fu;
+        uint32_t even = c.w[T4] & 0x0F0F0F0Fu, odd = (c.w[T4] >> 4) & 0x0F0F0F0Fu;
+        asm("" : "+v"(even));                      // see WhatTable::four: else two extracts more per four codes
+        asm("" : "+v"(odd));
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             bf16x2 p;
