@@ -13,10 +13,15 @@
 // of row r at position c ^ (r & 7), so that the 8 lanes a read serves together, 8 rows of one chunk, hit different banks),
 // codes as whole row pieces.  (Codes and step sizes loaded by the lanes that use them touch 32 cache lines per
 // instruction: 1.5 instead of 1.2 us per K step.)
-// Measured, us: 2 bit, 333 tokens: 4096 x 4096 41 -> 28 (and the re-layout of the codes, 6, gone), 4096 x 11008 104 -> 65
-// (14 gone); 4 bit, 150 tokens, 11008 x 4096 45 -> 38 (10 gone).  What bounds it: 0.7 us of each step's 1.2 (64 tokens) or
-// 1.45 (96) do not depend on the tokens, i.e. the rebuild of the weights and the staging; neither three stages of LDS with
-// loads two steps ahead nor the rebuild spread between the products of the slice before (both built) made a step shorter.
+// What bounds it is the rebuild.  Beside a 32x32x16 product (33 cycles) a SIMD issues some 4.9 arithmetic instructions, every
+// further one costs 4 cycles (two waves, measured with independent instructions; max(33, 13.5 + 4 n) fits), and here a
+// product goes with 5 (96 tokens, 2 bit, working layout) to 14 (64 tokens, 4 bit) of them.  Switched off one at a time (2 bit,
+// 64 tokens, 4096 x 4096, 24.5 us): the rebuild 15.4, all loads 21.5, the LDS reads 24.1; everything but the products 11.8.  So
+//   - the rebuild of slice t + 1 is spread between the products of slice t, and everything a step starts with is read in the
+//     last slice of the step before, behind the barrier that sits in front of that slice (333 tokens, 4096 x 11008, us:
+//     2 bit 63 -> 60, 3 bit, working layout 70 -> 65; 4 bit 66 -> 64).
+// Measured, us: 2 bit, 333 tokens: 4096 x 4096 41 -> 28 (and the re-layout of the codes, 6, gone), 4096 x 11008 104 -> 60
+// (14 gone); 4 bit, 150 tokens, 11008 x 4096 45 -> 38 (10 gone).
 #include "common.h"
 #include "dense_codes.h"
 #include "kernels.h"
@@ -96,37 +101,36 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
         coff[it] = (uint32_t)(n0 + row) * a.code_row_bytes + (uint32_t)code_chunk_swz<NCH>(row, e % NCH) * 16u;
     }
     const uint32_t srow = (uint32_t)(n0 + wave * 16 + (lane >> 3));        // rows of the step sizes: 8 per instruction, two instructions
-    auto load_step = [&](int step, int buf) {
+    // Load number d of those a wave issues per K step: codes, step sizes and zero points, then tokens.
+    constexpr int C_LOADS = (C_INSTR + 7) / 8, S_LOADS = 2 * (1 + L::ZW), LOADS = C_LOADS + S_LOADS + A_LOADS;
+    auto load = [&](int d, int step, int buf) {
         const uint32_t base = lds0 + (uint32_t)buf * L::STEP;
-#pragma unroll
-        for (int it = 0; it < A_LOADS; ++it)
+        if (d < C_LOADS) {
+            if (C_INSTR % 8 == 0 || d * 8 + wave < C_INSTR)
+                load_to_lds16_at(rW, base + L::TOK + (uint32_t)((d * 8 + wave) * 1024), coff[d] + (uint32_t)step * (NCH * 16));
+        } else if (d < C_LOADS + S_LOADS) {
+            const int e = d - C_LOADS, it = e / (1 + L::ZW), what = e % (1 + L::ZW);           // what: step size, zero point (, its second word)
+            const int seg = step * 8 + (lane & 7);
+            const uint32_t j = a.spg_magic ? __umulhi((uint32_t)seg, a.spg_magic) : (uint32_t)seg;
+            const bool ok = seg < n_segs;
+            const uint32_t gi = (srow + 8 * it) * (uint32_t)a.G + j;
+            const uint32_t at = base + L::TOK + L::CODES + (uint32_t)((wave * 2 + it) * 256) + (uint32_t)what * L::ROWW;
+            if constexpr (SRC == kWorking) load_to_lds4_at(rS, at, ok ? gi * 8u + 4u * what : kOobOffset);
+            else if (what == 0) load_to_lds4_at(rS, at, ok ? gi * 4u : kOobOffset);
+            else if constexpr (SRC == kFloatZ) load_to_lds4_at(rZ, at, ok ? gi * 4u : kOobOffset);
+            else load_to_lds4_at(rZ, at, ((srow + 8 * it) * a.z_row_words + ((j * BITS) >> 5)) * 4u + 4u * (what - 1));
+        } else {
+            const int it = d - C_LOADS - S_LOADS;
             load_to_lds16_at(rX, base + (uint32_t)((wave * A_LOADS + it) * 1024),
                              step * kMidBK + col[it] < a.I ? off[it] + (uint32_t)step * (kMidBK * 2) : kOobOffset);
-#pragma unroll
-        for (int it = 0; it < (C_INSTR + 7) / 8; ++it)
-            if (C_INSTR % 8 == 0 || it * 8 + wave < C_INSTR)
-                load_to_lds16_at(rW, base + L::TOK + (uint32_t)((it * 8 + wave) * 1024), coff[it] + (uint32_t)step * (NCH * 16));
-        const int seg = step * 8 + (lane & 7);
-        const uint32_t j = a.spg_magic ? __umulhi((uint32_t)seg, a.spg_magic) : (uint32_t)seg;
-        const bool ok = seg < n_segs;
-#pragma unroll
-        for (int it = 0; it < 2; ++it) {
-            const uint32_t gi = (srow + 8 * it) * (uint32_t)a.G + j;
-            const uint32_t at = base + L::TOK + L::CODES + (uint32_t)((wave * 2 + it) * 256);
-            if constexpr (SRC == kWorking) {
-                load_to_lds4_at(rS, at, ok ? gi * 8u : kOobOffset);
-                load_to_lds4_at(rS, at + L::ROWW, ok ? gi * 8u + 4u : kOobOffset);
-            } else {
-                load_to_lds4_at(rS, at, ok ? gi * 4u : kOobOffset);
-                if constexpr (SRC == kFloatZ) {
-                    load_to_lds4_at(rZ, at + L::ROWW, ok ? gi * 4u : kOobOffset);
-                } else {
-                    const uint32_t zo = ((srow + 8 * it) * a.z_row_words + ((j * BITS) >> 5)) * 4u;
-                    load_to_lds4_at(rZ, at + L::ROWW, zo);
-                    if constexpr (L::ZW == 2) load_to_lds4_at(rZ, at + 2 * L::ROWW, zo + 4u);
-                }
-            }
         }
+    };
+    // part P of 3 of a step's loads
+    auto load_part = [&](auto part, int step, int buf) {
+        constexpr int P = decltype(part)::value;
+#pragma unroll
+        for (int d = 0; d < LOADS; ++d)
+            if (d * 3 / LOADS == P) load(d, step, buf);
     };
     struct Seg { uint32_t w[WPS]; };
     auto eight = [&](const WhatTable<BITS> &tab, const Seg &sg, auto t) -> bf16x8 {
@@ -152,19 +156,21 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
 #pragma unroll
             for (int q = 0; q < 16; ++q) acc[b][i][q] = 0.0f;
 
-    load_step(0, 0);
-    for (int step = 0; step < steps; ++step) {
-        wait_all_and_barrier();           // everything of this step is in LDS; everyone is done with the other half
-        if (step + 1 < steps) load_step(step + 1, (step + 1) & 1);
-        const unsigned char *const here = smem_raw + (uint32_t)(step & 1) * L::STEP;
-        // this lane's segment (number 2 kg + h of the step) of both 32-row blocks
-        Seg cur[2];
-        WhatTable<BITS> tab[2];
-        const uint32_t seg = (uint32_t)(step * 8 + 2 * kg + h);
-        const uint32_t zshift = ((a.spg_magic ? __umulhi(seg, a.spg_magic) : seg) * BITS) & 31u;
+    Seg cur[2];
+    WhatTable<BITS> tab[2];
+    bf16x8 x[2][MI], w[2][2];
+    // this lane's segment (number 2 kg + h of the step) of both 32-row blocks, with what it takes to rebuild the weights
+    float ws[2];
+    uint32_t wz[2][L::ZW];
+    auto read_codes = [&](int buf) {
+        const unsigned char *const here = smem_raw + (uint32_t)buf * L::STEP;
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
             const int row = wn * 64 + b * 32 + r;
+            const uint32_t *const sw = reinterpret_cast<const uint32_t *>(here + L::TOK + L::CODES) + row * 8 + 2 * kg + h;
+            ws[b] = __uint_as_float(sw[0]);
+#pragma unroll
+            for (int k = 0; k < L::ZW; ++k) wz[b][k] = sw[(k + 1) * (L::ROWW / 4)];
             const unsigned char *const codes = here + L::TOK + row * (NCH * 16);
             if constexpr (WPS == 2) {
                 const uintx2 v = *reinterpret_cast<const uintx2 *>(codes + code_chunk_swz<NCH>(row, kg) * 16 + h * 8);
@@ -176,39 +182,80 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
                 const uintx4 v = *reinterpret_cast<const uintx4 *>(codes + code_chunk_swz<NCH>(row, 2 * kg + h) * 16);
                 cur[b].w[0] = v[0]; cur[b].w[1] = v[1]; cur[b].w[2] = v[2]; cur[b].w[3] = v[3];
             }
-            const uint32_t *const sw = reinterpret_cast<const uint32_t *>(here + L::TOK + L::CODES) + row * 8 + 2 * kg + h;
-            constexpr uint32_t ROWS = L::ROWW / 4;
-            float z = __uint_as_float(sw[ROWS]);
-            if constexpr (SRC == kPackedZ) {
-                const uint32_t v = L::ZW == 2 ? __builtin_amdgcn_alignbit(sw[(L::ZW - 1) * ROWS + ROWS], sw[ROWS], zshift) : sw[ROWS] >> zshift;
-                z = (float)(v & ((1u << BITS) - 1u));
-            }
-            tab[b].build(__uint_as_float(sw[0]), z);
         }
-        const unsigned char *const tile = here + r * 512;
-        auto frag = [&](int i, int t) -> bf16x8 {
-            return *reinterpret_cast<const bf16x8 *>(tile + i * (32 * 512) + (((kg * 8 + h * 4 + t) ^ (r & 7)) * 16));
-        };
-        bf16x8 x[2][MI], w[2][2];
+    };
+    auto build = [&](int step, int b) {
+        float z = __uint_as_float(wz[b][0]);
+        if constexpr (SRC == kPackedZ) {
+            const uint32_t seg = (uint32_t)(step * 8 + 2 * kg + h);
+            const uint32_t zshift = ((a.spg_magic ? __umulhi(seg, a.spg_magic) : seg) * BITS) & 31u;
+            const uint32_t v = L::ZW == 2 ? __builtin_amdgcn_alignbit(wz[b][L::ZW - 1], wz[b][0], zshift) : wz[b][0] >> zshift;
+            z = (float)(v & ((1u << BITS) - 1u));
+        }
+        tab[b].build(ws[b], z);
+    };
+    const unsigned char *const tile = smem_raw + r * 512;
+    auto read_x = [&](int slot, int buf, int t) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i) x[0][i] = frag(i, 0);
+        for (int i = 0; i < MI; ++i)
+            x[slot][i] = *reinterpret_cast<const bf16x8 *>(tile + (uint32_t)buf * L::STEP + i * (32 * 512) + (((kg * 8 + h * 4 + t) ^ (r & 7)) * 16));
+    };
+    auto products = [&](int slot) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b) w[0][b] = eight(tab[b], cur[b], IC<0>{});
-        auto slice = [&](auto tc) {
-            constexpr int t = decltype(tc)::value;
-            if constexpr (t < 3) {
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int i = 0; i < MI; ++i) x[(t + 1) & 1][i] = frag(i, t + 1);
+            for (int b = 0; b < 2; ++b)
+                acc[b][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[slot][b], x[slot][i], acc[b][i], 0, 0, 0);
+    };
+    // one product, one LDS read, a share of the arithmetic, repeated
+    auto weave = [&](auto valu) {
 #pragma unroll
-                for (int b = 0; b < 2; ++b) w[(t + 1) & 1][b] = eight(tab[b], cur[b], IC<(t + 1) & 3>{});
-            }
+        for (int q = 0; q < 2 * MI; ++q) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, decltype(valu)::value, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr int kVal = (BITS == 4 ? 52 : 40) / (2 * MI) + 1;
+
 #pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    acc[b][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[t & 1][b], x[t & 1][i], acc[b][i], 0, 0, 0);
-        };
-        slice(IC<0>{}); slice(IC<1>{}); slice(IC<2>{}); slice(IC<3>{});
+    for (int d = 0; d < LOADS; ++d) load(d, 0, 0);
+    wait_all_and_barrier();
+    if (steps > 1) load_part(IC<0>{}, 1, 1);
+    read_codes(0);
+    read_x(0, 0, 0);
+    build(0, 0); build(0, 1);
+    w[0][0] = eight(tab[0], cur[0], IC<0>{}); w[0][1] = eight(tab[1], cur[1], IC<0>{});
+    __builtin_amdgcn_sched_barrier(0);
+    for (int step = 0; step < steps; ++step) {
+        const int buf = step & 1;
+        if (step + 1 < steps) load_part(IC<1>{}, step + 1, buf ^ 1);
+        __builtin_amdgcn_sched_barrier(0);
+        read_x(1, buf, 1);
+        products(0);
+        w[1][0] = eight(tab[0], cur[0], IC<1>{}); w[1][1] = eight(tab[1], cur[1], IC<1>{});
+        weave(IC<kVal>{});
+        if (step + 1 < steps) load_part(IC<2>{}, step + 1, buf ^ 1);
+        __builtin_amdgcn_sched_barrier(0);
+        read_x(0, buf, 2);
+        products(1);
+        w[0][0] = eight(tab[0], cur[0], IC<2>{}); w[0][1] = eight(tab[1], cur[1], IC<2>{});
+        weave(IC<kVal>{});
+        read_x(1, buf, 3);
+        products(0);
+        w[1][0] = eight(tab[0], cur[0], IC<3>{}); w[1][1] = eight(tab[1], cur[1], IC<3>{});
+        weave(IC<kVal>{});
+        wait_all_and_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        if (step + 2 < steps) load_part(IC<0>{}, step + 2, buf);
+        __builtin_amdgcn_sched_barrier(0);
+        read_codes(buf ^ 1);
+        read_x(0, buf ^ 1, 0);
+        products(1);
+        build(step + 1, 0); build(step + 1, 1);
+        w[0][0] = eight(tab[0], cur[0], IC<0>{}); w[0][1] = eight(tab[1], cur[1], IC<0>{});
+        weave(IC<kVal + 4>{});
     }
 
     // ---- sums: acc[b][i][q] is row 8 (q / 4) + 4 h + q % 4 of block b, token 32 i + r.  One 32-row block of every wave at a
@@ -249,6 +296,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
         }
     }
 }
+
 
 template <int BITS, int SRC, int BM> void launch_t(MidArgs a, hipStream_t st)
 {
