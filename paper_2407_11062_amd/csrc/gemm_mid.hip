@@ -19,7 +19,8 @@
 // 64 tokens, 4096 x 4096, 24.5 us): the rebuild 15.4, all loads 21.5, the LDS reads 24.1; everything but the products 11.8.  So
 //   - the rebuild of slice t + 1 is spread between the products of slice t, and everything a step starts with is read in the
 //     last slice of the step before, behind the barrier that sits in front of that slice (333 tokens, 4096 x 11008, us:
-//     2 bit 63 -> 60, 3 bit, working layout 70 -> 65; 4 bit 66 -> 64).
+//     2 bit 63 -> 60, 3 bit, working layout 70 -> 65; 4 bit 66 -> 64);
+//   - where the tiles still fill the chip, 128 tokens share a rebuilt weight (k_gemm_mid_tall below).
 // Measured, us: 2 bit, 333 tokens: 4096 x 4096 41 -> 28 (and the re-layout of the codes, 6, gone), 4096 x 11008 104 -> 60
 // (14 gone); 4 bit, 150 tokens, 11008 x 4096 45 -> 38 (10 gone).
 #include "common.h"
@@ -36,6 +37,7 @@ namespace {
 struct MidArgs {
     const bf16_t *X; const uint32_t *codes; const float *s; const uint32_t *zp; const float *zf; bf16_t *Y;
     int T, I, O, G;
+    int group;
     uint32_t spg_magic;            // ceil(2^32 / (g/32)), 0 for g = 32: group of a segment
     uint32_t code_row_bytes, z_row_words;
     uint32_t x_bytes, codes_bytes, s_bytes, z_bytes;
@@ -57,7 +59,7 @@ template <int BITS, int SRC, int BM> struct MidLds {
 // position of the 16-byte chunk c of a row's codes: the lanes of a read (32 rows, one segment) spread over the banks
 template <int NCH> __device__ __forceinline__ int code_chunk_swz(int row, int c)
 {
-    return NCH == 4 ? c ^ ((row >> 1) & 3) : NCH == 8 ? c ^ (row & 7) : c;            // rows of 96 bytes spread by themselves
+    return NCH == 2 ? c ^ ((row >> 2) & 1) : NCH == 4 ? c ^ ((row >> 1) & 3) : NCH == 8 ? c ^ (row & 7) : c;            // rows of 96 bytes spread by themselves
 }
 
 template <int BITS, int SRC, int BM>
@@ -298,10 +300,377 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
 }
 
 
+// ---- 128 tokens per tile -----------------------------------------------------------------------------------
+// Four products per rebuilt fragment instead of two or three, so the matrix cores have less arithmetic to wait for (6.7
+// instructions a product at 2 bit, 7 at 4; 6.8 and 9.5 with 96 tokens).  Two stages of 256-wide K steps would take 176 KB
+// of LDS, so a step is 128 wide: a wave multiplies one segment of it, and the lanes h = 0 and 1 of a row take 16 of its codes
+// each.  With the room that leaves, tokens are fetched two steps ahead (three stages), codes four; step sizes and zero points
+// come four steps at a time, 16 bytes a lane.  A lane's byte offsets never change: the buffers move along K, which is scalar work
+// (offsets per lane and load were 30 of 123 instructions a step).  Every wave issues the same number of loads a step, so
+// the barrier waits for a count and not for the loads of the step after next.
+// Measured, us, 1000 tokens, 4096 x 4096, from the packed arrays (128 x 128 tiles behind a re-layout / here): 2 bit 57 / 40, 3 bit
+// 60 / 45, 4 bit 61 / 41; from the working layout 47 / 35, 48 / 36, 50 / 38.  What bounds it: 1940 cycles a step, of which the
+// products need 1056, the arithmetic beside them 1290; without the loads of a step 1500.
+template <int BITS, int SRC, int BM> struct TallLds {
+    static constexpr int WPS = SRC == kWorking ? WorkCodes<BITS>::kWords : BITS;
+    static constexpr int NCH = WPS;
+    static constexpr int ZW = SRC == kPackedZ && BITS == 3 ? 2 : 1;
+    // tokens: three stages; codes: four, 1 KB per wave and its 16 rows; step sizes and zero points of four steps: two
+    static constexpr uint32_t TOK = BM * 128 * 2, CODES = 8 * 1024, SUPER = 16 * 1024;
+    static constexpr uint32_t CODES_AT = 3 * TOK, SUPERS = CODES_AT + 4 * CODES, TOTAL = SUPERS + 2 * SUPER;
+    static_assert(TOTAL <= 160 * 1024, "LDS of one CU");
+};
+
+template <int BITS, int SRC, int BM>
+__global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
+{
+    typedef TallLds<BITS, SRC, BM> L;
+    constexpr int MI = BM / 32, WPS = L::WPS, NCH = L::NCH, BK = 128;
+    constexpr int N = 1 + MI;                 // loads a wave issues per K step: codes, tokens
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave & 1, kg = wave >> 1, r = lane & 31, h = lane >> 5;
+
+    const int nb = (int)gridDim.x, xcd = (int)(blockIdx.x & 7), rem = nb & 7;
+    const int pid = xcd * (nb >> 3) + (xcd < rem ? xcd : rem) + (int)(blockIdx.x >> 3);
+    const int m0 = (pid % a.tiles_m) * BM, n0 = (pid / a.tiles_m) * kMidBN;
+
+    const int steps = (a.I + BK - 1) / BK;
+    const uint32_t lds0 = lds_addr_of(smem_raw);
+
+    // ---- loads of one K step: every lane keeps one byte offset per instruction for good, the buffers move along (scalar work)
+    uint32_t off[MI];
+#pragma unroll
+    for (int it = 0; it < MI; ++it) {
+        const int row = (wave * MI + it) * 4 + (lane >> 4);
+        off[it] = m0 + row < a.T ? ((uint32_t)(m0 + row) * (uint32_t)a.I + (uint32_t)(((lane & 15) ^ (row & 7)) * 8)) * 2u : kOobOffset;
+    }
+    const int crow = wave * 16 + lane / NCH;
+    const uint32_t coff = lane < 16 * NCH ? (uint32_t)(n0 + crow) * a.code_row_bytes + (uint32_t)code_chunk_swz<NCH>(crow, lane % NCH) * 16u : kOobOffset;
+    // Step sizes and zero points of four steps (a superstep) at a time, 16-byte chunks of a row's groups: 64 bytes a row of each,
+    // (s, z) pairs 128, packed zero points 16 that hold them all.  Chunk c of a row sits at position c ^ (row / 2) (pairs: row).
+    const int dshift = a.group == 32 ? 0 : a.group == 64 ? 1 : 2;          // segment of a step -> group of a step
+    uint32_t soff[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        if constexpr (SRC == kWorking) {
+            const int row = wave * 16 + e * 8 + (lane >> 3), c = (lane & 7) ^ (row & 7);
+            soff[e] = c < (8 >> dshift) ? (uint32_t)(n0 + row) * (uint32_t)a.G * 8u + (uint32_t)c * 16u : kOobOffset;
+        } else if (SRC == kFloatZ || e == 0) {
+            const int row = wave * 16 + (lane >> 2), c = (lane & 3) ^ ((row >> 1) & 3);
+            soff[e] = c < (4 >> dshift) ? (uint32_t)(n0 + row) * (uint32_t)a.G * 4u + (uint32_t)c * 16u : kOobOffset;
+        } else {
+            soff[e] = lane < 16 ? (uint32_t)(n0 + wave * 16 + lane) * a.z_row_words * 4u : kOobOffset;
+        }
+    }
+    // number of the first group of a step, carried from step to step: a group ends every `per` steps, or 4 >> dshift end in one
+    const int per = a.group > 128 ? a.group / 128 : 1, inc = 4 >> dshift;
+    struct Group {
+        int j, at;
+        __device__ __forceinline__ void next(int per, int inc) { ++at; const bool wrap = at == per; j += wrap ? inc : 0; at = wrap ? 0 : at; }
+    };
+    auto load_super = [&](int step) {              // the superstep that begins with this step
+        const bool live = step < steps;
+        const uint32_t j = live ? (uint32_t)(a.group >= 128 ? step / per : step * inc) : 0u;
+        const uint32_t to = lds0 + L::SUPERS + (uint32_t)((step >> 2) & 1) * L::SUPER;
+        constexpr uint32_t SB = SRC == kWorking ? 8u : 4u;
+        const RawRsrc rS = make_raw_rsrc((const char *)a.s + j * SB, live ? a.s_bytes - j * SB : 0u);
+        if constexpr (SRC == kWorking) {
+            load_to_lds16_at(rS, to + (uint32_t)(wave * 2048), soff[0]);
+            load_to_lds16_at(rS, to + (uint32_t)(wave * 2048 + 1024), soff[1]);
+        } else {
+            load_to_lds16_at(rS, to + (uint32_t)(wave * 1024), soff[0]);
+            const uint32_t zat = SRC == kFloatZ ? j * 4u : ((j * BITS) >> 5) * 4u;
+            const RawRsrc rZ = make_raw_rsrc((SRC == kFloatZ ? (const char *)a.zf : (const char *)a.zp) + zat, live ? a.z_bytes - zat : 0u);
+            load_to_lds16_at(rZ, to + 8192u + (uint32_t)(wave * 1024), soff[1]);
+        }
+    };
+    // The buffers move along K, so that a lane keeps its byte offset; past the last step nothing is in range (zeros).
+    struct Moving {
+        uint64_t base; uint32_t left;
+        __device__ __forceinline__ void by(uint32_t n) { base += n; left -= n; }
+        __device__ __forceinline__ RawRsrc at(bool live) const
+        {
+            RawRsrc r;
+            r.w[0] = (int)(uint32_t)base; r.w[1] = (int)(uint32_t)(base >> 32); r.w[2] = live ? (int)left : 0; r.w[3] = 0x00020000;
+            return r;
+        }
+    };
+    Moving bX{(uint64_t)a.X & 0xFFFFFFFFFFFFull, a.x_bytes}, bW{(uint64_t)a.codes & 0xFFFFFFFFFFFFull, a.codes_bytes};
+    RawRsrc rX, rW;
+    auto aim_x = [&](int step) { rX = bX.at(step < steps); bX.by(BK * 2); };            // the steps in order
+    auto aim_codes = [&](int step) { rW = bW.at(step < steps); bW.by(NCH * 16); };
+    // tokens past the end of the rows come as zeros; called in front of the loads of every step
+    auto mask_last = [&](int step) {
+        if (step == steps - 1 && a.I % BK != 0) {
+#pragma unroll
+            for (int it = 0; it < MI; ++it) {
+                const int row = (wave * MI + it) * 4 + (lane >> 4);
+                if (((lane & 15) ^ (row & 7)) * 8 >= a.I % BK) off[it] = kOobOffset;
+            }
+        }
+    };
+    auto load_codes = [&](int step) {
+        load_to_lds16_at(rW, lds0 + L::CODES_AT + (uint32_t)(step & 3) * L::CODES + (uint32_t)(wave * 1024), coff);
+    };
+    constexpr int MH = (MI + 1) / 2;       // token loads issued in the last slice of the step before
+    auto load_x = [&](int from, int to, uint32_t stage) {
+#pragma unroll
+        for (int it = 0; it < MI; ++it)
+            if (it >= from && it < to) load_to_lds16_at(rX, lds0 + stage + (uint32_t)((wave * MI + it) * 1024), off[it]);
+    };
+
+    floatx16 acc[2][MI];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc[b][i][q] = 0.0f;
+
+    // A wave multiplies the segment kg of a step; the lanes h = 0 and 1 of a row take 16 of its codes each, eight per product.
+    // Codes, step size and zero point of a step are read from LDS a slice before they are rebuilt.
+    constexpr int HW = WPS == 2 ? 1 : 2;
+    constexpr bool kShared = BITS == 2 && SRC != kWorking;     // 2-bit codes as packed: the lookups of a word serve both products
+    struct Raw { uint32_t c[2][HW], s[2], z[2][L::ZW], zshift, keep; };
+    Raw raw;
+    uint32_t cur[2][HW], lo[2][4], hi[2][4];
+    WhatTable<BITS> tab[2];
+    bf16x8 x[2][MI], w[2][2];
+    Group gr{0, 0};                       // of the step that is read next
+    int super_j = 0, seg_left = (a.I >> 5) - kg;       // first group of its superstep; segments from this wave's on to the end of the row
+    auto read_raw = [&](int step) {       // the steps in order
+        super_j = (step & 3) == 0 ? gr.j : super_j;
+        const unsigned char *const sup = smem_raw + L::SUPERS + (uint32_t)((step >> 2) & 1) * L::SUPER;
+        const unsigned char *const here = smem_raw + L::CODES_AT + (uint32_t)(step & 3) * L::CODES;
+        const int slot = gr.j - super_j + (kg >> dshift);           // of the segment's group among those of the superstep
+        const uint32_t zbit = (uint32_t)(gr.j + (kg >> dshift)) * BITS - (((uint32_t)super_j * BITS) & ~31u);
+        const int row = wn * 64 + r;      // row + 32 lies a constant further on everywhere
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const unsigned char *const codes = here + b * 2048 + (row >> 4) * 1024 + (row & 15) * (NCH * 16);
+            if constexpr (WPS == 2) {
+                raw.c[b][0] = *reinterpret_cast<const uint32_t *>(codes + code_chunk_swz<NCH>(row, kg >> 1) * 16 + (kg & 1) * 8 + h * 4);
+            } else if constexpr (WPS == 3) {
+                const uint32_t *const v = reinterpret_cast<const uint32_t *>(codes + kg * 12 + h * 4);
+                raw.c[b][0] = v[0]; raw.c[b][1] = v[1];
+            } else {
+                const uintx2 v = *reinterpret_cast<const uintx2 *>(codes + code_chunk_swz<NCH>(row, kg) * 16 + h * 8);
+                raw.c[b][0] = v[0]; raw.c[b][1] = v[1];
+            }
+            if constexpr (SRC == kWorking) {
+                const uintx2 v = *reinterpret_cast<const uintx2 *>(sup + b * 4096 + row * 128 + (((slot >> 1) ^ (row & 7)) * 16) + (slot & 1) * 8);
+                raw.s[b] = v[0]; raw.z[b][0] = v[1];
+            } else {
+                const uint32_t at = (uint32_t)(b * 2048 + row * 64 + (((slot >> 2) ^ ((row >> 1) & 3)) * 16) + (slot & 3) * 4);
+                raw.s[b] = *reinterpret_cast<const uint32_t *>(sup + at);
+                if constexpr (SRC == kFloatZ) {
+                    raw.z[b][0] = *reinterpret_cast<const uint32_t *>(sup + 8192 + at);
+                } else {
+                    const uint32_t *const p = reinterpret_cast<const uint32_t *>(sup + 8192 + b * 2048 + (row >> 4) * 1024 + (row & 15) * 16) + (zbit >> 5);
+#pragma unroll
+                    for (int k = 0; k < L::ZW; ++k) raw.z[b][k] = p[k];
+                }
+            }
+        }
+        raw.zshift = zbit & 31u;
+        raw.keep = seg_left > 0 ? ~0u : 0u;
+        seg_left -= 4;
+        gr.next(per, inc);
+    };
+    auto build = [&]() {                  // from raw
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            // segments past the end of the rows: the step size and the zero point are what follows the row, the weights have to be zeros
+            float z;
+            if constexpr (SRC == kPackedZ) {
+                const uint32_t v = L::ZW == 2 ? __builtin_amdgcn_alignbit(raw.z[b][L::ZW - 1], raw.z[b][0], raw.zshift) : raw.z[b][0] >> raw.zshift;
+                z = (float)(v & ((1u << BITS) - 1u));
+            } else {
+                z = __uint_as_float(raw.z[b][0] & raw.keep);
+            }
+            tab[b].build(__uint_as_float(raw.s[b] & raw.keep), z);
+            if constexpr (WPS == 3) {     // 16 codes are 48 bits: the second half of a segment starts in the middle of a word
+                cur[b][0] = __builtin_amdgcn_alignbit(raw.c[b][1], raw.c[b][0], (uint32_t)h * 16u);
+                cur[b][1] = raw.c[b][1] >> ((uint32_t)h * 16u);
+            } else {
+#pragma unroll
+                for (int k = 0; k < HW; ++k) cur[b][k] = raw.c[b][k];
+            }
+        }
+    };
+    auto look_up = [&]() {                // bytes of the codes k, k + 4, k + 8 and k + 12
+        if constexpr (kShared) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t c = (cur[b][0] >> (2 * k)) & 0x03030303u;
+                    lo[b][k] = __builtin_amdgcn_perm(tab[b].lo[0], tab[b].lo[0], c);
+                    hi[b][k] = __builtin_amdgcn_perm(tab[b].hi[0], tab[b].hi[0], c);
+                }
+        }
+    };
+    auto eight = [&](int b, auto t) -> bf16x8 {
+        constexpr int T4 = decltype(t)::value;
+        if constexpr (kShared) {
+            uintx4 u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) u[k] = __builtin_amdgcn_perm(hi[b][k], lo[b][k], T4 ? 0x07030602u : 0x05010400u);
+            return unslot_of<BITS>(__builtin_bit_cast(bf16x8, u));
+        } else if constexpr (SRC == kWorking) {
+            WorkCodes<BITS> c;
+#pragma unroll
+            for (int k = 0; k < HW; ++k) c.w[k] = cur[b][k];
+            return tab[b].template eight<T4>(c);
+        } else {
+            CodeWords<BITS> c;
+#pragma unroll
+            for (int k = 0; k < HW; ++k) c.w[k] = cur[b][k];
+            return unslot_of<BITS>(eight_of<BITS, T4>(tab[b], c));
+        }
+    };
+    auto read_x = [&](int slot, const unsigned char *here, int t) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+            x[slot][i] = *reinterpret_cast<const bf16x8 *>(here + (i * 32 + r) * 256 + (((kg * 4 + h * 2 + t) ^ (r & 7)) * 16));
+    };
+    auto products = [&](int slot) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+                acc[b][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[slot][b], x[slot][i], acc[b][i], 0, 0, 0);
+    };
+    auto weave = [&](auto valu) {
+#pragma unroll
+        for (int q = 0; q < 2 * MI; ++q) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, decltype(valu)::value, 0);
+            __builtin_amdgcn_sched_group_barrier(0x004, 5, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // instructions of arithmetic in the two slices of a step
+    constexpr int kV0 = (BITS == 2 ? (kShared ? 52 : 54) : BITS == 3 ? (SRC == kWorking ? 70 : 88) : 68) / (2 * MI) + 1;
+    constexpr int kV1 = (BITS == 2 ? (kShared ? 60 : 44) : BITS == 3 ? (SRC == kWorking ? 48 : 60) : 60) / (2 * MI) + 1;
+    auto wait_and_barrier = [&](auto left) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(decltype(left)::value));
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto pin = [&]() {          // what the rebuild reads is not to be used before this point
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int k = 0; k < (kShared ? 4 : HW); ++k) {
+                if constexpr (kShared) asm volatile("" : "+v"(lo[b][k]), "+v"(hi[b][k]));
+                else asm volatile("" : "+v"(cur[b][k]));
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto keep = [&](int slot) {        // ... and what it yields is there by now
+        asm volatile("" : "+v"(w[slot][0]), "+v"(w[slot][1]));
+    };
+    auto pin_tables = [&]() {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int k = 0; k < HW; ++k) asm volatile("" : "+v"(cur[b][k]));
+    };
+
+    load_super(0);
+    aim_codes(0); load_codes(0); aim_codes(1); load_codes(1);
+    mask_last(0); aim_x(0); load_x(0, MI, 0);
+    aim_codes(2); load_codes(2);
+    mask_last(1); aim_x(1); load_x(0, MI, L::TOK);
+    aim_codes(3); load_codes(3);
+    mask_last(2); aim_x(2); load_x(0, MH, 2 * L::TOK);
+    wait_and_barrier(IC<N + 1 + MH>{});
+    read_raw(0);
+    read_x(0, smem_raw, 0);
+    build(); look_up();
+    w[0][0] = eight(0, IC<0>{}); w[0][1] = eight(1, IC<0>{});
+    read_raw(1);
+    __builtin_amdgcn_sched_barrier(0);
+    auto one_step = [&](int step, auto stage) __attribute__((always_inline)) {
+        constexpr uint32_t S0 = decltype(stage)::value * L::TOK, S1 = (decltype(stage)::value + 1) % 3 * L::TOK,
+                           S2 = (decltype(stage)::value + 2) % 3 * L::TOK;
+        load_x(MH, MI, S2);
+        mask_last(step + 3);
+        if ((step & 3) == 0) load_super(step + 4);
+        pin();
+        aim_x(step + 3); aim_codes(step + 4);
+        read_x(1, smem_raw + S0, 1);
+        products(0);
+        w[1][0] = eight(0, IC<1>{}); w[1][1] = eight(1, IC<1>{});
+        build();
+        weave(IC<kV0>{});
+        keep(1);
+        pin_tables();
+        wait_and_barrier(IC<N>{});
+        load_codes(step + 4);
+        load_x(0, MH, S0);
+        __builtin_amdgcn_sched_barrier(0);
+        read_raw(step + 2);
+        read_x(0, smem_raw + S1, 0);
+        products(1);
+        look_up();
+        w[0][0] = eight(0, IC<0>{}); w[0][1] = eight(1, IC<0>{});
+        weave(IC<kV1>{});
+        keep(0);
+    };
+    for (int step = 0;;) {
+        one_step(step, IC<0>{}); if (++step >= steps) break;
+        one_step(step, IC<1>{}); if (++step >= steps) break;
+        one_step(step, IC<2>{}); if (++step >= steps) break;
+    }
+    wait_and_barrier(IC<0>{});
+
+    constexpr uint32_t WAVE_BYTES = BM * 32 * 4;
+    static_assert(8 * WAVE_BYTES <= L::TOTAL, "the sums go where the tiles were");
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                floatx4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = acc[b][i][4 * q + e];
+                *reinterpret_cast<floatx4 *>(smem_raw + wave * WAVE_BYTES + (i * 32 + r) * 128 + (((2 * q + h) ^ (r & 7)) * 16)) = v;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < BM / 4 / 8; ++k) {
+            const int tok = kg * (BM / 4) + k * 8 + (lane >> 3), ch = lane & 7;
+            floatx4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int g = 0; g < kMidKG; ++g) {
+                const floatx4 v = *reinterpret_cast<const floatx4 *>(smem_raw + (g * 2 + wn) * WAVE_BYTES + tok * 128 + ((ch ^ (tok & 7)) * 16));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[e] += v[e];
+            }
+            const int o = n0 + wn * 64 + b * 32 + ch * 4;
+            if (m0 + tok < a.T && o < a.O) {
+                bf16x4 y;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] = (bf16_t)sum[e];
+                *reinterpret_cast<bf16x4 *>(a.Y + (size_t)(m0 + tok) * a.O + o) = y;
+            }
+        }
+    }
+}
+
 template <int BITS, int SRC, int BM> void launch_t(MidArgs a, hipStream_t st)
 {
-    constexpr int smem = (int)MidLds<BITS, SRC, BM>::TOTAL;
-    auto kern = k_gemm_mid<BITS, SRC, BM>;
+    constexpr int smem = BM >= 128 ? (int)TallLds<BITS, SRC, BM>::TOTAL : (int)MidLds<BITS, SRC, BM < 128 ? BM : 64>::TOTAL;
+    void (*kern)(MidArgs);
+    if constexpr (BM >= 128) kern = k_gemm_mid_tall<BITS, SRC, BM>; else kern = k_gemm_mid<BITS, SRC, BM>;
     static std::atomic<uint64_t> allowed{0};          // more dynamic LDS than the default limit: once per device
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev > 63) dev = 0;
@@ -315,19 +684,27 @@ template <int BITS, int SRC, int BM> void launch_t(MidArgs a, hipStream_t st)
 }
 
 // What a launch with token tiles of `bm` takes, in us: rounds of workgroups (one per compute unit), each 6 us and 1.2 (64
-// tokens) or 1.45 (96) us per 256-wide K step; fitted at 4096, 8192 and 11008 inputs.
+// tokens), 1.45 (96) or 2.05 (128) us per 256-wide K step; fitted at 4096, 8192 and 11008 inputs.
 int64_t rounds_of(const Problem &p, int bm) { return (((p.T + bm - 1) / bm) * ((p.O + kMidBN - 1) / kMidBN) + 255) / 256; }
 double launch_us(const Problem &p, int bm)
 {
-    return (double)rounds_of(p, bm) * (6.0 + (double)((p.I + kMidBK - 1) / kMidBK) * (bm == 64 ? 1.2 : 1.45));
+    return (double)rounds_of(p, bm) * (6.0 + (double)((p.I + kMidBK - 1) / kMidBK) * (bm == 64 ? 1.2 : bm == 96 ? 1.45 : 2.05));
 }
 
-int token_tile(const Problem &p) { return launch_us(p, 96) < launch_us(p, 64) ? 96 : 64; }
+// The tall kernel finds the groups of a 128-wide step by counting: groups of 32 or 64, or whole steps.  One round only: in two
+// the 96-token tiles (or the tile kernels) are faster (2000 tokens, 4096 x 4096, 2 bit: 82 us, the tile kernel 75).
+bool tall_applies(const Problem &p) { return (p.g == 32 || p.g == 64 || p.g % 128 == 0) && rounds_of(p, 128) == 1; }
+
+int token_tile(const Problem &p)
+{
+    const int low = launch_us(p, 96) < launch_us(p, 64) ? 96 : 64;
+    return tall_applies(p) && launch_us(p, 128) < launch_us(p, low) ? 128 : low;
+}
 
 template <int SRC> void launch_src(const Problem &p, const MidArgs &a, hipStream_t st)
 {
-    const bool tall = token_tile(p) == 96;
-#define EQAT_MID(B) do { if (tall) launch_t<B, SRC, 96>(a, st); else launch_t<B, SRC, 64>(a, st); } while (0)
+    const int bm = token_tile(p);
+#define EQAT_MID(B) do { if (bm == 128) launch_t<B, SRC, 128>(a, st); else if (bm == 96) launch_t<B, SRC, 96>(a, st); else launch_t<B, SRC, 64>(a, st); } while (0)
     if (p.bits == 2) EQAT_MID(2); else if (p.bits == 3) EQAT_MID(3); else EQAT_MID(4);
 #undef EQAT_MID
 }
@@ -336,7 +713,7 @@ MidArgs mid_args(const Problem &p, const void *X, const void *codes, const void 
 {
     MidArgs a{};
     a.X = (const bf16_t *)X; a.codes = (const uint32_t *)codes; a.s = (const float *)s; a.Y = (bf16_t *)Y;
-    a.T = (int)p.T; a.I = (int)p.I; a.O = (int)p.O; a.G = (int)p.G;
+    a.T = (int)p.T; a.I = (int)p.I; a.O = (int)p.O; a.G = (int)p.G; a.group = (int)p.g;
     a.spg_magic = p.g == 32 ? 0u : (uint32_t)((((uint64_t)1 << 32) + (uint64_t)(p.g / 32) - 1) / (uint64_t)(p.g / 32));
     a.x_bytes = (uint32_t)(p.T * p.I * 2);
     return a;
@@ -355,10 +732,10 @@ FwdRoute mid_route(const Problem &p, bool from_packed)
     return FwdRoute{from_packed && p.bits == 3 && p.T > 2 * tokens && rounds_of(p, tokens) > 1 ? FWD_RELAY_MID : FWD_MID, tokens, kMidBN};
 }
 
-double mid_us(const Problem &p) { return std::min(launch_us(p, 96), launch_us(p, 64)); }
+double mid_us(const Problem &p) { return launch_us(p, token_tile(p)); }
 
-// Against the 128 x 128-tile kernel, which takes 0.55 us per 64-wide K tile while a compute unit has one tile at most and
-// 0.9 or more beyond that (11008 x 4096: 256 tokens, 172 tiles: 43 us there, 46-49 here in two rounds; 288 tokens, 258
+// Against the 128 x 128-tile kernel, which takes 0.55 (few tiles) to 0.65 us (256 tiles) per 64-wide K tile while a compute unit
+// has one tile at most and 0.9 or more beyond that (11008 x 4096: 256 tokens, 172 tiles: 43 us there, 46-49 here in two rounds; 288 tokens, 258
 // tiles: 61 and 47; 400 tokens: 63 and 57).  More than two rounds here, or more than two tiles per compute unit there: the
 // 256 x 256 tiles are the better kernel (11008 x 4096, 515 tokens: 68 us in tiles, 84 here).  The GEMMs alone are compared:
 // a forward from the packed arrays saves the re-layout as well and would gain a little earlier, but every forward entry point
@@ -368,7 +745,8 @@ bool mid_applies(const Problem &p)
     if (!p.act_bf16 || !group_by_magic(p) || p.T <= 32) return false;
     if (p.T <= 64) return !gemv_work_applies(p);
     const int64_t tiles = ((p.T + 127) / 128) * ((p.O + 127) / 128);
-    return tiles <= 512 && mid_us(p) < 4.0 + (double)((p.I + 63) / 64) * (tiles <= 256 ? 0.55 : 0.9);
+    const double k_tile = tiles <= 256 ? std::max(0.55, 0.48 + 0.17 * (double)tiles / 256.0) : 0.9;
+    return tiles <= 512 && mid_us(p) < 4.0 + (double)((p.I + 63) / 64) * k_tile;
 }
 
 void launch_mid(const Problem &p, const void *X, const void *Wpacked, const float *s, const void *zpacked, const float *zfloat,
