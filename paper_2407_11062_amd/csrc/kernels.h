@@ -88,6 +88,13 @@ void launch_gemv(const Problem &p, const void *X, const void *Wpacked, const flo
 // whether mulhi(segment, ceil(2^32 / (g / 32))) is the group of every segment of a row
 inline bool group_by_magic(const Problem &p) { return (p.I / 32) * (p.g / 32) < ((int64_t)1 << 32); }
 
+// ---- gemm_ksplit.hip (fwd / dX on codes in the working layout, few 128 x 128 output tiles) --------------------
+// Workgroups that share a tile of the forward (bt = false) or dX (bt = true); 0: the tile kernels of gemm_mfma.hip compute it.
+int ksplit_parts(const Problem &p, bool bt, const SkScratch &sk);
+size_t ksplit_bytes(const Problem &p, bool bt, int parts);          // of sk.partials; 0 for one part
+void launch_ksplit(const Problem &p, bool bt, const void *A, const void *codes, const void *sz, void *C, const SkScratch &sk,
+                   int parts, hipStream_t st);
+
 // ---- gemm_mid.hip (forward for few output tiles) --------------------------------------------
 bool mid_applies(const Problem &p);
 FwdRoute mid_route(const Problem &p, bool from_packed);
