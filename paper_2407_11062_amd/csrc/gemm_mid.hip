@@ -15,14 +15,15 @@
 // instruction: 1.5 instead of 1.2 us per K step.)
 // What bounds it is the rebuild.  Beside a 32x32x16 product (33 cycles) a SIMD issues some 4.9 arithmetic instructions, every
 // further one costs 4 cycles (two waves, measured with independent instructions; max(33, 13.5 + 4 n) fits), and here a
-// product goes with 5 (96 tokens, 2 bit, working layout) to 14 (64 tokens, 4 bit) of them.  Switched off one at a time (2 bit,
+// product goes with 5.5 (96 tokens, 2 bit, working layout) to 13 (64 tokens, 4 bit) of them.  Switched off one at a time (2 bit,
 // 64 tokens, 4096 x 4096, 24.5 us): the rebuild 15.4, all loads 21.5, the LDS reads 24.1; everything but the products 11.8.  So
-//   - the rebuild of slice t + 1 is spread between the products of slice t, and everything a step starts with is read in the
-//     last slice of the step before, behind the barrier that sits in front of that slice (333 tokens, 4096 x 11008, us:
-//     2 bit 63 -> 60, 3 bit, working layout 70 -> 65; 4 bit 66 -> 64);
+//   - a K step is four slices of 16 per wave; the barrier sits in the middle of a step, behind the reads of all its tokens: in
+//     the third slice the next step's codes are read, in the fourth its tables and first weights are made, so that no slice waits
+//     for LDS, and every slice's rebuild is spread evenly between the products of the slice before;
+//   - addresses are scalar work: the buffers move along K, the lanes' offsets stay;
 //   - where the tiles still fill the chip, 128 tokens share a rebuilt weight (k_gemm_mid_tall below).
-// Measured, us: 2 bit, 333 tokens: 4096 x 4096 41 -> 28 (and the re-layout of the codes, 6, gone), 4096 x 11008 104 -> 60
-// (14 gone); 4 bit, 150 tokens, 11008 x 4096 45 -> 38 (10 gone).
+// Measured, us, 333 tokens, from the packed arrays (the chain of a step behind its barrier / this): 4096 x 4096 2 bit 26.4 -> 23.2,
+// 3 bit 35 -> 31.4, 4 bit 30.9 -> 25.2; 4096 x 11008 61 -> 54, 70 -> 60, 72 -> 58.
 #include "common.h"
 #include "dense_codes.h"
 #include "kernels.h"
@@ -52,7 +53,8 @@ template <int BITS, int SRC, int BM> struct MidLds {
     static constexpr int WPS = SRC == kWorking ? WorkCodes<BITS>::kWords : BITS;      // words per segment
     static constexpr int NCH = 2 * WPS;                                               // 16-byte chunks of a row's codes
     static constexpr int ZW = SRC == kPackedZ && BITS == 3 ? 2 : 1;
-    static constexpr uint32_t TOK = BM * kMidBK * 2, CODES = kMidBN * NCH * 16, ROWW = kMidBN * 8 * 4;
+    static constexpr uint32_t WAVE_CODES = NCH == 4 ? 1024 : 2048;                    // the 16 rows that a wave fetches
+    static constexpr uint32_t TOK = BM * kMidBK * 2, CODES = 8 * WAVE_CODES, ROWW = kMidBN * 8 * 4;
     static constexpr uint32_t STEP = TOK + CODES + (1 + ZW) * ROWW, TOTAL = 2 * STEP;
     static_assert(TOTAL <= 160 * 1024, "LDS of one CU");
 };
@@ -62,13 +64,26 @@ template <int NCH> __device__ __forceinline__ int code_chunk_swz(int row, int c)
     return NCH == 2 ? c ^ ((row >> 2) & 1) : NCH == 4 ? c ^ ((row >> 1) & 3) : NCH == 8 ? c ^ (row & 7) : c;            // rows of 96 bytes spread by themselves
 }
 
+// A buffer that moves along K instead of the lanes' offsets into it: scalar work.  Past the last step nothing is in range.
+struct Moving {
+    uint64_t base; uint32_t left;
+    __device__ __forceinline__ Moving(const void *p, uint32_t bytes) : base((uint64_t)p & 0xFFFFFFFFFFFFull), left(bytes) {}
+    __device__ __forceinline__ void by(uint32_t n) { base += n; left -= n; }
+    __device__ __forceinline__ RawRsrc at(bool live) const
+    {
+        RawRsrc r;
+        r.w[0] = (int)(uint32_t)base; r.w[1] = (int)(uint32_t)(base >> 32); r.w[2] = live ? (int)left : 0; r.w[3] = 0x00020000;
+        return r;
+    }
+};
+
 template <int BITS, int SRC, int BM>
 __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
 {
     typedef MidLds<BITS, SRC, BM> L;
     constexpr int MI = BM / 32, WPS = L::WPS, NCH = L::NCH;
     constexpr int A_LOADS = BM / 16;                  // direct-to-LDS instructions per wave and K step (two rows each)
-    constexpr int C_INSTR = kMidBN * NCH / 64;        // ... for the codes, in all
+    constexpr int C_LOADS = NCH == 4 ? 1 : 2;         // ... for the codes
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 1, kg = wave >> 1, r = lane & 31, h = lane >> 5;
@@ -79,75 +94,80 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
     const int pid = xcd * (nb >> 3) + (xcd < rem ? xcd : rem) + (int)(blockIdx.x >> 3);
     const int m0 = (pid % a.tiles_m) * BM, n0 = (pid / a.tiles_m) * kMidBN;
 
-    const RawRsrc rX = make_raw_rsrc(a.X, a.x_bytes);
-    const RawRsrc rW = make_raw_rsrc(a.codes, a.codes_bytes);
-    const RawRsrc rS = make_raw_rsrc(a.s, a.s_bytes);
-    const RawRsrc rZ = make_raw_rsrc(SRC == kFloatZ ? (const void *)a.zf : (const void *)a.zp, a.z_bytes);
     const int n_segs = a.I >> 5, steps = (a.I + kMidBK - 1) / kMidBK;
     const uint32_t lds0 = lds_addr_of(smem_raw);
 
     // ---- loads of one K step.  Rows past T or O are out of range of their buffers (zeros); columns past I: tokens and
-    // step sizes come as zeros, the codes there are whatever follows the row.
+    // step sizes come as zeros, the codes there are whatever follows the row.  The lanes' byte offsets into tokens and codes
+    // stay as they are, the buffers move along K.
     uint32_t off[A_LOADS];
-    int col[A_LOADS];
 #pragma unroll
     for (int it = 0; it < A_LOADS; ++it) {
         const int row = (wave * A_LOADS + it) * 2 + h;
-        col[it] = (r ^ (row & 7)) * 8;
-        off[it] = m0 + row < a.T ? ((uint32_t)(m0 + row) * (uint32_t)a.I + (uint32_t)col[it]) * 2u : kOobOffset;
+        off[it] = m0 + row < a.T ? ((uint32_t)(m0 + row) * (uint32_t)a.I + (uint32_t)((r ^ (row & 7)) * 8)) * 2u : kOobOffset;
     }
-    uint32_t coff[(C_INSTR + 7) / 8];
+    uint32_t coff[C_LOADS];
 #pragma unroll
-    for (int it = 0; it < (C_INSTR + 7) / 8; ++it) {
-        const int e = (it * 8 + wave) * 64 + lane, row = e / NCH;
-        coff[it] = (uint32_t)(n0 + row) * a.code_row_bytes + (uint32_t)code_chunk_swz<NCH>(row, e % NCH) * 16u;
+    for (int it = 0; it < C_LOADS; ++it) {
+        const int e = it * 64 + lane, row = wave * 16 + e / NCH;
+        coff[it] = e < 16 * NCH ? (uint32_t)(n0 + row) * a.code_row_bytes + (uint32_t)code_chunk_swz<NCH>(row, e % NCH) * 16u : kOobOffset;
     }
     const uint32_t srow = (uint32_t)(n0 + wave * 16 + (lane >> 3));        // rows of the step sizes: 8 per instruction, two instructions
-    // Load number d of those a wave issues per K step: codes, step sizes and zero points, then tokens.
-    constexpr int C_LOADS = (C_INSTR + 7) / 8, S_LOADS = 2 * (1 + L::ZW), LOADS = C_LOADS + S_LOADS + A_LOADS;
-    auto load = [&](int d, int step, int buf) {
-        const uint32_t base = lds0 + (uint32_t)buf * L::STEP;
-        if (d < C_LOADS) {
-            if (C_INSTR % 8 == 0 || d * 8 + wave < C_INSTR)
-                load_to_lds16_at(rW, base + L::TOK + (uint32_t)((d * 8 + wave) * 1024), coff[d] + (uint32_t)step * (NCH * 16));
-        } else if (d < C_LOADS + S_LOADS) {
-            const int e = d - C_LOADS, it = e / (1 + L::ZW), what = e % (1 + L::ZW);           // what: step size, zero point (, its second word)
-            const int seg = step * 8 + (lane & 7);
-            const uint32_t j = a.spg_magic ? __umulhi((uint32_t)seg, a.spg_magic) : (uint32_t)seg;
-            const bool ok = seg < n_segs;
-            const uint32_t gi = (srow + 8 * it) * (uint32_t)a.G + j;
-            const uint32_t at = base + L::TOK + L::CODES + (uint32_t)((wave * 2 + it) * 256) + (uint32_t)what * L::ROWW;
-            if constexpr (SRC == kWorking) load_to_lds4_at(rS, at, ok ? gi * 8u + 4u * what : kOobOffset);
-            else if (what == 0) load_to_lds4_at(rS, at, ok ? gi * 4u : kOobOffset);
-            else if constexpr (SRC == kFloatZ) load_to_lds4_at(rZ, at, ok ? gi * 4u : kOobOffset);
-            else load_to_lds4_at(rZ, at, ((srow + 8 * it) * a.z_row_words + ((j * BITS) >> 5)) * 4u + 4u * (what - 1));
-        } else {
-            const int it = d - C_LOADS - S_LOADS;
-            load_to_lds16_at(rX, base + (uint32_t)((wave * A_LOADS + it) * 1024),
-                             step * kMidBK + col[it] < a.I ? off[it] + (uint32_t)step * (kMidBK * 2) : kOobOffset);
+    const uint32_t each = a.spg_magic == 0u ? ~0u : 0u;                    // groups of 32: every segment is one
+    auto group_of = [&](uint32_t seg) { return __umulhi(seg, a.spg_magic) + (seg & each); };
+    Moving bX(a.X, a.x_bytes), bW(a.codes, a.codes_bytes);
+    RawRsrc rX, rW;
+    uint32_t s_left = 0, z_left = 0;
+    uint32_t sgroup = 0;                 // of this lane's segment
+    uint32_t soff = 0;                   // 0, or out of range where the segment lies past the end of the rows
+    int to_aim = steps;                  // counters of their own: a step number that lanes compute with ends up in a vector register, and
+    uint32_t seg = (uint32_t)(lane & 7); // with it the descriptors
+    auto aim = [&]() {                   // at the next step; past the last one nothing is in range (zeros)
+        const bool live = to_aim-- > 0;
+        rX = bX.at(live); rW = bW.at(live);
+        bX.by(kMidBK * 2); bW.by(NCH * 16);
+        s_left = live ? a.s_bytes : 0u; z_left = live ? a.z_bytes : 0u;
+        sgroup = group_of(seg);
+        soff = (int)seg < n_segs ? 0u : kOobOffset;
+        seg += 8;
+    };
+    // in front of the loads of every step
+    auto mask_last = [&](int step) {
+        if (step == steps - 1 && a.I % kMidBK != 0) {
+#pragma unroll
+            for (int it = 0; it < A_LOADS; ++it) {
+                const int row = (wave * A_LOADS + it) * 2 + h;
+                if ((r ^ (row & 7)) * 8 >= a.I % kMidBK) off[it] = kOobOffset;
+            }
         }
     };
-    // part P of 3 of a step's loads
-    auto load_part = [&](auto part, int step, int buf) {
+    // Load number d of those a wave issues per K step: codes, step sizes and zero points, then tokens.
+    constexpr int S_LOADS = 2 * (1 + L::ZW), LOADS = C_LOADS + S_LOADS + A_LOADS;
+    auto load = [&](int d, int buf) {
+        const uint32_t base = lds0 + (uint32_t)buf * L::STEP;
+        const RawRsrc rS = make_raw_rsrc(a.s, s_left), rZ = make_raw_rsrc(SRC == kFloatZ ? (const void *)a.zf : (const void *)a.zp, z_left);
+        if (d < C_LOADS) {
+            load_to_lds16_at(rW, base + L::TOK + (uint32_t)wave * L::WAVE_CODES + (uint32_t)(d * 1024), coff[d]);
+        } else if (d < C_LOADS + S_LOADS) {
+            const int e = d - C_LOADS, it = e / (1 + L::ZW), what = e % (1 + L::ZW);           // what: step size, zero point (, its second word)
+            const uint32_t gi = (srow + 8 * it) * (uint32_t)a.G + sgroup;
+            const uint32_t at = base + L::TOK + L::CODES + (uint32_t)((wave * 2 + it) * 256) + (uint32_t)what * L::ROWW;
+            if constexpr (SRC == kWorking) load_to_lds4_at(rS, at, (gi * 8u + 4u * what) | soff);
+            else if (what == 0) load_to_lds4_at(rS, at, (gi * 4u) | soff);
+            else if constexpr (SRC == kFloatZ) load_to_lds4_at(rZ, at, (gi * 4u) | soff);
+            else load_to_lds4_at(rZ, at, ((srow + 8 * it) * a.z_row_words + ((sgroup * BITS) >> 5)) * 4u + 4u * (what - 1));
+        } else {
+            const int it = d - C_LOADS - S_LOADS;
+            load_to_lds16_at(rX, base + (uint32_t)((wave * A_LOADS + it) * 1024), off[it]);
+        }
+    };
+    // part P of 2 of a step's loads
+    auto load_part = [&](auto part, int buf) {
         constexpr int P = decltype(part)::value;
 #pragma unroll
         for (int d = 0; d < LOADS; ++d)
-            if (d * 3 / LOADS == P) load(d, step, buf);
-    };
-    struct Seg { uint32_t w[WPS]; };
-    auto eight = [&](const WhatTable<BITS> &tab, const Seg &sg, auto t) -> bf16x8 {
-        constexpr int T4 = decltype(t)::value;
-        if constexpr (SRC == kWorking) {
-            WorkCodes<BITS> c;
-#pragma unroll
-            for (int k = 0; k < WPS; ++k) c.w[k] = sg.w[k];
-            return tab.template eight<T4>(c);
-        } else {
-            CodeWords<BITS> c;
-#pragma unroll
-            for (int k = 0; k < WPS; ++k) c.w[k] = sg.w[k];
-            return unslot_of<BITS>(eight_of<BITS, T4>(tab, c));
-        }
+            if (d * 2 / LOADS == P) load(d, buf);
+        __builtin_amdgcn_sched_barrier(0);
     };
 
     floatx16 acc[2][MI];
@@ -158,107 +178,168 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
 #pragma unroll
             for (int q = 0; q < 16; ++q) acc[b][i][q] = 0.0f;
 
-    Seg cur[2];
+    // This lane's segment (number 2 kg + h of the step) of both 32-row blocks, with what it takes to rebuild the weights: read
+    // from LDS a slice before it is needed.
+    struct Raw { uint32_t c[2][WPS], s[2], z[2][L::ZW], zshift; };
+    Raw raw;
+    uint32_t cur[2][WPS];
     WhatTable<BITS> tab[2];
-    bf16x8 x[2][MI], w[2][2];
-    // this lane's segment (number 2 kg + h of the step) of both 32-row blocks, with what it takes to rebuild the weights
-    float ws[2];
-    uint32_t wz[2][L::ZW];
-    auto read_codes = [&](int buf) {
+    constexpr bool kShared = BITS == 2 && SRC != kWorking;     // 2-bit codes as packed: the lookups of a word serve two slices
+    uint32_t lo[2][4], hi[2][4];
+    bf16x8 x[4][MI], w[2][2];
+    uint32_t raw_seg = (uint32_t)(2 * kg);        // of the lanes h = 0
+    auto read_raw = [&](int buf) {        // the steps in order
         const unsigned char *const here = smem_raw + (uint32_t)buf * L::STEP;
+        if constexpr (SRC == kPackedZ) raw.zshift = ((h ? group_of(raw_seg + 1) : group_of(raw_seg)) * BITS) & 31u;
+        raw_seg += 8;
+        const int row = wn * 64 + r;                  // row + 32 lies a constant further on everywhere
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const int row = wn * 64 + b * 32 + r;
-            const uint32_t *const sw = reinterpret_cast<const uint32_t *>(here + L::TOK + L::CODES) + row * 8 + 2 * kg + h;
-            ws[b] = __uint_as_float(sw[0]);
+            const uint32_t *const sw = reinterpret_cast<const uint32_t *>(here + L::TOK + L::CODES) + (row + b * 32) * 8 + 2 * kg + h;
+            raw.s[b] = sw[0];
 #pragma unroll
-            for (int k = 0; k < L::ZW; ++k) wz[b][k] = sw[(k + 1) * (L::ROWW / 4)];
-            const unsigned char *const codes = here + L::TOK + row * (NCH * 16);
+            for (int k = 0; k < L::ZW; ++k) raw.z[b][k] = sw[(k + 1) * (L::ROWW / 4)];
+            const unsigned char *const codes = here + L::TOK + (uint32_t)((row >> 4) + 2 * b) * L::WAVE_CODES + (row & 15) * (NCH * 16);
             if constexpr (WPS == 2) {
                 const uintx2 v = *reinterpret_cast<const uintx2 *>(codes + code_chunk_swz<NCH>(row, kg) * 16 + h * 8);
-                cur[b].w[0] = v[0]; cur[b].w[1] = v[1];
+                raw.c[b][0] = v[0]; raw.c[b][1] = v[1];
             } else if constexpr (WPS == 3) {
                 const uint32_t *const v = reinterpret_cast<const uint32_t *>(codes + (2 * kg + h) * 12);
-                cur[b].w[0] = v[0]; cur[b].w[1] = v[1]; cur[b].w[2] = v[2];
+                raw.c[b][0] = v[0]; raw.c[b][1] = v[1]; raw.c[b][2] = v[2];
             } else {
                 const uintx4 v = *reinterpret_cast<const uintx4 *>(codes + code_chunk_swz<NCH>(row, 2 * kg + h) * 16);
-                cur[b].w[0] = v[0]; cur[b].w[1] = v[1]; cur[b].w[2] = v[2]; cur[b].w[3] = v[3];
+                raw.c[b][0] = v[0]; raw.c[b][1] = v[1]; raw.c[b][2] = v[2]; raw.c[b][3] = v[3];
             }
         }
     };
-    auto build = [&](int step, int b) {
-        float z = __uint_as_float(wz[b][0]);
-        if constexpr (SRC == kPackedZ) {
-            const uint32_t seg = (uint32_t)(step * 8 + 2 * kg + h);
-            const uint32_t zshift = ((a.spg_magic ? __umulhi(seg, a.spg_magic) : seg) * BITS) & 31u;
-            const uint32_t v = L::ZW == 2 ? __builtin_amdgcn_alignbit(wz[b][L::ZW - 1], wz[b][0], zshift) : wz[b][0] >> zshift;
-            z = (float)(v & ((1u << BITS) - 1u));
+    auto build = [&]() {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            float z = __uint_as_float(raw.z[b][0]);
+            if constexpr (SRC == kPackedZ) {
+                const uint32_t v = L::ZW == 2 ? __builtin_amdgcn_alignbit(raw.z[b][L::ZW - 1], raw.z[b][0], raw.zshift) : raw.z[b][0] >> raw.zshift;
+                z = (float)(v & ((1u << BITS) - 1u));
+            }
+            tab[b].build(__uint_as_float(raw.s[b]), z);
+#pragma unroll
+            for (int k = 0; k < WPS; ++k) cur[b][k] = raw.c[b][k];
         }
-        tab[b].build(ws[b], z);
     };
+    auto look_up = [&](int word) {                // bytes of the codes k, k + 4, k + 8 and k + 12 of a word
+        if constexpr (kShared) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t c = (cur[b][word] >> (2 * k)) & 0x03030303u;
+                    lo[b][k] = __builtin_amdgcn_perm(tab[b].lo[0], tab[b].lo[0], c);
+                    hi[b][k] = __builtin_amdgcn_perm(tab[b].hi[0], tab[b].hi[0], c);
+                }
+        }
+    };
+    auto eight = [&](int b, auto t) -> bf16x8 {
+        constexpr int T4 = decltype(t)::value;
+        if constexpr (kShared) {
+            uintx4 u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) u[k] = __builtin_amdgcn_perm(hi[b][k], lo[b][k], T4 % 2 ? 0x07030602u : 0x05010400u);
+            return unslot_of<BITS>(__builtin_bit_cast(bf16x8, u));
+        } else if constexpr (SRC == kWorking) {
+            WorkCodes<BITS> c;
+#pragma unroll
+            for (int k = 0; k < WPS; ++k) c.w[k] = cur[b][k];
+            return tab[b].template eight<T4>(c);
+        } else {
+            CodeWords<BITS> c;
+#pragma unroll
+            for (int k = 0; k < WPS; ++k) c.w[k] = cur[b][k];
+            return unslot_of<BITS>(eight_of<BITS, T4>(tab[b], c));
+        }
+    };
+    auto rebuild = [&](int slot, auto t) { w[slot][0] = eight(0, t); w[slot][1] = eight(1, t); };
     const unsigned char *const tile = smem_raw + r * 512;
-    auto read_x = [&](int slot, int buf, int t) {
+    auto read_x = [&](int t, int buf) {
 #pragma unroll
         for (int i = 0; i < MI; ++i)
-            x[slot][i] = *reinterpret_cast<const bf16x8 *>(tile + (uint32_t)buf * L::STEP + i * (32 * 512) + (((kg * 8 + h * 4 + t) ^ (r & 7)) * 16));
+            x[t][i] = *reinterpret_cast<const bf16x8 *>(tile + (uint32_t)buf * L::STEP + i * (32 * 512) + (((kg * 8 + h * 4 + t) ^ (r & 7)) * 16));
     };
-    auto products = [&](int slot) {
+    auto products = [&](int t) {
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int b = 0; b < 2; ++b)
-                acc[b][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[slot][b], x[slot][i], acc[b][i], 0, 0, 0);
+                acc[b][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[t & 1][b], x[t][i], acc[b][i], 0, 0, 0);
     };
-    // one product, one LDS read, a share of the arithmetic, repeated
-    auto weave = [&](auto valu) {
+    // What a slice rebuilds from is not used before it, and what it rebuilds is there at its end; between the two one product, a few
+    // LDS reads and a share of the arithmetic (`n` instructions) in turns.
+    auto begin = [&]() {
 #pragma unroll
-        for (int q = 0; q < 2 * MI; ++q) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, decltype(valu)::value, 0);
+        for (int b = 0; b < 2; ++b) {
+#pragma unroll
+            for (int k = 0; k < WPS; ++k) asm volatile("" : "+v"(cur[b][k]));
+            if constexpr (kShared) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(lo[b][k]), "+v"(hi[b][k]));
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    constexpr int kVal = (BITS == 4 ? 52 : 40) / (2 * MI) + 1;
-
+    auto weave = [&](auto n) {
 #pragma unroll
-    for (int d = 0; d < LOADS; ++d) load(d, 0, 0);
+        for (int q = 0; q < 2 * MI; ++q) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, decltype(n)::value / (2 * MI) + 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x004, 5, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto end = [&](int slot) { asm volatile("" : "+v"(w[slot][0]), "+v"(w[slot][1])); };
+    constexpr int kRebuild = BITS == 2 ? (kShared ? 16 : 24) : BITS == 3 ? (SRC == kWorking ? 24 : 40) : 46;      // of one slice
+    constexpr int kTables = BITS == 2 ? 26 : BITS == 3 ? 42 : 12, kLook = kShared ? 30 : 0;
+
+    mask_last(0); aim();
+    load_part(IC<0>{}, 0); load_part(IC<1>{}, 0);
     wait_all_and_barrier();
-    if (steps > 1) load_part(IC<0>{}, 1, 1);
-    read_codes(0);
-    read_x(0, 0, 0);
-    build(0, 0); build(0, 1);
-    w[0][0] = eight(tab[0], cur[0], IC<0>{}); w[0][1] = eight(tab[1], cur[1], IC<0>{});
+    mask_last(1); aim();
+    load_part(IC<0>{}, 1); load_part(IC<1>{}, 1);
+    read_raw(0);
+    read_x(0, 0);
+    build(); look_up(0);
+    rebuild(0, IC<0>{});
     __builtin_amdgcn_sched_barrier(0);
-    for (int step = 0; step < steps; ++step) {
-        const int buf = step & 1;
-        if (step + 1 < steps) load_part(IC<1>{}, step + 1, buf ^ 1);
-        __builtin_amdgcn_sched_barrier(0);
-        read_x(1, buf, 1);
+    auto one_step = [&](int step, auto par) __attribute__((always_inline)) {
+        constexpr int buf = decltype(par)::value;
+        mask_last(step + 2);
+        begin();
+        read_x(1, buf); read_x(2, buf);
         products(0);
-        w[1][0] = eight(tab[0], cur[0], IC<1>{}); w[1][1] = eight(tab[1], cur[1], IC<1>{});
-        weave(IC<kVal>{});
-        if (step + 1 < steps) load_part(IC<2>{}, step + 1, buf ^ 1);
-        __builtin_amdgcn_sched_barrier(0);
-        read_x(0, buf, 2);
+        rebuild(1, IC<1>{}); look_up(1);
+        weave(IC<kRebuild + kLook + 10>{}); end(1);
+        begin();
+        read_x(3, buf);
         products(1);
-        w[0][0] = eight(tab[0], cur[0], IC<2>{}); w[0][1] = eight(tab[1], cur[1], IC<2>{});
-        weave(IC<kVal>{});
-        read_x(1, buf, 3);
-        products(0);
-        w[1][0] = eight(tab[0], cur[0], IC<3>{}); w[1][1] = eight(tab[1], cur[1], IC<3>{});
-        weave(IC<kVal>{});
-        wait_all_and_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        if (step + 2 < steps) load_part(IC<0>{}, step + 2, buf);
-        __builtin_amdgcn_sched_barrier(0);
-        read_codes(buf ^ 1);
-        read_x(0, buf ^ 1, 0);
-        products(1);
-        build(step + 1, 0); build(step + 1, 1);
-        w[0][0] = eight(tab[0], cur[0], IC<0>{}); w[0][1] = eight(tab[1], cur[1], IC<0>{});
-        weave(IC<kVal + 4>{});
+        rebuild(0, IC<2>{});
+        aim();
+        weave(IC<kRebuild + 6>{}); end(0);
+        wait_all_and_barrier();           // the next step is in LDS; everyone has this one's tokens in registers
+        load_part(IC<0>{}, buf);
+        begin();
+        read_raw(buf ^ 1); read_x(0, buf ^ 1);
+        products(2);
+        rebuild(1, IC<3>{});
+        weave(IC<kRebuild + 6>{}); end(1);
+        load_part(IC<1>{}, buf);
+        products(3);
+        build(); look_up(0);
+        rebuild(0, IC<0>{});
+        weave(IC<kRebuild + kTables + kLook>{}); end(0);
+    };
+    for (int step = 0;;) {
+        one_step(step, IC<0>{}); if (++step >= steps) break;
+        one_step(step, IC<1>{}); if (++step >= steps) break;
     }
+    wait_all_and_barrier();
 
     // ---- sums: acc[b][i][q] is row 8 (q / 4) + 4 h + q % 4 of block b, token 32 i + r.  One 32-row block of every wave at a
     // time passes through LDS as [wave][token][32 rows] (the 16-byte chunk c of a token at c ^ (token & 7)); wave (wn, kg) then
@@ -302,7 +383,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
 
 // ---- 128 tokens per tile -----------------------------------------------------------------------------------
 // Four products per rebuilt fragment instead of two or three, so the matrix cores have less arithmetic to wait for (6.7
-// instructions a product at 2 bit, 7 at 4; 6.8 and 9.5 with 96 tokens).  Two stages of 256-wide K steps would take 176 KB
+// instructions a product at 2 bit, 7 at 4; 7.1 and 9.5 with 96 tokens).  Two stages of 256-wide K steps would take 176 KB
 // of LDS, so a step is 128 wide: a wave multiplies one segment of it, and the lanes h = 0 and 1 of a row take 16 of its codes
 // each.  With the room that leaves, tokens are fetched two steps ahead (three stages), codes four; step sizes and zero points
 // come four steps at a time, 16 bytes a lane.  A lane's byte offsets never change: the buffers move along K, which is scalar work
@@ -385,18 +466,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
             load_to_lds16_at(rZ, to + 8192u + (uint32_t)(wave * 1024), soff[1]);
         }
     };
-    // The buffers move along K, so that a lane keeps its byte offset; past the last step nothing is in range (zeros).
-    struct Moving {
-        uint64_t base; uint32_t left;
-        __device__ __forceinline__ void by(uint32_t n) { base += n; left -= n; }
-        __device__ __forceinline__ RawRsrc at(bool live) const
-        {
-            RawRsrc r;
-            r.w[0] = (int)(uint32_t)base; r.w[1] = (int)(uint32_t)(base >> 32); r.w[2] = live ? (int)left : 0; r.w[3] = 0x00020000;
-            return r;
-        }
-    };
-    Moving bX{(uint64_t)a.X & 0xFFFFFFFFFFFFull, a.x_bytes}, bW{(uint64_t)a.codes & 0xFFFFFFFFFFFFull, a.codes_bytes};
+    Moving bX(a.X, a.x_bytes), bW(a.codes, a.codes_bytes);
     RawRsrc rX, rW;
     auto aim_x = [&](int step) { rX = bX.at(step < steps); bX.by(BK * 2); };            // the steps in order
     auto aim_codes = [&](int step) { rW = bW.at(step < steps); bW.by(NCH * 16); };
@@ -684,11 +754,12 @@ template <int BITS, int SRC, int BM> void launch_t(MidArgs a, hipStream_t st)
 }
 
 // What a launch with token tiles of `bm` takes, in us: rounds of workgroups (one per compute unit), each 6 us and 1.2 (64
-// tokens), 1.45 (96) or 2.05 (128) us per 256-wide K step; fitted at 4096, 8192 and 11008 inputs.
+// tokens), 1.45 (96) or 1.95 (128) us per 256-wide K step: an upper figure for the first two, which have become faster since
+// (1.08 and 1.4 at 192 workgroups), so that the lines to the other kernels stay where both sides were measured.
 int64_t rounds_of(const Problem &p, int bm) { return (((p.T + bm - 1) / bm) * ((p.O + kMidBN - 1) / kMidBN) + 255) / 256; }
 double launch_us(const Problem &p, int bm)
 {
-    return (double)rounds_of(p, bm) * (6.0 + (double)((p.I + kMidBK - 1) / kMidBK) * (bm == 64 ? 1.2 : bm == 96 ? 1.45 : 2.05));
+    return (double)rounds_of(p, bm) * (6.0 + (double)((p.I + kMidBK - 1) / kMidBK) * (bm == 64 ? 1.2 : bm == 96 ? 1.45 : 1.95));
 }
 
 // The tall kernel finds the groups of a 128-wide step by counting: groups of 32 or 64, or whole steps.  One round only: in two
@@ -734,19 +805,20 @@ FwdRoute mid_route(const Problem &p, bool from_packed)
 
 double mid_us(const Problem &p) { return launch_us(p, token_tile(p)); }
 
-// Against the 128 x 128-tile kernel, which takes 0.55 (few tiles) to 0.65 us (256 tiles) per 64-wide K tile while a compute unit
-// has one tile at most and 0.9 or more beyond that (11008 x 4096: 256 tokens, 172 tiles: 43 us there, 46-49 here in two rounds; 288 tokens, 258
-// tiles: 61 and 47; 400 tokens: 63 and 57).  More than two rounds here, or more than two tiles per compute unit there: the
-// 256 x 256 tiles are the better kernel (11008 x 4096, 515 tokens: 68 us in tiles, 84 here).  The GEMMs alone are compared:
-// a forward from the packed arrays saves the re-layout as well and would gain a little earlier, but every forward entry point
-// shares the rule, so that their results stay bitwise equal.
+// Against k_gemm_ksplit while there are at most 256 tiles of 128 x 128 (4.8 us and 0.8 to 1.1, with the fill, a pair of 64-wide K
+// tiles; 1024 inputs, 2000 tokens, 2048 rows: 12 us there, 14 here), and against the 128 x 128-tile kernel with two tiles per
+// compute unit beyond that (0.9 us per K tile; 11008 x 4096: 288 tokens, 258 tiles 61 us there and 42 here; 400 tokens 63 and 51).
+// More than two rounds here, or more than two tiles per compute unit there: the 256 x 256 tiles are the better kernel.  The GEMMs
+// alone are compared: a forward from the packed arrays saves the re-layout as well and would gain a little earlier, but every
+// forward entry point shares the rule, so that their results stay bitwise equal.
 bool mid_applies(const Problem &p)
 {
     if (!p.act_bf16 || !group_by_magic(p) || p.T <= 32) return false;
     if (p.T <= 64) return !gemv_work_applies(p);
     const int64_t tiles = ((p.T + 127) / 128) * ((p.O + 127) / 128);
-    const double k_tile = tiles <= 256 ? std::max(0.55, 0.48 + 0.17 * (double)tiles / 256.0) : 0.9;
-    return tiles <= 512 && mid_us(p) < 4.0 + (double)((p.I + 63) / 64) * k_tile;
+    const double other = tiles <= 256 ? 4.8 + (double)((p.I + 127) / 128) * (0.8 + 0.3 * (double)tiles / 256.0)
+                                      : 4.0 + (double)((p.I + 63) / 64) * 0.9;
+    return tiles <= 512 && mid_us(p) < other;
 }
 
 void launch_mid(const Problem &p, const void *X, const void *Wpacked, const float *s, const void *zpacked, const float *zfloat,
