@@ -1213,10 +1213,25 @@ typedef DwTile<128, 128, 64, 2, 2, 2> DwTileSmall;
 typedef DwTile<256, 256, 64, 2, 2, 4> DwTileBig;
 static_assert(DwTileSmall::BM == TileSmall::BM && DwTileBig::BM == TileBig::BM, "group-fits-in-tile tests use Tile*::BM");
 
-// the big tile unless it would leave a large part of the 256 CUs without a workgroup
-bool use_small_tile(int64_t m, int64_t n)
+// dW: the big tile unless it would leave a large part of the 256 CUs without a workgroup
+bool use_small_dw_tile(int64_t m, int64_t n)
 {
     return ((m + 255) / 256) * ((n + 255) / 256) < 160;
+}
+
+// fwd / dX with more tiles than k_gemm_ksplit takes: big tiles where they fill most of the chip, or where the small ones do not
+// fit two per compute unit (dX of 5120 x 5120, 1792 tokens: 140 big tiles 99 us, 560 small ones 133; 2048 -> 5504: 154 big tiles 46,
+// small 60), or, each shared by two or three workgroups, where the contraction is long enough to pay for the parts: small tiles
+// take 0.9 us per K tile, a share of a big one 1.55 (the chip's power limit), 0.085 us per part comes on top (dX, 11008 -> 4096:
+// 1280 tokens 157 -> 111 us, 2048 tokens 184 -> 164; 4096 -> 4096, 1280 tokens: 67 -> 64, 2048 tokens: 74, 80 if it were taken).
+enum class TileChoice { Small, Big, BigShared };
+TileChoice q_tile(int64_t m, int64_t n, int64_t k, bool scratch)
+{
+    const int64_t big = ((m + 255) / 256) * ((n + 255) / 256), small = ((m + 127) / 128) * ((n + 127) / 128);
+    if (big >= 160 || small > 512) return TileChoice::Big;
+    const int64_t c = 32 / ((big + 7) / 8), k_tiles = (k + 63) / 64;           // contributors per tile, as plan_tiles deals them out
+    if (!scratch || c < 2 || c > 3 || k_tiles < 32) return TileChoice::Small;
+    return 5.0 + 1.55 * (double)((k_tiles + c - 1) / c) + 0.085 * (double)(big * c) < 4.0 + 0.9 * (double)k_tiles ? TileChoice::BigShared : TileChoice::Small;
 }
 
 // The kernels need more dynamic LDS than the default limit; the attribute is per kernel AND per device, so it is set
@@ -1254,11 +1269,14 @@ int resident_workgroups(size_t smem)
 //     equal runs (with more rounds, cutting the last 1.x of them into runs measured slower than leaving the last round
 //     partly filled: 7B gate, 5.4 rounds: -3 %; 13B gate, 3.4 rounds: -4 %);
 //   - with at most half a round of tiles beyond the whole rounds, those few tiles are split among groups of workgroups.
-SkPlan plan_tiles(int ntiles, int pairs, int resident, float *partials, uint32_t *counters, bool runs = true)
+SkPlan plan_tiles(int ntiles, int pairs, int resident, float *partials, uint32_t *counters, bool runs = true, bool share = false)
 {
     SkPlan sk{};
     sk.pairs = pairs; sk.partials = partials; sk.counters = counters;
-    if (ntiles <= resident) return sk;                       // walk = 0
+    if (ntiles <= resident) {                                // walk = 0: one workgroup per tile, unless they are to share
+        if (share && partials != nullptr && counters != nullptr && 2 * ((ntiles + 7) / 8) <= resident / 8) { sk.walk = 1; sk.split = 1; }
+        return sk;
+    }
     sk.walk = 1;
     const int W = resident / 8, per = ntiles / 8, full = per / W;
     const bool even = (per % W == 0) && (ntiles % 8 == 0);
@@ -1281,7 +1299,7 @@ template <bool BT, typename TS> constexpr size_t q_smem_bytes()
     return 2 * (size_t)(TS::BM * TS::BK + (BT ? TS::BK * LDB : TS::BN * LDB)) * sizeof(bf16_t) + (size_t)TS::WGM * TS::WGN * kStoreStageBytes;
 }
 template <bool BT, typename TS>
-QLaunchPlan plan_q(int M, int N, int K, float *partials, uint32_t *counters)
+QLaunchPlan plan_q(int M, int N, int K, float *partials, uint32_t *counters, bool share)
 {
     QLaunchPlan q{};
     q.tiles_m = (M + TS::BM - 1) / TS::BM;
@@ -1296,20 +1314,20 @@ QLaunchPlan plan_q(int M, int N, int K, float *partials, uint32_t *counters)
     // (grid a multiple of 8, one share per XCD).
     q.ntiles = q.tiles_m * q.tiles_n;
     const int resident = resident_workgroups(q_smem_bytes<BT, TS>());
-    q.sk = plan_tiles(q.ntiles, ((K + TS::BK - 1) / TS::BK + 1) / 2, resident, partials, counters);
+    q.sk = plan_tiles(q.ntiles, ((K + TS::BK - 1) / TS::BK + 1) / 2, resident, partials, counters, true, share);
     q.grid = q.sk.walk ? resident : q.ntiles;
     q.cut_inst = (q.sk.walk && (q.sk.dp_rounds == 0 || q.sk.split)) || K % (2 * TS::BK) != 0;
     return q;
 }
 
 template <int BITS, bool BT, typename TS>
-void launch_q(const GemmQArgs &args, hipStream_t st)
+void launch_q(const GemmQArgs &args, hipStream_t st, bool share = false)
 {
     constexpr size_t smem = q_smem_bytes<BT, TS>();
     static_assert(smem + 64 <= 160 * 1024, "LDS of one CU");
     GemmQArgs a = args;
     a.c_bytes = (uint32_t)((size_t)a.M * a.N * 2);
-    const QLaunchPlan q = plan_q<BT, TS>(a.M, a.N, a.K, a.sk.partials, a.sk.counters);
+    const QLaunchPlan q = plan_q<BT, TS>(a.M, a.N, a.K, a.sk.partials, a.sk.counters, share);
     a.tiles_m = q.tiles_m; a.tiles_n = q.tiles_n; a.band = q.band; a.sk = q.sk;
     const dim3 grid(q.grid), block(64 * TS::WGM * TS::WGN);
     if (q.cut_inst) {
@@ -1328,8 +1346,8 @@ void launch_q(const GemmQArgs &args, hipStream_t st)
 template <bool BT>
 void launch_q_bits(int bits, const GemmQArgs &a, hipStream_t st)
 {
-    const bool small = use_small_tile(a.M, a.N);
-#define EQAT_GO(B) do { if (small) launch_q<B, BT, TileSmall>(a, st); else launch_q<B, BT, TileBig>(a, st); } while (0)
+    const TileChoice tile = q_tile(a.M, a.N, a.K, a.sk.partials != nullptr && a.sk.counters != nullptr);
+#define EQAT_GO(B) do { if (tile == TileChoice::Small) launch_q<B, BT, TileSmall>(a, st); else launch_q<B, BT, TileBig>(a, st, tile == TileChoice::BigShared); } while (0)
     if (bits == 2) EQAT_GO(2); else if (bits == 3) EQAT_GO(3); else EQAT_GO(4);
 #undef EQAT_GO
 }
@@ -1380,7 +1398,7 @@ void launch_dw_t(const GemmDwArgs &args, const SkScratch &scratch, hipStream_t s
 template <typename WT, bool AP>
 bool launch_dw_bits(int bits, const GemmDwArgs &a, const SkScratch &sk, hipStream_t st)   // returns whether per-segment partials were written
 {
-    const bool small = use_small_tile(a.I, a.O);
+    const bool small = use_small_dw_tile(a.I, a.O);
 #define EQAT_GO(B) do { if (small) launch_dw_t<B, WT, AP, DwTileSmall>(a, sk, st); else launch_dw_t<B, WT, AP, DwTileBig>(a, sk, st); } while (0)
     if (bits == 2) EQAT_GO(2); else if (bits == 3) EQAT_GO(3); else EQAT_GO(4);
 #undef EQAT_GO
@@ -1400,11 +1418,12 @@ void sk_scratch_bytes(const Problem &p, bool bwd, size_t *partial_bytes, size_t 
     *counter_bytes = p.act_bf16 ? (size_t)kSkCounterWords * sizeof(uint32_t) : 0;     // whatever the token count
     if (!p.act_bf16 || p.T == 0) return;
     float *const some_p = reinterpret_cast<float *>(16); uint32_t *const some_c = reinterpret_cast<uint32_t *>(16);
-    auto one = [&](int64_t m, int64_t n, int64_t k, bool runs) {
-        const bool small = use_small_tile(m, n);
+    auto one = [&](int64_t m, int64_t n, int64_t k, bool dw) {
+        const TileChoice tile = dw ? (use_small_dw_tile(m, n) ? TileChoice::Small : TileChoice::Big) : q_tile(m, n, k, true);
+        const bool small = tile == TileChoice::Small;
         const int b = small ? TileSmall::BM : TileBig::BM, resident = kMaxCus * (small ? 2 : 1);
         const int ntiles = (int)(((m + b - 1) / b) * ((n + b - 1) / b));
-        const SkPlan sk = plan_tiles(ntiles, (int)(((k + 63) / 64 + 1) / 2), resident, some_p, some_c, runs);
+        const SkPlan sk = plan_tiles(ntiles, (int)(((k + 63) / 64 + 1) / 2), resident, some_p, some_c, !dw, tile == TileChoice::BigShared);
         if (!sk.walk) return;
         const int W = resident / 8, n_sk = (ntiles + 7) / 8 - sk.dp_rounds * W;
         if (n_sk <= 0) return;
@@ -1412,11 +1431,11 @@ void sk_scratch_bytes(const Problem &p, bool bwd, size_t *partial_bytes, size_t 
     };
     const SkScratch some{some_p, some_c};
     if (const int parts = ksplit_parts(p, false, some)) *partial_bytes = std::max(*partial_bytes, ksplit_bytes(p, false, parts));
-    else one(p.T, p.O, p.I, true);
+    else one(p.T, p.O, p.I, false);
     if (!bwd) return;
     if (const int parts = ksplit_parts(p, true, some)) *partial_bytes = std::max(*partial_bytes, ksplit_bytes(p, true, parts));
-    else one(p.T, p.I, p.O, true);
-    one(p.I, p.O, p.T, false);
+    else one(p.T, p.I, p.O, false);
+    one(p.I, p.O, p.T, true);
 }
 
 // Test aid: work item number j of workgroup `block` in the launch that the forward (gemm = 0), the dX (gemm = 1) or the dW
@@ -1429,7 +1448,7 @@ int plan_item_for_test(const Problem &p, int gemm, int block, int j, int32_t ite
     if (!p.act_bf16 || p.T < 1 || gemm < 0 || gemm > 2 || block < 0 || j < 0) return -1;
     if (gemm == 2) {
         float *const some_p = reinterpret_cast<float *>(16); uint32_t *const some_c = reinterpret_cast<uint32_t *>(16);
-        const bool small = use_small_tile(p.I, p.O);
+        const bool small = use_small_dw_tile(p.I, p.O);
         const DwLaunchPlan d = small ? plan_dw<bf16_t, true, DwTileSmall>((int)p.I, (int)p.O, (int)p.T, some_p, some_c)
                                      : plan_dw<bf16_t, true, DwTileBig>((int)p.I, (int)p.O, (int)p.T, some_p, some_c);
         if (block >= d.grid) return -1;
@@ -1447,9 +1466,10 @@ int plan_item_for_test(const Problem &p, int gemm, int block, int j, int32_t ite
     }
     const int M = (int)p.T, N = (int)(gemm == 0 ? p.O : p.I), K = (int)(gemm == 0 ? p.I : p.O);
     float *const some_p = reinterpret_cast<float *>(16); uint32_t *const some_c = reinterpret_cast<uint32_t *>(16);
-    const bool small = use_small_tile(M, N);
-    const QLaunchPlan q = gemm == 0 ? (small ? plan_q<false, TileSmall>(M, N, K, some_p, some_c) : plan_q<false, TileBig>(M, N, K, some_p, some_c))
-                                    : (small ? plan_q<true, TileSmall>(M, N, K, some_p, some_c) : plan_q<true, TileBig>(M, N, K, some_p, some_c));
+    const TileChoice tile = q_tile(M, N, K, true);
+    const bool small = tile == TileChoice::Small, share = tile == TileChoice::BigShared;
+    const QLaunchPlan q = gemm == 0 ? (small ? plan_q<false, TileSmall>(M, N, K, some_p, some_c, false) : plan_q<false, TileBig>(M, N, K, some_p, some_c, share))
+                                    : (small ? plan_q<true, TileSmall>(M, N, K, some_p, some_c, false) : plan_q<true, TileBig>(M, N, K, some_p, some_c, share));
     if (block >= q.grid) return -1;
     SkItem it{};
     bool ok;

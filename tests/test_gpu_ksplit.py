@@ -1,4 +1,4 @@
-"""fwd / dX with few output tiles (k_gemm_ksplit): two K groups in a workgroup and up to four workgroups per tile.  Contraction
+"""fwd / dX with few output tiles (k_gemm_ksplit; 256 x 256 tiles shared by workgroups): two K groups in a workgroup and up to four workgroups per tile.  Contraction
 lengths that end in either group's K tile, odd numbers of K-tile pairs, ragged tiles, one to four parts; against the oracle."""
 import numpy as np
 import pytest
@@ -18,7 +18,9 @@ CASES = [(70, 96, 40, 32),          # one pair
          (129, 512, 1480, 64),      # 3 parts, K ends inside the second group's tile
          (130, 256, 2056, 32),      # 4 parts, K ends inside the first group's tile, no second one
          (256, 1024, 3000, -1),     # 4 parts
-         (600, 2048, 4096, 128)]    # 3 parts, a last tile of 88 tokens
+         (600, 2048, 4096, 128),    # 3 parts, a last tile of 88 tokens
+         (2560, 2048, 5504, 64),    # 80 tiles of 256 x 256, three workgroups each (the tile kernel)
+         (2590, 2528, 10256, 32)]   # 110 of them, two each; K ends inside a K tile
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
