@@ -42,7 +42,7 @@ struct MidArgs {
     uint32_t spg_magic;            // ceil(2^32 / (g/32)), 0 for g = 32: group of a segment
     uint32_t code_row_bytes, z_row_words;
     uint32_t x_bytes, codes_bytes, s_bytes, z_bytes;
-    int tiles_m, tiles_n;
+    int tiles_m, tiles_n, band;    // band: token tiles that an XCD walks together, 0: all of them
 };
 
 constexpr int kMidBN = 128, kMidBK = 256, kMidKG = 4, kMidNT = 512;
@@ -62,6 +62,22 @@ template <int BITS, int SRC, int BM> struct MidLds {
 template <int NCH> __device__ __forceinline__ int code_chunk_swz(int row, int c)
 {
     return NCH == 2 ? c ^ ((row >> 2) & 1) : NCH == 4 ? c ^ ((row >> 1) & 3) : NCH == 8 ? c ^ (row & 7) : c;            // rows of 96 bytes spread by themselves
+}
+
+// Every XCD gets a contiguous range of tiles, token tiles of one weight tile next to each other: the codes are fetched into one
+// L2 only.  With many token tiles that has every XCD read all of X for a weight tile or two: they are walked in bands instead.
+__device__ __forceinline__ void tile_of(const MidArgs &a, int bm, int &m0, int &n0)
+{
+    const uint32_t nb = gridDim.x, xcd = blockIdx.x & 7, rem = nb & 7;
+    uint32_t pid = xcd * (nb >> 3) + (xcd < rem ? xcd : rem) + (blockIdx.x >> 3), first = 0, rows = (uint32_t)a.tiles_m;
+    if (a.band > 0) {
+        const uint32_t band = (uint32_t)a.band, width = band * (uint32_t)a.tiles_n, which = pid / width;
+        pid -= which * width;
+        first = which * band;
+        rows = rows - first < band ? rows - first : band;
+    }
+    m0 = (int)(first + pid % rows) * bm;
+    n0 = (int)(pid / rows) * kMidBN;
 }
 
 // A buffer that moves along K instead of the lanes' offsets into it: scalar work.  Past the last step nothing is in range.
@@ -88,11 +104,8 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 1, kg = wave >> 1, r = lane & 31, h = lane >> 5;
 
-    // Every XCD gets a contiguous range of tiles, token tiles of one weight tile next to each other: the codes are fetched
-    // into one L2 only.
-    const int nb = (int)gridDim.x, xcd = (int)(blockIdx.x & 7), rem = nb & 7;
-    const int pid = xcd * (nb >> 3) + (xcd < rem ? xcd : rem) + (int)(blockIdx.x >> 3);
-    const int m0 = (pid % a.tiles_m) * BM, n0 = (pid / a.tiles_m) * kMidBN;
+    int m0, n0;
+    tile_of(a, BM, m0, n0);
 
     const int n_segs = a.I >> 5, steps = (a.I + kMidBK - 1) / kMidBK;
     const uint32_t lds0 = lds_addr_of(smem_raw);
@@ -412,9 +425,8 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 1, kg = wave >> 1, r = lane & 31, h = lane >> 5;
 
-    const int nb = (int)gridDim.x, xcd = (int)(blockIdx.x & 7), rem = nb & 7;
-    const int pid = xcd * (nb >> 3) + (xcd < rem ? xcd : rem) + (int)(blockIdx.x >> 3);
-    const int m0 = (pid % a.tiles_m) * BM, n0 = (pid / a.tiles_m) * kMidBN;
+    int m0, n0;
+    tile_of(a, BM, m0, n0);
 
     const int steps = (a.I + BK - 1) / BK;
     const uint32_t lds0 = lds_addr_of(smem_raw);
@@ -736,6 +748,17 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
     }
 }
 
+// Token tiles of a band, where the column is longer than 20 of them: an XCD holds 32 tiles at a time, and a panel of 64 tokens
+// is 4 to 8 times as heavy as one of codes, so that 4 x 8 of them (3 x 10 with taller tiles) read the least.
+// 2048 tokens, 11008 -> 1024, 2 bit: 76 us in columns, 53 in bands; 1536 tokens 65 and 47; 2048 tokens, 5504 -> 2560: 80 and 70.  With
+// shorter columns the codes, which two XCDs then fetch, weigh more: 300 tokens, 4096 -> 8192 30 us in columns, 33 in bands.
+int band_of(int tiles_m, int bm)
+{
+    if (tiles_m <= 20) return 0;
+    const int most = bm == 64 ? 4 : 3, bands = (tiles_m + most - 1) / most;
+    return (tiles_m + bands - 1) / bands;                             // of equal height
+}
+
 template <int BITS, int SRC, int BM> void launch_t(MidArgs a, hipStream_t st)
 {
     constexpr int smem = BM >= 128 ? (int)TallLds<BITS, SRC, BM>::TOTAL : (int)MidLds<BITS, SRC, BM < 128 ? BM : 64>::TOTAL;
@@ -750,6 +773,7 @@ template <int BITS, int SRC, int BM> void launch_t(MidArgs a, hipStream_t st)
     }
     a.tiles_m = (a.T + BM - 1) / BM;
     a.tiles_n = (a.O + kMidBN - 1) / kMidBN;
+    a.band = band_of(a.tiles_m, BM);
     kern<<<dim3((unsigned)(a.tiles_m * a.tiles_n)), dim3(kMidNT), smem, st>>>(a);
 }
 

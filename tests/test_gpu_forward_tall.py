@@ -45,3 +45,22 @@ def test_forward_on_128_token_tiles(T, I, O, g, bits):
     sb = sd.clone()
     sb[1::2] = float("nan")
     assert torch.equal(eq.eqat_qlinear_fwd(Xd, Wp, sb, zp, bits, g)[:, 0::2], Y[:, 0::2])
+
+
+@pytest.mark.parametrize("bits,g", [(2, 32), (3, 96), (4, 64)])
+@pytest.mark.parametrize("T,O", [(1281, 1016), (1345, 136), (1850, 1016), (1990, 1000), (2700, 776)])
+def test_forward_in_bands_of_token_tiles(T, O, bits, g):
+    """More than 20 token tiles, in bands of unequal height: every tile is written once, at its own place."""
+    I = 2880
+    kind, tokens, _ = route(T, I, O, bits, g, PACKED)
+    assert kind == MID and -(-T // tokens) > 20
+    X, W, s, z, _ = make_case(("bands", T, O), T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
+    Xd, sd = dev(X), dev(s)
+    Wp, zp = eq.eqat_pack(dev(W), sd, dev(z), bits, g)
+    Y = eq.eqat_qlinear_fwd(Xd, Wp, sd, zp, bits, g)
+    some = sorted({t for e in range(0, T + 1, 64) for t in (e - 1, e) if 0 <= t < T} | {T - 1})
+    assert relerr(Y[some], oracle.qlinear_fwd(npf(X)[some], Wp.cpu().numpy(), s.numpy(), zp.cpu().numpy(), bits, g)) <= TOL[torch.bfloat16]
+    # few tokens at a time have no bands; sums in another order differ by fp32 roundings before the one to bf16 (2^-8 of an output)
+    for t in range(0, T, 640):
+        few = eq.eqat_qlinear_fwd(Xd[t:t + 640], Wp, sd, zp, bits, g).float()
+        assert (Y[t:t + 640].float() - few).abs().max() <= 2.0 ** -7 * few.abs().max()
