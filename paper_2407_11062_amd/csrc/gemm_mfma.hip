@@ -1213,10 +1213,20 @@ typedef DwTile<128, 128, 64, 2, 2, 2> DwTileSmall;
 typedef DwTile<256, 256, 64, 2, 2, 4> DwTileBig;
 static_assert(DwTileSmall::BM == TileSmall::BM && DwTileBig::BM == TileBig::BM, "group-fits-in-tile tests use Tile*::BM");
 
-// dW: the big tile unless it would leave a large part of the 256 CUs without a workgroup
-bool use_small_dw_tile(int64_t m, int64_t n)
+// dW: a round of big tiles (one per compute unit) takes 12 us and 1.35 a K tile of 64 tokens, a round of small ones (two per compute
+// unit, a quarter of the work each) 7 us and 0.88, and a small number of tiles beyond whole rounds costs most of a round unless
+// the contraction is long (they are split then).  So the small tiles are taken where they fill one round, and, up to 2048 tokens,
+// where the big ones leave at most a quarter of a second round while the small ones need two and a half at most; the big
+// ones where the small ones would go into a second round (130 to 159 big tiles): up to 9 K tiles that is a draw, and with
+// few more than 512 and a long contraction the split ones are level or ahead.  Measured, us, dW ds dz of Block-AP, g = 64, big / small:
+// 2560 x 6912 (270 big tiles): 515 tokens 59 / 46, 1000 72 / 60, 2048 105 / 98; 4096 x 5120 (320): 1000 75 / 64, 2048 119 / 106, 4096 171 / 174;
+// 5120 x 5120 (400): 1000 79 / 83; 3072 x 3072 (144): 300 26.4 / 25.8, 1000 37 / 39, 2048 51 / 66, 8192 143 / 163; 2560 x 3328 (130):
+// 1536 tokens 15 % faster big, 8192 6 % slower.
+bool use_small_dw_tile(int64_t m, int64_t n, int64_t tokens)
 {
-    return ((m + 255) / 256) * ((n + 255) / 256) < 160;
+    const int64_t big = ((m + 255) / 256) * ((n + 255) / 256), small = ((m + 127) / 128) * ((n + 127) / 128);
+    if (big >= 160) return big > 256 && big <= 320 && tokens <= 2048;
+    return small <= 512 || tokens <= 576 || (small < 544 && tokens > 2048);
 }
 
 // fwd / dX with more tiles than k_gemm_ksplit takes: big tiles where they fill most of the chip, or where the small ones do not
@@ -1398,7 +1408,7 @@ void launch_dw_t(const GemmDwArgs &args, const SkScratch &scratch, hipStream_t s
 template <typename WT, bool AP>
 bool launch_dw_bits(int bits, const GemmDwArgs &a, const SkScratch &sk, hipStream_t st)   // returns whether per-segment partials were written
 {
-    const bool small = use_small_dw_tile(a.I, a.O);
+    const bool small = use_small_dw_tile(a.I, a.O, a.T);
 #define EQAT_GO(B) do { if (small) launch_dw_t<B, WT, AP, DwTileSmall>(a, sk, st); else launch_dw_t<B, WT, AP, DwTileBig>(a, sk, st); } while (0)
     if (bits == 2) EQAT_GO(2); else if (bits == 3) EQAT_GO(3); else EQAT_GO(4);
 #undef EQAT_GO
@@ -1419,7 +1429,7 @@ void sk_scratch_bytes(const Problem &p, bool bwd, size_t *partial_bytes, size_t 
     if (!p.act_bf16 || p.T == 0) return;
     float *const some_p = reinterpret_cast<float *>(16); uint32_t *const some_c = reinterpret_cast<uint32_t *>(16);
     auto one = [&](int64_t m, int64_t n, int64_t k, bool dw) {
-        const TileChoice tile = dw ? (use_small_dw_tile(m, n) ? TileChoice::Small : TileChoice::Big) : q_tile(m, n, k, true);
+        const TileChoice tile = dw ? (use_small_dw_tile(m, n, k) ? TileChoice::Small : TileChoice::Big) : q_tile(m, n, k, true);
         const bool small = tile == TileChoice::Small;
         const int b = small ? TileSmall::BM : TileBig::BM, resident = kMaxCus * (small ? 2 : 1);
         const int ntiles = (int)(((m + b - 1) / b) * ((n + b - 1) / b));
@@ -1448,7 +1458,7 @@ int plan_item_for_test(const Problem &p, int gemm, int block, int j, int32_t ite
     if (!p.act_bf16 || p.T < 1 || gemm < 0 || gemm > 2 || block < 0 || j < 0) return -1;
     if (gemm == 2) {
         float *const some_p = reinterpret_cast<float *>(16); uint32_t *const some_c = reinterpret_cast<uint32_t *>(16);
-        const bool small = use_small_dw_tile(p.I, p.O);
+        const bool small = use_small_dw_tile(p.I, p.O, p.T);
         const DwLaunchPlan d = small ? plan_dw<bf16_t, true, DwTileSmall>((int)p.I, (int)p.O, (int)p.T, some_p, some_c)
                                      : plan_dw<bf16_t, true, DwTileBig>((int)p.I, (int)p.O, (int)p.T, some_p, some_c);
         if (block >= d.grid) return -1;
