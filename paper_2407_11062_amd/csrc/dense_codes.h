@@ -43,7 +43,7 @@ __device__ __forceinline__ uint32_t spread_3bit(uint32_t x)
 }
 
 // the 8 weights of MFMA t of a segment, in slot order
-template <int BITS, int T4>
+template <int BITS, int T4, bool KEEP_WORDS = true>
 __device__ __forceinline__ bf16x8 eight_of(const WhatTable<BITS> &tab, const CodeWords<BITS> &c)
 {
     uintx4 u;
@@ -57,8 +57,10 @@ __device__ __forceinline__ bf16x8 eight_of(const WhatTable<BITS> &tab, const Cod
         }
     } else if constexpr (BITS == 4) {
         uint32_t even = c.w[T4] & 0x0F0F0F0Fu, odd = (c.w[T4] >> 4) & 0x0F0F0F0Fu;
-        asm("" : "+v"(even));                      // see WhatTable::four: else two extracts more per four codes
-        asm("" : "+v"(odd));
+        if constexpr (KEEP_WORDS) {                // see WhatTable::four: else two extracts more per four codes
+            asm("" : "+v"(even));
+            asm("" : "+v"(odd));
+        }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             bf16x2 p;

@@ -178,10 +178,12 @@ template <int BITS, int FORM> __host__ __device__ constexpr int run_code_slot(in
     const int wd = c / 16, k = c % 16, p = k % 4, q = k / 4;        // 2 bit: codes 4 q + p of a word come out of shift 2 p
     return 8 * (2 * wd + p / 2) + 4 * (p % 2) + q;
 }
-template <int BITS, int FORM, int T4>
+template <int BITS, int FORM, int T4, int NG>
 __device__ __forceinline__ bf16x8 run_eight_of(const WhatTable<BITS> &tab, const CodeWords<BITS> &c)
 {
-    if constexpr (FORM != kPairs) return eight_of<BITS, T4>(tab, c);
+    // with a group per segment the kernel waits for its loads, and masked 4-bit words that stay words cost more than they save (one
+    // token, 4 bit, g = 32, 5440/14528 block: 97 us without them, 102 with; g = 64, 4544/13120: 86 and 84)
+    if constexpr (FORM != kPairs) return eight_of<BITS, T4, NG != 8>(tab, c);
     const uint32_t w = c.w[T4 / 2];
     uintx4 u;
     uint32_t d0, d1;
@@ -293,10 +295,10 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
             const bf16x8 b1 = *reinterpret_cast<const bf16x8 *>(xrow + 8);
             const bf16x8 b2 = *reinterpret_cast<const bf16x8 *>(xrow + 16);
             const bf16x8 b3 = *reinterpret_cast<const bf16x8 *>(xrow + 24);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, FORM, 0>(tab, cw), b0, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, FORM, 1>(tab, cw), b1, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, FORM, 2>(tab, cw), b2, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, FORM, 3>(tab, cw), b3, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, FORM, 0, NG>(tab, cw), b0, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, FORM, 1, NG>(tab, cw), b1, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, FORM, 2, NG>(tab, cw), b2, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(run_eight_of<BITS, FORM, 3, NG>(tab, cw), b3, acc, 0, 0, 0);
             if constexpr (FORM == kSegments) __builtin_amdgcn_sched_barrier(0);
         }
     }
