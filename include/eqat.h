@@ -351,6 +351,14 @@ eqat_status eqat_block_ap_update(const eqat_desc *d, const eqat_adamw *h, void *
 eqat_status eqat_plan_item(const eqat_desc *d, int gemm, int block, int j, int32_t *item, int32_t *exists);
 
 /*
+ * Test aid (host only, nothing is launched): the bytes [*first, *end) of a workspace of `ws_bytes` bytes, for a call of kind `op`
+ * (eqat_op), within which its forward (gemm = 0), dX (1) or dW (2) launch on a GPU of `cus` compute units (8 or more) writes the
+ * accumulator parts of tiles that several workgroups share; *end = *first where it writes none.  EQAT_ERR_WORKSPACE for a
+ * size that the call itself refuses.  bf16 activations, tokens >= 1.
+ */
+eqat_status eqat_plan_scratch(const eqat_desc *d, int op, int gemm, int cus, size_t ws_bytes, size_t *first, size_t *end);
+
+/*
  * Test aid (host only, nothing is launched): the kernel that a forward of this descriptor (bf16 activations, tokens >= 1)
  * takes, from the packed arrays as they are (source 1: eqat_qlinear_fwd, 2: eqat_qlinear_fwd_z) or from codes in the working
  * layout (0: every other forward).  route[3] = { 0 tiled GEMM; 1 GEMM for few tiles; 2 matrix-vector with streamed

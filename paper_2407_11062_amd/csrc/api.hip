@@ -143,8 +143,8 @@ eqat_status check_ws(const WsLayout &l, const void *ws, size_t ws_bytes)
 
 inline eqat::SkScratch sk_of(const WsLayout &l, char *w8)
 {
-    if (l.sk_ctr_bytes == 0) return eqat::SkScratch{nullptr, nullptr};
-    return eqat::SkScratch{l.sk_part_bytes != 0 ? reinterpret_cast<float *>(w8 + l.sk_part) : nullptr,
+    if (l.sk_ctr_bytes == 0) return eqat::SkScratch{nullptr, 0, nullptr};
+    return eqat::SkScratch{l.sk_part_bytes != 0 ? reinterpret_cast<float *>(w8 + l.sk_part) : nullptr, l.sk_part_bytes,
                            reinterpret_cast<uint32_t *>(w8 + l.sk_ctr)};
 }
 
@@ -529,7 +529,7 @@ static eqat_status prepared_operands(const Problem &p, const void *prepared, con
     char *p8 = (char *)const_cast<void *>(prepared), *w8 = (char *)ws;
     q->codes = p8 + pl.codes;
     q->sz = w8 + l.sz;
-    q->sk = eqat::SkScratch{l.sk_part_bytes != 0 ? (float *)(w8 + l.sk_part) : nullptr,
+    q->sk = eqat::SkScratch{l.sk_part_bytes != 0 ? (float *)(w8 + l.sk_part) : nullptr, l.sk_part_bytes,
                             pl.sk_ctr_bytes != 0 ? (uint32_t *)(p8 + pl.sk_ctr) : nullptr};
     q->part = (float *)(w8 + l.part);
     q->dwhat = (float *)(w8 + l.dwhat);
@@ -603,6 +603,25 @@ eqat_status eqat_plan_item(const eqat_desc *d, int gemm, int block, int j, int32
     const int rc = eqat::plan_item_for_test(p, gemm, block, j, item);
     if (rc < 0) return EQAT_ERR_SHAPE;
     *exists = rc;
+    return EQAT_OK;
+}
+
+// Test aid (host only): the part of a workspace that a launch writes accumulator parts to.
+eqat_status eqat_plan_scratch(const eqat_desc *d, int op, int gemm, int cus, size_t ws_bytes, size_t *first, size_t *end)
+{
+    Problem p;
+    if (eqat_status e = check_desc(d, true, &p)) return e;
+    if (first == nullptr || end == nullptr) return EQAT_ERR_NULL;
+    if (!p.act_bf16) return EQAT_ERR_DTYPE;                          // the fp32 path writes no parts
+    if (p.T < 1 || op < EQAT_OP_FQ_FWD || op > EQAT_OP_QP_BWD || gemm < 0 || gemm > (op_is_bwd(op) ? 2 : 0) || cus < 8) return EQAT_ERR_SHAPE;
+    const WsLayout l = ws_layout(p, op);
+    char *const some = reinterpret_cast<char *>(256);                // an address to plan with, nothing is done with it
+    if (eqat_status e = check_ws(l, some, ws_bytes)) return e;
+    eqat::SkScratch sk = sk_of(l, some);
+    if (op_is_prepared(op)) sk = eqat::SkScratch{reinterpret_cast<float *>(some), l.sk_part_bytes, reinterpret_cast<uint32_t *>(some)};
+    const bool parts = gemm != 0 || fwd_route(p, op == EQAT_OP_Q_FWD, false).kernel == eqat::FWD_TILES;
+    *first = l.sk_part;
+    *end = l.sk_part + (parts ? eqat::parts_written_for_test(p, gemm, cus, sk) : 0);
     return EQAT_OK;
 }
 

@@ -24,6 +24,7 @@ namespace {
 
 constexpr int kKsBM = 128, kKsBN = 128, kKsBK = 64, kKsNT = 512;      // per K group and K tile; threads of both groups
 constexpr int kKsMaxParts = 4;                                        // the last contributor has that many in flight
+constexpr size_t kKsPartBytes = (size_t)kKsBM * kKsBN * sizeof(float);
 
 
 struct KsArgs {
@@ -366,7 +367,8 @@ int ksplit_parts(const Problem &p, bool bt, const SkScratch &sk)
     if (!p.act_bf16 || p.T < 1 || !group_by_magic(p)) return 0;
     const Shape s = shape_of(p, bt);
     if (s.tiles > 256) return 0;
-    const int most = sk.partials == nullptr || sk.counters == nullptr ? 1 : std::min(std::min(kKsMaxParts, 256 / s.tiles), s.pairs / 4);
+    const int room = sk.partials == nullptr || sk.counters == nullptr ? 1 : (int)std::min<size_t>(sk.bytes / (s.tiles * kKsPartBytes), kKsMaxParts);
+    const int most = std::min(std::min(room, 256 / s.tiles), s.pairs / 4);
     int best = 1;
     double best_us = 4.5 + 0.95 * s.pairs;
     for (int c = 2; c <= most; ++c) {
@@ -378,7 +380,7 @@ int ksplit_parts(const Problem &p, bool bt, const SkScratch &sk)
 
 size_t ksplit_bytes(const Problem &p, bool bt, int parts)
 {
-    return parts > 1 ? (size_t)shape_of(p, bt).tiles * parts * (kKsBM * kKsBN * sizeof(float)) : 0;
+    return parts > 1 ? (size_t)shape_of(p, bt).tiles * parts * kKsPartBytes : 0;
 }
 
 void launch_ksplit(const Problem &p, bool bt, const void *A, const void *codes, const void *sz, void *C, const SkScratch &sk, int parts,

@@ -1229,18 +1229,44 @@ bool use_small_dw_tile(int64_t m, int64_t n, int64_t tokens)
     return small <= 512 || tokens <= 576 || (small < 544 && tokens > 2048);
 }
 
+// Workgroups that a device of `cus` compute units runs at the same time (LDS is what limits these kernels), rounded down to a
+// multiple of 8.
+constexpr int kMaxCus = 256;            // compute units of an MI355X; the workspace is sized for this many
+constexpr int kSkCounterWords = 2 * 2 * 2 * kMaxCus;  // 2 G arrival counters and 2 G flags, G <= 2 workgroups per compute unit
+constexpr int per_cu(size_t smem) { return smem * 2 <= 160 * 1024 ? 2 : 1; }
+int resident_workgroups(int cus, int per_cu) { return (cus * per_cu) & ~7; }
+int current_cus()
+{
+    static int cus_of[64] = {0};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev > 63) dev = 0;
+    if (cus_of[dev] == 0) {
+        int n = 0;
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = kMaxCus;
+        cus_of[dev] = n < kMaxCus ? n : kMaxCus;
+    }
+    return cus_of[dev];
+}
+// What a plan that cuts tiles of `tile` outputs may write: two parts per resident workgroup.  The workspace is sized for the plans
+// of kMaxCus compute units; with fewer of them another plan may cut where those do not, so every plan asks for the room it needs.
+size_t parts_bytes(int resident, int tile) { return (size_t)resident * 2 * (size_t)tile * sizeof(float); }
+bool parts_fit(const SkScratch &s, int resident, int tile)
+{
+    return s.partials != nullptr && s.counters != nullptr && s.bytes >= parts_bytes(resident, tile);
+}
+
 // fwd / dX with more tiles than k_gemm_ksplit takes: big tiles where they fill most of the chip, or where the small ones do not
 // fit two per compute unit (dX of 5120 x 5120, 1792 tokens: 140 big tiles 99 us, 560 small ones 133; 2048 -> 5504: 154 big tiles 46,
 // small 60), or, each shared by two or three workgroups, where the contraction is long enough to pay for the parts: small tiles
 // take 0.9 us per K tile, a share of a big one 1.55 (the chip's power limit), 0.085 us per part comes on top (dX, 11008 -> 4096:
 // 1280 tokens 157 -> 111 us, 2048 tokens 184 -> 164; 4096 -> 4096, 1280 tokens: 67 -> 64, 2048 tokens: 74, 80 if it were taken).
 enum class TileChoice { Small, Big, BigShared };
-TileChoice q_tile(int64_t m, int64_t n, int64_t k, bool scratch)
+TileChoice q_tile(int64_t m, int64_t n, int64_t k, int cus, const SkScratch &scratch)
 {
     const int64_t big = ((m + 255) / 256) * ((n + 255) / 256), small = ((m + 127) / 128) * ((n + 127) / 128);
     if (big >= 160 || small > 512) return TileChoice::Big;
-    const int64_t c = 32 / ((big + 7) / 8), k_tiles = (k + 63) / 64;           // contributors per tile, as plan_tiles deals them out
-    if (!scratch || c < 2 || c > 3 || k_tiles < 32) return TileChoice::Small;
+    const int64_t c = resident_workgroups(cus, 1) / 8 / ((big + 7) / 8), k_tiles = (k + 63) / 64;   // contributors per tile, as plan_tiles deals them out
+    if (!parts_fit(scratch, resident_workgroups(cus, 1), TileBig::BM * TileBig::BN) || c < 2 || c > 3 || k_tiles < 32) return TileChoice::Small;
     return 5.0 + 1.55 * (double)((k_tiles + c - 1) / c) + 0.085 * (double)(big * c) < 4.0 + 0.9 * (double)k_tiles ? TileChoice::BigShared : TileChoice::Small;
 }
 
@@ -1255,42 +1281,25 @@ template <typename K> void allow_dynamic_lds(K kern, size_t smem, uint64_t &done
     done |= (uint64_t)1 << dev;
 }
 
-// Workgroups of `smem` bytes of LDS that the device runs at the same time (LDS is what limits these kernels), rounded
-// down to a multiple of 8.
-constexpr int kMaxCus = 256;            // compute units of an MI355X; the workspace is sized for this many
-constexpr int kSkCounterWords = 2 * 2 * 2 * kMaxCus;  // 2 G arrival counters and 2 G flags, G <= 2 workgroups per compute unit
-int resident_workgroups(size_t smem)
-{
-    static int cus_of[64] = {0};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev > 63) dev = 0;
-    if (cus_of[dev] == 0) {
-        int n = 0;
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = kMaxCus;
-        cus_of[dev] = n < kMaxCus ? n : kMaxCus;
-    }
-    const int per_cu = smem * 2 <= 160 * 1024 ? 2 : 1;
-    return (cus_of[dev] * per_cu) & ~7;
-}
-
-// How `resident` workgroups share `ntiles` tiles of `pairs` K-tile pairs each (see SkPlan).  One workgroup per tile
+// How `resident` workgroups share `ntiles` tiles of `tile` outputs and `pairs` K-tile pairs each (see SkPlan).  One workgroup per tile
 // when they all fit; otherwise whole tiles, except that (K long enough)
 //   - between one and two rounds of tiles, with more than half a round beyond the first, every tile is cut along K into
 //     equal runs (with more rounds, cutting the last 1.x of them into runs measured slower than leaving the last round
 //     partly filled: 7B gate, 5.4 rounds: -3 %; 13B gate, 3.4 rounds: -4 %);
 //   - with at most half a round of tiles beyond the whole rounds, those few tiles are split among groups of workgroups.
-SkPlan plan_tiles(int ntiles, int pairs, int resident, float *partials, uint32_t *counters, bool runs = true, bool share = false)
+SkPlan plan_tiles(int ntiles, int tile, int pairs, int resident, const SkScratch &scratch, bool runs = true, bool share = false)
 {
     SkPlan sk{};
-    sk.pairs = pairs; sk.partials = partials; sk.counters = counters;
+    sk.pairs = pairs; sk.partials = scratch.partials; sk.counters = scratch.counters;
+    const bool room = parts_fit(scratch, resident, tile);
     if (ntiles <= resident) {                                // walk = 0: one workgroup per tile, unless they are to share
-        if (share && partials != nullptr && counters != nullptr && 2 * ((ntiles + 7) / 8) <= resident / 8) { sk.walk = 1; sk.split = 1; }
+        if (share && room && 2 * ((ntiles + 7) / 8) <= resident / 8) { sk.walk = 1; sk.split = 1; }
         return sk;
     }
     sk.walk = 1;
     const int W = resident / 8, per = ntiles / 8, full = per / W;
     const bool even = (per % W == 0) && (ntiles % 8 == 0);
-    const bool may_cut = !even && pairs >= 4 && partials != nullptr && counters != nullptr;
+    const bool may_cut = !even && pairs >= 4 && room;
     sk.dp_rounds = (may_cut && runs && full == 1) ? 0 : (per + (ntiles % 8 ? 1 : 0) + W - 1) / W;
     // Few tiles beyond the whole rounds (at most half a round on every XCD): whole tiles first, then the rest split.
     // The tile arithmetic promises (1 - 1/c) of a round; measured, 5.4 rounds (7B gate, up) gain 2.6 %, 3.4 rounds (13B
@@ -1309,7 +1318,7 @@ template <bool BT, typename TS> constexpr size_t q_smem_bytes()
     return 2 * (size_t)(TS::BM * TS::BK + (BT ? TS::BK * LDB : TS::BN * LDB)) * sizeof(bf16_t) + (size_t)TS::WGM * TS::WGN * kStoreStageBytes;
 }
 template <bool BT, typename TS>
-QLaunchPlan plan_q(int M, int N, int K, float *partials, uint32_t *counters, bool share)
+QLaunchPlan plan_q(int M, int N, int K, int cus, const SkScratch &scratch, bool share)
 {
     QLaunchPlan q{};
     q.tiles_m = (M + TS::BM - 1) / TS::BM;
@@ -1323,21 +1332,21 @@ QLaunchPlan plan_q(int M, int N, int K, float *partials, uint32_t *counters, boo
     // At most as many workgroups as the chip holds at once; with more tiles than that every workgroup walks several
     // (grid a multiple of 8, one share per XCD).
     q.ntiles = q.tiles_m * q.tiles_n;
-    const int resident = resident_workgroups(q_smem_bytes<BT, TS>());
-    q.sk = plan_tiles(q.ntiles, ((K + TS::BK - 1) / TS::BK + 1) / 2, resident, partials, counters, true, share);
+    const int resident = resident_workgroups(cus, per_cu(q_smem_bytes<BT, TS>()));
+    q.sk = plan_tiles(q.ntiles, TS::BM * TS::BN, ((K + TS::BK - 1) / TS::BK + 1) / 2, resident, scratch, true, share);
     q.grid = q.sk.walk ? resident : q.ntiles;
     q.cut_inst = (q.sk.walk && (q.sk.dp_rounds == 0 || q.sk.split)) || K % (2 * TS::BK) != 0;
     return q;
 }
 
 template <int BITS, bool BT, typename TS>
-void launch_q(const GemmQArgs &args, hipStream_t st, bool share = false)
+void launch_q(const GemmQArgs &args, const SkScratch &scratch, hipStream_t st, bool share = false)
 {
     constexpr size_t smem = q_smem_bytes<BT, TS>();
     static_assert(smem + 64 <= 160 * 1024, "LDS of one CU");
     GemmQArgs a = args;
     a.c_bytes = (uint32_t)((size_t)a.M * a.N * 2);
-    const QLaunchPlan q = plan_q<BT, TS>(a.M, a.N, a.K, a.sk.partials, a.sk.counters, share);
+    const QLaunchPlan q = plan_q<BT, TS>(a.M, a.N, a.K, current_cus(), scratch, share);
     a.tiles_m = q.tiles_m; a.tiles_n = q.tiles_n; a.band = q.band; a.sk = q.sk;
     const dim3 grid(q.grid), block(64 * TS::WGM * TS::WGN);
     if (q.cut_inst) {
@@ -1354,10 +1363,10 @@ void launch_q(const GemmQArgs &args, hipStream_t st, bool share = false)
 }
 
 template <bool BT>
-void launch_q_bits(int bits, const GemmQArgs &a, hipStream_t st)
+void launch_q_bits(int bits, const GemmQArgs &a, const SkScratch &scratch, hipStream_t st)
 {
-    const TileChoice tile = q_tile(a.M, a.N, a.K, a.sk.partials != nullptr && a.sk.counters != nullptr);
-#define EQAT_GO(B) do { if (tile == TileChoice::Small) launch_q<B, BT, TileSmall>(a, st); else launch_q<B, BT, TileBig>(a, st, tile == TileChoice::BigShared); } while (0)
+    const TileChoice tile = q_tile(a.M, a.N, a.K, current_cus(), scratch);
+#define EQAT_GO(B) do { if (tile == TileChoice::Small) launch_q<B, BT, TileSmall>(a, scratch, st); else launch_q<B, BT, TileBig>(a, scratch, st, tile == TileChoice::BigShared); } while (0)
     if (bits == 2) EQAT_GO(2); else if (bits == 3) EQAT_GO(3); else EQAT_GO(4);
 #undef EQAT_GO
 }
@@ -1366,14 +1375,14 @@ void launch_q_bits(int bits, const GemmQArgs &a, hipStream_t st)
 // grid is what the chip holds at once and sk says who computes what), or every tile has a workgroup of its own.
 struct DwLaunchPlan { int tiles_m, tiles_n, ntiles, grid; SkPlan sk; bool cut; };
 template <typename WT, bool AP, typename TS>
-DwLaunchPlan plan_dw(int I, int O, int T, float *partials, uint32_t *counters)
+DwLaunchPlan plan_dw(int I, int O, int T, int cus, const SkScratch &scratch)
 {
     DwLaunchPlan d{};
     d.tiles_m = (I + TS::BM - 1) / TS::BM;
     d.tiles_n = (O + TS::BN - 1) / TS::BN;
     d.ntiles = d.tiles_m * d.tiles_n;
-    const int resident = resident_workgroups(dw_smem_bytes<WT, AP, TS::BM, TS::BN, TS::BK, TS::NS, TS::WGM, TS::WGN>());
-    d.sk = plan_tiles(d.ntiles, ((T + TS::BK - 1) / TS::BK + 1) / 2, resident, partials, counters, false);
+    const int resident = resident_workgroups(cus, per_cu(dw_smem_bytes<WT, AP, TS::BM, TS::BN, TS::BK, TS::NS, TS::WGM, TS::WGN>()));
+    d.sk = plan_tiles(d.ntiles, TS::BM * TS::BN, ((T + TS::BK - 1) / TS::BK + 1) / 2, resident, scratch, false);
     d.cut = d.sk.walk && (d.sk.dp_rounds == 0 || d.sk.split);
     if (!d.cut) d.sk = SkPlan{};
     d.grid = d.cut ? resident : d.ntiles;
@@ -1385,8 +1394,9 @@ void launch_dw_t(const GemmDwArgs &args, const SkScratch &scratch, hipStream_t s
 {
     constexpr size_t smem = dw_smem_bytes<WT, AP, TS::BM, TS::BN, TS::BK, TS::NS, TS::WGM, TS::WGN>();
     static_assert(smem + 64 <= 160 * 1024, "LDS of one CU");
+    static_assert(per_cu(smem) == (TS::BM == TileSmall::BM ? 2 : 1), "plan_dw_of takes one pair of types for all");
     GemmDwArgs a = args;
-    const DwLaunchPlan d = plan_dw<WT, AP, TS>(a.I, a.O, a.T, scratch.partials, scratch.counters);
+    const DwLaunchPlan d = plan_dw<WT, AP, TS>(a.I, a.O, a.T, current_cus(), scratch);
     a.tiles_m = d.tiles_m;
     a.tiles_n = d.tiles_n;
     a.direct = (TS::BM % a.g == 0) ? 1 : 0;
@@ -1420,6 +1430,44 @@ bool launch_dw_bits(int bits, const GemmDwArgs &a, const SkScratch &sk, hipStrea
 // workspace reservation: either tile shape may be picked at launch
 bool dw_needs_partials(const Problem &p) { return (TileSmall::BM % p.g) != 0; }
 
+namespace {
+
+// as much as any plan asks for; nothing is read or written through it
+const SkScratch kAnyRoom{reinterpret_cast<float *>(16), ~(size_t)0, reinterpret_cast<uint32_t *>(16)};
+
+QLaunchPlan plan_q_of(const Problem &p, bool bt, int cus, const SkScratch &sk, TileChoice *choice)
+{
+    const int M = (int)p.T, N = (int)(bt ? p.I : p.O), K = (int)(bt ? p.O : p.I);
+    *choice = q_tile(M, N, K, cus, sk);
+    const bool small = *choice == TileChoice::Small, share = *choice == TileChoice::BigShared;
+    if (bt) return small ? plan_q<true, TileSmall>(M, N, K, cus, sk, false) : plan_q<true, TileBig>(M, N, K, cus, sk, share);
+    return small ? plan_q<false, TileSmall>(M, N, K, cus, sk, false) : plan_q<false, TileBig>(M, N, K, cus, sk, share);
+}
+// (weight type and phase make no difference to the plan: the LDS of both tiles allows the same workgroups per compute unit)
+DwLaunchPlan plan_dw_of(const Problem &p, int cus, const SkScratch &sk, bool *small)
+{
+    *small = use_small_dw_tile(p.I, p.O, p.T);
+    return *small ? plan_dw<bf16_t, true, DwTileSmall>((int)p.I, (int)p.O, (int)p.T, cus, sk)
+                  : plan_dw<bf16_t, true, DwTileBig>((int)p.I, (int)p.O, (int)p.T, cus, sk);
+}
+
+// Bytes from sk.partials on within which a launch of the forward (gemm = 0), the dX (1) or the dW (2) GEMM writes its parts.
+size_t parts_written(const Problem &p, int gemm, int cus, const SkScratch &sk)
+{
+    constexpr int kSmall = TileSmall::BM * TileSmall::BN, kBig = TileBig::BM * TileBig::BN;
+    if (gemm == 2) {
+        bool small;
+        const DwLaunchPlan d = plan_dw_of(p, cus, sk, &small);
+        return d.cut ? parts_bytes(d.grid, small ? kSmall : kBig) : 0;
+    }
+    if (const int parts = ksplit_parts(p, gemm == 1, sk)) return ksplit_bytes(p, gemm == 1, parts);
+    TileChoice choice;
+    const QLaunchPlan q = plan_q_of(p, gemm == 1, cus, sk, &choice);
+    return q.sk.walk && (q.sk.dp_rounds == 0 || q.sk.split) ? parts_bytes(q.grid, choice == TileChoice::Small ? kSmall : kBig) : 0;
+}
+
+}  // namespace
+
 // Scratch that cutting tiles along K needs, for whichever of the GEMMs of a problem may do so (bwd: fwd, dX and dW,
 // else the forward alone): the largest of their needs, with the full complement of compute units.
 void sk_scratch_bytes(const Problem &p, bool bwd, size_t *partial_bytes, size_t *counter_bytes)
@@ -1427,26 +1475,10 @@ void sk_scratch_bytes(const Problem &p, bool bwd, size_t *partial_bytes, size_t 
     *partial_bytes = 0;
     *counter_bytes = p.act_bf16 ? (size_t)kSkCounterWords * sizeof(uint32_t) : 0;     // whatever the token count
     if (!p.act_bf16 || p.T == 0) return;
-    float *const some_p = reinterpret_cast<float *>(16); uint32_t *const some_c = reinterpret_cast<uint32_t *>(16);
-    auto one = [&](int64_t m, int64_t n, int64_t k, bool dw) {
-        const TileChoice tile = dw ? (use_small_dw_tile(m, n, k) ? TileChoice::Small : TileChoice::Big) : q_tile(m, n, k, true);
-        const bool small = tile == TileChoice::Small;
-        const int b = small ? TileSmall::BM : TileBig::BM, resident = kMaxCus * (small ? 2 : 1);
-        const int ntiles = (int)(((m + b - 1) / b) * ((n + b - 1) / b));
-        const SkPlan sk = plan_tiles(ntiles, (int)(((k + 63) / 64 + 1) / 2), resident, some_p, some_c, !dw, tile == TileChoice::BigShared);
-        if (!sk.walk) return;
-        const int W = resident / 8, n_sk = (ntiles + 7) / 8 - sk.dp_rounds * W;
-        if (n_sk <= 0) return;
-        *partial_bytes = std::max(*partial_bytes, (size_t)resident * 2 * b * b * sizeof(float));
-    };
-    const SkScratch some{some_p, some_c};
-    if (const int parts = ksplit_parts(p, false, some)) *partial_bytes = std::max(*partial_bytes, ksplit_bytes(p, false, parts));
-    else one(p.T, p.O, p.I, false);
-    if (!bwd) return;
-    if (const int parts = ksplit_parts(p, true, some)) *partial_bytes = std::max(*partial_bytes, ksplit_bytes(p, true, parts));
-    else one(p.T, p.I, p.O, false);
-    one(p.I, p.O, p.T, true);
+    for (int gemm = 0; gemm < (bwd ? 3 : 1); ++gemm) *partial_bytes = std::max(*partial_bytes, parts_written(p, gemm, kMaxCus, kAnyRoom));
 }
+
+size_t parts_written_for_test(const Problem &p, int gemm, int cus, const SkScratch &sk) { return parts_written(p, gemm, cus, sk); }
 
 // Test aid: work item number j of workgroup `block` in the launch that the forward (gemm = 0), the dX (gemm = 1) or the dW
 // (gemm = 2; tile rows: in-features, tile columns: out-features, K: tokens) GEMM of this problem makes, as the kernel
@@ -1457,10 +1489,8 @@ int plan_item_for_test(const Problem &p, int gemm, int block, int j, int32_t ite
 {
     if (!p.act_bf16 || p.T < 1 || gemm < 0 || gemm > 2 || block < 0 || j < 0) return -1;
     if (gemm == 2) {
-        float *const some_p = reinterpret_cast<float *>(16); uint32_t *const some_c = reinterpret_cast<uint32_t *>(16);
-        const bool small = use_small_dw_tile(p.I, p.O, p.T);
-        const DwLaunchPlan d = small ? plan_dw<bf16_t, true, DwTileSmall>((int)p.I, (int)p.O, (int)p.T, some_p, some_c)
-                                     : plan_dw<bf16_t, true, DwTileBig>((int)p.I, (int)p.O, (int)p.T, some_p, some_c);
+        bool small;
+        const DwLaunchPlan d = plan_dw_of(p, current_cus(), kAnyRoom, &small);
         if (block >= d.grid) return -1;
         SkItem it{};
         bool ok;
@@ -1474,12 +1504,8 @@ int plan_item_for_test(const Problem &p, int gemm, int block, int j, int32_t ite
         for (int k = 0; k < 12; ++k) item[k] = v[k];
         return ok ? 1 : 0;
     }
-    const int M = (int)p.T, N = (int)(gemm == 0 ? p.O : p.I), K = (int)(gemm == 0 ? p.I : p.O);
-    float *const some_p = reinterpret_cast<float *>(16); uint32_t *const some_c = reinterpret_cast<uint32_t *>(16);
-    const TileChoice tile = q_tile(M, N, K, true);
-    const bool small = tile == TileChoice::Small, share = tile == TileChoice::BigShared;
-    const QLaunchPlan q = gemm == 0 ? (small ? plan_q<false, TileSmall>(M, N, K, some_p, some_c, false) : plan_q<false, TileBig>(M, N, K, some_p, some_c, share))
-                                    : (small ? plan_q<true, TileSmall>(M, N, K, some_p, some_c, false) : plan_q<true, TileBig>(M, N, K, some_p, some_c, share));
+    TileChoice choice;
+    const QLaunchPlan q = plan_q_of(p, gemm == 1, current_cus(), kAnyRoom, &choice);
     if (block >= q.grid) return -1;
     SkItem it{};
     bool ok;
@@ -1501,11 +1527,10 @@ void launch_mfma_fwd(const Problem &p, const void *X, const void *codes, const v
     if (p.T == 0) return;
     if (const int parts = ksplit_parts(p, false, sk)) { launch_ksplit(p, false, X, codes, sz, Y, sk, parts, st); return; }
     GemmQArgs a{};
-    a.sk.partials = sk.partials; a.sk.counters = sk.counters;
     a.A = (const bf16_t *)X; a.codes = (const uint32_t *)codes; a.sz = (const floatx2 *)sz; a.C = (bf16_t *)Y;
     a.M = (int)p.T; a.N = (int)p.O; a.K = (int)p.I; a.I = (int)p.I; a.G = (int)p.G; a.g = (int)p.g;
     a.a_bytes = (uint32_t)(p.T * p.I * 2); a.codes_bytes = (uint32_t)work_code_bytes(p); a.sz_bytes = (uint32_t)(p.O * p.G * 8);
-    launch_q_bits<false>(p.bits, a, st);
+    launch_q_bits<false>(p.bits, a, sk, st);
 }
 
 void launch_mfma_dx(const Problem &p, const void *dY, const void *codes, const void *sz, void *dX, const SkScratch &sk,
@@ -1514,11 +1539,10 @@ void launch_mfma_dx(const Problem &p, const void *dY, const void *codes, const v
     if (p.T == 0) return;
     if (const int parts = ksplit_parts(p, true, sk)) { launch_ksplit(p, true, dY, codes, sz, dX, sk, parts, st); return; }
     GemmQArgs a{};
-    a.sk.partials = sk.partials; a.sk.counters = sk.counters;
     a.A = (const bf16_t *)dY; a.codes = (const uint32_t *)codes; a.sz = (const floatx2 *)sz; a.C = (bf16_t *)dX;
     a.M = (int)p.T; a.N = (int)p.I; a.K = (int)p.O; a.I = (int)p.I; a.G = (int)p.G; a.g = (int)p.g;
     a.a_bytes = (uint32_t)(p.T * p.O * 2); a.codes_bytes = (uint32_t)work_code_bytes(p); a.sz_bytes = (uint32_t)(p.O * p.G * 8);
-    launch_q_bits<true>(p.bits, a, st);
+    launch_q_bits<true>(p.bits, a, sk, st);
 }
 
 void launch_mfma_dw(const Problem &p, bool block_ap, const void *X, const void *dY, const void *W, const void *codes,

@@ -49,9 +49,11 @@ void launch_reduce_partials(const float *part_ds, const float *part_dz, float *d
 // ---- gemm_mfma.hip (bf16 activations) -----------------------------------------------------------
 // Scratch of the GEMM launches that cut the tiles of a partly filled last round along K: one buffer of fp32 accumulator
 // tiles and one arrival counter per tile.  The counters must be zero when a launch starts; every launch leaves them zero.
-// Either pointer NULL: tiles are never cut.
-struct SkScratch { float *partials; uint32_t *counters; };
+// Either pointer NULL, or too few bytes for what a plan would write: tiles are not cut.
+struct SkScratch { float *partials; size_t bytes; uint32_t *counters; };
 int plan_item_for_test(const Problem &p, int gemm, int block, int j, int32_t item[12]);      // test aid, see gemm_mfma.hip
+// Test aid: bytes from sk.partials on within which the launch of a GEMM (0 fwd, 1 dX, 2 dW) on a device of `cus` compute units writes.
+size_t parts_written_for_test(const Problem &p, int gemm, int cus, const SkScratch &sk);
 void sk_scratch_bytes(const Problem &p, bool bwd, size_t *partial_bytes, size_t *counter_bytes);
 // Y[T,O] = X[T,I] * What[O,I]^T with What = (code - zbar) * s rebuilt per tile from packed codes.
 void launch_mfma_fwd(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, const SkScratch &sk,

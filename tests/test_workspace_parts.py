@@ -1,0 +1,46 @@
+"""Where launches put the accumulator parts of tiles that several workgroups share: inside the workspace that the call was given, on a GPU of
+any number of compute units (host only: `eqat_plan_scratch` asks the functions that plan the launches)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_2407_11062_amd as eq
+
+OPS = {eq.OP_FQ_FWD: 1, eq.OP_FQ_BWD: 3, eq.OP_Q_FWD: 1, eq.OP_Q_BWD: 3, eq.OP_QP_FWD: 1, eq.OP_QP_BWD: 3}      # GEMMs that a call launches
+
+
+def need(T, I, O, op, bits=2, g=32):
+    return eq.lib().eqat_workspace_bytes(ctypes.byref(eq.make_desc(T, I, O, bits, g, eq.BF16, eq.BF16)), op)
+
+
+def parts(T, I, O, op, gemm, cus, ws_bytes, bits=2, g=32):
+    """(first, past the last) byte of the workspace that the launch writes parts to; None: the call refuses that workspace"""
+    first, end = ctypes.c_size_t(), ctypes.c_size_t()
+    d = eq.make_desc(T, I, O, bits, g, eq.BF16, eq.BF16)
+    rc = eq.lib().eqat_plan_scratch(ctypes.byref(d), op, gemm, cus, ws_bytes, ctypes.byref(first), ctypes.byref(end))
+    assert rc in (0, 7), eq.lib().eqat_status_string(rc)
+    return None if rc else (first.value, end.value)
+
+
+def ragged_shapes(n, seed):
+    rng = np.random.default_rng(seed)
+    for _ in range(n):
+        T = int(np.exp(rng.uniform(0, np.log(9000))))
+        I = 32 * int(np.exp(rng.uniform(np.log(4), np.log(700))))
+        yield T, I, 8 * int(np.exp(rng.uniform(np.log(16), np.log(3000))))
+
+
+@pytest.mark.parametrize("cus", [256, 208, 128, 64, 32, 8])
+def test_parts_stay_inside_the_workspace_on_any_number_of_compute_units(cus):
+    written = set()
+    # 4096 tokens, 512 -> 20480: 256 compute units share the tiles of dX alone, 128 would cut those of dW, whose parts are larger
+    for T, I, O in [(4096, 512, 20480), (1280, 4096, 4096), (2560, 2048, 5504), (8192, 4096, 11008), *ragged_shapes(4000, 5)]:
+        for op in (eq.OP_FQ_BWD, eq.OP_Q_FWD, eq.OP_QP_BWD):
+            ws_bytes = need(T, I, O, op)
+            for gemm in range(OPS[op]):
+                first, end = parts(T, I, O, op, gemm, cus, ws_bytes)
+                assert end <= ws_bytes, (T, I, O, op, gemm, first, end, ws_bytes)
+                if end > first:
+                    written.add(gemm)
+    assert written == {0, 1, 2} or cus < 256
