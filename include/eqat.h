@@ -26,7 +26,12 @@
  *   Stream     `stream` is a hipStream_t (NULL = default stream).  All work is
  *              enqueued there; no call synchronises.  Outputs are overwritten.
  *   Workspace  Caller-provided scratch of at least eqat_workspace_bytes(desc, op)
- *              bytes, 256-byte aligned; contents undefined afterwards.
+ *              bytes, 256-byte aligned; contents undefined afterwards.  The part of
+ *              it that only lets workgroups share an output tile (few tokens: parts
+ *              of the sums) may be missing: the codes and pairs do not depend on the
+ *              token count, so that of 8192 tokens of a 4096 x 4096 layer serves one
+ *              token as well.  Tiles are not shared then, and the sums are added up
+ *              in another order.  Less than the call needs gives EQAT_ERR_WORKSPACE.
  *   Errors     Arguments are checked on the host before anything is launched and
  *              the first violation is returned; nothing is thrown or aborted.
  *   Numerics   round() is round-half-to-even of the correctly rounded binary32
@@ -39,7 +44,8 @@
  *              Preconditions (not checked): s a normal,
  *              finite, positive binary32 number (>= 2^-126; the min/max rule
  *              never gives less than 1e-10), |z| <= 2^20, all inputs finite.
- *   Determinism  Same inputs give bitwise the same outputs.
+ *   Determinism  Same inputs (and the same workspace size, if it is below
+ *              eqat_workspace_bytes) give bitwise the same outputs.
  */
 #ifndef EQAT_H_
 #define EQAT_H_

@@ -5,6 +5,7 @@
 #include "kernels.h"
 #include "prof.h"
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <vector>
@@ -81,7 +82,7 @@ eqat_status check_desc(const eqat_desc *d, bool with_tokens, Problem *p)
     return EQAT_OK;
 }
 
-struct WsLayout { size_t codes, clamp, sz, part, dwhat, sk_ctr, sk_ctr_bytes, sk_part, sk_part_bytes, total; };
+struct WsLayout { size_t codes, clamp, sz, part, dwhat, sk_ctr, sk_ctr_bytes, sk_part, sk_part_bytes, total, needed; };
 
 inline bool op_is_bwd(int op) { return op == EQAT_OP_FQ_BWD || op == EQAT_OP_Q_BWD || op == EQAT_OP_QP_BWD; }
 inline bool op_is_prepared(int op) { return op == EQAT_OP_QP_FWD || op == EQAT_OP_QP_BWD; }
@@ -99,7 +100,7 @@ PreparedLayout prepared_layout(const Problem &p)
     l.codes = take(p.act_bf16 ? eqat::work_code_bytes(p) : (size_t)p.O * p.I * p.bits / 8);
     l.zb = take((size_t)p.O * p.G * 4);
     size_t unused = 0;
-    eqat::sk_scratch_bytes(p, true, &unused, &l.sk_ctr_bytes);
+    eqat::sk_scratch_bytes(p, true, &unused, &unused, &l.sk_ctr_bytes);
     l.sk_ctr = take(l.sk_ctr_bytes);
     l.total = off;
     return l;
@@ -121,33 +122,39 @@ WsLayout ws_layout(const Problem &p, int op)
         // GEMM launches that cut tiles along K: arrival counters (cleared by the first kernel of every call; their
         // size and place do not depend on the token count; a prepared layer carries its own) and, last, the
         // accumulator parts (large, sparsely touched, never initialised; present only for shapes whose tiles are cut).
-        eqat::sk_scratch_bytes(p, bwd, &l.sk_part_bytes, &l.sk_ctr_bytes);
+        // Parts of launches that would share tiles only to fill the chip may be missing: a workspace that was sized for
+        // another token count is taken, and those launches give every tile one workgroup.
+        size_t needed = 0;
+        eqat::sk_scratch_bytes(p, bwd, &l.sk_part_bytes, &needed, &l.sk_ctr_bytes);
         if (prepared) l.sk_ctr_bytes = 0;
         l.sk_ctr = take(l.sk_ctr_bytes);
         l.sk_part = take(l.sk_part_bytes);
+        l.needed = l.sk_part + align256(needed);
     } else {
         if (!fq) l.sz = take(sz_b);
         if (bwd) l.dwhat = take(dwhat_b);
     }
     l.total = off;
+    if (!p.act_bf16) l.needed = l.total;
     return l;
 }
 
 eqat_status check_ws(const WsLayout &l, const void *ws, size_t ws_bytes)
 {
-    if (l.total == 0) return EQAT_OK;
-    if (ws == nullptr || ws_bytes < l.total) return EQAT_ERR_WORKSPACE;
+    if (l.needed == 0) return EQAT_OK;
+    if (ws == nullptr || ws_bytes < l.needed) return EQAT_ERR_WORKSPACE;
     if (!aligned(ws, 256)) return EQAT_ERR_ALIGN;
     return EQAT_OK;
 }
 
-inline eqat::SkScratch sk_of(const WsLayout &l, char *w8)
+// `prepared_counters`: those of a prepared layer, whose workspace has none
+inline eqat::SkScratch sk_of(const WsLayout &l, char *w8, size_t ws_bytes, uint32_t *prepared_counters = nullptr)
 {
-    if (l.sk_ctr_bytes == 0) return eqat::SkScratch{nullptr, 0, nullptr};
-    return eqat::SkScratch{l.sk_part_bytes != 0 ? reinterpret_cast<float *>(w8 + l.sk_part) : nullptr, l.sk_part_bytes,
-                           reinterpret_cast<uint32_t *>(w8 + l.sk_ctr)};
+    uint32_t *const counters = prepared_counters != nullptr ? prepared_counters : l.sk_ctr_bytes != 0 ? reinterpret_cast<uint32_t *>(w8 + l.sk_ctr) : nullptr;
+    // no more than the size that eqat_workspace_bytes gives: a larger workspace changes no plan
+    const size_t bytes = ws_bytes > l.sk_part ? std::min(ws_bytes - l.sk_part, l.sk_part_bytes) : 0;
+    return eqat::SkScratch{bytes != 0 ? reinterpret_cast<float *>(w8 + l.sk_part) : nullptr, bytes, counters};
 }
-
 
 inline eqat_status launch_status() { return hipGetLastError() == hipSuccess ? EQAT_OK : EQAT_ERR_DEVICE; }
 
@@ -304,7 +311,7 @@ static eqat_status fq_fwd_any(const eqat_desc *d, const void *X, const void *W, 
     hipStream_t st = (hipStream_t)stream;
     char *w8 = (char *)ws;
     if (p.act_bf16) {
-        const eqat::SkScratch sk = sk_of(l, w8);
+        const eqat::SkScratch sk = sk_of(l, w8, ws_bytes);
         if (!kept) { ProfScope ps(eqat::PK_QUANTIZE, st); eqat::launch_quantize(p, W, s, z, w8 + l.codes, keep ? w8 + l.clamp : nullptr, w8 + l.sz, nullptr, false, sk.counters, (uint32_t)(l.sk_ctr_bytes / 4), st); }
         if (p.T > 0) fwd_on_work(p, X, w8 + l.codes, w8 + l.sz, Y, sk, st);
     } else {
@@ -371,7 +378,7 @@ static eqat_status fq_bwd_any(const eqat_desc *d, const void *X, const void *W, 
     hipStream_t st = (hipStream_t)stream;
     char *w8 = (char *)ws;
     if (p.act_bf16) {
-        const eqat::SkScratch sk = sk_of(l, w8);
+        const eqat::SkScratch sk = sk_of(l, w8, ws_bytes);
         if (!kept) { ProfScope ps(eqat::PK_QUANTIZE, st); eqat::launch_quantize(p, W, s, z, w8 + l.codes, w8 + l.clamp, w8 + l.sz, nullptr, false, sk.counters, (uint32_t)(l.sk_ctr_bytes / 4), st); }
         if (dX != nullptr) { ProfScope ps(eqat::PK_GEMM_DX, st); eqat::launch_mfma_dx(p, dY, w8 + l.codes, w8 + l.sz, dX, sk, st); }
         if (want_w)
@@ -455,7 +462,7 @@ static eqat_status qlinear_fwd_any(const eqat_desc *d, const void *X, const uint
         eqat::launch_gemv(p, X, Wpacked, s, zpacked, zfloat, Y, st);
         return launch_status();
     }
-    const eqat::SkScratch sk = sk_of(l, w8);
+    const eqat::SkScratch sk = sk_of(l, w8, ws_bytes);
     qlinear_prepare_into(p, Wpacked, s, zpacked, zfloat, w8 + l.codes, w8 + l.sz, sk.counters, l.sk_ctr_bytes, st);
     const QOperands q{p.act_bf16 ? (const void *)(w8 + l.codes) : (const void *)Wpacked, w8 + l.sz, sk, nullptr, nullptr};
     return qlinear_fwd_run(p, X, s, q, Y, st);
@@ -478,7 +485,7 @@ static eqat_status qlinear_bwd_any(const eqat_desc *d, const void *X, const uint
     if (dX == nullptr && !want_g) return EQAT_OK;
     hipStream_t st = (hipStream_t)stream;
     char *w8 = (char *)ws;
-    const eqat::SkScratch sk = sk_of(l, w8);
+    const eqat::SkScratch sk = sk_of(l, w8, ws_bytes);
     if (!kept) qlinear_prepare_into(p, Wpacked, s, zpacked, zfloat, w8 + l.codes, w8 + l.sz, sk.counters, l.sk_ctr_bytes, st);
     const QOperands q{p.act_bf16 ? (const void *)(w8 + l.codes) : (const void *)Wpacked, w8 + l.sz, sk,
                       (float *)(w8 + l.part), (float *)(w8 + l.dwhat)};
@@ -529,8 +536,7 @@ static eqat_status prepared_operands(const Problem &p, const void *prepared, con
     char *p8 = (char *)const_cast<void *>(prepared), *w8 = (char *)ws;
     q->codes = p8 + pl.codes;
     q->sz = w8 + l.sz;
-    q->sk = eqat::SkScratch{l.sk_part_bytes != 0 ? (float *)(w8 + l.sk_part) : nullptr, l.sk_part_bytes,
-                            pl.sk_ctr_bytes != 0 ? (uint32_t *)(p8 + pl.sk_ctr) : nullptr};
+    q->sk = sk_of(l, w8, ws_bytes, pl.sk_ctr_bytes != 0 ? (uint32_t *)(p8 + pl.sk_ctr) : nullptr);
     q->part = (float *)(w8 + l.part);
     q->dwhat = (float *)(w8 + l.dwhat);
     if (make_pairs)
@@ -617,8 +623,7 @@ eqat_status eqat_plan_scratch(const eqat_desc *d, int op, int gemm, int cus, siz
     const WsLayout l = ws_layout(p, op);
     char *const some = reinterpret_cast<char *>(256);                // an address to plan with, nothing is done with it
     if (eqat_status e = check_ws(l, some, ws_bytes)) return e;
-    eqat::SkScratch sk = sk_of(l, some);
-    if (op_is_prepared(op)) sk = eqat::SkScratch{reinterpret_cast<float *>(some), l.sk_part_bytes, reinterpret_cast<uint32_t *>(some)};
+    const eqat::SkScratch sk = sk_of(l, some, ws_bytes, op_is_prepared(op) ? reinterpret_cast<uint32_t *>(some) : nullptr);
     const bool parts = gemm != 0 || fwd_route(p, op == EQAT_OP_Q_FWD, false).kernel == eqat::FWD_TILES;
     *first = l.sk_part;
     *end = l.sk_part + (parts ? eqat::parts_written_for_test(p, gemm, cus, sk) : 0);
@@ -764,7 +769,7 @@ eqat_status eqat_fq_quantize_batched(int n, const eqat_desc *descs, const void *
         const WsLayout l = ws_layout(p, EQAT_OP_FQ_BWD);
         if (eqat_status e = check_ws(l, ws[i], ws_bytes[i])) return e;
         char *w8 = (char *)ws[i];
-        const eqat::SkScratch sk = sk_of(l, w8);
+        const eqat::SkScratch sk = sk_of(l, w8, ws_bytes[i]);
         jobs[i] = eqat::QuantizeJob{p, W[i], s[i], z[i], w8 + l.codes, w8 + l.clamp, w8 + l.sz, nullptr, sk.counters,
                                     (uint32_t)(l.sk_ctr_bytes / 4)};
     }

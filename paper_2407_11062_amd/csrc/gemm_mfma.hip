@@ -1466,16 +1466,30 @@ size_t parts_written(const Problem &p, int gemm, int cus, const SkScratch &sk)
     return q.sk.walk && (q.sk.dp_rounds == 0 || q.sk.split) ? parts_bytes(q.grid, choice == TileChoice::Small ? kSmall : kBig) : 0;
 }
 
+// Whether a launch with fewer tiles than workgroups shares them (k_gemm_ksplit, big tiles) where there is room for the parts.
+bool shares_to_fill(const Problem &p, int gemm)
+{
+    if (gemm == 2) return false;
+    if (ksplit_parts(p, gemm == 1, kAnyRoom)) return true;
+    TileChoice choice;
+    (void)plan_q_of(p, gemm == 1, kMaxCus, kAnyRoom, &choice);
+    return choice == TileChoice::BigShared;
+}
+
 }  // namespace
 
 // Scratch that cutting tiles along K needs, for whichever of the GEMMs of a problem may do so (bwd: fwd, dX and dW,
 // else the forward alone): the largest of their needs, with the full complement of compute units.
-void sk_scratch_bytes(const Problem &p, bool bwd, size_t *partial_bytes, size_t *counter_bytes)
+void sk_scratch_bytes(const Problem &p, bool bwd, size_t *partial_bytes, size_t *needed_bytes, size_t *counter_bytes)
 {
-    *partial_bytes = 0;
+    *partial_bytes = *needed_bytes = 0;
     *counter_bytes = p.act_bf16 ? (size_t)kSkCounterWords * sizeof(uint32_t) : 0;     // whatever the token count
     if (!p.act_bf16 || p.T == 0) return;
-    for (int gemm = 0; gemm < (bwd ? 3 : 1); ++gemm) *partial_bytes = std::max(*partial_bytes, parts_written(p, gemm, kMaxCus, kAnyRoom));
+    for (int gemm = 0; gemm < (bwd ? 3 : 1); ++gemm) {
+        const size_t bytes = parts_written(p, gemm, kMaxCus, kAnyRoom);
+        *partial_bytes = std::max(*partial_bytes, bytes);
+        if (!shares_to_fill(p, gemm)) *needed_bytes = std::max(*needed_bytes, bytes);
+    }
 }
 
 size_t parts_written_for_test(const Problem &p, int gemm, int cus, const SkScratch &sk) { return parts_written(p, gemm, cus, sk); }

@@ -8,6 +8,7 @@ import oracle
 import paper_2407_11062_amd as eq
 from paper_2407_11062_amd import synth
 from test_gpu_parity import TOL, dev, make_case, npf, relerr
+from test_workspace_parts import parts
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +50,24 @@ def test_dx_and_forward_with_few_tiles(T, I, O, g, bits):
     dYb[T // 2] = float("nan")
     rest = [t for t in range(T) if t != T // 2]
     assert torch.equal(eq.eqat_fq_linear_bwd(Xd, Wd, sd, zd, dYb, bits, g, want=("dX",), ws=ws, kept=True)["dX"][rest], dX[rest])
+
+
+@pytest.mark.parametrize("T,I,O,g", [(130, 256, 2056, 32), (600, 2048, 4096, 128), (2560, 2048, 5504, 64)])
+def test_without_room_for_parts_the_tiles_are_not_shared(T, I, O, g):
+    """A workspace that was sized for another token count: the same results but for the order of the sums."""
+    bits = 2
+    X, W, s, z, dY = make_case(("noroom", T, I, O), T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
+    Xd, Wd, sd, zd, dYd = dev(X), dev(W), dev(s), dev(z), dev(dY)
+    some = sorted({0, 31, 32, 63, 64, 127, T // 2, T - 1})
+    ref = oracle.fq_linear_bwd(None, npf(W), s.numpy(), z.numpy(), npf(dY)[some], bits, g, want=("dX",))["dX"]
+    Yref = oracle.fq_linear_fwd(npf(X)[some], npf(W), s.numpy(), z.numpy(), bits, g)
+    first, end = parts(T, I, O, eq.OP_FQ_BWD, 1, 256, 1 << 30, bits, g)
+    assert end > first
+    for room in (0, (end - first) // 2):
+        guard = torch.full((first + room + 4096,), 0xA5, dtype=torch.uint8, device=Xd.device)
+        ws = guard[:first + room]
+        Y = eq.eqat_fq_linear_fwd(Xd, Wd, sd, zd, bits, g, ws=ws, keep=True)
+        dX = eq.eqat_fq_linear_bwd(Xd, Wd, sd, zd, dYd, bits, g, want=("dX",), ws=ws, kept=True)["dX"]
+        assert relerr(dX[some], ref) <= TOL[torch.bfloat16] and relerr(Y[some], Yref) <= TOL[torch.bfloat16]
+        assert bool((guard[first + room:] == 0xA5).all())
+        assert torch.equal(dX, eq.eqat_fq_linear_bwd(Xd, Wd, sd, zd, dYd, bits, g, want=("dX",), ws=ws, kept=True)["dX"])

@@ -44,3 +44,32 @@ def test_parts_stay_inside_the_workspace_on_any_number_of_compute_units(cus):
                 if end > first:
                     written.add(gemm)
     assert written == {0, 1, 2} or cus < 256
+
+
+@pytest.mark.parametrize("I,O", [(4096, 4096), (11008, 4096), (8192, 1024)])
+def test_a_workspace_sized_for_many_tokens_serves_few(I, O):
+    for op, gemms in OPS.items():
+        ws_bytes = need(8192, I, O, op)
+        for T in (1, 2, 17, 64, 128, 256, 333, 515, 1000, 1280, 2048):
+            for gemm in range(gemms):
+                first, end = parts(T, I, O, op, gemm, 256, ws_bytes)          # not refused
+                assert end <= ws_bytes
+
+
+def test_what_the_codes_and_pairs_take_is_still_asked_for():
+    for op in OPS:
+        first, _ = parts(256, 4096, 4096, op, 0, 256, 1 << 30)
+        assert parts(256, 4096, 4096, op, 0, 256, first) == (first, first)     # no room for parts: none are written
+        assert parts(256, 4096, 4096, op, 0, 256, first - 1) is None
+    # tiles that are cut because they do not fill whole rounds need their parts, as ever: 13B q projection, 320 tiles
+    for op in (eq.OP_Q_FWD, eq.OP_QP_BWD):
+        n = need(4096, 5120, 5120, op)
+        assert parts(4096, 5120, 5120, op, 0, 256, n)[1] <= n and parts(4096, 5120, 5120, op, 0, 256, n - 256) is None
+
+
+def test_more_workspace_than_asked_for_changes_no_plan():
+    for T, I, O in ragged_shapes(500, 6):
+        for cus in (256, 128):
+            n = need(T, I, O, eq.OP_FQ_BWD)
+            for gemm in range(3):
+                assert parts(T, I, O, eq.OP_FQ_BWD, gemm, cus, n) == parts(T, I, O, eq.OP_FQ_BWD, gemm, cus, n + (1 << 28))
