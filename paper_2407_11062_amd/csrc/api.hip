@@ -82,6 +82,15 @@ eqat_status check_desc(const eqat_desc *d, bool with_tokens, Problem *p)
     return EQAT_OK;
 }
 
+// Which kernel computes a forward, from the caller's packed arrays as they are (eqat_qlinear_fwd, _z) or from codes in the
+// working layout (all others).
+eqat::FwdRoute fwd_route(const Problem &p, bool from_packed, bool floatz)
+{
+    if (from_packed ? eqat::gemv_applies(p) : eqat::gemv_work_applies(p)) return eqat::gemv_route(p, floatz);
+    if (eqat::mid_applies(p)) return eqat::mid_route(p, from_packed);
+    return eqat::FwdRoute{eqat::FWD_TILES, 0, 0};
+}
+
 struct WsLayout { size_t codes, clamp, sz, part, dwhat, sk_ctr, sk_ctr_bytes, sk_part, sk_part_bytes, total, needed; };
 
 inline bool op_is_bwd(int op) { return op == EQAT_OP_FQ_BWD || op == EQAT_OP_Q_BWD || op == EQAT_OP_QP_BWD; }
@@ -100,7 +109,7 @@ PreparedLayout prepared_layout(const Problem &p)
     l.codes = take(p.act_bf16 ? eqat::work_code_bytes(p) : (size_t)p.O * p.I * p.bits / 8);
     l.zb = take((size_t)p.O * p.G * 4);
     size_t unused = 0;
-    eqat::sk_scratch_bytes(p, true, &unused, &unused, &l.sk_ctr_bytes);
+    eqat::sk_scratch_bytes(p, false, false, &unused, &unused, &l.sk_ctr_bytes);
     l.sk_ctr = take(l.sk_ctr_bytes);
     l.total = off;
     return l;
@@ -125,7 +134,8 @@ WsLayout ws_layout(const Problem &p, int op)
         // Parts of launches that would share tiles only to fill the chip may be missing: a workspace that was sized for
         // another token count is taken, and those launches give every tile one workgroup.
         size_t needed = 0;
-        eqat::sk_scratch_bytes(p, bwd, &l.sk_part_bytes, &needed, &l.sk_ctr_bytes);
+        const bool tiles = p.T > 0 && fwd_route(p, op == EQAT_OP_Q_FWD, false).kernel == eqat::FWD_TILES;
+        eqat::sk_scratch_bytes(p, tiles, bwd, &l.sk_part_bytes, &needed, &l.sk_ctr_bytes);
         if (prepared) l.sk_ctr_bytes = 0;
         l.sk_ctr = take(l.sk_ctr_bytes);
         l.sk_part = take(l.sk_part_bytes);
@@ -276,15 +286,6 @@ eqat_status eqat_unpack(const eqat_desc *d, const uint8_t *Wpacked, const uint8_
 }
 
 }  // extern "C"
-
-// Which kernel computes a forward, from the caller's packed arrays as they are (eqat_qlinear_fwd, _z) or from codes in the
-// working layout (all others).
-static eqat::FwdRoute fwd_route(const Problem &p, bool from_packed, bool floatz)
-{
-    if (from_packed ? eqat::gemv_applies(p) : eqat::gemv_work_applies(p)) return eqat::gemv_route(p, floatz);
-    if (eqat::mid_applies(p)) return eqat::mid_route(p, from_packed);
-    return eqat::FwdRoute{eqat::FWD_TILES, 0, 0};
-}
 
 // Forward on codes in the working layout.
 static void fwd_on_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, const eqat::SkScratch &sk, hipStream_t st)

@@ -1478,14 +1478,14 @@ bool shares_to_fill(const Problem &p, int gemm)
 
 }  // namespace
 
-// Scratch that cutting tiles along K needs, for whichever of the GEMMs of a problem may do so (bwd: fwd, dX and dW,
-// else the forward alone): the largest of their needs, with the full complement of compute units.
-void sk_scratch_bytes(const Problem &p, bool bwd, size_t *partial_bytes, size_t *needed_bytes, size_t *counter_bytes)
+// Scratch that cutting or sharing tiles needs, for whichever of the GEMMs of a problem may do so (fwd: the forward, bwd: dX and
+// dW): the largest of their needs, with the full complement of compute units.
+void sk_scratch_bytes(const Problem &p, bool fwd, bool bwd, size_t *partial_bytes, size_t *needed_bytes, size_t *counter_bytes)
 {
     *partial_bytes = *needed_bytes = 0;
     *counter_bytes = p.act_bf16 ? (size_t)kSkCounterWords * sizeof(uint32_t) : 0;     // whatever the token count
     if (!p.act_bf16 || p.T == 0) return;
-    for (int gemm = 0; gemm < (bwd ? 3 : 1); ++gemm) {
+    for (int gemm = fwd ? 0 : 1; gemm < (bwd ? 3 : 1); ++gemm) {
         const size_t bytes = parts_written(p, gemm, kMaxCus, kAnyRoom);
         *partial_bytes = std::max(*partial_bytes, bytes);
         if (!shares_to_fill(p, gemm)) *needed_bytes = std::max(*needed_bytes, bytes);

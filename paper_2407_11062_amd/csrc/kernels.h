@@ -54,9 +54,9 @@ struct SkScratch { float *partials; size_t bytes; uint32_t *counters; };
 int plan_item_for_test(const Problem &p, int gemm, int block, int j, int32_t item[12]);      // test aid, see gemm_mfma.hip
 // Test aid: bytes from sk.partials on within which the launch of a GEMM (0 fwd, 1 dX, 2 dW) on a device of `cus` compute units writes.
 size_t parts_written_for_test(const Problem &p, int gemm, int cus, const SkScratch &sk);
-// Bytes of that scratch for the launches of a forward or (bwd) a forward and a backward.  *partial_bytes: what their plans write;
+// Bytes of that scratch for the launches of a forward that takes the tile kernels (fwd), a backward (bwd), or both.  *partial_bytes: what their plans write;
 // *needed_bytes: what a call cannot do without: launches that share tiles only to fill the chip run unshared in less.
-void sk_scratch_bytes(const Problem &p, bool bwd, size_t *partial_bytes, size_t *needed_bytes, size_t *counter_bytes);
+void sk_scratch_bytes(const Problem &p, bool fwd, bool bwd, size_t *partial_bytes, size_t *needed_bytes, size_t *counter_bytes);
 // Y[T,O] = X[T,I] * What[O,I]^T with What = (code - zbar) * s rebuilt per tile from packed codes.
 void launch_mfma_fwd(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, const SkScratch &sk,
                      hipStream_t st);

@@ -73,3 +73,17 @@ def test_more_workspace_than_asked_for_changes_no_plan():
             n = need(T, I, O, eq.OP_FQ_BWD)
             for gemm in range(3):
                 assert parts(T, I, O, eq.OP_FQ_BWD, gemm, cus, n) == parts(T, I, O, eq.OP_FQ_BWD, gemm, cus, n + (1 << 28))
+
+
+def test_no_room_for_parts_that_no_launch_writes():
+    """Whatever the kernel of the forward: the workspace ends where the last launch that writes parts ends, or where they would begin."""
+    seen = set()
+    for T, I, O in [(1, 4096, 4096), (1, 4096, 11008), (8, 5120, 13824), (333, 4096, 4096), (333, 4096, 11008), *ragged_shapes(3000, 7)]:
+        for op in (eq.OP_Q_FWD, eq.OP_QP_FWD, eq.OP_FQ_FWD):
+            n = need(T, I, O, op)
+            first, end = parts(T, I, O, op, 0, 256, n)
+            assert n == end, (T, I, O, op, first, end, n)
+            seen.add((op, end > first))
+    assert len(seen) == 6
+    # decoding: codes of the working layout, pairs, counters and no more
+    assert need(1, 4096, 4096, eq.OP_Q_FWD, 2, 64) == 4096 * 4096 // 4 + 4096 * 64 * 8 + 8192
