@@ -65,7 +65,8 @@ struct SkPlan {
     int dp_rounds;         // whole tiles per workgroup: tiles loc0 + r * (G / 8) of its XCD, r < dp_rounds
     int split;             // 1: the tiles beyond the whole rounds are split among groups of workgroups (see above)
     int pairs;             // K-tile pairs per output tile
-    float *partials;       // [G][2] accumulator tiles (a run has at most a head and a tail piece)
+    int slots;             // parts per workgroup: 1 where tiles are split, 2 for runs
+    float *partials;       // [G][2] accumulator tiles (a run has at most a head and a tail piece), [G] where tiles are split
     uint32_t *counters;    // [2][2 G], zero: arrivals, then flags, one each per tile that may be cut (at most 2 G / 8 per XCD)
 };
 struct SkItem {
@@ -162,7 +163,7 @@ __device__ __forceinline__ bool sk_hand_in(const SkPlan &sk, const SkItem &it, A
     // stores of the contributor that keeps its part in registers go to an out-of-range offset, where they are dropped.
     const uint32_t st_base = second ? kOobOffset : (uint32_t)tid * 16u;
     const __amdgpu_buffer_rsrc_t mine =
-        make_rsrc(sk.partials + ((size_t)blockIdx.x * 2 + (!split && me == 0 ? it.first_slot : 0)) * kTile, kTileBytes);
+        make_rsrc(sk.partials + ((size_t)blockIdx.x * sk.slots + (!split && me == 0 ? it.first_slot : 0)) * kTile, kTileBytes);
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -208,7 +209,7 @@ __device__ __forceinline__ bool sk_hand_in(const SkPlan &sk, const SkItem &it, A
     for (int k = 0; k < n_take; ++k) {
         const int from = split ? it.first + k : it.first + (1 - me);                  // contributor whose part this is
         const int slot = (!split && me == 1) ? it.first_slot : 0;
-        const __amdgpu_buffer_rsrc_t theirs = make_rsrc(sk.partials + (((size_t)from * 8 + xcd) * 2 + slot) * kTile, kTileBytes);
+        const __amdgpu_buffer_rsrc_t theirs = make_rsrc(sk.partials + (((size_t)from * 8 + xcd) * sk.slots + slot) * kTile, kTileBytes);
         // NB blocks in flight at a time.  In the fwd / dX kernels two (32 registers): with more (two parts together, 64
         // registers) they spilled or lost their second workgroup per CU, because the pipeline state of the next tile is
         // alive here.
@@ -1247,12 +1248,13 @@ int current_cus()
     }
     return cus_of[dev];
 }
-// What a plan that cuts tiles of `tile` outputs may write: two parts per resident workgroup.  The workspace is sized for the plans
-// of kMaxCus compute units; with fewer of them another plan may cut where those do not, so every plan asks for the room it needs.
-size_t parts_bytes(int resident, int tile) { return (size_t)resident * 2 * (size_t)tile * sizeof(float); }
-bool parts_fit(const SkScratch &s, int resident, int tile)
+// What a plan that cuts tiles of `tile` outputs may write: one part per resident workgroup if it splits tiles, two if it deals out
+// runs.  The workspace is sized for the plans of kMaxCus compute units; with fewer of them another plan may cut where those do
+// not, so every plan asks for the room it needs.
+size_t parts_bytes(int resident, int tile, bool split) { return (size_t)resident * (split ? 1 : 2) * (size_t)tile * sizeof(float); }
+bool parts_fit(const SkScratch &s, int resident, int tile, bool split)
 {
-    return s.partials != nullptr && s.counters != nullptr && s.bytes >= parts_bytes(resident, tile);
+    return s.partials != nullptr && s.counters != nullptr && s.bytes >= parts_bytes(resident, tile, split);
 }
 
 // fwd / dX with more tiles than k_gemm_ksplit takes: big tiles where they fill most of the chip, or where the small ones do not
@@ -1266,7 +1268,7 @@ TileChoice q_tile(int64_t m, int64_t n, int64_t k, int cus, const SkScratch &scr
     const int64_t big = ((m + 255) / 256) * ((n + 255) / 256), small = ((m + 127) / 128) * ((n + 127) / 128);
     if (big >= 160 || small > 512) return TileChoice::Big;
     const int64_t c = resident_workgroups(cus, 1) / 8 / ((big + 7) / 8), k_tiles = (k + 63) / 64;   // contributors per tile, as plan_tiles deals them out
-    if (!parts_fit(scratch, resident_workgroups(cus, 1), TileBig::BM * TileBig::BN) || c < 2 || c > 3 || k_tiles < 32) return TileChoice::Small;
+    if (!parts_fit(scratch, resident_workgroups(cus, 1), TileBig::BM * TileBig::BN, true) || c < 2 || c > 3 || k_tiles < 32) return TileChoice::Small;
     return 5.0 + 1.55 * (double)((k_tiles + c - 1) / c) + 0.085 * (double)(big * c) < 4.0 + 0.9 * (double)k_tiles ? TileChoice::BigShared : TileChoice::Small;
 }
 
@@ -1290,23 +1292,23 @@ template <typename K> void allow_dynamic_lds(K kern, size_t smem, uint64_t &done
 SkPlan plan_tiles(int ntiles, int tile, int pairs, int resident, const SkScratch &scratch, bool runs = true, bool share = false)
 {
     SkPlan sk{};
-    sk.pairs = pairs; sk.partials = scratch.partials; sk.counters = scratch.counters;
-    const bool room = parts_fit(scratch, resident, tile);
+    sk.pairs = pairs; sk.slots = 2; sk.partials = scratch.partials; sk.counters = scratch.counters;
+    const bool room = parts_fit(scratch, resident, tile, true), room_for_runs = parts_fit(scratch, resident, tile, false);
     if (ntiles <= resident) {                                // walk = 0: one workgroup per tile, unless they are to share
-        if (share && room && 2 * ((ntiles + 7) / 8) <= resident / 8) { sk.walk = 1; sk.split = 1; }
+        if (share && room && 2 * ((ntiles + 7) / 8) <= resident / 8) { sk.walk = 1; sk.split = 1; sk.slots = 1; }
         return sk;
     }
     sk.walk = 1;
     const int W = resident / 8, per = ntiles / 8, full = per / W;
     const bool even = (per % W == 0) && (ntiles % 8 == 0);
     const bool may_cut = !even && pairs >= 4 && room;
-    sk.dp_rounds = (may_cut && runs && full == 1) ? 0 : (per + (ntiles % 8 ? 1 : 0) + W - 1) / W;
+    sk.dp_rounds = (may_cut && room_for_runs && runs && full == 1) ? 0 : (per + (ntiles % 8 ? 1 : 0) + W - 1) / W;
     // Few tiles beyond the whole rounds (at most half a round on every XCD): whole tiles first, then the rest split.
     // The tile arithmetic promises (1 - 1/c) of a round; measured, 5.4 rounds (7B gate, up) gain 2.6 %, 3.4 rounds (13B
     // gate) 1.5-2.3 %: the partly filled round that the split replaces ran at a higher clock, and the instantiation that
     // can cut is 1-5 % slower in its main loop.  Beyond six whole rounds the promise is smaller than that price.
     const int n_sk_max = per + (ntiles % 8 ? 1 : 0) - full * W;
-    if (may_cut && full <= 6 && n_sk_max >= 1 && 2 * n_sk_max <= W && pairs >= 2 * kSkMaxSplit) { sk.dp_rounds = full; sk.split = 1; }
+    if (may_cut && full <= 6 && n_sk_max >= 1 && 2 * n_sk_max <= W && pairs >= 2 * kSkMaxSplit) { sk.dp_rounds = full; sk.split = 1; sk.slots = 1; }
     return sk;
 }
 
@@ -1458,12 +1460,12 @@ size_t parts_written(const Problem &p, int gemm, int cus, const SkScratch &sk)
     if (gemm == 2) {
         bool small;
         const DwLaunchPlan d = plan_dw_of(p, cus, sk, &small);
-        return d.cut ? parts_bytes(d.grid, small ? kSmall : kBig) : 0;
+        return d.cut ? parts_bytes(d.grid, small ? kSmall : kBig, d.sk.split != 0) : 0;
     }
     if (const int parts = ksplit_parts(p, gemm == 1, sk)) return ksplit_bytes(p, gemm == 1, parts);
     TileChoice choice;
     const QLaunchPlan q = plan_q_of(p, gemm == 1, cus, sk, &choice);
-    return q.sk.walk && (q.sk.dp_rounds == 0 || q.sk.split) ? parts_bytes(q.grid, choice == TileChoice::Small ? kSmall : kBig) : 0;
+    return q.sk.walk && (q.sk.dp_rounds == 0 || q.sk.split) ? parts_bytes(q.grid, choice == TileChoice::Small ? kSmall : kBig, q.sk.split != 0) : 0;
 }
 
 // Whether a launch with fewer tiles than workgroups shares them (k_gemm_ksplit, big tiles) where there is room for the parts.

@@ -87,3 +87,11 @@ def test_no_room_for_parts_that_no_launch_writes():
     assert len(seen) == 6
     # decoding: codes of the working layout, pairs, counters and no more
     assert need(1, 4096, 4096, eq.OP_Q_FWD, 2, 64) == 4096 * 4096 // 4 + 4096 * 64 * 8 + 8192
+
+
+def test_split_tiles_have_one_part_per_workgroup():
+    """Runs begin and end inside tiles: two parts per workgroup.  A split or shared tile takes one of each of its workgroups."""
+    part = 256 * 256 * 4
+    for shape, gemm, slots in (((1280, 4096, 4096), 1, 1), ((4096, 5120, 5120), 0, 1), ((4096, 5120, 6656), 0, 2)):
+        first, end = parts(*shape, eq.OP_FQ_BWD, gemm, 256, 1 << 30)
+        assert end - first == 256 * slots * part, shape
