@@ -830,7 +830,10 @@ FwdRoute mid_route(const Problem &p, bool from_packed)
 double mid_us(const Problem &p) { return launch_us(p, token_tile(p)); }
 
 // Against k_gemm_ksplit while there are at most 256 tiles of 128 x 128 (4.8 us and 0.8 to 1.1, with the fill, a pair of 64-wide K
-// tiles; 1024 inputs, 2000 tokens, 2048 rows: 12 us there, 14 here), and against the 128 x 128-tile kernel with two tiles per
+// tiles; 1024 inputs, 2000 tokens, 2048 rows: 12 us there, 14 here; with more than 640 inputs one round of 64- or 96-token tiles is
+// ahead whatever these estimates say, which leave out what a launch there costs beside its K tiles: from the packed arrays / from
+// a prepared layer, us, 832 x 552, 443 tokens 10.1 here, 15.2 there / 896 x 1680, 109 tokens 12.0 and 14.3; in 64 of 64 such sizes
+// between 672 and 1280 inputs by 1 to 80 %), and against the 128 x 128-tile kernel with two tiles per
 // compute unit beyond that (0.9 us per K tile; 11008 x 4096: 288 tokens, 258 tiles 61 us there and 42 here; 400 tokens 63 and 51).
 // More than two rounds here, or more than two tiles per compute unit there: the 256 x 256 tiles are the better kernel.  The GEMMs
 // alone are compared: a forward from the packed arrays saves the re-layout as well and would gain a little earlier, but every
@@ -840,6 +843,8 @@ bool mid_applies(const Problem &p)
     if (!p.act_bf16 || !group_by_magic(p) || p.T <= 32) return false;
     if (p.T <= 64) return !gemv_work_applies(p);
     const int64_t tiles = ((p.T + 127) / 128) * ((p.O + 127) / 128);
+    const int bm = token_tile(p);
+    if (tiles <= 256 && p.I > 640 && bm < 128 && rounds_of(p, bm) == 1) return true;
     const double other = tiles <= 256 ? 4.8 + (double)((p.I + 127) / 128) * (0.8 + 0.3 * (double)tiles / 256.0)
                                       : 4.0 + (double)((p.I + 63) / 64) * 0.9;
     return tiles <= 512 && mid_us(p) < other;

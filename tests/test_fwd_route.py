@@ -67,6 +67,15 @@ def test_3_bit_codes_are_relaid_where_two_rounds_rebuild_them():
     assert route(333, 4096, 4096, 3, 128)[0] == MID and route(192, 4096, 28672, 3, 128) == (MID, 96, 128)
 
 
+def test_one_round_of_short_token_tiles_takes_the_kernel_for_few_tiles():
+    # from 641 inputs on, whatever the estimates of both kernels say (they overrate this one where the contraction is short)
+    for T, I, O, bits, g in ((443, 832, 552, 2, 32), (85, 800, 2504, 3, 32), (135, 800, 2120, 4, 32), (825, 896, 552, 2, 128), (174, 1184, 2792, 3, 32),
+                             (101, 864, 3528, 4, -1), (725, 672, 632, 4, -1)):
+        assert route(T, I, O, bits, g) == (MID, 64, 128) and route(T, I, O, bits, g, WORK) == (MID, 64, 128), (T, I, O)
+    assert route(1389, 896, 1936, 3, 128) == (MID, 96, 128)
+    assert route(443, 640, 552, 2, 32)[0] == TILES and route(2026, 704, 1672, 2, -1)[0] == TILES          # 640 inputs; two rounds
+
+
 def test_the_entry_point_does_not_matter_from_17_tokens_on():
     rng = np.random.default_rng(7)
     seen = set()
