@@ -353,8 +353,20 @@ eqat_status eqat_block_ap_update(const eqat_desc *d, const eqat_adamw *h, void *
  * tile's counter, workgroups in the launch, K-tile pairs per tile, tile rows, tile columns }; *exists = 0 past the last
  * item j of workgroup `block`.  EQAT_ERR_SHAPE for block outside the launch, gemm not 0, 1 or 2, j < 0.  Lets a test check,
  * without a GPU, that every K-tile pair of every tile is computed exactly once for any shape.
+ * This is the launch of the tile kernels, given all the workspace it asks for.  A forward may take another kernel altogether
+ * (eqat_fwd_route), and a forward or dX of few output tiles runs in the kernel that eqat_shared_item is about.
  */
 eqat_status eqat_plan_item(const eqat_desc *d, int gemm, int block, int j, int32_t *item, int32_t *exists);
+
+/*
+ * Test aid (host only, nothing is launched): the same for a forward (gemm = 0) or dX (gemm = 1) with at most 256 output tiles of
+ * 128 x 128, whose tiles are shared by one to four workgroups, a stretch of the K-tile pairs each (two groups of waves of a
+ * workgroup take the tiles of a pair).  *exists = 0 where another kernel computes it, and past the last workgroup; else
+ * item[10] = { tile row, tile column, first and past-the-last K-tile pair of workgroup `block`, which part of the tile this is, parts
+ * of the tile, workgroups in the launch, K-tile pairs per tile, tile rows, tile columns }.  The parts of a tile are counted in at the
+ * counter with the number of the tile.
+ */
+eqat_status eqat_shared_item(const eqat_desc *d, int gemm, int block, int32_t *item, int32_t *exists);
 
 /*
  * Test aid (host only, nothing is launched): the bytes [*first, *end) of a workspace of `ws_bytes` bytes, for a call of kind `op`
@@ -367,7 +379,7 @@ eqat_status eqat_plan_scratch(const eqat_desc *d, int op, int gemm, int cus, siz
 /*
  * Test aid (host only, nothing is launched): the kernel that a forward of this descriptor (bf16 activations, tokens >= 1)
  * takes, from the packed arrays as they are (source 1: eqat_qlinear_fwd, 2: eqat_qlinear_fwd_z) or from codes in the working
- * layout (0: every other forward).  route[3] = { 0 tiled GEMM; 1 GEMM for few tiles; 2 matrix-vector with streamed
+ * layout (0: every other forward).  route[3] = { 0 tiled GEMM (which one: eqat_shared_item); 1 GEMM for few tiles; 2 matrix-vector with streamed
  * tokens; 3 matrix-vector, any group; 4 matrix-vector, 5 the same segment by segment, 6 the same in pairs of lookups;
  * 7 a re-layout of the codes, then 1,  tokens,  rows that a workgroup computes (0 for the tiled GEMM) }.  Lets a test
  * assert that its sizes reach the kernel it is about.

@@ -62,13 +62,25 @@ __device__ __forceinline__ void ks_store(const floatx16 (&v)[2], unsigned char *
     }
 }
 
-__device__ __forceinline__ void ks_tile(int p, int tiles_m, int tiles_n, int &tm, int &tn)
+// What workgroup `bid` of `nb` computes: a stretch of K-tile pairs of one tile.  Every XCD gets a contiguous range of (part, tile)
+// numbers, tiles in bands of four tile rows.
+struct KsItem { int number, tile, part, tm, tn, first_pair, pairs; };
+__host__ __device__ __forceinline__ KsItem ks_item(int bid, int nb, int tiles_m, int tiles_n, int parts, int pairs)
 {
+    KsItem it;
+    const int xcd = bid & 7, rem = nb & 7, ntiles = tiles_m * tiles_n;
+    it.number = xcd * (nb >> 3) + (xcd < rem ? xcd : rem) + (bid >> 3);
+    it.part = it.number / ntiles;
+    it.tile = it.number - it.part * ntiles;
     constexpr int band_rows = 4;
-    const int width = band_rows * tiles_n, band = p / width, first = band * band_rows;
-    const int rows = tiles_m - first < band_rows ? tiles_m - first : band_rows, in = p - band * width;
-    tm = first + in % rows;
-    tn = in / rows;
+    const int width = band_rows * tiles_n, band = it.tile / width, first = band * band_rows;
+    const int rows = tiles_m - first < band_rows ? tiles_m - first : band_rows, in = it.tile - band * width;
+    it.tm = first + in % rows;
+    it.tn = in / rows;
+    const int base = pairs / parts, extra = pairs % parts;
+    it.first_pair = it.part * base + (it.part < extra ? it.part : extra);
+    it.pairs = base + (it.part < extra ? 1 : 0);
+    return it;
 }
 
 template <int BITS, bool BT>
@@ -82,15 +94,10 @@ __global__ __launch_bounds__(kKsNT) void k_gemm_ksplit(const KsArgs a)
     bf16_t *const sA = reinterpret_cast<bf16_t *>(smem_raw + (uint32_t)kg * ks_group_bytes<BT>());
     bf16_t *const sB = sA + 2 * A_ELEMS;
 
-    const int nb = (int)gridDim.x, xcd = (int)(blockIdx.x & 7), rem = nb & 7;
-    const int pid = xcd * (nb >> 3) + (xcd < rem ? xcd : rem) + (int)(blockIdx.x >> 3);
-    const int ntiles = a.tiles_m * a.tiles_n, part = pid / ntiles, tile = pid - part * ntiles;
-    int tm, tn;
-    ks_tile(tile, a.tiles_m, a.tiles_n, tm, tn);
-    const int m0 = tm * kKsBM, n0 = tn * kKsBN;
-    const int base = a.pairs / a.parts_per_tile, extra = a.pairs % a.parts_per_tile;
-    const int kb = part * base + (part < extra ? part : extra), n = base + (part < extra ? 1 : 0);
-    const int k_first = (2 * kb + kg) * kKsBK;
+    const KsItem item = ks_item((int)blockIdx.x, (int)gridDim.x, a.tiles_m, a.tiles_n, a.parts_per_tile, a.pairs);
+    const int pid = item.number, ntiles = a.tiles_m * a.tiles_n, tile = item.tile;
+    const int m0 = item.tm * kKsBM, n0 = item.tn * kKsBN, n = item.pairs;
+    const int k_first = (2 * item.first_pair + kg) * kKsBK;
 
     const __amdgpu_buffer_rsrc_t rCodes = make_rsrc(a.codes, a.codes_bytes);
     const __amdgpu_buffer_rsrc_t rS = make_rsrc(a.sz, a.sz_bytes);
@@ -381,6 +388,19 @@ int ksplit_parts(const Problem &p, bool bt, const SkScratch &sk)
 size_t ksplit_bytes(const Problem &p, bool bt, int parts)
 {
     return parts > 1 ? (size_t)shape_of(p, bt).tiles * parts * kKsPartBytes : 0;
+}
+
+bool ksplit_item_for_test(const Problem &p, bool bt, const SkScratch &sk, int block, int32_t item[10])
+{
+    const int parts = ksplit_parts(p, bt, sk);
+    if (parts == 0) return false;
+    const Shape s = shape_of(p, bt);
+    const int tiles_m = (s.M + kKsBM - 1) / kKsBM, tiles_n = (s.N + kKsBN - 1) / kKsBN, grid = s.tiles * parts;
+    if (block >= grid) return false;
+    const KsItem it = ks_item(block, grid, tiles_m, tiles_n, parts, s.pairs);
+    const int32_t v[10] = {it.tm, it.tn, it.first_pair, it.first_pair + it.pairs, it.part, parts, grid, s.pairs, tiles_m, tiles_n};
+    for (int k = 0; k < 10; ++k) item[k] = v[k];
+    return true;
 }
 
 void launch_ksplit(const Problem &p, bool bt, const void *A, const void *codes, const void *sz, void *C, const SkScratch &sk, int parts,

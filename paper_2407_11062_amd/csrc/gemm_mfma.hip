@@ -1498,7 +1498,7 @@ size_t parts_written_for_test(const Problem &p, int gemm, int cus, const SkScrat
 
 // Test aid: work item number j of workgroup `block` in the launch that the forward (gemm = 0), the dX (gemm = 1) or the dW
 // (gemm = 2; tile rows: in-features, tile columns: out-features, K: tokens) GEMM of this problem makes, as the kernel
-// itself works it out (the tile kernels' launch, also where the dispatch takes another route at that token count).
+// itself works it out (the tile kernels' launch, also where the dispatch takes another route at that token count, or k_gemm_ksplit).
 // item = {tile row, tile column, first and past-the-last K-tile pair, contributors of the tile, the first contributor's index in its XCD, 1 for a split tile, counter index, grid, K-tile pairs per tile, tile rows, tile
 // columns}.  Returns 1, 0 past the workgroup's last item, -1 for a bad argument.
 int plan_item_for_test(const Problem &p, int gemm, int block, int j, int32_t item[12])

@@ -96,6 +96,7 @@ inline bool group_by_magic(const Problem &p) { return (p.I / 32) * (p.g / 32) < 
 // Workgroups that share a tile of the forward (bt = false) or dX (bt = true); 0: the tile kernels of gemm_mfma.hip compute it.
 int ksplit_parts(const Problem &p, bool bt, const SkScratch &sk);
 size_t ksplit_bytes(const Problem &p, bool bt, int parts);          // of sk.partials; 0 for one part
+bool ksplit_item_for_test(const Problem &p, bool bt, const SkScratch &sk, int block, int32_t item[10]);      // test aid
 void launch_ksplit(const Problem &p, bool bt, const void *A, const void *codes, const void *sz, void *C, const SkScratch &sk,
                    int parts, hipStream_t st);
 
