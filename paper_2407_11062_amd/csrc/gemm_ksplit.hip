@@ -368,12 +368,15 @@ Shape shape_of(const Problem &p, bool bt)
 
 // One round of workgroups (more tiles: the tile kernel has two workgroups per compute unit and is level or ahead, 1280 tokens, 4096 x
 // 4096: 62 us there, two rounds here 66).  A launch takes 4.5 us, 0.95 a pair of K tiles and, where a tile has several
-// contributors, 2.5 us and 0.045 per part; a part is at least four pairs.
+// contributors, 2.5 us and 0.045 per part; a part is at least four pairs.  Two or four whole K tiles are too few for two groups: the
+// tile kernel needs no sum of theirs (forward on a prepared layer, us, there / here: 128 inputs, 150 tokens, 3224 rows 9.1 / 9.8, 3546
+// tokens, 880 rows 10.0 / 10.8; 256 inputs, 617 tokens, 3480 rows 10.8 / 11.6; dX, 128 rows, 74 tokens, 24128 inputs 18.5 / 19.2).
+// Lengths that are no multiple of two K tiles take its slower instantiation and stay here (192 inputs: 12.0 and 10.4).
 int ksplit_parts(const Problem &p, bool bt, const SkScratch &sk)
 {
     if (!p.act_bf16 || p.T < 1 || !group_by_magic(p)) return 0;
     const Shape s = shape_of(p, bt);
-    if (s.tiles > 256) return 0;
+    if (s.tiles > 256 || (s.K <= 4 * kKsBK && s.K % (2 * kKsBK) == 0)) return 0;
     const int room = sk.partials == nullptr || sk.counters == nullptr ? 1 : (int)std::min<size_t>(sk.bytes / (s.tiles * kKsPartBytes), kKsMaxParts);
     const int most = std::min(std::min(room, 256 / s.tiles), s.pairs / 4);
     int best = 1;

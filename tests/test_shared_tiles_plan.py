@@ -67,6 +67,9 @@ def test_known_launches():
     assert parts_of(256, 11008, 4096, 1) == 1 and parts_of(1280, 4096, 4096, 1) == 0           # 172 tiles; 320: the tile kernels
     assert parts_of(1, 4096, 4096, 0) == 4 and route(1, 4096, 4096, 2, 32, WORK)[0] == TILES   # one token on a prepared layer
     assert parts_of(333, 4096, 4096, 0) == 0                                                   # k_gemm_mid
+    # two or four whole K tiles: the tile kernel; any other length up to them is shared by the two K groups
+    for K, parts in ((32, 1), (64, 1), (96, 1), (128, 0), (160, 1), (192, 1), (256, 0), (288, 1), (384, 1)):
+        assert parts_of(100, K, 512, 0) == parts and parts_of(100, 512, K, 1) == parts, K
 
 
 def test_bad_arguments():
