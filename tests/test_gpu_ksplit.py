@@ -7,26 +7,44 @@ import torch
 import oracle
 import paper_2407_11062_amd as eq
 from paper_2407_11062_amd import synth
+from test_fwd_route import TILES, WORK, route
 from test_gpu_parity import TOL, dev, make_case, npf, relerr
+from test_shared_tiles_plan import parts_of
+from test_work_plan import items_of_launch
 from test_workspace_parts import parts
 
 pytestmark = pytest.mark.gpu
 
-# tokens, in, out, group: dX contracts over out (parts of its tiles in the comment), the forward over in
-CASES = [(70, 96, 40, 32),          # one pair
-         (300, 352, 200, 32),       # two
-         (1000, 4096, 264, 64),     # three pairs, 256 tiles
-         (129, 512, 1480, 64),      # 3 parts, K ends inside the second group's tile
-         (130, 256, 2056, 32),      # 4 parts, K ends inside the first group's tile, no second one
-         (256, 1024, 3000, -1),     # 4 parts
-         (600, 2048, 4096, 128),    # 3 parts, a last tile of 88 tokens
-         (2560, 2048, 5504, 64),    # 80 tiles of 256 x 256, three workgroups each (the tile kernel)
-         (2590, 2528, 10256, 32)]   # 110 of them, two each; K ends inside a K tile
+# tokens, in, out, group, and what dX, which contracts over out, runs on: workgroups per tile of k_gemm_ksplit, or the tile kernel (edge
+# of its tiles, workgroups per tile)
+CASES = [(70, 96, 40, 32, 1),          # one pair; the forward too
+         (300, 352, 200, 32, 1),       # two; the forward three
+         (1000, 4096, 264, 64, 1),     # three pairs, 256 tiles
+         (129, 512, 1480, 64, 3),      # K ends inside the second group's tile
+         (130, 256, 2056, 32, 4),      # K ends inside the first group's tile, no second one
+         (256, 1024, 3000, -1, 4),
+         (600, 2048, 4096, 128, 3),    # a last tile of 88 tokens
+         (200, 12000, 128, 32, (128, 1)),                   # two whole K tiles
+         (330, 1120, 256, 32, (128, 1)),                    # four
+         (2560, 2048, 5504, 64, (256, 3)),                  # 80 tiles
+         (2590, 2528, 10256, 32, (128, 1)),                 # 420 tiles; K ends inside a K tile
+         (2590, 2528, 12296, 32, (256, 2))]                 # 110 tiles; K ends inside a K tile
+
+
+def assert_way(T, I, O, gemm, bits, g, way):
+    if isinstance(way, int):
+        assert parts_of(T, I, O, gemm, bits, g) == way
+    else:
+        items, _, _, tiles_m, tiles_n = items_of_launch(T, I, O, gemm)
+        edge, parts = way
+        assert parts_of(T, I, O, gemm, bits, g) == 0 and {it[4] for _, _, it in items} == {parts}
+        assert (tiles_m, tiles_n) == (-(-T // edge), -(-(I if gemm else O) // edge))
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
-@pytest.mark.parametrize("T,I,O,g", CASES)
-def test_dx_and_forward_with_few_tiles(T, I, O, g, bits):
+@pytest.mark.parametrize("T,I,O,g,way", CASES)
+def test_dx_and_forward_with_few_tiles(T, I, O, g, way, bits):
+    assert_way(T, I, O, 1, bits, g, way)
     X, W, s, z, dY = make_case(("ksplit", T, I, O), T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
     Xd, Wd, sd, zd, dYd = dev(X), dev(W), dev(s), dev(z), dev(dY)
     some = sorted({t for t in (0, 31, 32, 63, 64, 100, 127, 128, 191, 255, 256, 511, 512, T // 2, T - 2, T - 1) if 0 <= t < T})
@@ -71,3 +89,34 @@ def test_without_room_for_parts_the_tiles_are_not_shared(T, I, O, g):
         assert relerr(dX[some], ref) <= TOL[torch.bfloat16] and relerr(Y[some], Yref) <= TOL[torch.bfloat16]
         assert bool((guard[first + room:] == 0xA5).all())
         assert torch.equal(dX, eq.eqat_fq_linear_bwd(Xd, Wd, sd, zd, dYd, bits, g, want=("dX",), ws=ws, kept=True)["dX"])
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("T,I,O,g,way", [(1, 2048, 264, 64, 4), (16, 1056, 1032, 32, 2), (7, 544, 72, -1, 1), (3, 256, 136, 32, (128, 1))])
+def test_forward_of_a_few_tokens_on_a_prepared_layer(T, I, O, g, way, bits):
+    """Up to 16 tokens only the packed arrays have matrix-vector kernels: shared tiles, with an odd number of pairs and a row that ends
+    inside a K tile; two pairs of whole K tiles in the tile kernel."""
+    assert_way(T, I, O, 0, bits, g, way)
+    X, W, s, z, _ = make_case(("fewprep", T, I, O), T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
+    Xd, sd = dev(X), dev(s)
+    Wp, zp = eq.eqat_pack(dev(W), sd, dev(z), bits, g)
+    prepared = eq.eqat_qlinear_prepare(Wp, zp, I, bits, g)
+    Y = eq.eqat_qlinear_fwd_prepared(Xd, prepared, sd, O, bits, g)
+    assert relerr(Y, oracle.qlinear_fwd(npf(X), Wp.cpu().numpy(), s.numpy(), zp.cpu().numpy(), bits, g)) <= TOL[torch.bfloat16]
+    for _ in range(2):
+        assert torch.equal(Y, eq.eqat_qlinear_fwd_prepared(Xd, prepared, sd, O, bits, g))
+
+
+# the forward on 128 x 128 tiles of the tile kernel (257 to 512 of them that k_gemm_mid leaves), whole K tiles and pieces of one
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("T,I,O,g", [(2200, 352, 2056, 32), (2048, 512, 2176, 64), (1100, 2016, 5640, 96), (1999, 1920, 3304, -1)])
+def test_forward_on_128_by_128_tiles(T, I, O, g, bits):
+    assert route(T, I, O, bits, g, WORK)[0] == TILES
+    assert_way(T, I, O, 0, bits, g, (128, 1))
+    X, W, s, z, _ = make_case(("small tiles", T, I, O), T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
+    Xd, Wd, sd, zd = dev(X), dev(W), dev(s), dev(z)
+    Y = eq.eqat_fq_linear_fwd(Xd, Wd, sd, zd, bits, g)
+    some = sorted({t for e in range(0, T + 1, 128) for t in (e - 1, e, e + 33) if 0 <= t < T} | {T - 1})
+    assert relerr(Y[some], oracle.fq_linear_fwd(npf(X)[some], npf(W), s.numpy(), z.numpy(), bits, g)) <= TOL[torch.bfloat16]
+    Wp, zp = eq.eqat_pack(Wd, sd, zd, bits, g)
+    assert torch.equal(Y, eq.eqat_qlinear_fwd(Xd, Wp, sd, zp, bits, g))
