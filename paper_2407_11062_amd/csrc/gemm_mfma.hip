@@ -1262,10 +1262,18 @@ bool parts_fit(const SkScratch &s, int resident, int tile, bool split)
 // small 60), or, each shared by two or three workgroups, where the contraction is long enough to pay for the parts: small tiles
 // take 0.9 us per K tile, a share of a big one 1.55 (the chip's power limit), 0.085 us per part comes on top (dX, 11008 -> 4096:
 // 1280 tokens 157 -> 111 us, 2048 tokens 184 -> 164; 4096 -> 4096, 1280 tokens: 67 -> 64, 2048 tokens: 74, 80 if it were taken).
+// The few small tiles beyond 512 are split eight ways where K is long, and a forward that reads few (s, z) pairs is faster on them
+// than on 130 to 159 big tiles: 2-bit codes with at most 8 groups a row, each 16 K tiles or more, and from 48 K tiles on
+// (513 to 544 tiles, 99 random sizes, from level to 12 % faster; us, small / big: one group per row, 532 tiles, 9792 inputs 176 / 195, 528 tiles,
+// 4384 inputs 90 / 95; g = 1024, 516 tiles, 4096 inputs 81 / 85), 3-bit codes with one group and 96 K tiles (520 tiles, 5952 inputs
+// 116 / 123).  Shorter ones are level or slower (536 tiles, 2688 inputs 60 / 59), and so is g = 512 from 530 tiles on.
 enum class TileChoice { Small, Big, BigShared };
-TileChoice q_tile(int64_t m, int64_t n, int64_t k, int cus, const SkScratch &scratch)
+TileChoice q_tile(const Problem &p, bool bt, int cus, const SkScratch &scratch)
 {
+    const int64_t m = p.T, n = bt ? p.I : p.O, k = bt ? p.O : p.I;
     const int64_t big = ((m + 255) / 256) * ((n + 255) / 256), small = ((m + 127) / 128) * ((n + 127) / 128);
+    if (!bt && big < 160 && small > 512 && small <= 544 && parts_fit(scratch, resident_workgroups(cus, 2), TileSmall::BM * TileSmall::BN, true)
+        && (p.bits == 2 ? p.G <= 8 && p.g >= 1024 && k >= 48 * 64 : p.bits == 3 && p.G == 1 && k >= 96 * 64)) return TileChoice::Small;
     if (big >= 160 || small > 512) return TileChoice::Big;
     const int64_t c = resident_workgroups(cus, 1) / 8 / ((big + 7) / 8), k_tiles = (k + 63) / 64;   // contributors per tile, as plan_tiles deals them out
     if (!parts_fit(scratch, resident_workgroups(cus, 1), TileBig::BM * TileBig::BN, true) || c < 2 || c > 3 || k_tiles < 32) return TileChoice::Small;
@@ -1365,11 +1373,11 @@ void launch_q(const GemmQArgs &args, const SkScratch &scratch, hipStream_t st, b
 }
 
 template <bool BT>
-void launch_q_bits(int bits, const GemmQArgs &a, const SkScratch &scratch, hipStream_t st)
+void launch_q_bits(const Problem &p, const GemmQArgs &a, const SkScratch &scratch, hipStream_t st)
 {
-    const TileChoice tile = q_tile(a.M, a.N, a.K, current_cus(), scratch);
+    const TileChoice tile = q_tile(p, BT, current_cus(), scratch);
 #define EQAT_GO(B) do { if (tile == TileChoice::Small) launch_q<B, BT, TileSmall>(a, scratch, st); else launch_q<B, BT, TileBig>(a, scratch, st, tile == TileChoice::BigShared); } while (0)
-    if (bits == 2) EQAT_GO(2); else if (bits == 3) EQAT_GO(3); else EQAT_GO(4);
+    if (p.bits == 2) EQAT_GO(2); else if (p.bits == 3) EQAT_GO(3); else EQAT_GO(4);
 #undef EQAT_GO
 }
 
@@ -1440,7 +1448,7 @@ const SkScratch kAnyRoom{reinterpret_cast<float *>(16), ~(size_t)0, reinterpret_
 QLaunchPlan plan_q_of(const Problem &p, bool bt, int cus, const SkScratch &sk, TileChoice *choice)
 {
     const int M = (int)p.T, N = (int)(bt ? p.I : p.O), K = (int)(bt ? p.O : p.I);
-    *choice = q_tile(M, N, K, cus, sk);
+    *choice = q_tile(p, bt, cus, sk);
     const bool small = *choice == TileChoice::Small, share = *choice == TileChoice::BigShared;
     if (bt) return small ? plan_q<true, TileSmall>(M, N, K, cus, sk, false) : plan_q<true, TileBig>(M, N, K, cus, sk, share);
     return small ? plan_q<false, TileSmall>(M, N, K, cus, sk, false) : plan_q<false, TileBig>(M, N, K, cus, sk, share);
@@ -1468,14 +1476,16 @@ size_t parts_written(const Problem &p, int gemm, int cus, const SkScratch &sk)
     return q.sk.walk && (q.sk.dp_rounds == 0 || q.sk.split) ? parts_bytes(q.grid, choice == TileChoice::Small ? kSmall : kBig, q.sk.split != 0) : 0;
 }
 
-// Whether a launch with fewer tiles than workgroups shares them (k_gemm_ksplit, big tiles) where there is room for the parts.
-bool shares_to_fill(const Problem &p, int gemm)
+// Whether a launch takes parts that it can go without: it shares its tiles because they are few (k_gemm_ksplit, big tiles), or
+// another choice of tiles needs none.
+bool can_do_without_parts(const Problem &p, int gemm)
 {
     if (gemm == 2) return false;
     if (ksplit_parts(p, gemm == 1, kAnyRoom)) return true;
-    TileChoice choice;
+    TileChoice choice, other;
     (void)plan_q_of(p, gemm == 1, kMaxCus, kAnyRoom, &choice);
-    return choice == TileChoice::BigShared;
+    (void)plan_q_of(p, gemm == 1, kMaxCus, SkScratch{}, &other);
+    return other != choice;
 }
 
 }  // namespace
@@ -1490,7 +1500,7 @@ void sk_scratch_bytes(const Problem &p, bool fwd, bool bwd, size_t *partial_byte
     for (int gemm = fwd ? 0 : 1; gemm < (bwd ? 3 : 1); ++gemm) {
         const size_t bytes = parts_written(p, gemm, kMaxCus, kAnyRoom);
         *partial_bytes = std::max(*partial_bytes, bytes);
-        if (!shares_to_fill(p, gemm)) *needed_bytes = std::max(*needed_bytes, bytes);
+        if (!can_do_without_parts(p, gemm)) *needed_bytes = std::max(*needed_bytes, bytes);
     }
 }
 
@@ -1546,7 +1556,7 @@ void launch_mfma_fwd(const Problem &p, const void *X, const void *codes, const v
     a.A = (const bf16_t *)X; a.codes = (const uint32_t *)codes; a.sz = (const floatx2 *)sz; a.C = (bf16_t *)Y;
     a.M = (int)p.T; a.N = (int)p.O; a.K = (int)p.I; a.I = (int)p.I; a.G = (int)p.G; a.g = (int)p.g;
     a.a_bytes = (uint32_t)(p.T * p.I * 2); a.codes_bytes = (uint32_t)work_code_bytes(p); a.sz_bytes = (uint32_t)(p.O * p.G * 8);
-    launch_q_bits<false>(p.bits, a, sk, st);
+    launch_q_bits<false>(p, a, sk, st);
 }
 
 void launch_mfma_dx(const Problem &p, const void *dY, const void *codes, const void *sz, void *dX, const SkScratch &sk,
@@ -1558,7 +1568,7 @@ void launch_mfma_dx(const Problem &p, const void *dY, const void *codes, const v
     a.A = (const bf16_t *)dY; a.codes = (const uint32_t *)codes; a.sz = (const floatx2 *)sz; a.C = (bf16_t *)dX;
     a.M = (int)p.T; a.N = (int)p.I; a.K = (int)p.O; a.I = (int)p.I; a.G = (int)p.G; a.g = (int)p.g;
     a.a_bytes = (uint32_t)(p.T * p.O * 2); a.codes_bytes = (uint32_t)work_code_bytes(p); a.sz_bytes = (uint32_t)(p.O * p.G * 8);
-    launch_q_bits<true>(p.bits, a, sk, st);
+    launch_q_bits<true>(p, a, sk, st);
 }
 
 void launch_mfma_dw(const Problem &p, bool block_ap, const void *X, const void *dY, const void *W, const void *codes,

@@ -120,3 +120,23 @@ def test_forward_on_128_by_128_tiles(T, I, O, g, bits):
     assert relerr(Y[some], oracle.fq_linear_fwd(npf(X)[some], npf(W), s.numpy(), z.numpy(), bits, g)) <= TOL[torch.bfloat16]
     Wp, zp = eq.eqat_pack(Wd, sd, zd, bits, g)
     assert torch.equal(Y, eq.eqat_qlinear_fwd(Xd, Wp, sd, zp, bits, g))
+
+
+@pytest.mark.parametrize("bits,I,g", [(2, 3072, 1024), (2, 3104, -1), (3, 6176, -1)])
+def test_forward_on_few_more_than_512_small_tiles(bits, I, g):
+    """544 of them on 512 workgroups: one each, the rest split eight ways, with whole K tiles and with a piece of one at the end.  Without room
+    for the parts the big tiles take it."""
+    T, O = 4350, 2040
+    first, end = parts(T, I, O, eq.OP_FQ_FWD, 0, 256, 1 << 30, bits, g)
+    assert end - first == 512 * 128 * 128 * 4
+    X, W, s, z, _ = make_case(("544", I), T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
+    Xd, Wd, sd, zd = dev(X), dev(W), dev(s), dev(z)
+    some = sorted({t for e in range(0, T + 1, 512) for t in (e - 1, e, e + 33) if 0 <= t < T} | {T - 1})
+    ref = oracle.fq_linear_fwd(npf(X)[some], npf(W), s.numpy(), z.numpy(), bits, g)
+    for n in (end, first):
+        guard = torch.full((n + 4096,), 0xA5, dtype=torch.uint8, device=Xd.device)
+        Y = eq.eqat_fq_linear_fwd(Xd, Wd, sd, zd, bits, g, ws=guard[:n])
+        assert relerr(Y[some], ref) <= TOL[torch.bfloat16]
+        assert torch.equal(Y, eq.eqat_fq_linear_fwd(Xd, Wd, sd, zd, bits, g, ws=guard[:n]))
+        assert bool((guard[n:] == 0xA5).all())
+    assert torch.equal(eq.eqat_fq_linear_fwd(Xd, Wd, sd, zd, bits, g), eq.eqat_fq_linear_fwd(Xd, Wd, sd, zd, bits, g, ws=torch.empty(end, dtype=torch.uint8, device=Xd.device)))

@@ -134,3 +134,16 @@ def test_bad_arguments():
     f32 = eq.make_desc(512, 512, 512, 2, 32, eq.F32, eq.F32)
     assert L.eqat_plan_item(ctypes.byref(f32), 0, 0, 0, item, ctypes.byref(ex)) != 0
     assert L.eqat_plan_item(r, 0, 0, 0, item, ctypes.byref(ex)) == 0 and ex.value == 1
+
+
+def test_small_tiles_beyond_one_round_where_groups_are_long():
+    # 133 big tiles or 518 small ones: the forward of 2-bit codes with one group per row splits the six beyond 512, eight ways
+    def grid_tiles(bits, g, gemm=0, T=1723, I=11712, O=4648):
+        d = eq.make_desc(T, I, O, bits, g, eq.BF16, eq.BF16)
+        item, ex = (ctypes.c_int32 * 12)(), ctypes.c_int32()
+        assert eq.lib().eqat_plan_item(ctypes.byref(d), gemm, 0, 0, item, ctypes.byref(ex)) == 0
+        return item[8], item[10] * item[11]
+    assert grid_tiles(2, -1) == grid_tiles(2, 11712 // 3) == grid_tiles(3, -1) == (512, 518)
+    assert grid_tiles(2, 64) == grid_tiles(4, -1) == grid_tiles(3, 11712 // 3) == grid_tiles(2, -1, I=3008) == grid_tiles(3, -1, I=6080) == (133, 133)
+    assert grid_tiles(2, -1, O=4872) == (140, 140)                         # 546 small ones
+    assert grid_tiles(2, -1, gemm=1, I=4640, O=11712)[0] == 133
