@@ -1265,15 +1265,15 @@ bool parts_fit(const SkScratch &s, int resident, int tile, bool split)
 // The few small tiles beyond 512 are split eight ways where K is long, and a forward that reads few (s, z) pairs is faster on them
 // than on 130 to 159 big tiles: 2-bit codes with at most 8 groups a row, each 16 K tiles or more, and from 48 K tiles on
 // (513 to 544 tiles, 99 random sizes, from level to 12 % faster; us, small / big: one group per row, 532 tiles, 9792 inputs 176 / 195, 528 tiles,
-// 4384 inputs 90 / 95; g = 1024, 516 tiles, 4096 inputs 81 / 85), 3-bit codes with one group and 96 K tiles (520 tiles, 5952 inputs
-// 116 / 123).  Shorter ones are level or slower (536 tiles, 2688 inputs 60 / 59), and so is g = 512 from 530 tiles on.
+// 4384 inputs 90 / 95; g = 1024, 516 tiles, 4096 inputs 81 / 85).  Shorter ones are level or slower (536 tiles, 2688 inputs 60 / 59), and so
+// are g = 512 from 530 tiles on and 3-bit codes (one group, 540 tiles, 7968 inputs 159 / 156, 525 tiles, 15168 inputs 277 / 288).
 enum class TileChoice { Small, Big, BigShared };
 TileChoice q_tile(const Problem &p, bool bt, int cus, const SkScratch &scratch)
 {
     const int64_t m = p.T, n = bt ? p.I : p.O, k = bt ? p.O : p.I;
     const int64_t big = ((m + 255) / 256) * ((n + 255) / 256), small = ((m + 127) / 128) * ((n + 127) / 128);
     if (!bt && big < 160 && small > 512 && small <= 544 && parts_fit(scratch, resident_workgroups(cus, 2), TileSmall::BM * TileSmall::BN, true)
-        && (p.bits == 2 ? p.G <= 8 && p.g >= 1024 && k >= 48 * 64 : p.bits == 3 && p.G == 1 && k >= 96 * 64)) return TileChoice::Small;
+        && p.bits == 2 && p.G <= 8 && p.g >= 1024 && k >= 48 * 64) return TileChoice::Small;
     if (big >= 160 || small > 512) return TileChoice::Big;
     const int64_t c = resident_workgroups(cus, 1) / 8 / ((big + 7) / 8), k_tiles = (k + 63) / 64;   // contributors per tile, as plan_tiles deals them out
     if (!parts_fit(scratch, resident_workgroups(cus, 1), TileBig::BM * TileBig::BN, true) || c < 2 || c > 3 || k_tiles < 32) return TileChoice::Small;
