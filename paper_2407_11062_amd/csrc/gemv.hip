@@ -343,7 +343,8 @@ template <int TR> constexpr int kWideSub = TR >= 64 ? 1 : TR >= 16 ? 2 : 4;     
 template <int TR> constexpr int kWideRowBytes = 4 * kWideSub<TR> * 64 + 16;
 template <int TR> constexpr int kWideWaveBytes = TR * kWideRowBytes<TR>;
 
-template <int BITS, int SRC, int NG, int TR, int RB>
+// KEEP: masked 4-bit words stay words, see wide_keeps_words below
+template <int BITS, int SRC, int NG, int TR, int RB, bool KEEP>
 __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs a)
 {
     constexpr int RS = kWideRS, SUB = kWideSub<TR>, ROWB = kWideRowBytes<TR>, NB = (TR + 15) / 16, WPS = SRC == kWorking ? WorkCodes<BITS>::kWords : BITS, CW = RS * WPS / 4, XC = TR * SUB / 4;
@@ -481,8 +482,8 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
                         CodeWords<BITS> cw;
 #pragma unroll
                         for (int j = 0; j < WPS; ++j) cw.w[j] = run.cq[rb][(u * WPS + j) / 4][(u * WPS + j) % 4];
-                        w[rb][0] = eight_of<BITS, 0>(tab[rb], cw); w[rb][1] = eight_of<BITS, 1>(tab[rb], cw);
-                        w[rb][2] = eight_of<BITS, 2>(tab[rb], cw); w[rb][3] = eight_of<BITS, 3>(tab[rb], cw);
+                        w[rb][0] = eight_of<BITS, 0, KEEP>(tab[rb], cw); w[rb][1] = eight_of<BITS, 1, KEEP>(tab[rb], cw);
+                        w[rb][2] = eight_of<BITS, 2, KEEP>(tab[rb], cw); w[rb][3] = eight_of<BITS, 3, KEEP>(tab[rb], cw);
                     }
                 }
 #pragma unroll
@@ -602,11 +603,24 @@ FwdRoute gemv_route(const Problem &p, bool floatz)
     return FwdRoute{FWD_GEMV_WIDE, tokens, tokens >= 32 && p.O >= 2 * kGemvRows * 256 ? 2 * kGemvRows : kGemvRows};
 }
 
-template <int BITS, int SRC, int NG, int TR, int RB>
+static int wide_runs(int I) { return (I / 32 + 4 * kWideRS - 1) / (4 * kWideRS); }
+// 17 to 32 tokens, 4-bit codes as packed, groups of 64: with words that stay words the kernel is 2 to 15 % faster, but 2 to 6 % slower
+// where all its eight waves have the same number of runs (two row blocks: one or two) or four have one each and the launch more
+// than 256 workgroups.  24 tokens, us, kept / not: 4096 inputs x 4096 rows 8.3 / 7.9, 12288 x 7168 29.5 / 28.3, 2048 x 7168
+// 8.4 / 8.0; 5120 x 8192 10 % the other way.  Other groups and token counts gain everywhere (8 and 12 tokens 1 to 10 %).
+static bool wide_keeps_words(int I, int O, int rows)
+{
+    const int runs = wide_runs(I), blocks = (O + rows - 1) / rows;
+    return !((runs % kGemvMaxWaves == 0 && (rows == kGemvRows || runs <= 2 * kGemvMaxWaves)) || (runs == 4 && blocks > 256));
+}
+template <int BITS, int SRC, int NG, int TR, int RB, bool KEEP = true>
 static void launch_wide_t(const GemvArgs &a, hipStream_t st)
 {
-    auto kern = k_gemv_wide<BITS, SRC, NG, TR, RB>;
-    const int n_runs = (a.I / 32 + 4 * kWideRS - 1) / (4 * kWideRS), trips = (n_runs + kGemvMaxWaves - 1) / kGemvMaxWaves;
+    if constexpr (KEEP && BITS == 4 && SRC != kWorking && NG == 2 && TR == 32) {
+        if (!wide_keeps_words(a.I, a.O, RB * kGemvRows)) return launch_wide_t<BITS, SRC, NG, TR, RB, false>(a, st);
+    }
+    auto kern = k_gemv_wide<BITS, SRC, NG, TR, RB, KEEP>;
+    const int n_runs = wide_runs(a.I), trips = (n_runs + kGemvMaxWaves - 1) / kGemvMaxWaves;
     const int waves = (n_runs + trips - 1) / trips;
     const size_t smem = (size_t)waves * kWideWaveBytes<TR>;      // at least the 1 KB per wave and token block of the final sum
     static_assert(kWideWaveBytes<TR> >= (TR + 15) / 16 * RB * 1024 && kGemvMaxWaves * kWideWaveBytes<TR> <= 160 * 1024, "LDS of the final sum, of one CU");

@@ -798,6 +798,13 @@ WIDE_CASES = [
     ("w11", 24, 1056, 8208, 4, 32, (WIDE, 32, 32)),
     ("w12", 64, 4128, 8216, 2, 32, (WIDE, 64, 32)),
 ]
+# 4-bit codes, groups of 64, 17 to 32 tokens: the second form of k_gemv_wide (the same number of runs for eight waves, one or two row
+# blocks, a last run cut short; one run each for four waves of more than 256 workgroups)
+WIDE_CASES += [
+    ("w13", 24, 3648, 72, 4, 64, (WIDE, 32, 16)),
+    ("w14", 32, 8128, 8200, 4, 64, (WIDE, 32, 32)),
+    ("w15", 17, 1600, 4112, 4, 64, (WIDE, 32, 16)),
+]
 # k_gemm_mid: few K steps and a piece of one, ragged last token tiles of 64 and 96 and weight tiles at every width of codes, a row
 # that ends inside a 16-byte chunk of 3-bit codes, groups of 32, groups wider than a K step and not dividing it, packed zero
 # points that straddle words, two rounds of workgroups, group sizes k_gemv_wide does not take
