@@ -23,7 +23,7 @@ namespace eqat {
 namespace {
 
 constexpr int kKsBM = 128, kKsBN = 128, kKsBK = 64, kKsNT = 512;      // per K group and K tile; threads of both groups
-constexpr int kKsMaxParts = 4;                                        // the last contributor has that many in flight
+constexpr int kKsMaxParts = 4;                                        // workgroups per tile: the last one has all their parts in flight
 constexpr size_t kKsPartBytes = (size_t)kKsBM * kKsBN * sizeof(float);
 
 
@@ -328,12 +328,11 @@ __global__ __launch_bounds__(kKsNT) void k_gemm_ksplit(const KsArgs a)
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) sum[j][e] = 0.0f;
-        intx4 v[4][8];
+        intx4 v[kKsMaxParts][8];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) fetch(k, v[k]);
+        for (int k = 0; k < kKsMaxParts; ++k) fetch(k, v[k]);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) add(v[k]);
-        for (int k = 4; k < a.parts_per_tile; ++k) { fetch(k, v[0]); add(v[0]); }
+        for (int k = 0; k < kKsMaxParts; ++k) add(v[k]);
     }
     __syncthreads();
     ks_store(sum, smem_raw + wave * kStoreStageBytes, make_rsrc(a.C, a.c_bytes), m0 + wm * 64 + kg * 32, n0 + wn * 64, a.M, a.N, lane);

@@ -93,6 +93,49 @@ struct Moving {
     }
 };
 
+// Sums of the four K quarters: acc[b][i][q] is row 8 (q / 4) + 4 h + q % 4 of block b, token 32 i + r.  One 32-row block of every wave
+// at a time passes through LDS as [wave][token][32 rows] (the 16-byte chunk c of a token at c ^ (token & 7)); wave (wn, kg) then
+// adds the four K quarters, in order, for the kg-th quarter of the tokens and stores 64 bytes of a row per 8 lanes.
+template <int BM, uint32_t TOTAL>
+__device__ __forceinline__ void store_sums(const MidArgs &a, const floatx16 (&acc)[2][BM / 32], unsigned char *smem_raw, int m0, int n0, int wave, int lane)
+{
+    const int wn = wave & 1, kg = wave >> 1, r = lane & 31, h = lane >> 5;
+    constexpr uint32_t WAVE_BYTES = BM * 32 * 4;
+    static_assert(8 * WAVE_BYTES <= TOTAL, "the sums go where the tiles were");
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < BM / 32; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                floatx4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = acc[b][i][4 * q + e];
+                *reinterpret_cast<floatx4 *>(smem_raw + wave * WAVE_BYTES + (i * 32 + r) * 128 + (((2 * q + h) ^ (r & 7)) * 16)) = v;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < BM / 4 / 8; ++k) {
+            const int tok = kg * (BM / 4) + k * 8 + (lane >> 3), ch = lane & 7;
+            floatx4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int g = 0; g < kMidKG; ++g) {
+                const floatx4 v = *reinterpret_cast<const floatx4 *>(smem_raw + (g * 2 + wn) * WAVE_BYTES + tok * 128 + ((ch ^ (tok & 7)) * 16));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[e] += v[e];
+            }
+            const int o = n0 + wn * 64 + b * 32 + ch * 4;
+            if (m0 + tok < a.T && o < a.O) {           // O is a multiple of 8
+                bf16x4 y;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] = (bf16_t)sum[e];
+                *reinterpret_cast<bf16x4 *>(a.Y + (size_t)(m0 + tok) * a.O + o) = y;
+            }
+        }
+    }
+}
+
 template <int BITS, int SRC, int BM>
 __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
 {
@@ -354,45 +397,8 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
     }
     wait_all_and_barrier();
 
-    // ---- sums: acc[b][i][q] is row 8 (q / 4) + 4 h + q % 4 of block b, token 32 i + r.  One 32-row block of every wave at a
-    // time passes through LDS as [wave][token][32 rows] (the 16-byte chunk c of a token at c ^ (token & 7)); wave (wn, kg) then
-    // adds the four K quarters, in order, for the kg-th quarter of the tokens and stores 64 bytes of a row per 8 lanes.
-    constexpr uint32_t WAVE_BYTES = BM * 32 * 4;
-    static_assert(8 * WAVE_BYTES <= L::TOTAL, "the sums go where the tiles were");
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                floatx4 v;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = acc[b][i][4 * q + e];
-                *reinterpret_cast<floatx4 *>(smem_raw + wave * WAVE_BYTES + (i * 32 + r) * 128 + (((2 * q + h) ^ (r & 7)) * 16)) = v;
-            }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < BM / 4 / 8; ++k) {
-            const int tok = kg * (BM / 4) + k * 8 + (lane >> 3), ch = lane & 7;
-            floatx4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int g = 0; g < kMidKG; ++g) {
-                const floatx4 v = *reinterpret_cast<const floatx4 *>(smem_raw + (g * 2 + wn) * WAVE_BYTES + tok * 128 + ((ch ^ (tok & 7)) * 16));
-#pragma unroll
-                for (int e = 0; e < 4; ++e) sum[e] += v[e];
-            }
-            const int o = n0 + wn * 64 + b * 32 + ch * 4;
-            if (m0 + tok < a.T && o < a.O) {           // O is a multiple of 8
-                bf16x4 y;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) y[e] = (bf16_t)sum[e];
-                *reinterpret_cast<bf16x4 *>(a.Y + (size_t)(m0 + tok) * a.O + o) = y;
-            }
-        }
-    }
+    store_sums<BM, L::TOTAL>(a, acc, smem_raw, m0, n0, wave, lane);
 }
-
 
 // ---- 128 tokens per tile -----------------------------------------------------------------------------------
 // Four products per rebuilt fragment instead of two or three, so the matrix cores have less arithmetic to wait for (6.7
@@ -405,21 +411,22 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
 // Measured, us, 1000 tokens, 4096 x 4096, from the packed arrays (128 x 128 tiles behind a re-layout / here): 2 bit 57 / 40, 3 bit
 // 60 / 45, 4 bit 61 / 41; from the working layout 47 / 35, 48 / 36, 50 / 38.  What bounds it: 1940 cycles a step, of which the
 // products need 1056, the arithmetic beside them 1290; without the loads of a step 1500.
-template <int BITS, int SRC, int BM> struct TallLds {
+constexpr int kTallBM = 128;
+template <int BITS, int SRC> struct TallLds {
     static constexpr int WPS = SRC == kWorking ? WorkCodes<BITS>::kWords : BITS;
     static constexpr int NCH = WPS;
     static constexpr int ZW = SRC == kPackedZ && BITS == 3 ? 2 : 1;
     // tokens: three stages; codes: four, 1 KB per wave and its 16 rows; step sizes and zero points of four steps: two
-    static constexpr uint32_t TOK = BM * 128 * 2, CODES = 8 * 1024, SUPER = 16 * 1024;
+    static constexpr uint32_t TOK = kTallBM * 128 * 2, CODES = 8 * 1024, SUPER = 16 * 1024;
     static constexpr uint32_t CODES_AT = 3 * TOK, SUPERS = CODES_AT + 4 * CODES, TOTAL = SUPERS + 2 * SUPER;
     static_assert(TOTAL <= 160 * 1024, "LDS of one CU");
 };
 
-template <int BITS, int SRC, int BM>
+template <int BITS, int SRC>
 __global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
 {
-    typedef TallLds<BITS, SRC, BM> L;
-    constexpr int MI = BM / 32, WPS = L::WPS, NCH = L::NCH, BK = 128;
+    typedef TallLds<BITS, SRC> L;
+    constexpr int BM = kTallBM, MI = BM / 32, WPS = L::WPS, NCH = L::NCH, BK = 128;
     constexpr int N = 1 + MI;                 // loads a wave issues per K step: codes, tokens
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -712,40 +719,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
     }
     wait_and_barrier(IC<0>{});
 
-    constexpr uint32_t WAVE_BYTES = BM * 32 * 4;
-    static_assert(8 * WAVE_BYTES <= L::TOTAL, "the sums go where the tiles were");
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                floatx4 v;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = acc[b][i][4 * q + e];
-                *reinterpret_cast<floatx4 *>(smem_raw + wave * WAVE_BYTES + (i * 32 + r) * 128 + (((2 * q + h) ^ (r & 7)) * 16)) = v;
-            }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < BM / 4 / 8; ++k) {
-            const int tok = kg * (BM / 4) + k * 8 + (lane >> 3), ch = lane & 7;
-            floatx4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int g = 0; g < kMidKG; ++g) {
-                const floatx4 v = *reinterpret_cast<const floatx4 *>(smem_raw + (g * 2 + wn) * WAVE_BYTES + tok * 128 + ((ch ^ (tok & 7)) * 16));
-#pragma unroll
-                for (int e = 0; e < 4; ++e) sum[e] += v[e];
-            }
-            const int o = n0 + wn * 64 + b * 32 + ch * 4;
-            if (m0 + tok < a.T && o < a.O) {
-                bf16x4 y;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) y[e] = (bf16_t)sum[e];
-                *reinterpret_cast<bf16x4 *>(a.Y + (size_t)(m0 + tok) * a.O + o) = y;
-            }
-        }
-    }
+    store_sums<BM, L::TOTAL>(a, acc, smem_raw, m0, n0, wave, lane);
 }
 
 // Token tiles of a band, where the column is longer than 20 of them: an XCD holds 32 tiles at a time, and a panel of 64 tokens
@@ -761,9 +735,10 @@ int band_of(int tiles_m, int bm)
 
 template <int BITS, int SRC, int BM> void launch_t(MidArgs a, hipStream_t st)
 {
-    constexpr int smem = BM >= 128 ? (int)TallLds<BITS, SRC, BM>::TOTAL : (int)MidLds<BITS, SRC, BM < 128 ? BM : 64>::TOTAL;
+    int smem;
     void (*kern)(MidArgs);
-    if constexpr (BM >= 128) kern = k_gemm_mid_tall<BITS, SRC, BM>; else kern = k_gemm_mid<BITS, SRC, BM>;
+    if constexpr (BM == kTallBM) { kern = k_gemm_mid_tall<BITS, SRC>; smem = (int)TallLds<BITS, SRC>::TOTAL; }
+    else { kern = k_gemm_mid<BITS, SRC, BM>; smem = (int)MidLds<BITS, SRC, BM>::TOTAL; }
     static std::atomic<uint64_t> allowed{0};          // more dynamic LDS than the default limit: once per device
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev > 63) dev = 0;
