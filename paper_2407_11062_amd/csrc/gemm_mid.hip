@@ -804,13 +804,16 @@ FwdRoute mid_route(const Problem &p, bool from_packed)
 
 double mid_us(const Problem &p) { return launch_us(p, token_tile(p)); }
 
-// Against k_gemm_ksplit while there are at most 256 tiles of 128 x 128 (4.8 us and 0.8 to 1.1, with the fill, a pair of 64-wide K
-// tiles; 1024 inputs, 2000 tokens, 2048 rows: 12 us there, 14 here; with more than 640 inputs one round of 64- or 96-token tiles is
-// ahead whatever these estimates say, which leave out what a launch there costs beside its K tiles: from the packed arrays / from
-// a prepared layer, us, 832 x 552, 443 tokens 10.1 here, 15.2 there / 896 x 1680, 109 tokens 12.0 and 14.3; in 64 of 64 such sizes
-// between 672 and 1280 inputs by 1 to 80 %), and against the 128 x 128-tile kernel with two tiles per
-// compute unit beyond that (0.9 us per K tile; 11008 x 4096: 288 tokens, 258 tiles 61 us there and 42 here; 400 tokens 63 and 51).
-// More than two rounds here, or more than two tiles per compute unit there: the 256 x 256 tiles are the better kernel.  The GEMMs
+// Against k_gemm_ksplit while there are at most 256 tiles of 128 x 128 (with one workgroup per tile 4.8 us and 0.8 to 1.1, with
+// the fill, a pair of 64-wide K tiles; 1024 inputs, 2000 tokens, 2048 rows: 12 us there, 14 here).  With more than 640 inputs one
+// round of 64- or 96-token tiles runs here whatever these estimates say.  Where the contraction is short they leave out what a
+// launch there costs beside its K tiles: us, here / there, from the packed arrays 443 tokens, 832 x 552 10.1 / 15.2, from a prepared
+// layer 109 tokens, 896 x 1680 12.0 / 14.3, and in all of 64 sizes between 672 and 1280 inputs by 1 to 80 %.  Where it is long
+// and the tiles are few, several workgroups share a tile there, which this rule does not weigh: from the packed arrays / prepared,
+// 128 tokens, 28672 x 8192 121 here and 127 there / 113 and 106; 256 tokens, 11008 x 4096 49 and 51 / 48 and 46; 256 tokens, 8192 x 1024
+// 36 and 31 / 35 and 27.
+// Against the 128 x 128-tile kernel with two tiles per compute unit beyond 256 tiles (0.9 us per K tile; 11008 x 4096: 288 tokens,
+// 258 tiles 61 us there and 42 here; 400 tokens 63 and 51).  More than two rounds here, or more than two tiles per compute unit there: the 256 x 256 tiles are the better kernel.  The GEMMs
 // alone are compared: a forward from the packed arrays saves the re-layout as well and would gain a little earlier, but every
 // forward entry point shares the rule, so that their results stay bitwise equal.
 bool mid_applies(const Problem &p)

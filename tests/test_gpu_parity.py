@@ -206,11 +206,11 @@ def test_groups_wider_than_a_tile_sum_their_partials(I, g):
 
 # More output tiles than the chip holds workgroups: every workgroup of the fwd / dX kernel then walks several tiles with
 # its K loop running through the tile boundaries.  Ragged in every dimension, K-tile counts 5 (odd: one padding K tile
-# per output tile) and 6; the third case walks with the small (128 x 128) tile (144 big tiles = 576 small ones).
+# per output tile) and 6; the third case is one that does not walk (144 big tiles would be 576 small ones, more than are resident).
 WALK_CASES = [
     ("walk_fwd", 4400, 320, 4104, 2, 64),      # fwd: 18 x 17 = 306 tiles of 256 x 256
     ("walk_dx", 4400, 4128, 328, 3, 32),       # dX: 18 x 17 tiles, K = O = 328
-    ("walk_small", 4096, 256, 2304, 4, 128),   # fwd: 32 x 18 = 576 tiles of 128 x 128
+    ("walk_small", 4096, 256, 2304, 4, 128),   # fwd: 144 tiles of 256 x 256 on 256 workgroups; dX: 64 tiles of 128 x 128, two workgroups each
     ("walk_k64", 4400, 64, 4104, 2, 64),       # fwd: one K tile per output tile (the start-up loads already reach into the next)
     ("walk_dx_k128", 4400, 4128, 128, 2, 32),  # dX: two K tiles per output tile
 ]
@@ -228,16 +228,16 @@ SPLIT_CASES = [
     ("cut_fwd", 4400, 512, 4104, 2, 64),       # fwd: 18 x 17 = 306 tiles of 256 x 256, 4 K-tile pairs each
     ("cut_dx", 4400, 4128, 520, 3, 32),        # dX: 306 tiles, K = O = 520: 5 pairs, the last one half past the end
     ("cut_dw", 600, 4416, 4104, 2, 64),        # dW: 18 x 17 tiles, K = T = 600
-    ("cut_small", 4096, 512, 2304, 4, 128),    # fwd: 576 tiles of 128 x 128 on 512 resident workgroups
+    ("cut_small", 4096, 512, 2304, 4, 128),    # fwd: 144 tiles of 256 x 256, none of them cut; dX: 128 of 128 x 128, two K groups in a workgroup
     ("cut_dw_perchan", 520, 4352, 4096, 2, -1),  # dW, 17 x 16 tiles, one group per row (partials + reduce kernel)
     # few tiles beyond the first round and a long K: a whole tile per workgroup, then every remaining tile split among
-    # four (small tiles: eight) workgroups, whose parts the first of them adds up in their order
+    # four (few of them: eight) workgroups, whose parts the last of them to arrive adds up in their order
     ("split_fwd", 4400, 2048, 4104, 2, 64),    # fwd: 306 tiles, 16 K-tile pairs
     ("split_dx", 4400, 4128, 2056, 3, 32),     # dX: 306 tiles, K = O = 2056: 17 pairs (uneven pieces, ragged last K tile)
-    ("split_small", 4096, 2048, 2304, 4, 128), # fwd: 576 tiles of 128 x 128, 16 pairs, eight contributors
+    ("split_small", 4096, 2048, 2304, 4, 128), # fwd: 144 tiles of 256 x 256; dX: 512 of 128 x 128, one workgroup each (split ones: test_gpu_ksplit)
     ("split_3r", 4400, 2048, 8440, 2, 64),     # fwd: 18 x 33 = 594 tiles (not a multiple of 8): two whole rounds, then 10 or 11 tiles per XCD split two ways
     ("split_dw", 2100, 4352, 4104, 3, 64),     # dW: 17 x 17 = 289 tiles, K = T = 2100: 17 pairs, six contributors per split tile
-    ("split_dw_small", 2100, 2304, 4096, 4, 128), # dW: 18 x 32 = 576 tiles of 128 x 128 on 512 resident workgroups, eight contributors
+    ("split_dw_small", 2100, 2304, 4096, 4, 128), # dW: 9 x 16 = 144 tiles of 256 x 256, none of them cut (split ones of 128 x 128: test_gpu_dw_tiles)
     ("split_dw_perchan", 2100, 4352, 4096, 2, -1),  # dW: 17 x 16 tiles, one group per row (per-block partials + reduce kernel), eight contributors
 ]
 

@@ -3,10 +3,11 @@
 The kernels compute an output tile either whole, in one workgroup, or in pieces along K: as the head and tail of
 "runs" (two contributors at most), or split among a group of workgroups.  The function that tells a workgroup its
 items is compiled for host and device alike; `eqat_plan_item` calls the host side of it with the launch geometry the
-library would use.  Here every workgroup's items are listed and it is checked that every K-tile pair of every tile is
-computed exactly once, that what a piece says about its tile (contributors, first contributor, counter) is what the
-pieces of that tile really are, and that no two tiles cut in one launch share a counter.  No GPU is needed (without one
-the library plans for the 256 compute units of an MI355X).
+library would use (the launches of the tile kernels; those of k_gemm_ksplit: test_shared_tiles_plan).  Here every
+workgroup's items are listed and it is checked that every K-tile pair of every tile is computed exactly once, that what a
+piece says about its tile (contributors, first contributor, counter) is what the pieces of that tile really are, and that
+no two tiles cut in one launch share a counter.  No GPU is needed (without one the library plans for the 256 compute units
+of an MI355X).
 """
 import ctypes
 
