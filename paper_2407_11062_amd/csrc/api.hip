@@ -91,7 +91,7 @@ eqat::FwdRoute fwd_route(const Problem &p, bool from_packed, bool floatz)
     return eqat::FwdRoute{eqat::FWD_TILES, 0, 0};
 }
 
-struct WsLayout { size_t codes, clamp, sz, part, dwhat, sk_ctr, sk_ctr_bytes, sk_part, sk_part_bytes, total, needed; };
+struct WsLayout { size_t codes, clamp, sz, part, dwhat, what, what_bytes, sk_ctr, sk_ctr_bytes, sk_part, sk_part_bytes, total, needed; };
 
 inline bool op_is_bwd(int op) { return op == EQAT_OP_FQ_BWD || op == EQAT_OP_Q_BWD || op == EQAT_OP_QP_BWD; }
 inline bool op_is_prepared(int op) { return op == EQAT_OP_QP_FWD || op == EQAT_OP_QP_BWD; }
@@ -143,9 +143,11 @@ WsLayout ws_layout(const Problem &p, int op)
     } else {
         if (!fq) l.sz = take(sz_b);
         if (bwd) l.dwhat = take(dwhat_b);
+        // What beside dWhat, for a backward of few tiles; in a workspace that was sized for another token count it may be missing (one launch more then)
+        l.needed = off;
+        if (bwd) { l.what_bytes = eqat::f32_what_bytes(p); l.what = take(l.what_bytes); }
     }
     l.total = off;
-    if (!p.act_bf16) l.needed = l.total;
     return l;
 }
 
@@ -164,6 +166,11 @@ inline eqat::SkScratch sk_of(const WsLayout &l, char *w8, size_t ws_bytes, uint3
     // no more than the size that eqat_workspace_bytes gives: a larger workspace changes no plan
     const size_t bytes = ws_bytes > l.sk_part ? std::min(ws_bytes - l.sk_part, l.sk_part_bytes) : 0;
     return eqat::SkScratch{bytes != 0 ? reinterpret_cast<float *>(w8 + l.sk_part) : nullptr, bytes, counters};
+}
+
+inline float *what_of(const WsLayout &l, char *w8, size_t ws_bytes)
+{
+    return l.what_bytes != 0 && ws_bytes >= l.what + l.what_bytes ? reinterpret_cast<float *>(w8 + l.what) : nullptr;
 }
 
 inline eqat_status launch_status() { return hipGetLastError() == hipSuccess ? EQAT_OK : EQAT_ERR_DEVICE; }
@@ -387,15 +394,14 @@ static eqat_status fq_bwd_any(const eqat_desc *d, const void *X, const void *W, 
                                  (float *)(w8 + l.part), sk, st);
     } else {
         ProfScope ps(eqat::PK_F32, st);
-        if (dX != nullptr && p.T > 0) eqat::launch_f32_dx(p, false, dY, W, s, z, (float *)(w8 + l.dwhat), dX, st);
-        if (want_w) eqat::launch_f32_dw(p, true, X, dY, W, s, z, (float *)(w8 + l.dwhat), dW, ds, dz, st);
+        eqat::launch_f32_bwd(p, true, X, dY, W, s, z, (float *)(w8 + l.dwhat), what_of(l, w8, ws_bytes), dX, dW, ds, dz, st);
     }
     return launch_status();
 }
 
 // What the E2E-QP GEMMs read: codes (working layout; fp32 activations: the dense stream), the (s, z) pairs, the
 // scratch of launches that cut tiles, the array of per-32-column partials of dW, the fp32 dWhat of the fp32 path.
-struct QOperands { const void *codes; const void *sz; eqat::SkScratch sk; float *part; float *dwhat; };
+struct QOperands { const void *codes; const void *sz; eqat::SkScratch sk; float *part; float *dwhat, *what; };
 
 static eqat_status qlinear_fwd_run(const Problem &p, const void *X, const float *s, const QOperands &q, void *Y, hipStream_t st)
 {
@@ -414,8 +420,7 @@ static eqat_status qlinear_bwd_run(const Problem &p, const void *X, const float 
         if (want_g) eqat::launch_mfma_dw(p, false, X, dY, nullptr, q.codes, nullptr, q.sz, s, nullptr, ds, dz, q.part, q.sk, st);
     } else {
         ProfScope ps(eqat::PK_F32, st);
-        if (dX != nullptr && p.T > 0) eqat::launch_f32_dx(p, true, dY, q.codes, s, q.sz, q.dwhat, dX, st);
-        if (want_g) eqat::launch_f32_dw(p, false, X, dY, q.codes, s, q.sz, q.dwhat, nullptr, ds, dz, st);
+        eqat::launch_f32_bwd(p, false, X, dY, q.codes, s, q.sz, q.dwhat, q.what, dX, nullptr, ds, dz, st);
     }
     return launch_status();
 }
@@ -465,7 +470,7 @@ static eqat_status qlinear_fwd_any(const eqat_desc *d, const void *X, const uint
     }
     const eqat::SkScratch sk = sk_of(l, w8, ws_bytes);
     qlinear_prepare_into(p, Wpacked, s, zpacked, zfloat, w8 + l.codes, w8 + l.sz, sk.counters, l.sk_ctr_bytes, st);
-    const QOperands q{p.act_bf16 ? (const void *)(w8 + l.codes) : (const void *)Wpacked, w8 + l.sz, sk, nullptr, nullptr};
+    const QOperands q{p.act_bf16 ? (const void *)(w8 + l.codes) : (const void *)Wpacked, w8 + l.sz, sk, nullptr, nullptr, nullptr};
     return qlinear_fwd_run(p, X, s, q, Y, st);
 }
 
@@ -489,7 +494,7 @@ static eqat_status qlinear_bwd_any(const eqat_desc *d, const void *X, const uint
     const eqat::SkScratch sk = sk_of(l, w8, ws_bytes);
     if (!kept) qlinear_prepare_into(p, Wpacked, s, zpacked, zfloat, w8 + l.codes, w8 + l.sz, sk.counters, l.sk_ctr_bytes, st);
     const QOperands q{p.act_bf16 ? (const void *)(w8 + l.codes) : (const void *)Wpacked, w8 + l.sz, sk,
-                      (float *)(w8 + l.part), (float *)(w8 + l.dwhat)};
+                      (float *)(w8 + l.part), (float *)(w8 + l.dwhat), what_of(l, w8, ws_bytes)};
     return qlinear_bwd_run(p, X, s, q, dY, dX, ds, dz, st);
 }
 
@@ -540,6 +545,7 @@ static eqat_status prepared_operands(const Problem &p, const void *prepared, con
     q->sk = sk_of(l, w8, ws_bytes, pl.sk_ctr_bytes != 0 ? (uint32_t *)(p8 + pl.sk_ctr) : nullptr);
     q->part = (float *)(w8 + l.part);
     q->dwhat = (float *)(w8 + l.dwhat);
+    q->what = what_of(l, w8, ws_bytes);
     if (make_pairs)
         qlinear_prepare_into(p, nullptr, s, nullptr, z != nullptr ? z : (const float *)(p8 + pl.zb), nullptr, w8 + l.sz, nullptr, 0, st);
     return EQAT_OK;

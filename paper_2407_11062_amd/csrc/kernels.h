@@ -128,11 +128,11 @@ void launch_adamw(const AdamGroup *groups, float beta1, float beta2, float eps, 
 // ---- gemm_f32.hip (fp32 activations; binary32 products and sums, exact division everywhere) --------
 void launch_f32_fwd(const Problem &p, bool packed, const void *X, const void *W_or_codes, const float *s, const void *z_or_sz,
                     void *Y, hipStream_t st);
-// `what` is scratch for O*I floats (dWhat's)
-void launch_f32_dx(const Problem &p, bool packed, const void *dY, const void *W_or_codes, const float *s, const void *z_or_sz,
-                   float *what, void *dX, hipStream_t st);
-// dWhat[O,I] fp32 = dY^T X into `dwhat` (scratch O*I floats), then the per-group epilogue.
-void launch_f32_dw(const Problem &p, bool block_ap, const void *X, const void *dY, const void *W_or_codes, const float *s,
-                   const void *z_or_sz, float *dwhat, void *dW, float *ds, float *dz, hipStream_t st);
+// What a backward asks for beside the O*I floats of `dwhat` to run in two launches instead of four (0: it does not).
+size_t f32_what_bytes(const Problem &p);
+// dX (may be NULL) = dY What; dWhat[O,I] = dY^T X into `dwhat` (scratch of O*I floats), then the per-group epilogue into dW, ds, dz (each may be
+// NULL).  `what`: f32_what_bytes() of scratch, or NULL.
+void launch_f32_bwd(const Problem &p, bool block_ap, const void *X, const void *dY, const void *W_or_codes, const float *s,
+                    const void *z_or_sz, float *dwhat, float *what, void *dX, void *dW, float *ds, float *dz, hipStream_t st);
 
 }  // namespace eqat

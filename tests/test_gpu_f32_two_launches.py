@@ -1,0 +1,46 @@
+"""The fp32 backward in two launches (few tiles, What beside dWhat in the workspace) against the same call in a workspace without room for What,
+which takes the four launches in a row: the same sums in the same order, bitwise."""
+import pytest
+import torch
+
+import oracle
+import paper_2407_11062_amd as eq
+from test_gpu_parity import dev, make_case, npf, relerr
+
+pytestmark = pytest.mark.gpu
+
+# remainders of the 32 x 32 tiles, the smallest out-feature count that reads What from memory, 240 and 256 tiles of 64 x 64 (the last one: four launches)
+SHAPES = [(1, 32, 33, 32), (31, 96, 40, 96), (65, 160, 72, 32), (257, 512, 520, 128), (960, 1024, 64, -1), (1024, 1024, 64, 256)]
+
+
+@pytest.mark.parametrize("T,I,O,g", SHAPES)
+@pytest.mark.parametrize("bits,wdt", [(2, torch.float32), (3, torch.bfloat16), (4, torch.float32)])
+def test_two_launches_equal_four(T, I, O, g, bits, wdt):
+    X, W, s, z, dY = make_case(("f32two", T, I, O, bits), T, I, O, bits, g, torch.float32, wdt)
+    s[::5, 0] = 2.0 ** -127                           # a denormal step size: its reciprocal is no use, the quotients are divided out
+    Xd, Wd, sd, zd, dYd = dev(X), dev(W), dev(s), dev(z), dev(dY)
+    full = eq.workspace(eq.make_desc(T, I, O, bits, g, eq.F32, eq._dt(Wd)), eq.OP_FQ_BWD, Xd.device)
+    room = O * I * 4
+    assert (full.numel() > room + 256) == (T != 1024)
+    small = full[:(room + 255) // 256 * 256].clone()
+    full.fill_(0xFF)
+    small.fill_(0xFF)
+    got = eq.eqat_fq_linear_bwd(Xd, Wd, sd, zd, dYd, bits, g, ws=full)
+    want = eq.eqat_fq_linear_bwd(Xd, Wd, sd, zd, dYd, bits, g, ws=small)
+    for k in ("dX", "dW", "ds", "dz"):
+        assert torch.equal(got[k], want[k]), k
+    s[::5, 0] = s[::5, -1] if s.shape[1] > 1 else 0.01
+    sd = dev(s)
+    got = eq.eqat_fq_linear_bwd(Xd, Wd, sd, zd, dYd, bits, g, ws=full)
+    if T * I * O < 1 << 25:
+        ref = oracle.fq_linear_bwd(npf(X), npf(W), s.numpy(), z.numpy(), npf(dY), bits, g)
+        for k in ("dX", "ds", "dz"):
+            assert relerr(got[k], ref[k]) <= 1e-5, k
+        assert relerr(got["dW"], ref["dW"]) <= (1e-5 if wdt == torch.float32 else 2e-2)
+        assert relerr(eq.eqat_fq_linear_fwd(Xd, Wd, sd, zd, bits, g), oracle.fq_linear_fwd(npf(X), npf(W), s.numpy(), z.numpy(), bits, g)) <= 1e-5
+    Wp, zp = eq.eqat_pack(Wd, sd, zd, bits, g)
+    got = eq.eqat_qlinear_bwd(Xd, Wp, sd, zp, dYd, I, bits, g)
+    ws = eq.workspace(eq.make_desc(T, I, O, bits, g, eq.F32, eq.BF16), eq.OP_Q_BWD, Xd.device)
+    less = ws[: ws.numel() - room].clone() if T != 1024 else ws
+    want = eq.eqat_qlinear_bwd(Xd, Wp, sd, zp, dYd, I, bits, g, ws=less)
+    assert torch.equal(got["dX"], want["dX"]) and torch.equal(got["ds"], want["ds"])
