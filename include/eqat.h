@@ -385,6 +385,9 @@ eqat_status eqat_plan_scratch(const eqat_desc *d, int op, int gemm, int cus, siz
  * assert that its sizes reach the kernel it is about.
  */
 eqat_status eqat_fwd_route(const eqat_desc *d, int source, int32_t *route);
+/* Test aid (host only): tokens = token tile of the kernel for few output tiles where dX takes it (a call with the workspace of
+ * eqat_workspace_bytes), 0 where another kernel computes it. */
+eqat_status eqat_dx_route(const eqat_desc *d, int32_t *tokens);
 
 /*
  * Optional per-kernel timing (measurement aid, not part of the paper's method).

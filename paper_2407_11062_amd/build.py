@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.environ.get("EQAT_OBJ_DIR", os.path.join(HERE, "_build"))
 LIB = os.environ.get("EQAT_LIB_OUT", os.path.join(HERE, "libeqat.so"))
-SOURCES = ["api.hip", "quant.hip", "gemm_f32.hip", "gemm_ksplit.hip", "gemm_mfma.hip", "gemm_mid.hip", "gemv.hip", "train_step.hip"]
+SOURCES = ["api.hip", "quant.hip", "gemm_f32.hip", "gemm_ksplit.hip", "gemm_mfma.hip", "gemm_mid.hip", "gemm_mid_dx.hip", "gemv.hip", "train_step.hip"]
 # measurement aids of bench.py (a bare MFMA loop, a plain copy): a library of their own, not part of the product
 PEAKS_SOURCE = "bench_peaks.hip"
 PEAKS_LIB = os.environ.get("EQAT_PEAKS_LIB_OUT", os.path.join(HERE, "libeqat_peaks.so"))

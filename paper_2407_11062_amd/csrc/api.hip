@@ -664,6 +664,17 @@ eqat_status eqat_fwd_route(const eqat_desc *d, int source, int32_t *route)
     return EQAT_OK;
 }
 
+eqat_status eqat_dx_route(const eqat_desc *d, int32_t *tokens)
+{
+    Problem p;
+    if (eqat_status e = check_desc(d, true, &p)) return e;
+    if (tokens == nullptr) return EQAT_ERR_NULL;
+    if (!p.act_bf16) return EQAT_ERR_DTYPE;
+    if (p.T < 1) return EQAT_ERR_SHAPE;
+    *tokens = eqat::mid_dx_tokens_for_test(p);
+    return EQAT_OK;
+}
+
 // Test aid: what a forward call that keeps its state, or eqat_qlinear_prepare, left behind, in plain arrays.
 eqat_status eqat_unpack_state(const eqat_desc *d, int kind, const void *state, int32_t *codes, uint8_t *clamped, float *zbar,
                               void *stream)

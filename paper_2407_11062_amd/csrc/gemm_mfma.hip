@@ -1461,6 +1461,35 @@ DwLaunchPlan plan_dw_of(const Problem &p, int cus, const SkScratch &sk, bool *sm
                   : plan_dw<bf16_t, true, DwTileBig>((int)p.I, (int)p.O, (int)p.T, cus, sk);
 }
 
+// Token tiles of k_gemm_mid_dx where dX takes that kernel, else 0: up to two rounds of its workgroups, where it is estimated to be faster than
+// k_gemm_ksplit or the tiles of k_gemm_q.  Their estimates here are fits to dX alone, operands cold (196 random sizes, 50 to 2200
+// tokens, 768 to 12000 in-features, 768 to 16000 out-features: the rule takes no kernel more than 2 % slower than the one it leaves
+// and is within 1 % of the best choice at each size; 8 % faster in the mean, 25 to 50 % where one or two rounds are well filled.  us, that
+// kernel / here: 515 tokens, 3 bit 4096 -> 4096 37.7 / 31.8, 11008 -> 4096 99 / 74; 1000 tokens, 4 bit 11008 -> 4096 128 / 107, 4096 -> 4096 level).
+int mid_dx_tokens(const Problem &p, int cus, const SkScratch &sk)
+{
+    int tokens = 0;
+    const double here = mid_dx_us(p, &tokens);
+    if (here >= 1e30) return 0;
+    const int64_t big = ((p.T + 255) / 256) * ((p.I + 255) / 256), small = ((p.T + 127) / 128) * ((p.I + 127) / 128);
+    const double k_tiles = (double)((p.O + 63) / 64);
+    double there;
+    if (const int parts = ksplit_parts(p, true, sk)) {
+        const double pairs = (double)(((p.O + 127) / 128 + parts - 1) / parts), groups = (double)(small * parts);
+        there = (parts == 1 ? 5.8 : 6.5 + 0.03 * groups) + pairs * (0.8 + 0.5 * groups / 256.0 * std::min(1.0, pairs / 32.0));
+    } else {
+        switch (q_tile(p, true, cus, sk)) {
+        case TileChoice::Small: there = 4.0 + (p.O % 128 == 0 ? 0.95 : 1.4) * k_tiles; break;       // a ragged contraction runs in the slower instantiation
+        case TileChoice::Big: there = 5.0 + 1.4 * k_tiles * (double)((big + 255) / 256); break;
+        default: {
+            const int64_t c = resident_workgroups(cus, 1) / 8 / ((big + 7) / 8);
+            there = 5.0 + 1.55 * (double)(((int64_t)k_tiles + c - 1) / c) + 0.085 * (double)(big * c);
+        }
+        }
+    }
+    return here < there ? tokens : 0;
+}
+
 // Bytes from sk.partials on within which a launch of the forward (gemm = 0), the dX (1) or the dW (2) GEMM writes its parts.
 size_t parts_written(const Problem &p, int gemm, int cus, const SkScratch &sk)
 {
@@ -1470,6 +1499,7 @@ size_t parts_written(const Problem &p, int gemm, int cus, const SkScratch &sk)
         const DwLaunchPlan d = plan_dw_of(p, cus, sk, &small);
         return d.cut ? parts_bytes(d.grid, small ? kSmall : kBig, d.sk.split != 0) : 0;
     }
+    if (gemm == 1 && mid_dx_tokens(p, cus, sk)) return 0;
     if (const int parts = ksplit_parts(p, gemm == 1, sk)) return ksplit_bytes(p, gemm == 1, parts);
     TileChoice choice;
     const QLaunchPlan q = plan_q_of(p, gemm == 1, cus, sk, &choice);
@@ -1505,6 +1535,8 @@ void sk_scratch_bytes(const Problem &p, bool fwd, bool bwd, size_t *partial_byte
 }
 
 size_t parts_written_for_test(const Problem &p, int gemm, int cus, const SkScratch &sk) { return parts_written(p, gemm, cus, sk); }
+
+int mid_dx_tokens_for_test(const Problem &p) { return mid_dx_tokens(p, current_cus(), kAnyRoom); }
 
 // Test aid: work item number j of workgroup `block` in the launch that the forward (gemm = 0), the dX (gemm = 1) or the dW
 // (gemm = 2; tile rows: in-features, tile columns: out-features, K: tokens) GEMM of this problem makes, as the kernel
@@ -1563,6 +1595,7 @@ void launch_mfma_dx(const Problem &p, const void *dY, const void *codes, const v
                     hipStream_t st)
 {
     if (p.T == 0) return;
+    if (const int tokens = mid_dx_tokens(p, current_cus(), sk)) { launch_mid_dx(p, tokens, dY, codes, sz, dX, st); return; }
     if (const int parts = ksplit_parts(p, true, sk)) { launch_ksplit(p, true, dY, codes, sz, dX, sk, parts, st); return; }
     GemmQArgs a{};
     a.A = (const bf16_t *)dY; a.codes = (const uint32_t *)codes; a.sz = (const floatx2 *)sz; a.C = (bf16_t *)dX;

@@ -54,6 +54,7 @@ struct SkScratch { float *partials; size_t bytes; uint32_t *counters; };
 int plan_item_for_test(const Problem &p, int gemm, int block, int j, int32_t item[12]);      // test aid, see gemm_mfma.hip
 // Test aid: bytes from sk.partials on within which the launch of a GEMM (0 fwd, 1 dX, 2 dW) on a device of `cus` compute units writes.
 size_t parts_written_for_test(const Problem &p, int gemm, int cus, const SkScratch &sk);
+int mid_dx_tokens_for_test(const Problem &p);      // test aid: token tile of k_gemm_mid_dx where dX takes it (with all the scratch a plan may ask for), else 0
 // Bytes of that scratch for the launches of a forward that takes the tile kernels (fwd), a backward (bwd), or both.  *partial_bytes: what their plans write;
 // *needed_bytes: what a call cannot do without: launches that share tiles only to fill the chip run unshared in less.
 void sk_scratch_bytes(const Problem &p, bool fwd, bool bwd, size_t *partial_bytes, size_t *needed_bytes, size_t *counter_bytes);
@@ -109,6 +110,10 @@ double mid_us(const Problem &p);                  // what it takes, as the rules
 void launch_mid(const Problem &p, const void *X, const void *Wpacked, const float *s, const void *zpacked, const float *zfloat,
                 void *Y, hipStream_t st);
 void launch_mid_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, hipStream_t st);
+
+// ---- gemm_mid_dx.hip (dX for few output tiles, on codes in the working layout) -------------------------
+double mid_dx_us(const Problem &p, int *tokens);      // what it takes, as the rule of dispatch estimates it, and with which token tiles; 1e30: too many tiles
+void launch_mid_dx(const Problem &p, int tokens, const void *dY, const void *codes, const void *sz, void *dX, hipStream_t st);
 
 // ---- train_step.hip (Block-AP step glue: reconstruction loss, AdamW over {W, s, z}) --------------------
 size_t recon_loss_ws_bytes();
