@@ -94,12 +94,23 @@ def frac_measured(tflops, peaks):
     return round(tflops / m, 4) if m else None
 
 
+def launch_flop(prof, k, flop_per_launch):
+    """Mean flop of a launch of GEMM class k (flop_per_launch: of one GEMM, mean over the linears); gemm_bwd is dX and dW in one launch.  None where some linears
+    run their backward in one launch and some in two: the mean over all linears is that of neither."""
+    if k == "gemm_fwd":
+        return flop_per_launch
+    if "gemm_bwd" in prof and ("gemm_dx" in prof or "gemm_dw" in prof):
+        return None
+    return 2 * flop_per_launch if k == "gemm_bwd" else flop_per_launch
+
+
 def kernel_table(prof, flop_per_launch, peaks):
     out = {}
     for k, (ms, n) in prof.items():
         out[k] = {"launches": n, "avg_ms": round(ms / n, 4)}
-        if k.startswith("gemm_"):
-            tf = flop_per_launch / (ms / n * 1e-3) / 1e12
+        flop = launch_flop(prof, k, flop_per_launch) if k.startswith("gemm_") else None
+        if flop is not None:
+            tf = flop / (ms / n * 1e-3) / 1e12
             out[k].update({"tflops": round(tf, 2), "frac": round(tf / PEAK_BF16_TFLOPS, 4),
                            "frac_of_measured_peak": frac_measured(tf, peaks)})
     return out
@@ -215,11 +226,12 @@ def main():
     ms_step = t["mean_ms"]
     tflops = flops_step / (ms_step * 1e-3) / 1e12
 
-    # dominant kernel of the step: all three GEMM kernels do 2*T*I*O flop per launch
-    gemms = {k: v for k, v in prof.items() if k.startswith("gemm_")}
+    # dominant kernel of the step: the GEMM kernels do 2*T*I*O flop per launch, dX and dW in one launch twice that
+    flop_per_launch = 2.0 * T * sum_io / len(layers)          # mean over the seven shapes
+    gemms = {k: v for k, v in prof.items() if k.startswith("gemm_") and launch_flop(prof, k, flop_per_launch) is not None}
     dom = max(gemms, key=lambda k: gemms[k][0])
     dom_ms, dom_n = gemms[dom]
-    flop_per_launch = 2.0 * T * sum_io / len(layers)          # mean over the seven shapes
+    flop_per_launch = launch_flop(prof, dom, flop_per_launch)
     dom_tflops = flop_per_launch / (dom_ms / dom_n * 1e-3) / 1e12
     traffic = None
     tpath = os.path.join(ROOT, "profiles", "hbm_traffic.json")
@@ -232,7 +244,7 @@ def main():
                 "traffic": traffic, "traffic_source": "profiles/hbm_traffic.json (rocprofv3 --pmc runs of this bench, committed)",
                 "avg_launch_ms": round(dom_ms / dom_n, 4), "launches": dom_n,
                 "flop_per_launch": flop_per_launch}
-    kernels = kernel_table(prof, flop_per_launch, peaks)
+    kernels = kernel_table(prof, 2.0 * T * sum_io / len(layers), peaks)
     if "quantize" in prof:
         # W and (s, z) in; codes, clamp bit-plane and (s, zbar) pairs out
         # (one launch per step over all linears of the block)

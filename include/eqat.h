@@ -123,7 +123,8 @@ eqat_status eqat_fq_linear_fwd(const eqat_desc *d, const void *X, const void *W,
  * Eq.(4) is printed with -1; -s is the derivative of Eq.(2) for a zero point in
  * integer units, and the printed form equals dz / s.  The appendix writes the
  * upper bound as 2^(N-1); Eq.(1)'s 2^N - 1 is used.
- * Any of dX, dW, ds, dz may be NULL and is then skipped.
+ * Any of dX, dW, ds, dz may be NULL and is then skipped.  dW, ds and dz do not depend on which outputs are asked for; dX asked for
+ * together with any of them may come from a common launch that sums in another order than the launch for dX alone.
  */
 eqat_status eqat_fq_linear_bwd(const eqat_desc *d, const void *X, const void *W, const float *s,
                                const float *z, const void *dY, void *dX, void *dW, float *ds, float *dz,
@@ -385,9 +386,10 @@ eqat_status eqat_plan_scratch(const eqat_desc *d, int op, int gemm, int cus, siz
  * assert that its sizes reach the kernel it is about.
  */
 eqat_status eqat_fwd_route(const eqat_desc *d, int source, int32_t *route);
-/* Test aid (host only): tokens = token tile of the kernel for few output tiles where dX takes it (a call with the workspace of
- * eqat_workspace_bytes), 0 where another kernel computes it. */
-eqat_status eqat_dx_route(const eqat_desc *d, int32_t *tokens);
+/* Test aid (host only): what computes dX in a call with the workspace of eqat_workspace_bytes.  route[2] = { asked for alone: the token tile of the
+ * kernel for few output tiles, 0: another kernel;  asked for with dW, ds or dz (block_ap: eqat_fq_linear_bwd, else the E2E-QP calls): -1 a launch of
+ * its own, as alone; else a launch that it shares with dW: 0, 1 256 x 256 tiles (1: contraction of no whole K-tile pairs), else such a token tile }. */
+eqat_status eqat_dx_route(const eqat_desc *d, int block_ap, int32_t *route);
 
 /*
  * Optional per-kernel timing (measurement aid, not part of the paper's method).

@@ -100,7 +100,7 @@ def lib():
         L.eqat_shared_item.argtypes = [dp, ctypes.c_int, ctypes.c_int, vp, vp]
         L.eqat_plan_scratch.argtypes = [dp, ctypes.c_int, ctypes.c_int, ctypes.c_int, sz, ctypes.POINTER(sz), ctypes.POINTER(sz)]
         L.eqat_fwd_route.argtypes = [dp, ctypes.c_int, vp]
-        L.eqat_dx_route.argtypes = [dp, vp]
+        L.eqat_dx_route.argtypes = [dp, ctypes.c_int, vp]
         L.eqat_qlinear_bwd_prepared_kept.argtypes = L.eqat_qlinear_bwd_prepared.argtypes
         L.eqat_unpack_state.argtypes = [dp, ctypes.c_int, vp, vp, vp, vp, vp]
         L.eqat_recon_loss_workspace_bytes.restype, L.eqat_recon_loss_workspace_bytes.argtypes = sz, []

@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.environ.get("EQAT_OBJ_DIR", os.path.join(HERE, "_build"))
 LIB = os.environ.get("EQAT_LIB_OUT", os.path.join(HERE, "libeqat.so"))
-SOURCES = ["api.hip", "quant.hip", "gemm_f32.hip", "gemm_ksplit.hip", "gemm_mfma.hip", "gemm_mid.hip", "gemm_mid_dx.hip", "gemv.hip", "train_step.hip"]
+SOURCES = ["gemm_mfma.hip", "gemm_bwd_ap_bf16.hip", "gemm_bwd_ap_f32.hip", "gemm_bwd_e2e.hip", "gemm_mid.hip", "gemv.hip", "api.hip", "quant.hip", "gemm_f32.hip", "gemm_ksplit.hip", "gemm_mid_dx.hip", "train_step.hip"]
 # measurement aids of bench.py (a bare MFMA loop, a plain copy): a library of their own, not part of the product
 PEAKS_SOURCE = "bench_peaks.hip"
 PEAKS_LIB = os.environ.get("EQAT_PEAKS_LIB_OUT", os.path.join(HERE, "libeqat_peaks.so"))
@@ -32,7 +32,7 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(_compile, SOURCES + [PEAKS_SOURCE]))
     for out, parts in ((LIB, objs[:-1]), (PEAKS_LIB, objs[-1:])):
         r = subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *os.environ.get("EQAT_EXTRA_LINK_FLAGS", "").split(),

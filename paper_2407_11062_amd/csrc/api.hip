@@ -206,7 +206,7 @@ int eqat_profile_kernels(void) { return eqat::PK_COUNT; }
 const char *eqat_profile_kernel_name(int k)
 {
     static const char *names[] = {"init_minmax", "quantize", "e2e_prepare", "gemm_fwd", "gemm_dx",
-                                                "gemm_dw", "reduce_partials", "f32_path", "gemv", "recon_loss", "adamw_update"};
+                                                "gemm_dw", "gemm_bwd", "reduce_partials", "f32_path", "gemv", "recon_loss", "adamw_update"};
     static_assert(sizeof(names) / sizeof(names[0]) == eqat::PK_COUNT, "one name per kernel class");
     return (k >= 0 && k < eqat::PK_COUNT) ? names[k] : "?";
 }
@@ -388,10 +388,7 @@ static eqat_status fq_bwd_any(const eqat_desc *d, const void *X, const void *W, 
     if (p.act_bf16) {
         const eqat::SkScratch sk = sk_of(l, w8, ws_bytes);
         if (!kept) { ProfScope ps(eqat::PK_QUANTIZE, st); eqat::launch_quantize(p, W, s, z, w8 + l.codes, w8 + l.clamp, w8 + l.sz, nullptr, false, sk.counters, (uint32_t)(l.sk_ctr_bytes / 4), st); }
-        if (dX != nullptr) { ProfScope ps(eqat::PK_GEMM_DX, st); eqat::launch_mfma_dx(p, dY, w8 + l.codes, w8 + l.sz, dX, sk, st); }
-        if (want_w)
-            eqat::launch_mfma_dw(p, true, X, dY, W, w8 + l.codes, w8 + l.clamp, w8 + l.sz, s, dW, ds, dz,
-                                 (float *)(w8 + l.part), sk, st);
+        eqat::launch_mfma_bwd(p, true, X, dY, W, w8 + l.codes, w8 + l.clamp, w8 + l.sz, s, dX, dW, ds, dz, (float *)(w8 + l.part), sk, st);
     } else {
         ProfScope ps(eqat::PK_F32, st);
         eqat::launch_f32_bwd(p, true, X, dY, W, s, z, (float *)(w8 + l.dwhat), what_of(l, w8, ws_bytes), dX, dW, ds, dz, st);
@@ -414,10 +411,8 @@ static eqat_status qlinear_fwd_run(const Problem &p, const void *X, const float 
 static eqat_status qlinear_bwd_run(const Problem &p, const void *X, const float *s, const QOperands &q, const void *dY,
                                    void *dX, float *ds, float *dz, hipStream_t st)
 {
-    const bool want_g = (ds != nullptr || dz != nullptr);
     if (p.act_bf16) {
-        if (dX != nullptr) { ProfScope ps(eqat::PK_GEMM_DX, st); eqat::launch_mfma_dx(p, dY, q.codes, q.sz, dX, q.sk, st); }
-        if (want_g) eqat::launch_mfma_dw(p, false, X, dY, nullptr, q.codes, nullptr, q.sz, s, nullptr, ds, dz, q.part, q.sk, st);
+        eqat::launch_mfma_bwd(p, false, X, dY, nullptr, q.codes, nullptr, q.sz, s, dX, nullptr, ds, dz, q.part, q.sk, st);
     } else {
         ProfScope ps(eqat::PK_F32, st);
         eqat::launch_f32_bwd(p, false, X, dY, q.codes, s, q.sz, q.dwhat, q.what, dX, nullptr, ds, dz, st);
@@ -664,14 +659,14 @@ eqat_status eqat_fwd_route(const eqat_desc *d, int source, int32_t *route)
     return EQAT_OK;
 }
 
-eqat_status eqat_dx_route(const eqat_desc *d, int32_t *tokens)
+eqat_status eqat_dx_route(const eqat_desc *d, int block_ap, int32_t *route)
 {
     Problem p;
     if (eqat_status e = check_desc(d, true, &p)) return e;
-    if (tokens == nullptr) return EQAT_ERR_NULL;
+    if (route == nullptr) return EQAT_ERR_NULL;
     if (!p.act_bf16) return EQAT_ERR_DTYPE;
     if (p.T < 1) return EQAT_ERR_SHAPE;
-    *tokens = eqat::mid_dx_tokens_for_test(p);
+    eqat::dx_route_for_test(p, block_ap != 0, route);
     return EQAT_OK;
 }
 

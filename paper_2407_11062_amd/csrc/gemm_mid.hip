@@ -67,7 +67,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
     const int wn = wave & 1, kg = wave >> 1, r = lane & 31, h = lane >> 5;
 
     int m0, n0;
-    tile_of(a, BM, m0, n0);
+    tile_of(a, BM, blockIdx.x, gridDim.x, m0, n0);
 
     const int n_segs = a.I >> 5, steps = (a.I + kMidBK - 1) / kMidBK;
     const uint32_t lds0 = lds_addr_of(smem_raw);
@@ -352,7 +352,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
     const int wn = wave & 1, kg = wave >> 1, r = lane & 31, h = lane >> 5;
 
     int m0, n0;
-    tile_of(a, BM, m0, n0);
+    tile_of(a, BM, blockIdx.x, gridDim.x, m0, n0);
 
     const int steps = (a.I + BK - 1) / BK;
     const uint32_t lds0 = lds_addr_of(smem_raw);

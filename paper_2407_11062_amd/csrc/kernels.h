@@ -54,7 +54,7 @@ struct SkScratch { float *partials; size_t bytes; uint32_t *counters; };
 int plan_item_for_test(const Problem &p, int gemm, int block, int j, int32_t item[12]);      // test aid, see gemm_mfma.hip
 // Test aid: bytes from sk.partials on within which the launch of a GEMM (0 fwd, 1 dX, 2 dW) on a device of `cus` compute units writes.
 size_t parts_written_for_test(const Problem &p, int gemm, int cus, const SkScratch &sk);
-int mid_dx_tokens_for_test(const Problem &p);      // test aid: token tile of k_gemm_mid_dx where dX takes it (with all the scratch a plan may ask for), else 0
+void dx_route_for_test(const Problem &p, bool block_ap, int32_t route[2]);      // test aid, see eqat_dx_route
 // Bytes of that scratch for the launches of a forward that takes the tile kernels (fwd), a backward (bwd), or both.  *partial_bytes: what their plans write;
 // *needed_bytes: what a call cannot do without: launches that share tiles only to fill the chip run unshared in less.
 void sk_scratch_bytes(const Problem &p, bool fwd, bool bwd, size_t *partial_bytes, size_t *needed_bytes, size_t *counter_bytes);
@@ -73,6 +73,10 @@ void launch_mfma_dw(const Problem &p, bool block_ap, const void *X, const void *
                     const void *clampbits, const void *sz, const float *s, void *dW, float *ds, float *dz, float *part,
                     const SkScratch &sk, hipStream_t st);
 bool dw_needs_partials(const Problem &p);
+// Both of them (dX, or all of dW, ds and dz, may be NULL: the other alone), in one launch where that is faster.
+void launch_mfma_bwd(const Problem &p, bool block_ap, const void *X, const void *dY, const void *W, const void *codes,
+                     const void *clampbits, const void *sz, const float *s, void *dX, void *dW, float *ds, float *dz, float *part,
+                     const SkScratch &sk, hipStream_t st);
 
 // The kernel that a forward with bf16 activations takes, and the piece of the output that a workgroup of it computes (0: the
 // tile kernel plans that by itself).

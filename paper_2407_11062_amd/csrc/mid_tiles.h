@@ -22,10 +22,10 @@ constexpr int kMidBN = 128, kMidKG = 4, kMidNT = 512;
 
 // Every XCD gets a contiguous range of tiles, token tiles of one weight tile next to each other: the codes are fetched into one
 // L2 only.  With many token tiles that has every XCD read all of X for a weight tile or two: they are walked in bands instead.
-__device__ __forceinline__ void tile_of(const MidArgs &a, int bm, int &m0, int &n0)
+__device__ __forceinline__ void tile_of(const MidArgs &a, int bm, uint32_t bid, uint32_t nb, int &m0, int &n0)
 {
-    const uint32_t nb = gridDim.x, xcd = blockIdx.x & 7, rem = nb & 7;
-    uint32_t pid = xcd * (nb >> 3) + (xcd < rem ? xcd : rem) + (blockIdx.x >> 3), first = 0, rows = (uint32_t)a.tiles_m;
+    const uint32_t xcd = bid & 7, rem = nb & 7;
+    uint32_t pid = xcd * (nb >> 3) + (xcd < rem ? xcd : rem) + (bid >> 3), first = 0, rows = (uint32_t)a.tiles_m;
     if (a.band > 0) {
         const uint32_t band = (uint32_t)a.band, width = band * (uint32_t)a.tiles_n, which = pid / width;
         pid -= which * width;

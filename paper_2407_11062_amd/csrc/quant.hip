@@ -577,9 +577,10 @@ void launch_reduce_partials(const float *part_ds, const float *part_dz, float *d
                             uint32_t n_per, hipStream_t st)
 {
     const uint32_t n = (uint32_t)n_out;
-    // a wavefront per group as soon as a group has more partials than half of one; few partials: several groups per wavefront
+    // a wavefront per group as soon as a group has more partials than half of one; few partials: several groups per wavefront, up to eight one
+    // after another, as the tile kernel adds up a group that lies inside a tile (g = 256 does in tiles of 256, not in those of 128)
 #define EQAT_RED(L) k_reduce_partials<L><<<dim3(blocks_for(n_out, 256 / L), 2), dim3(256), 0, st>>>(part_ds, part_dz, ds, dz, s, n, n_per)
-    if (n_per > 32) EQAT_RED(64); else if (n_per > 8) EQAT_RED(16); else EQAT_RED(4);
+    if (n_per > 32) EQAT_RED(64); else if (n_per > 8) EQAT_RED(16); else EQAT_RED(1);
 #undef EQAT_RED
 }
 

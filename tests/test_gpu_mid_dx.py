@@ -16,17 +16,17 @@ CASES = [(1, 9216, 136, 32, 64), (65, 9216, 840, 64, 64), (1500, 1056, 264, 96, 
          (1040, 2176, 2056, 32, 96), (1041, 2208, 2160, 96, 96), (1000, 3584, 4104, 128, 128), (1000, 3616, 4216, 32, 128), (1100, 7168, 2056, 256, 128)]
 
 
-def dx_tokens(T, I, O, bits, g):
-    out = ctypes.c_int32()
-    rc = eq.lib().eqat_dx_route(ctypes.byref(eq.make_desc(T, I, O, bits, g, eq.BF16, eq.BF16)), ctypes.byref(out))
+def dx_route(T, I, O, bits, g, block_ap, w=eq.BF16):
+    out = (ctypes.c_int32 * 2)()
+    rc = eq.lib().eqat_dx_route(ctypes.byref(eq.make_desc(T, I, O, bits, g, eq.BF16, w)), int(block_ap), out)
     assert rc == 0, eq.lib().eqat_status_string(rc)
-    return out.value
+    return tuple(out)
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("T,I,O,g,tokens", CASES)
 def test_dx_for_few_tiles(T, I, O, g, tokens, bits):
-    assert dx_tokens(T, I, O, bits, g) == tokens
+    assert dx_route(T, I, O, bits, g, True)[0] == tokens
     X, W, s, z, dY = make_case(("middx", T, I, O), T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
     Wd, sd, zd, dYd = dev(W), dev(s), dev(z), dev(dY)
     some = sorted({t for t in (0, 31, 32, 63, 64, 95, 96, 127, 128, 255, 256, T // 2, T - 2, T - 1) if 0 <= t < T})
