@@ -139,8 +139,10 @@ SkPlan plan_tiles(int ntiles, int tile, int pairs, int resident, const SkScratch
     return sk;
 }
 
-// Geometry of a fwd / dX launch: tiles, the XCD band, who computes what (SkPlan), the grid, and which instantiation runs.
-struct QLaunchPlan { int tiles_m, tiles_n, band, ntiles, grid; SkPlan sk; bool cut_inst; };
+// Geometry of a fwd / dX launch: tiles, the XCD band, who computes what (SkPlan), the grid, and which instantiation runs.  A contraction of no whole
+// K-tile pairs has one of its own: in that for cut tiles, which could serve it, two workgroups of small tiles do not fit a compute unit's registers
+// (175 to 185 each) and big tiles spill: dX, 4104 -> 8960, 685 tokens 107 us there, 73 here, 4104 -> 11008, 515 tokens 104 and 71; forward 1 to 2.5 %.
+struct QLaunchPlan { int tiles_m, tiles_n, band, ntiles, grid; SkPlan sk; QMode mode; };
 int q_band(int tiles_m) { return std::max(2, std::min(8, tiles_m / 8)); }
 template <bool BT, typename TS>
 QLaunchPlan plan_q(int M, int N, int K, int cus, const SkScratch &scratch, bool share)
@@ -160,7 +162,7 @@ QLaunchPlan plan_q(int M, int N, int K, int cus, const SkScratch &scratch, bool 
     const int resident = resident_workgroups(cus, per_cu(q_smem_bytes<BT, TS>()));
     q.sk = plan_tiles(q.ntiles, TS::BM * TS::BN, ((K + TS::BK - 1) / TS::BK + 1) / 2, resident, scratch, true, share);
     q.grid = q.sk.walk ? resident : q.ntiles;
-    q.cut_inst = (q.sk.walk && (q.sk.dp_rounds == 0 || q.sk.split)) || K % (2 * TS::BK) != 0;
+    q.mode = q.sk.walk && (q.sk.dp_rounds == 0 || q.sk.split) ? kCut : K % (2 * TS::BK) != 0 ? kRagged : kWhole;
     return q;
 }
 
@@ -174,17 +176,14 @@ void launch_q(const GemmQArgs &args, const SkScratch &scratch, hipStream_t st, b
     const QLaunchPlan q = plan_q<BT, TS>(a.M, a.N, a.K, current_cus(), scratch, share);
     a.tiles_m = q.tiles_m; a.tiles_n = q.tiles_n; a.band = q.band; a.sk = q.sk;
     const dim3 grid(q.grid), block(64 * TS::WGM * TS::WGN);
-    if (q.cut_inst) {
-        auto kern = k_gemm_q<BITS, BT, kCut, TS::BM, TS::BN, TS::BK, TS::WGM, TS::WGN>;
-        static uint64_t attr_done = 0;
+    auto go = [&](auto kern, uint64_t &attr_done) {
         allow_dynamic_lds(kern, smem, attr_done);
         kern<<<grid, block, smem, st>>>(a);
-    } else {
-        auto kern = k_gemm_q<BITS, BT, kWhole, TS::BM, TS::BN, TS::BK, TS::WGM, TS::WGN>;
-        static uint64_t attr_done = 0;
-        allow_dynamic_lds(kern, smem, attr_done);
-        kern<<<grid, block, smem, st>>>(a);
-    }
+    };
+    static uint64_t done_cut = 0, done_ragged = 0, done_whole = 0;
+    if (q.mode == kCut) go(k_gemm_q<BITS, BT, kCut, TS::BM, TS::BN, TS::BK, TS::WGM, TS::WGN>, done_cut);
+    else if (q.mode == kRagged) go(k_gemm_q<BITS, BT, kRagged, TS::BM, TS::BN, TS::BK, TS::WGM, TS::WGN>, done_ragged);
+    else go(k_gemm_q<BITS, BT, kWhole, TS::BM, TS::BN, TS::BK, TS::WGM, TS::WGN>, done_whole);
 }
 
 template <bool BT>
@@ -300,7 +299,7 @@ double dx_us(const Problem &p, int cus, const SkScratch &sk, int *tokens)
         there = (parts == 1 ? 5.8 : 6.5 + 0.03 * groups) + pairs * (0.8 + 0.5 * groups / 256.0 * std::min(1.0, pairs / 32.0));
     } else {
         switch (q_tile(p, true, cus, sk)) {
-        case TileChoice::Small: there = 4.0 + (p.O % 128 == 0 ? 0.95 : 1.4) * k_tiles; break;       // a ragged contraction runs in the slower instantiation
+        case TileChoice::Small: there = 4.0 + 0.97 * k_tiles; break;
         case TileChoice::Big: there = 5.0 + 1.38 * k_tiles * rounds_cost(big, 32, k_tiles, true); break;
         default: {
             const int64_t c = resident_workgroups(cus, 1) / 8 / ((big + 7) / 8);
@@ -465,7 +464,7 @@ int plan_item_for_test(const Problem &p, int gemm, int block, int j, int32_t ite
     if (block >= q.grid) return -1;
     SkItem it{};
     bool ok;
-    if (q.cut_inst) {
+    if (q.mode == kCut) {
         ok = sk_item_of(q.sk, q.ntiles, q.tiles_m, q.tiles_n, q.band, block, q.grid, j, it);
     } else {        // whole tiles only, as in the kernel's other instantiation
         const int loc_step = q.sk.walk ? q.grid >> 3 : q.ntiles;

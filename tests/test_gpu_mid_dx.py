@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 # tokens, in, out, group, token tile
 CASES = [(1, 9216, 136, 32, 64), (65, 9216, 840, 64, 64), (1500, 1056, 264, 96, 64), (300, 5472, 1256, 32, 64), (130, 3232, 1096, -1, 64),
-         (1040, 2176, 2056, 32, 96), (1041, 2208, 2160, 96, 96), (1000, 3584, 4104, 128, 128), (1000, 3616, 4216, 32, 128), (1100, 7168, 2056, 256, 128)]
+         (1040, 2176, 2056, 32, 96), (1041, 2208, 2160, 96, 96), (1000, 3584, 4104, 128, 128), (1000, 3616, 4216, 32, 128), (1000, 4096, 11016, 256, 128)]
 
 
 def dx_route(T, I, O, bits, g, block_ap, w=eq.BF16):
