@@ -42,8 +42,11 @@ __device__ __forceinline__ uint32_t spread_3bit(uint32_t x)
     return (pairs | (pairs << 5)) & 0x07070707u;
 }
 
+// How 4-bit codes become floats: a field extract and a conversion per code; the masked words kept as words, a conversion per code (see WhatTable::four); or
+// kept and converted two at a time (two_codes), fewest instructions and the fastest where arithmetic bounds a kernel.
+enum CodeForm { kFields, kWords, kTwoCodes };
 // the 8 weights of MFMA t of a segment, in slot order
-template <int BITS, int T4, bool KEEP_WORDS = true>
+template <int BITS, int T4, int CODES = kTwoCodes>
 __device__ __forceinline__ bf16x8 eight_of(const WhatTable<BITS> &tab, const CodeWords<BITS> &c)
 {
     uintx4 u;
@@ -57,15 +60,24 @@ __device__ __forceinline__ bf16x8 eight_of(const WhatTable<BITS> &tab, const Cod
         }
     } else if constexpr (BITS == 4) {
         uint32_t even = c.w[T4] & 0x0F0F0F0Fu, odd = (c.w[T4] >> 4) & 0x0F0F0F0Fu;
-        if constexpr (KEEP_WORDS) {                // see WhatTable::four: else two extracts more per four codes
+        if constexpr (CODES != kFields) {
             asm("" : "+v"(even));
             asm("" : "+v"(odd));
+        }
+        float e[4], o[4];
+        if constexpr (CODES == kTwoCodes) {
+            const floatx2 e01 = two_codes<false>(even), e23 = two_codes<true>(even), o01 = two_codes<false>(odd), o23 = two_codes<true>(odd);
+            e[0] = e01[0]; e[1] = e01[1]; e[2] = e23[0]; e[3] = e23[1];
+            o[0] = o01[0]; o[1] = o01[1]; o[2] = o23[0]; o[3] = o23[1];
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) { e[k] = byte_to_float(even, k); o[k] = byte_to_float(odd, k); }
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             bf16x2 p;
-            p[0] = (bf16_t)__builtin_fmaf(byte_to_float(even, k), tab.s, tab.b);
-            p[1] = (bf16_t)__builtin_fmaf(byte_to_float(odd, k), tab.s, tab.b);
+            p[0] = (bf16_t)__builtin_fmaf(e[k], tab.s, tab.b);
+            p[1] = (bf16_t)__builtin_fmaf(o[k], tab.s, tab.b);
             u[k] = __builtin_bit_cast(uint32_t, p);
         }
     } else {

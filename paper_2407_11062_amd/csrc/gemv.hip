@@ -181,9 +181,8 @@ template <int BITS, int FORM> __host__ __device__ constexpr int run_code_slot(in
 template <int BITS, int FORM, int T4, int NG>
 __device__ __forceinline__ bf16x8 run_eight_of(const WhatTable<BITS> &tab, const CodeWords<BITS> &c)
 {
-    // with a group per segment the kernel waits for its loads, and masked 4-bit words that stay words cost more than they save (one
-    // token, 4 bit, g = 32, 5440/14528 block: 97 us without them, 102 with; g = 64, 4544/13120: 86 and 84)
-    if constexpr (FORM != kPairs) return eight_of<BITS, T4, NG != 8>(tab, c);
+    // 4 bit, us, a conversion per code / two at a time: one token, g = 32, 4096 x 11008 12.8 / 12.1, g = 64 11.9 / 11.4; g = 128 5.46 / 5.60 (4096 x 4096)
+    if constexpr (FORM != kPairs) return eight_of<BITS, T4, NG >= 4 ? kTwoCodes : kWords>(tab, c);
     const uint32_t w = c.w[T4 / 2];
     uintx4 u;
     uint32_t d0, d1;
@@ -343,7 +342,8 @@ template <int TR> constexpr int kWideSub = TR >= 64 ? 1 : TR >= 16 ? 2 : 4;     
 template <int TR> constexpr int kWideRowBytes = 4 * kWideSub<TR> * 64 + 16;
 template <int TR> constexpr int kWideWaveBytes = TR * kWideRowBytes<TR>;
 
-// KEEP: masked 4-bit words stay words, see wide_keeps_words below
+// KEEP: masked 4-bit words stay words, see wide_keeps_words below (then two codes are converted at a time, but for groups of 32 in the largest form, which has no
+// registers for it: 24 tokens, 7168 x 12288 45 us, 48 in pairs)
 template <int BITS, int SRC, int NG, int TR, int RB, bool KEEP>
 __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs a)
 {
@@ -441,6 +441,7 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
 
     // Fetched a run ahead where that costs no waves: 2-bit codes and few tokens (13824 x 5120, 8 tokens 17 -> 12 us; 4 bit or 16
     // tokens 5-15 % slower).
+    constexpr int kCodes = !KEEP ? kFields : NG == 4 && TR >= 32 && RB == 2 ? kWords : kTwoCodes;
     constexpr bool AHEAD = TR == 8 && BITS == 2;
     Run run, next;
     if constexpr (AHEAD) fetch_run(wave, next);
@@ -482,8 +483,8 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
                         CodeWords<BITS> cw;
 #pragma unroll
                         for (int j = 0; j < WPS; ++j) cw.w[j] = run.cq[rb][(u * WPS + j) / 4][(u * WPS + j) % 4];
-                        w[rb][0] = eight_of<BITS, 0, KEEP>(tab[rb], cw); w[rb][1] = eight_of<BITS, 1, KEEP>(tab[rb], cw);
-                        w[rb][2] = eight_of<BITS, 2, KEEP>(tab[rb], cw); w[rb][3] = eight_of<BITS, 3, KEEP>(tab[rb], cw);
+                        w[rb][0] = eight_of<BITS, 0, kCodes>(tab[rb], cw); w[rb][1] = eight_of<BITS, 1, kCodes>(tab[rb], cw);
+                        w[rb][2] = eight_of<BITS, 2, kCodes>(tab[rb], cw); w[rb][3] = eight_of<BITS, 3, kCodes>(tab[rb], cw);
                     }
                 }
 #pragma unroll
