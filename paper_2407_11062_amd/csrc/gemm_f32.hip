@@ -5,7 +5,7 @@
 // waves of a workgroup share one output tile and split the contraction in blocks of 32, operands come from global memory
 // straight into MFMA registers without LDS or a barrier, and the waves' sums meet in LDS once, in wave order.  (Before:
 // 64 x 64 tiles of scalar FMAs walked by one workgroup each, 32 of them, with an element-wise bounds check, and an epilogue of
-// one thread per group: 74 + 76 + 34 + 75 us for forward, dX, dWhat and epilogue of that linear; the whole pass takes 21 now.  2048 tokens, 2048 x 2048:
+// one thread per group: 74 + 76 + 34 + 75 us for forward, dX, dWhat and epilogue of that linear; the whole pass takes 19 now.  2048 tokens, 2048 x 2048:
 // 1589 -> 655 us for all.)  The error against 64 bits halves: eight or four short chains of sums in the place of one long one.
 // K order: lane half h of block k0 holds k0 + 16 h + e, e = 0 .. 15, for both operands; product e multiplies k0 + e and
 // k0 + 16 + e.
@@ -16,6 +16,7 @@ namespace eqat {
 
 // ---- operands: 16 consecutive contraction indices k .. k + 15 of row (or column) m; zeros outside the matrix -----------
 struct RowMajorF32 {       // element (m, k) = p[m][k]
+    static constexpr bool kPlain = true;
     const float *p; int rows, cols; uint32_t bytes;
     __device__ __forceinline__ void load(int m, int k, float (&v)[16]) const
     {
@@ -36,6 +37,7 @@ struct RowMajorF32 {       // element (m, k) = p[m][k]
     }
 };
 struct ColMajorF32 {       // element (m, k) = p[k][m].  Plain loads: What of a large bf16 matrix may exceed 2 GiB here
+    static constexpr bool kPlain = true;
     const float *p; int rows, cols;                      // rows: extent of k
     __device__ __forceinline__ void load(int m, int k, float (&v)[16]) const
     {
@@ -120,6 +122,7 @@ template <int BITS> struct PackedW {         // What[o][i] from packed codes and
     }
 };
 template <typename W> struct WeightRows {    // element (m, k) = What[m][k]
+    static constexpr bool kPlain = false;
     W w;
     __device__ __forceinline__ void load(int m, int k, float (&v)[16]) const { w.row(m, k, v); }
 };
@@ -188,18 +191,42 @@ __device__ __forceinline__ void f32_tile(const OpA &a, const OpB &b, float *__re
         for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-    for (int k0 = SPLIT ? wave * 32 : 0; k0 < K; k0 += SPLIT ? 32 * NW : 32) {
-        float va[MB][16], vb[NB][16];
+    // Plain operands of a 32 x 32 tile: the next block is loaded while one is multiplied, the chain of a wave is loads that wait on
+    // memory otherwise (backward: 256 x 512 x 512 14.3 -> 12.9 us, 512 x 512 x 1024 30.4 -> 23.7).  Rebuilt weights (forward 512 x 512
+    // x 512: 7.9 -> 8.7) and 64 x 64 tiles (backward 2048 x 2048 x 2048: 380 -> 433) lose more by the registers than they gain.
+    if constexpr (SPLIT && MB * NB == 1 && OpA::kPlain && OpB::kPlain) {
+        float va[2][16], vb[2][16];
+        auto load = [&](int k0, int to) {
+            a.load(m0 + r, k0 + 16 * h, va[to]);
+            b.load(n0 + r, k0 + 16 * h, vb[to]);
+        };
+        auto multiply = [&](int from) {
 #pragma unroll
-        for (int i = 0; i < MB; ++i) a.load(m0 + 32 * i + r, k0 + 16 * h, va[i]);
+            for (int e = 0; e < 16; ++e) acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[from][e], vb[from][e], acc[0][0], 0, 0, 0);
+        };
+        constexpr int kStep = 32 * NW;
+        if (wave * 32 < K) load(wave * 32, 0);
+        for (int k0 = wave * 32; k0 < K; k0 += 2 * kStep) {
+            if (k0 + kStep < K) load(k0 + kStep, 1);
+            multiply(0);
+            if (k0 + kStep >= K) break;
+            if (k0 + 2 * kStep < K) load(k0 + 2 * kStep, 0);
+            multiply(1);
+        }
+    } else {
+        for (int k0 = SPLIT ? wave * 32 : 0; k0 < K; k0 += SPLIT ? 32 * NW : 32) {
+            float va[MB][16], vb[NB][16];
 #pragma unroll
-        for (int j = 0; j < NB; ++j) b.load(n0 + 32 * j + r, k0 + 16 * h, vb[j]);
+            for (int i = 0; i < MB; ++i) a.load(m0 + 32 * i + r, k0 + 16 * h, va[i]);
 #pragma unroll
-        for (int e = 0; e < 16; ++e)
+            for (int j = 0; j < NB; ++j) b.load(n0 + 32 * j + r, k0 + 16 * h, vb[j]);
 #pragma unroll
-            for (int i = 0; i < MB; ++i)
+            for (int e = 0; e < 16; ++e)
 #pragma unroll
-                for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i][e], vb[j][e], acc[i][j], 0, 0, 0);
+                for (int i = 0; i < MB; ++i)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i][e], vb[j][e], acc[i][j], 0, 0, 0);
+        }
     }
     // acc[..][e] of a lane: row 8 (e / 4) + 4 h + e % 4, column r of the block
     if constexpr (!SPLIT) {
@@ -295,7 +322,7 @@ template <typename E> __global__ __launch_bounds__(256) void k_f32_epilogue(E ep
 // dX needs What, the gradients of the weights need dWhat, and neither needs the other: dWhat tiles and What in the first launch,
 // dX tiles and the per-group epilogue in the second.  What bounds such a call is launches, not work: each of the four in a row took
 // 3.6 to 6.5 us whatever it did (256 tokens, 512 x 512, 4 bit, g = 128; forward and backward 27.4 us with four launches in the
-// backward, 20.9 with two).  The tiles come first, they take longer.
+// backward, 20.9 with two, before the loads ahead in f32_tile).  The tiles come first, they take longer.
 template <typename W>
 __global__ __launch_bounds__(512) void k_f32_dwhat_and_what(ColMajorF32 dY, ColMajorF32 X, float *__restrict__ dwhat, int O, int I, int T, uint32_t tiles_n,
                                                             uint32_t tiles, W w, float *__restrict__ what)

@@ -44,3 +44,13 @@ def test_two_launches_equal_four(T, I, O, g, bits, wdt):
     less = ws[: ws.numel() - room].clone() if T != 1024 else ws
     want = eq.eqat_qlinear_bwd(Xd, Wp, sd, zp, dYd, I, bits, g, ws=less)
     assert torch.equal(got["dX"], want["dX"]) and torch.equal(got["ds"], want["ds"])
+
+
+# contractions of one, three and five blocks of 32 per wave (eight waves), whole and with a remainder, along the tokens (dW) and the rows (dX)
+@pytest.mark.parametrize("T,I,O", [(545, 64, 40), (768, 32, 250), (40, 64, 545), (256, 32, 768), (1025, 96, 36), (36, 96, 1025)])
+def test_blocks_loaded_ahead(T, I, O):
+    X, W, s, z, dY = make_case(("f32ahead", T, I, O), T, I, O, 3, 32, torch.float32, torch.float32)
+    got = eq.eqat_fq_linear_bwd(dev(X), dev(W), dev(s), dev(z), dev(dY), 3, 32)
+    ref = oracle.fq_linear_bwd(npf(X), npf(W), s.numpy(), z.numpy(), npf(dY), 3, 32)
+    for k in ("dX", "dW", "ds", "dz"):
+        assert relerr(got[k], ref[k]) <= 1e-5, k
