@@ -11,7 +11,7 @@
 // Measured, dX, us, tile kernel / here: 11008 -> 4096, 256 tokens: 2 bit 96 / 38, 4 bit 103 / 39; 4096 -> 4096: 256 tokens 36 / 23
 // and 38 / 24, 1000 tokens 42 / 40 and 46 / 44; 5504 -> 2048: 515 tokens 52 / 29 (the same call again and again, operands in the last
 // cache; the costs below and those of ksplit_parts come from such calls as well.  Among the other launches of a training pass 1000
-// tokens, 4096 -> 4096, 4 bit take 58 and at least 53).  What bounds it: a pair of K tiles is 1024
+// tokens, 4096 -> 4096, 4 bit took 58; dX comes here only where k_gemm_mid_dx is not faster).  What bounds it: a pair of K tiles is 1024
 // cycles of products beside 192 KB of LDS traffic (1536 cycles); the parts, written through to memory, cost 3 us and 0.045 each.
 #include "common.h"
 #include "gemm_tiles.h"
