@@ -354,15 +354,16 @@ eqat_status eqat_block_ap_update(const eqat_desc *d, const eqat_adamw *h, void *
  * tile's counter, workgroups in the launch, K-tile pairs per tile, tile rows, tile columns }; *exists = 0 past the last
  * item j of workgroup `block`.  EQAT_ERR_SHAPE for block outside the launch, gemm not 0, 1 or 2, j < 0.  Lets a test check,
  * without a GPU, that every K-tile pair of every tile is computed exactly once for any shape.
- * This is the launch of the tile kernels, given all the workspace it asks for.  A forward may take another kernel altogether
- * (eqat_fwd_route), and a forward or dX of few output tiles runs in the kernel that eqat_shared_item is about.
+ * This is the launch of the tile kernels, given all the workspace it asks for.  A forward or dX may take another kernel altogether
+ * (eqat_fwd_route, eqat_dx_route), one of few output tiles may run in the kernel that eqat_shared_item is about, and dX and dW of one call
+ * may share a launch (eqat_dx_route).
  */
 eqat_status eqat_plan_item(const eqat_desc *d, int gemm, int block, int j, int32_t *item, int32_t *exists);
 
 /*
  * Test aid (host only, nothing is launched): the same for a forward (gemm = 0) or dX (gemm = 1) with at most 256 output tiles of
  * 128 x 128, whose tiles are shared by one to four workgroups, a stretch of the K-tile pairs each (two groups of waves of a
- * workgroup take the tiles of a pair).  *exists = 0 where another kernel computes it, and past the last workgroup; else
+ * workgroup take the tiles of a pair).  *exists = 0 where another kernel computes it (dX: asked for alone), and past the last workgroup; else
  * item[10] = { tile row, tile column, first and past-the-last K-tile pair of workgroup `block`, which part of the tile this is, parts
  * of the tile, workgroups in the launch, K-tile pairs per tile, tile rows, tile columns }.  The parts of a tile are counted in at the
  * counter with the number of the tile.

@@ -614,7 +614,7 @@ eqat_status eqat_plan_item(const eqat_desc *d, int gemm, int block, int j, int32
     return EQAT_OK;
 }
 
-// Test aid (host only): how a fwd / dX launch of k_gemm_ksplit divides its work.
+// Test aid (host only): how a fwd / dX launch of k_gemm_ksplit divides its work (dX: asked for alone).
 eqat_status eqat_shared_item(const eqat_desc *d, int gemm, int block, int32_t *item, int32_t *exists)
 {
     Problem p;
@@ -623,7 +623,9 @@ eqat_status eqat_shared_item(const eqat_desc *d, int gemm, int block, int32_t *i
     if (!p.act_bf16) return EQAT_ERR_DTYPE;
     if (p.T < 1 || gemm < 0 || gemm > 1 || block < 0) return EQAT_ERR_SHAPE;
     const eqat::SkScratch any_room{reinterpret_cast<float *>(16), ~(size_t)0, reinterpret_cast<uint32_t *>(16)};      // never dereferenced
-    const bool runs = gemm == 1 || fwd_route(p, false, false).kernel == eqat::FWD_TILES;
+    int32_t dx[2] = {0, 0};
+    if (gemm == 1) eqat::dx_route_for_test(p, true, dx);
+    const bool runs = gemm == 1 ? dx[0] == 0 : fwd_route(p, false, false).kernel == eqat::FWD_TILES;
     *exists = runs && eqat::ksplit_item_for_test(p, gemm == 1, any_room, block, item) ? 1 : 0;
     return EQAT_OK;
 }

@@ -8,6 +8,7 @@ import oracle
 import paper_2407_11062_amd as eq
 from paper_2407_11062_amd import synth
 from test_fwd_route import TILES, WORK, route
+from test_gpu_mid_dx import dx_route
 from test_gpu_parity import TOL, dev, make_case, npf, relerr
 from test_shared_tiles_plan import parts_of
 from test_work_plan import items_of_launch
@@ -15,29 +16,40 @@ from test_workspace_parts import parts
 
 pytestmark = pytest.mark.gpu
 
-# tokens, in, out, group, and what dX, which contracts over out, runs on: workgroups per tile of k_gemm_ksplit, or the tile kernel (edge
-# of its tiles, workgroups per tile)
-CASES = [(70, 96, 40, 32, 1),          # one pair; the forward too
-         (300, 352, 200, 32, 1),       # two; the forward three
-         (1000, 4096, 264, 64, 1),     # three pairs, 256 tiles
+# tokens, in, out, group, and what dX asked for alone, which contracts over out, runs on: workgroups per tile of k_gemm_ksplit; the tile kernel (edge
+# of its tiles, numbers of workgroups per tile that occur); or None: k_gemm_mid_dx, and the row is there for its forward
+CASES = [(70, 96, 40, 32, None),       # the forward: one pair
+         (300, 352, 200, 32, None),    # three
+         (330, 1120, 256, 32, None),
+         (1000, 4096, 40, 32, 1),      # one pair, 256 tiles
+         (1000, 4096, 200, 32, 1),     # two
+         (1000, 4096, 264, 64, 1),     # three
          (129, 512, 1480, 64, 3),      # K ends inside the second group's tile
          (130, 256, 2056, 32, 4),      # K ends inside the first group's tile, no second one
          (256, 1024, 3000, -1, 4),
          (600, 2048, 4096, 128, 3),    # a last tile of 88 tokens
          (200, 12000, 128, 32, (128, 1)),                   # two whole K tiles
-         (330, 1120, 256, 32, (128, 1)),                    # four
+         (1000, 4096, 256, 32, (128, 1)),                   # four
          (2560, 2048, 5504, 64, (256, 3)),                  # 80 tiles
          (2590, 2528, 10256, 32, (128, 1)),                 # 420 tiles; K ends inside a K tile
-         (2590, 2528, 12296, 32, (256, 2))]                 # 110 tiles; K ends inside a K tile
+         (2590, 2528, 12296, 32, (256, 2)),                 # 110 tiles; K ends inside a K tile
+         # more than 256 tiles: one each, the rest split; with pieces of a K tile and without; and in runs
+         (4400, 4128, 2056, 32, (256, 1, 4, 5)), (4400, 4128, 2048, 32, (256, 1, 4, 5)), (4400, 5920, 1032, 32, (256, 1, 2)),
+         (4096, 2048, 2304, 128, (128, 1)), (4400, 8224, 200, 32, (256, 1))]          # 512 small tiles; 594 big ones, several for a workgroup
 
 
 def assert_way(T, I, O, gemm, bits, g, way):
+    other = gemm == 1 and dx_route(T, I, O, bits, g, True)[0]
+    if way is None:
+        assert other
+        return
+    assert not other
     if isinstance(way, int):
         assert parts_of(T, I, O, gemm, bits, g) == way
     else:
         items, _, _, tiles_m, tiles_n = items_of_launch(T, I, O, gemm)
-        edge, parts = way
-        assert parts_of(T, I, O, gemm, bits, g) == 0 and {it[4] for _, _, it in items} == {parts}
+        edge, *parts = way
+        assert parts_of(T, I, O, gemm, bits, g) == 0 and {it[4] for _, _, it in items} == set(parts)
         assert (tiles_m, tiles_n) == (-(-T // edge), -(-(I if gemm else O) // edge))
 
 
@@ -72,7 +84,9 @@ def test_dx_and_forward_with_few_tiles(T, I, O, g, way, bits):
 
 @pytest.mark.parametrize("T,I,O,g", [(130, 256, 2056, 32), (600, 2048, 4096, 128), (2560, 2048, 5504, 64)])
 def test_without_room_for_parts_the_tiles_are_not_shared(T, I, O, g):
-    """A workspace that was sized for another token count: the same results but for the order of the sums."""
+    """A workspace that was sized for another token count: the same results but for the order of the sums.  dX of the first is shared by fewer
+    workgroups in half the room; where none are shared, the first two run in k_gemm_mid_dx (at most 128 tiles of 128 x 128 are ever shared, which are at most 256 of
+    its 64-token tiles, and those are always estimated faster than one workgroup of k_gemm_ksplit per tile), the third on 128 x 128 tiles."""
     bits = 2
     X, W, s, z, dY = make_case(("noroom", T, I, O), T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
     Xd, Wd, sd, zd, dYd = dev(X), dev(W), dev(s), dev(z), dev(dY)
@@ -82,6 +96,8 @@ def test_without_room_for_parts_the_tiles_are_not_shared(T, I, O, g):
     first, end = parts(T, I, O, eq.OP_FQ_BWD, 1, 256, 1 << 30, bits, g)
     assert end > first
     for room in (0, (end - first) // 2):
+        at, past = parts(T, I, O, eq.OP_FQ_BWD, 1, 256, first + room, bits, g)
+        assert at == first and past - at == (room if T == 130 else 0)
         guard = torch.full((first + room + 4096,), 0xA5, dtype=torch.uint8, device=Xd.device)
         ws = guard[:first + room]
         Y = eq.eqat_fq_linear_fwd(Xd, Wd, sd, zd, bits, g, ws=ws, keep=True)

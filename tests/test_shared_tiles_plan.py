@@ -9,6 +9,12 @@ import paper_2407_11062_amd as eq
 from test_fwd_route import TILES, WORK, route
 
 
+def dx_tokens(T, I, O, bits=2, g=32):
+    route = (ctypes.c_int32 * 2)()
+    assert eq.lib().eqat_dx_route(ctypes.byref(eq.make_desc(T, I, O, bits, g, eq.BF16, eq.BF16)), 1, route) == 0
+    return route[0]
+
+
 def shared_items(T, I, O, gemm, bits=2, g=32):
     """items of all workgroups; none where another kernel computes this GEMM"""
     d = eq.make_desc(T, I, O, bits, g, eq.BF16, eq.BF16)
@@ -63,13 +69,27 @@ def test_every_pair_of_every_tile_is_computed_once():
 
 
 def test_known_launches():
-    assert parts_of(256, 4096, 11008, 1) == 4 and parts_of(1000, 4096, 4096, 1) == 1           # dX: 64 tiles, 256 tiles
+    assert parts_of(256, 4096, 11008, 1) == 4 and parts_of(1000, 4096, 2048, 1) == 1           # dX: 64 tiles, 256 tiles
     assert parts_of(256, 11008, 4096, 1) == 1 and parts_of(1280, 4096, 4096, 1) == 0           # 172 tiles; 320: the tile kernels
     assert parts_of(1, 4096, 4096, 0) == 4 and route(1, 4096, 4096, 2, 32, WORK)[0] == TILES   # one token on a prepared layer
     assert parts_of(333, 4096, 4096, 0) == 0                                                   # k_gemm_mid
     # two or four whole K tiles: the tile kernel; any other length up to them is shared by the two K groups
     for K, parts in ((32, 1), (64, 1), (96, 1), (128, 0), (160, 1), (192, 1), (256, 0), (288, 1), (384, 1)):
-        assert parts_of(100, K, 512, 0) == parts and parts_of(100, 512, K, 1) == parts, K
+        assert parts_of(100, K, 512, 0) == parts and parts_of(1000, 4096, K, 1) == parts, K
+
+
+def test_none_where_the_kernel_for_few_tiles_computes_dx():
+    """256 tiles of 128 x 128 and a long contraction, a handful of tiles and a short one: k_gemm_mid_dx (`eqat_dx_route`) and no other."""
+    for T, I, O in ((1000, 4096, 4096), (100, 512, 96), (70, 96, 40), (300, 352, 200)):
+        assert dx_tokens(T, I, O) != 0 and shared_items(T, I, O, 1) == [] and parts_of(T, I, O, 1) == 0
+    rng = np.random.default_rng(12)
+    seen = set()
+    for _ in range(500):
+        T, I, O = int(np.exp(rng.uniform(0, 8))), 32 * int(np.exp(rng.uniform(0, 6))), 8 * int(np.exp(rng.uniform(0, 8)))
+        way = (dx_tokens(T, I, O) != 0, bool(shared_items(T, I, O, 1)))
+        assert way != (True, True), (T, I, O)
+        seen.add(way)
+    assert len(seen) == 3
 
 
 def test_bad_arguments():
