@@ -228,13 +228,13 @@ SPLIT_CASES = [
     ("cut_fwd", 4400, 512, 4104, 2, 64),       # fwd: 18 x 17 = 306 tiles of 256 x 256, 4 K-tile pairs each
     ("cut_dx", 4400, 4128, 520, 3, 32),        # dX: 306 tiles, K = O = 520: 5 pairs, the last one half past the end
     ("cut_dw", 600, 4416, 4104, 2, 64),        # dW: 18 x 17 tiles, K = T = 600
-    ("cut_small", 4096, 512, 2304, 4, 128),    # fwd: 144 tiles of 256 x 256, none of them cut; dX: 128 of 128 x 128, two K groups in a workgroup
+    ("cut_small", 4096, 512, 2304, 4, 128),    # fwd: 144 tiles of 256 x 256, none of them cut; dX: 64-token tiles of k_gemm_mid_dx
     ("cut_dw_perchan", 520, 4352, 4096, 2, -1),  # dW, 17 x 16 tiles, one group per row (partials + reduce kernel)
     # few tiles beyond the first round and a long K: a whole tile per workgroup, then every remaining tile split among
     # four (few of them: eight) workgroups, whose parts the last of them to arrive adds up in their order
     ("split_fwd", 4400, 2048, 4104, 2, 64),    # fwd: 306 tiles, 16 K-tile pairs
-    ("split_dx", 4400, 4128, 2056, 3, 32),     # dX: 306 tiles, K = O = 2056: 17 pairs (uneven pieces, ragged last K tile)
-    ("split_small", 4096, 2048, 2304, 4, 128), # fwd: 144 tiles of 256 x 256; dX: 512 of 128 x 128, one workgroup each (split ones: test_gpu_ksplit)
+    ("split_dx", 4400, 4128, 2056, 3, 32),     # dX: 306 whole tiles in front of those of dW, K = O = 2056: 17 pairs, a ragged last K tile (alone, some split: test_gpu_ksplit)
+    ("split_small", 4096, 2048, 2304, 4, 128), # fwd: 144 tiles of 256 x 256; dX: as many, in front of those of dW (alone, 512 of 128 x 128: test_gpu_ksplit)
     ("split_3r", 4400, 2048, 8440, 2, 64),     # fwd: 18 x 33 = 594 tiles (not a multiple of 8): two whole rounds, then 10 or 11 tiles per XCD split two ways
     ("split_dw", 2100, 4352, 4104, 3, 64),     # dW: 17 x 17 = 289 tiles, K = T = 2100: 17 pairs, six contributors per split tile
     ("split_dw_small", 2100, 2304, 4096, 4, 128), # dW: 9 x 16 = 144 tiles of 256 x 256, none of them cut (split ones of 128 x 128: test_gpu_dw_tiles)
@@ -285,7 +285,8 @@ def test_a_non_finite_token_does_not_leak_into_its_neighbour(I, O, T):
     last K tile (and a padding tile) reach past the end of an activation row, i.e. into the next row.  The weights there
     are zero, but 0 * Inf is NaN: the chunks past K must not be loaded at all.  Row 7 of X and of dY carries Inf and
     NaN; every other row of Y (fwd, K = I) and of dX (K = O) must come out as without them.  The forward of 40 tokens takes
-    k_gemv_wide (runs of 512 inputs, cut short here) or k_gemm_mid, that of 300 and both dX the tile kernel."""
+    k_gemv_wide (runs of 512 inputs, cut short here) or k_gemm_mid, that of 300 k_gemm_ksplit, both dX k_gemm_mid_dx (dX in the tile kernels and in
+    k_gemm_ksplit: test_gpu_ksplit)."""
     bits, g = 2, 32
     assert route(T, I, O, bits, g)[0] == (TILES if T == 300 else MID if I == 96 else WIDE)
     X, W, s, z, dY = make_case(("leak", I, O), T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
