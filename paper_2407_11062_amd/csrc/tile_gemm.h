@@ -720,7 +720,9 @@ __device__ __forceinline__ bf16x8 frag_km16_swz(const bf16_t *tile, int col0, in
 // so issuing one costs a scalar move to M0, the load and one add.  Columns past `ld` start at an out-of-range offset and
 // advance like the others: tensors are smaller than 2 GiB, so 2 GiB plus any offset into one stays out of range (no
 // wrap-around); rows past the end of the matrix fail the buffer's range check.
-template <int BK, int COLS, int NW>
+// RUNNING: the offsets stay such.  Left to itself the compiler keeps, for a loop of two tiles a trip, an offset for either tile and adds a scalar to them:
+// twice the registers.
+template <int BK, int COLS, int NW, bool RUNNING = false>
 struct KmLoader {
     static constexpr int CPR = COLS / 8, RPI = kmRowsPerLoad<COLS>, LOADS = BK / RPI / NW;   // chunks per row, rows per instruction
     static_assert(BK % (RPI * NW) == 0 && CPR <= 64, "tile / wave mismatch");
@@ -747,6 +749,7 @@ struct KmLoader {
     {
         load_to_lds16_at(r, tile_lds + (uint32_t)(km_row_elems<COLS>((wave * LOADS + it) * RPI) * 2), off[it]);
         off[it] += adv;
+        if constexpr (RUNNING) asm("" : "+v"(off[it]));
     }
 };
 
@@ -794,12 +797,16 @@ __device__ __forceinline__ void gemm_dw_body(const GemmDwArgs &a, const int bid,
         kt0 = 2 * si.kb;
         nk = (2 * si.ke < nk ? 2 * si.ke : nk) - kt0;
     }
-    KmLoader<BK, BM, NW> ldX;
-    KmLoader<BK, BN, NW> ldY;
+    // fp32 weights, whole tiles: the loop is two registers short, and each reload (a vector-memory operation) waits for all loads under way.  dW, ds and
+    // dz, 3 bit, us so / with running offsets: 8192 tokens, 4096 x 4096 245 / 212; 1000 tokens, 11008 -> 4096 164 / 156; 2 bit 241 / 214 and 171 / 162.
+    // (In the instantiation that cuts tiles running offsets cost 30 registers in scratch.)
+    constexpr bool RUNNING = BLOCK_AP && sizeof(WT) == 4 && !CUT;
+    KmLoader<BK, BM, NW, RUNNING> ldX;
+    KmLoader<BK, BN, NW, RUNNING> ldY;
     ldX.init((int)a.I, m0, wave, lane);
     ldY.init((int)a.O, n0, wave, lane);
     if constexpr (CUT) { ldX.skip_tiles(kt0); ldY.skip_tiles(kt0); }
-    constexpr int LA = KmLoader<BK, BM, NW>::LOADS, LB = KmLoader<BK, BN, NW>::LOADS, ND = LA + LB;
+    constexpr int LA = decltype(ldX)::LOADS, LB = decltype(ldY)::LOADS, ND = LA + LB;
     // load number d (0 .. ND-1) of the NEXT K tile (tiles are fetched strictly in order) into LDS buffer `buf`
     auto issue_load = [&](int d, int buf) {
         if (d < LA) ldX.issue(rX, d, ldsA + (uint32_t)(buf * A_ELEMS * 2), wave);
