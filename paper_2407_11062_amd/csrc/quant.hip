@@ -403,8 +403,9 @@ __global__ __launch_bounds__(256) void k_init_minmax_wave(const InitBatch b, flo
 
 // Groups wider than a dW tile: ds / dz of group t from its n_per consecutive per-32-column partials, in one launch
 // (blockIdx.y: 0 = ds, 1 = dz).  LPG lanes share a group: each adds every LPG-th partial, an xor butterfly adds the lanes:
-// a fixed order.  One thread per group walking its partials alone left the chip with a few hundred wavefronts of serial,
-// uncoalesced loads (18 us per output at 4096 groups of 128 partials, 36 us for ds and dz; now 6 us for both).
+// a fixed order.  LPG = 4 (up to eight partials): the lanes fetch them and the sum runs partial by partial, as with one lane.  One thread per group walking its
+// partials alone left the chip with a few hundred wavefronts of serial, uncoalesced loads (18 us per output at 4096 groups of 128 partials, 36 us for ds and
+// dz; now 6 us for both).
 // `dz` (blockIdx.y = 1) is multiplied by -s[t]: the sum of the clamped dWhat becomes the gradient of the zero point.
 template <int LPG>
 __global__ __launch_bounds__(256) void k_reduce_partials(const float *__restrict__ part_ds, const float *__restrict__ part_dz,
@@ -417,9 +418,17 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const float *__restrict
     const uint32_t t = blockIdx.x * (256u / LPG) + threadIdx.x / LPG, l = threadIdx.x % LPG;
     if (out == nullptr || t >= n_out) return;         // LPG divides the wavefront: the lanes of a group leave together
     float acc = 0.0f;
-    for (uint32_t k = l; k < n_per; k += LPG) acc += part[(size_t)t * n_per + k];
+    if constexpr (LPG == 4) {
+        const float lo = l < n_per ? part[(size_t)t * n_per + l] : 0.0f, hi = l + 4 < n_per ? part[(size_t)t * n_per + l + 4] : 0.0f;
+#define EQAT_QUAD_LANE(V, K) __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(V), (K) * 0x55, 0xF, 0xF, true))
+        acc += EQAT_QUAD_LANE(lo, 0); acc += EQAT_QUAD_LANE(lo, 1); acc += EQAT_QUAD_LANE(lo, 2); acc += EQAT_QUAD_LANE(lo, 3);
+        acc += EQAT_QUAD_LANE(hi, 0); acc += EQAT_QUAD_LANE(hi, 1); acc += EQAT_QUAD_LANE(hi, 2); acc += EQAT_QUAD_LANE(hi, 3);
+#undef EQAT_QUAD_LANE
+    } else {
+        for (uint32_t k = l; k < n_per; k += LPG) acc += part[(size_t)t * n_per + k];
 #pragma unroll
-    for (int m = LPG / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m);
+        for (int m = LPG / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m);
+    }
     if (l == 0) out[t] = is_dz ? -s[t] * acc : acc;
 }
 
@@ -577,10 +586,12 @@ void launch_reduce_partials(const float *part_ds, const float *part_dz, float *d
                             uint32_t n_per, hipStream_t st)
 {
     const uint32_t n = (uint32_t)n_out;
-    // a wavefront per group as soon as a group has more partials than half of one; few partials: several groups per wavefront, up to eight one
-    // after another, as the tile kernel adds up a group that lies inside a tile (g = 256 does in tiles of 256, not in those of 128)
+    // a wavefront per group as soon as a group has more partials than half of one; few partials: several groups per wavefront, up to eight summed one
+    // after another, as the tile kernel adds up a group that lies inside a tile (g = 256 does in tiles of 256, not in those of 128).  Four lanes fetch them
+    // where there are few groups (dW, ds, dz, 62 tokens, 768 -> 11352, g = 256, 34056 groups, us with one lane / four: 27.3 / 25.9; 374 tokens, 3072 -> 1304
+    // 19.6 / 19.1), one where there are many (515 tokens, 4032 -> 11008, g = 96, 462336 groups 113.3 / 117.2; 2000 tokens, 4032 -> 4096 74.1 / 75.4).
 #define EQAT_RED(L) k_reduce_partials<L><<<dim3(blocks_for(n_out, 256 / L), 2), dim3(256), 0, st>>>(part_ds, part_dz, ds, dz, s, n, n_per)
-    if (n_per > 32) EQAT_RED(64); else if (n_per > 8) EQAT_RED(16); else EQAT_RED(1);
+    if (n_per > 32) EQAT_RED(64); else if (n_per > 8) EQAT_RED(16); else if (n_out < 65536) EQAT_RED(4); else EQAT_RED(1);
 #undef EQAT_RED
 }
 

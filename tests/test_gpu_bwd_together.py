@@ -55,3 +55,16 @@ def test_e2e(T, I, O, g, dx, cut, bits):
     assert relerr(both["dX"][some], ref) <= TOL[torch.bfloat16]
     again = eq.eqat_qlinear_bwd_prepared(Xd, prepared, sd, dYd, I, bits, g, z=zf, want=("dX", "ds", "dz"))
     assert all(torch.equal(again[k], both[k]) for k in both)
+
+
+@pytest.mark.parametrize("g", [96, 256])
+def test_few_partials_are_summed_alike_whatever_their_number(g):
+    """ds and dz of a row do not depend on how many rows there are (one lane of k_reduce_partials per group or four), with three and eight partials."""
+    T, I, O, few, bits = 40, 768, 24000, 1000, 2
+    X, W, s, z, dY = make_case(("fewpartials", g), T, I, O, bits, g, torch.bfloat16, torch.bfloat16)
+    Xd, Wd, sd, zd, dYd = dev(X), dev(W), dev(s), dev(z), dev(dY)
+    for k in ("ds", "dz"):
+        many = eq.eqat_fq_linear_bwd(Xd, Wd, sd, zd, dYd, bits, g, want=(k,))[k]
+        some = eq.eqat_fq_linear_bwd(Xd, Wd[:few].contiguous(), sd[:few].contiguous(), zd[:few].contiguous(), dYd[:, :few].contiguous(), bits, g, want=(k,))[k]
+        ref = oracle.fq_linear_bwd(npf(X), npf(W)[:few], s.numpy()[:few], z.numpy()[:few], npf(dY)[:, :few], bits, g, want=(k,))[k]
+        assert torch.equal(many[:few], some) and relerr(some, ref) <= TOL[torch.bfloat16]
