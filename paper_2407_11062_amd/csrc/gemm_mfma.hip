@@ -327,6 +327,28 @@ double dw_us(const Problem &p, bool block_ap)
     return small <= 256 ? 6.0 + 0.62 * k_tiles + extra : (7.0 + 0.88 * k_tiles + extra) * rounds_cost(small, 64, k_tiles, false);
 }
 
+// A backward that leaves compute units idle altogether, in one launch (every tile of both at once: the longer of them, dW's with the whole epilogue on few
+// compute units) and in two (small tiles of dW).
+struct FewTiles { double start, per_share, g32, apart, apart_per_share; };
+FewTiles few_tiles(const Problem &p, bool block_ap)
+{
+    if (!block_ap) return {10.0, 7.0, 1.0, 3.3, 2.3};
+    return p.w_bf16 ? FewTiles{15.0, 16.0, 2.5, 5.2, 5.0} : FewTiles{16.5, 20.0, 2.5, 6.0, 8.0};
+}
+double bwd_one_round_us(const Problem &p, bool block_ap, int dx, int64_t n2)
+{
+    const FewTiles f = few_tiles(p, block_ap);
+    const double k_tiles = (double)((p.T + 63) / 64), steps = (double)((p.O + 127) / 128);
+    const double dw = f.start + 0.96 * k_tiles + f.per_share * (double)n2 / 32.0 + (p.g == 32 ? f.g32 : 0.0);
+    const double there = dx == kBwdBig ? 6.7 + 1.19 * (double)((p.O + 63) / 64) : dx == 64 ? 5.6 + 0.64 * steps : dx == 96 ? 6.2 + 0.75 * steps : 6.6 + 0.83 * steps;
+    return std::max(dw, there) + (DwTileBig::BM % p.g != 0 ? 2.5 : 0.0);
+}
+double bwd_apart_few_us(const Problem &p, bool block_ap, double dx_alone_us, int64_t small)
+{
+    const FewTiles f = few_tiles(p, block_ap);
+    return f.apart + 0.62 * (double)((p.T + 63) / 64) + 1.25 * dx_alone_us + f.apart_per_share * (double)small / 256.0 + (DwTileSmall::BM % p.g != 0 ? 2.0 : 0.0);
+}
+
 // Token tiles of k_gemm_mid_dx where dX alone takes that kernel, else 0: up to two rounds of its workgroups, where it is estimated to be faster
 // than k_gemm_ksplit or the tiles of k_gemm_q.  196 random sizes, 50 to 2200 tokens, 768 to 12000 in-features, 768 to 16000 out-features: the rule
 // takes no kernel more than 2 % slower than the one it leaves and is within 1 % of the best choice in the mean; 8 % faster in the mean, 25 to 50 %
@@ -345,7 +367,10 @@ int mid_dx_tokens(const Problem &p, int cus, const SkScratch &sk)
 // (147 random sizes, 256 to 8192 tokens: 11 % faster in the mean with this rule, 12 % with the best choice at each): 515 tokens, 3 bit, E2E-QP
 // 11008 -> 4096 144 / 122; 1000 tokens, Block-AP, fp32 weights 4096 -> 11008 254 / 234; 4096 tokens, 3 bit, Block-AP 5120 -> 5120 380 / 351 (320 and 400
 // tiles: 1.25 and 1.56 rounds), 13824 -> 5120 967 / 905.  Whole rounds of both gain 1 % (8192 tokens, 4096 -> 4096 410 / 407) or lose it (11008 -> 4096
-// 1095 / 1101), and a single filled round of each does not care.
+// 1095 / 1101), and a single filled round of each does not care.  Where both together fill one round at most, the one launch takes as long as the longer of the
+// two, and dW in big tiles, an epilogue on a quarter of the compute units, is longer than in small ones: estimates of their own (fits to 1420 random sizes,
+// 1 to 9000 tokens, 200 to 14000 in-features, 64 to 14000 out-features; with the others in their place 157 calls were 5 % slower and up to 36 %, now 13 and 12 %,
+// and the mean gains 2 % more): 426 tokens, E2E-QP, 2752 -> 368 20.4 / 24.3 and 278 tokens, Block-AP, 1248 -> 448 22.2 / 25.7 stay apart.
 int bwd_together(const Problem &p, bool block_ap, int cus, const SkScratch &sk)
 {
     if (p.T < 1) return -1;
@@ -355,30 +380,35 @@ int bwd_together(const Problem &p, bool block_ap, int cus, const SkScratch &sk)
     const bool cut = plan_dw_of(p, cus, sk, &small_dw).cut;
     if (cut && small_dw) return -1;
     int alone = 0, best = -1;
-    const double apart = 3.0 + dx_us(p, cus, sk, &alone) + dw_us(p, block_ap), t2 = dw_tile_us(p, block_ap);
-    double us = 0.99 * apart;
-    const int64_t n2 = (tiles_of(p.I, p.O, 256, 256) + 7) / 8;
+    const double alone_us = dx_us(p, cus, sk, &alone), apart = 3.0 + alone_us + dw_us(p, block_ap), t2 = dw_tile_us(p, block_ap);
+    const int64_t n2 = (tiles_of(p.I, p.O, 256, 256) + 7) / 8, small = tiles_of(p.I, p.O, 128, 128);
+    double least = 1.0;                               // of the estimates with a margin, as shares of that of two launches
     for (const int dx : {(int)kBwdBig, 64, 96, 128}) {
         int64_t n1 = dx == kBwdBig ? tiles_of(p.T, p.I, 256, 256) : tiles_of(p.T, p.I, dx, 128);
         if (dx != kBwdBig && (cut || n1 > 700)) continue;
         n1 = (n1 + 7) / 8;
-        const double t1 = dx == kBwdBig ? 4.6 + 1.26 * (double)((p.O + 63) / 64) : 4.0 + (double)((p.O + 127) / 128) * (dx == 64 ? 0.78 : dx == 96 ? 0.83 : 0.98);
-        // n1 tiles on 32 compute units: `late` of them are done after `a`, the others after `b`
-        const int64_t late = n1 % 32;
-        const double b = (double)(n1 / 32) * t1, a = late ? b + t1 : b, even = ((double)n1 * t1 + (double)n2 * t2) / 32.0;
-        // the end of the last tile of dW: some whole number of them after a or b
-        double end = 1e30;
-        for (const double from : {a, b}) {
-            const double first = from + t2 * std::max(0.0, (double)(int64_t)((even - from) / t2) - 2.0);
-            for (int i = 0; i < 8; ++i) {
-                const double at = first + t2 * i;
-                const int64_t done = late * (int64_t)std::max(0.0, (at - a) / t2 + 1e-9) + (32 - late) * (int64_t)std::max(0.0, (at - b) / t2 + 1e-9);
-                if (done >= n2 && at < end) end = at;
+        double est;
+        if (small_dw && small <= 256 && n1 + n2 <= 32) {
+            est = bwd_one_round_us(p, block_ap, dx, n2) / (0.96 * bwd_apart_few_us(p, block_ap, alone_us, small));
+        } else {
+            const double t1 = dx == kBwdBig ? 4.6 + 1.26 * (double)((p.O + 63) / 64) : 4.0 + (double)((p.O + 127) / 128) * (dx == 64 ? 0.78 : dx == 96 ? 0.83 : 0.98);
+            // n1 tiles on 32 compute units: `late` of them are done after `a`, the others after `b`
+            const int64_t late = n1 % 32;
+            const double b = (double)(n1 / 32) * t1, a = late ? b + t1 : b, even = ((double)n1 * t1 + (double)n2 * t2) / 32.0;
+            // the end of the last tile of dW: some whole number of them after a or b
+            double end = 1e30;
+            for (const double from : {a, b}) {
+                const double first = from + t2 * std::max(0.0, (double)(int64_t)((even - from) / t2) - 2.0);
+                for (int i = 0; i < 8; ++i) {
+                    const double at = first + t2 * i;
+                    const int64_t done = late * (int64_t)std::max(0.0, (at - a) / t2 + 1e-9) + (32 - late) * (int64_t)std::max(0.0, (at - b) / t2 + 1e-9);
+                    if (done >= n2 && at < end) end = at;
+                }
             }
+            if (cut) end = even + 0.4 * t2;           // the pieces of its last tiles are short
+            est = (4.0 + 0.62 * std::max(end, a) + 0.38 * std::max(even, t1)) / (0.99 * apart);
         }
-        if (cut) end = even + 0.4 * t2;               // the pieces of its last tiles are short
-        const double est = 4.0 + 0.62 * std::max(end, a) + 0.38 * std::max(even, t1);
-        if (est < us) { us = est; best = dx == kBwdBig && p.O % 128 != 0 ? kBwdBigRagged : dx; }
+        if (est < least) { least = est; best = dx == kBwdBig && p.O % 128 != 0 ? kBwdBigRagged : dx; }
     }
     return best;
 }

@@ -1,0 +1,23 @@
+"""Which backward calls run dX and dW in one launch (`eqat_dx_route`, host only): sizes at which each way was measured to be the faster one."""
+import pytest
+
+import paper_2407_11062_amd as eq
+from test_gpu_mid_dx import dx_route
+
+F32W, BF16W, E2E = eq.F32, eq.BF16, None
+#        tokens, in, out, bits, group, weights, us in two launches, us in one (the best of its kernels for dX)
+APART = [(392, 672, 64, 4, 32, BF16W, 17.1, 23.1), (441, 832, 96, 2, 64, BF16W, 17.3, 22.6), (693, 1344, 512, 2, 32, BF16W, 24.1, 31.1),
+         (13, 2080, 256, 2, 32, BF16W, 16.5, 21.0), (120, 13056, 128, 2, 64, BF16W, 15.5, 18.4), (586, 1216, 256, 3, 32, E2E, 18.5, 20.4),
+         (426, 2752, 368, 3, 64, E2E, 20.4, 24.3), (278, 1248, 448, 2, 96, BF16W, 22.2, 25.7), (1, 7744, 272, 2, 32, BF16W, 17.6, 22.5)]
+ONE = [(515, 11008, 4096, 3, -1, E2E, 144, 122), (1000, 4096, 11008, 4, 128, F32W, 254, 234),
+       (4096, 5120, 5120, 3, 128, BF16W, 380, 351), (7, 896, 1024, 3, 128, F32W, 22.7, 19.4), (910, 256, 1400, 3, 128, E2E, 29.8, 25.3),
+       (118, 2304, 944, 2, 128, F32W, 23.2, 21.1), (2449, 576, 4224, 4, 96, F32W, 79.8, 67.1)]
+
+
+def together(T, I, O, bits, g, weights):
+    return dx_route(T, I, O, bits, g, weights is not None, weights if weights is not None else eq.BF16)[1] >= 0
+
+
+@pytest.mark.parametrize("T,I,O,bits,g,weights,apart_us,one_us", APART + ONE)
+def test_the_faster_way_is_taken(T, I, O, bits, g, weights, apart_us, one_us):
+    assert together(T, I, O, bits, g, weights) == (one_us < apart_us)
