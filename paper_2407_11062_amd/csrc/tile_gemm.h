@@ -787,7 +787,9 @@ __device__ __forceinline__ void gemm_dw_body(const GemmDwArgs &a, const int bid,
         if (!sk_item_of(a.sk, a.tiles_m * a.tiles_n, a.tiles_m, a.tiles_n, 8, bid, grid, item, si)) break;
         tm = si.tm; tn = si.tn;
     } else {
-        if (!tile_of_xcd_slot(grid, bid & 7, bid >> 3, a.tiles_m, a.tiles_n, tm, tn, 8)) return;
+        // (bid < grid, the number of tiles: there is always one.  A return here would put the loads of the kernel's arguments behind its branch, one after
+        // another: 155 tokens, 1920 -> 304, ds 8.15 us of kernel without, 8.45 with)
+        (void)tile_of_xcd_slot(grid, bid & 7, bid >> 3, a.tiles_m, a.tiles_n, tm, tn, 8);
     }
     const int m0 = tm * BM, n0 = tn * BN;      // m0: first in-feature i, n0: first out-feature o
     // K tiles (of BK tokens) of this item: all of them, or the pairs [kb, ke) of a part (an even number of tiles, except
