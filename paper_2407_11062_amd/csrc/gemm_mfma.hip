@@ -383,7 +383,7 @@ int bwd_together(const Problem &p, bool block_ap, int cus, const SkScratch &sk)
     const double alone_us = dx_us(p, cus, sk, &alone), apart = 3.0 + alone_us + dw_us(p, block_ap), t2 = dw_tile_us(p, block_ap);
     const int64_t n2 = (tiles_of(p.I, p.O, 256, 256) + 7) / 8, small = tiles_of(p.I, p.O, 128, 128);
     double least = 1.0;                               // of the estimates with a margin, as shares of that of two launches
-    for (const int dx : {(int)kBwdBig, 64, 96, 128}) {
+    for (const int dx : {64, 96, 128, (int)kBwdBig}) {
         int64_t n1 = dx == kBwdBig ? tiles_of(p.T, p.I, 256, 256) : tiles_of(p.T, p.I, dx, 128);
         if (dx != kBwdBig && (cut || n1 > 700)) continue;
         n1 = (n1 + 7) / 8;
