@@ -16,6 +16,8 @@ namespace eqat {
 constexpr int kBwdBig = 0, kBwdBigRagged = 1;       // what computes dX: 256 x 256 tiles, the same for any contraction length; 64, 96, 128: mid_dx_body with such token tiles
 
 // CUT: tiles of dW that are cut along T where dW has a launch of its own are cut alike here, with a workgroup per item (n_dw: workgroups of that launch).
+// Only plans that split tiles (SkPlan::split): a workgroup number has dp_rounds + 1 items at most and one part, and nobody waits for anybody.  The second
+// contributor of a run waits for the first one, which may not have been dispatched here: the grid is larger than what is resident.
 template <int BITS, typename WT, bool AP, int DX, bool CUT>
 __global__ __launch_bounds__(512) void k_gemm_bwd(const GemmQArgs q, const MidArgs m, const GemmDwArgs d, const int n_dx, const int n_dw)
 {
@@ -35,9 +37,10 @@ template <int BITS, typename WT, bool AP, int DX, bool CUT = false>
 void launch_bwd_t(const GemmQArgs &q, const MidArgs &m, const GemmDwArgs &d, int n_dx, int n_dw, hipStream_t st)
 {
     typedef DwTileBig D;
-    size_t smem = dw_smem_bytes<WT, AP, D::BM, D::BN, D::BK, D::NS, D::WGM, D::WGN>();
-    if constexpr (DX >= 64) smem = std::max(smem, (size_t)DxLds<BITS, DX>::TOTAL);
-    else smem = std::max(smem, q_smem_bytes<true, TileBig>());
+    constexpr size_t dw = dw_smem_bytes<WT, AP, D::BM, D::BN, D::BK, D::NS, D::WGM, D::WGN>();
+    constexpr size_t smem = std::max(dw, [] { if constexpr (DX >= 64) return (size_t)DxLds<BITS, DX>::TOTAL; else return q_smem_bytes<true, TileBig>(); }());
+    static_assert(smem + (CUT ? 64 : 0) <= 160 * 1024, "LDS of one CU; tiles that are cut have a word of their own");
+    static_assert(!CUT || DX < 64, "cut tiles of dW come with big tiles of dX (bwd_together)");
     auto kern = k_gemm_bwd<BITS, WT, AP, DX, CUT>;
     static std::atomic<uint64_t> allowed{0};          // more dynamic LDS than the default limit: once per device
     int dev = 0;

@@ -375,10 +375,11 @@ int bwd_together(const Problem &p, bool block_ap, int cus, const SkScratch &sk)
 {
     if (p.T < 1) return -1;
     // dW, ds and dz are bitwise the same whether or not dX is asked for: tiles of 256 that dW alone cuts along T are cut alike, as long as dX runs on such
-    // tiles, too (from 2048 tokens on, which others are not for); no common launch where it cuts tiles of 128
+    // tiles, too (from 1921 tokens on, 16 pairs of K tiles, which others are not for); no common launch where it cuts tiles of 128 or deals out runs
     bool small_dw;
-    const bool cut = plan_dw_of(p, cus, sk, &small_dw).cut;
-    if (cut && small_dw) return -1;
+    const DwLaunchPlan dw = plan_dw_of(p, cus, sk, &small_dw);
+    const bool cut = dw.cut;
+    if (cut && (small_dw || !dw.sk.split)) return -1;
     int alone = 0, best = -1;
     const double alone_us = dx_us(p, cus, sk, &alone), apart = 3.0 + alone_us + dw_us(p, block_ap), t2 = dw_tile_us(p, block_ap);
     const int64_t n2 = (tiles_of(p.I, p.O, 256, 256) + 7) / 8, small = tiles_of(p.I, p.O, 128, 128);

@@ -1,8 +1,10 @@
 """Which backward calls run dX and dW in one launch (`eqat_dx_route`, host only): sizes at which each way was measured to be the faster one."""
+import numpy as np
 import pytest
 
 import paper_2407_11062_amd as eq
 from test_gpu_mid_dx import dx_route
+from test_work_plan import items_of_launch
 
 F32W, BF16W, E2E = eq.F32, eq.BF16, None
 #        tokens, in, out, bits, group, weights, us in two launches, us in one (the best of its kernels for dX)
@@ -21,3 +23,18 @@ def together(T, I, O, bits, g, weights):
 @pytest.mark.parametrize("T,I,O,bits,g,weights,apart_us,one_us", APART + ONE)
 def test_the_faster_way_is_taken(T, I, O, bits, g, weights, apart_us, one_us):
     assert together(T, I, O, bits, g, weights) == (one_us < apart_us)
+
+
+def test_cut_tiles_of_dw_share_a_launch_only_where_nobody_waits():
+    """The grid of the common launch is larger than what is resident: its cut tiles are split ones, whose contributors wait for nobody (item[6]), and not
+    of runs.  dX is on 256 x 256 tiles there."""
+    rng = np.random.default_rng(8)
+    seen = 0
+    for T, I, O in [(2200, 4384, 4224), (2448, 14112, 1392), (1921, 4384, 4224)] + [
+            (int(rng.integers(1921, 6000)), 32 * int(rng.integers(60, 400)), 8 * int(rng.integers(300, 1400))) for _ in range(60)]:
+        cut = [it for _, _, it in items_of_launch(T, I, O, 2)[0] if it[4] > 1]
+        way = dx_route(T, I, O, 2, 32, True)[1]
+        if cut and way >= 0:
+            assert all(it[6] == 1 for it in cut) and way in (0, 1), (T, I, O)
+            seen += 1
+    assert seen >= 5
