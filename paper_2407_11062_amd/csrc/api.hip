@@ -143,7 +143,7 @@ WsLayout ws_layout(const Problem &p, int op)
     } else {
         if (!fq) l.sz = take(sz_b);
         if (bwd) l.dwhat = take(dwhat_b);
-        // What beside dWhat, for a backward of few tiles; in a workspace that was sized for another token count it may be missing (one launch more then)
+        // What beside dWhat, for a backward of few tiles; in a workspace that was sized for another token count it may be missing (two launches more then)
         l.needed = off;
         if (bwd) { l.what_bytes = eqat::f32_what_bytes(p); l.what = take(l.what_bytes); }
     }
