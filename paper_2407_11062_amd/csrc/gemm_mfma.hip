@@ -277,22 +277,22 @@ DwLaunchPlan plan_dw_of(const Problem &p, int cus, const SkScratch &sk, bool *sm
 
 // ---- what the launches of a backward take, in us, as the two rules below estimate it (fits to single calls, operands cold) ----------
 int64_t tiles_of(int64_t m, int64_t n, int edge_m, int edge_n) { return ((m + edge_m - 1) / edge_m) * ((n + edge_n - 1) / edge_n); }
-// Rounds that `tiles` one-per-compute-unit workgroups cost (workgroups go round the XCDs, 32 compute units each): a few beyond whole rounds are
+// Rounds that `tiles` one-per-compute-unit workgroups cost (workgroups go round the XCDs): a few beyond whole rounds are
 // split where the contraction is long (plan_tiles); else a partly filled round costs less than its share, the clock rises.
-double rounds_cost(int64_t tiles, int per_xcd, double k_tiles, bool dx)
+double rounds_cost(int64_t tiles, int per_xcd, int k_tiles, bool dx)
 {
     const double rounds = (double)((tiles + 7) / 8) / per_xcd, full = (double)(int64_t)rounds, part = rounds - full;
     if (full < 1.0) return 1.0;
     if (part == 0.0) return full;
-    if (full <= 6.0 && part <= 0.5 && k_tiles >= 32.0) return full + part + 0.15;
+    if (full <= 6.0 && part <= 0.5 && k_tiles >= 32) return full + part + 0.15;
     if (!dx) return full + std::max(0.8, __builtin_pow(part, 0.25));
-    return full == 1.0 && k_tiles >= 8.0 ? 1.1 + part : full + __builtin_pow(part, 0.35);
+    return full == 1.0 && k_tiles >= 8 ? 1.1 + part : full + __builtin_pow(part, 0.35);
 }
 // dX in a launch of its own; *tokens: token tile of k_gemm_mid_dx where it takes that, else 0
 double dx_us(const Problem &p, int cus, const SkScratch &sk, int *tokens)
 {
     const int64_t big = tiles_of(p.T, p.I, 256, 256), small = tiles_of(p.T, p.I, 128, 128);
-    const double k_tiles = (double)((p.O + 63) / 64);
+    const int k_tiles = (int)((p.O + 63) / 64);
     double there;
     if (const int parts = ksplit_parts(p, true, sk)) {
         const double pairs = (double)(((p.O + 127) / 128 + parts - 1) / parts), groups = (double)(small * parts);
@@ -300,15 +300,15 @@ double dx_us(const Problem &p, int cus, const SkScratch &sk, int *tokens)
     } else {
         switch (q_tile(p, true, cus, sk)) {
         case TileChoice::Small: there = 4.0 + 0.97 * k_tiles; break;
-        case TileChoice::Big: there = 5.0 + 1.38 * k_tiles * rounds_cost(big, 32, k_tiles, true); break;
+        case TileChoice::Big: there = 5.0 + 1.38 * k_tiles * rounds_cost(big, cus / 8, k_tiles, true); break;
         default: {
             const int64_t c = resident_workgroups(cus, 1) / 8 / ((big + 7) / 8);
-            there = 5.0 + 1.55 * (double)(((int64_t)k_tiles + c - 1) / c) + 0.085 * (double)(big * c);
+            there = 5.0 + 1.55 * (double)((k_tiles + c - 1) / c) + 0.085 * (double)(big * c);
         }
         }
     }
     int bm = 0;
-    const double here = mid_dx_us(p, &bm);
+    const double here = mid_dx_us(p, cus, &bm);
     *tokens = here < there ? bm : 0;
     return std::min(here, there);
 }
@@ -318,35 +318,35 @@ double dw_tile_us(const Problem &p, bool block_ap)
     const double k_tiles = (double)((p.T + 63) / 64);
     return !block_ap ? 12.0 + 1.37 * k_tiles : p.w_bf16 ? 14.5 + 1.38 * k_tiles : 24.0 + 1.65 * k_tiles;
 }
-double dw_us(const Problem &p, bool block_ap)
+double dw_us(const Problem &p, bool block_ap, int cus)
 {
-    const double k_tiles = (double)((p.T + 63) / 64);
-    if (!use_small_dw_tile(p.I, p.O, p.T)) return rounds_cost(tiles_of(p.I, p.O, 256, 256), 32, k_tiles, false) * dw_tile_us(p, block_ap);
+    const int k_tiles = (int)((p.T + 63) / 64);
+    if (!use_small_dw_tile(p.I, p.O, p.T)) return rounds_cost(tiles_of(p.I, p.O, 256, 256), cus / 8, k_tiles, false) * dw_tile_us(p, block_ap);
     const int64_t small = tiles_of(p.I, p.O, 128, 128);
     const double extra = !block_ap ? 0.0 : p.w_bf16 ? 2.0 : 5.0;
-    return small <= 256 ? 6.0 + 0.62 * k_tiles + extra : (7.0 + 0.88 * k_tiles + extra) * rounds_cost(small, 64, k_tiles, false);
+    return small <= cus ? 6.0 + 0.62 * k_tiles + extra : (7.0 + 0.88 * k_tiles + extra) * rounds_cost(small, cus / 4, k_tiles, false);
 }
 
 // A backward that leaves compute units idle altogether, in one launch (every tile of both at once: the longer of them, dW's with the whole epilogue on few
-// compute units) and in two (small tiles of dW).
+// compute units) and in two (small tiles of dW); `dw_share`: tiles of dW per compute unit.
 struct FewTiles { double start, per_share, g32, apart, apart_per_share; };
 FewTiles few_tiles(const Problem &p, bool block_ap)
 {
     if (!block_ap) return {10.0, 7.0, 1.0, 3.3, 2.3};
     return p.w_bf16 ? FewTiles{15.0, 16.0, 2.5, 5.2, 5.0} : FewTiles{16.5, 20.0, 2.5, 6.0, 8.0};
 }
-double bwd_one_round_us(const Problem &p, bool block_ap, int dx, int64_t n2)
+double bwd_one_round_us(const Problem &p, bool block_ap, int dx, double dw_share)
 {
     const FewTiles f = few_tiles(p, block_ap);
     const double k_tiles = (double)((p.T + 63) / 64), steps = (double)((p.O + 127) / 128);
-    const double dw = f.start + 0.96 * k_tiles + f.per_share * (double)n2 / 32.0 + (p.g == 32 ? f.g32 : 0.0);
+    const double dw = f.start + 0.96 * k_tiles + f.per_share * dw_share + (p.g == 32 ? f.g32 : 0.0);
     const double there = dx == kBwdBig ? 6.7 + 1.19 * (double)((p.O + 63) / 64) : dx == 64 ? 5.6 + 0.64 * steps : dx == 96 ? 6.2 + 0.75 * steps : 6.6 + 0.83 * steps;
     return std::max(dw, there) + (DwTileBig::BM % p.g != 0 ? 2.5 : 0.0);
 }
-double bwd_apart_few_us(const Problem &p, bool block_ap, double dx_alone_us, int64_t small)
+double bwd_apart_few_us(const Problem &p, bool block_ap, double dx_alone_us, double dw_share)
 {
     const FewTiles f = few_tiles(p, block_ap);
-    return f.apart + 0.62 * (double)((p.T + 63) / 64) + 1.25 * dx_alone_us + f.apart_per_share * (double)small / 256.0 + (DwTileSmall::BM % p.g != 0 ? 2.0 : 0.0);
+    return f.apart + 0.62 * (double)((p.T + 63) / 64) + 1.25 * dx_alone_us + f.apart_per_share * dw_share + (DwTileSmall::BM % p.g != 0 ? 2.0 : 0.0);
 }
 
 // Token tiles of k_gemm_mid_dx where dX alone takes that kernel, else 0: up to two rounds of its workgroups, where it is estimated to be faster
@@ -363,7 +363,7 @@ int mid_dx_tokens(const Problem &p, int cus, const SkScratch &sk)
 
 // dX and dW in one launch (gemm_bwd.h): what computes dX then (kBwdBig ... 128), or -1: two launches.  Each of the two alone leaves compute units idle in its
 // last round and starts and ends with the whole chip; together the tiles of dW, which come second, fill what those of dX leave.  The estimate deals
-// `n1` tiles of dX and then `n2` of dW out to the 32 compute units of an XCD, and lies between that and an even share.  us, two launches / one
+// `n1` tiles of dX and then `n2` of dW out to the compute units of an XCD, and lies between that and an even share.  us, two launches / one
 // (147 random sizes, 256 to 8192 tokens: 11 % faster in the mean with this rule, 12 % with the best choice at each): 515 tokens, 3 bit, E2E-QP
 // 11008 -> 4096 144 / 122; 1000 tokens, Block-AP, fp32 weights 4096 -> 11008 254 / 234; 4096 tokens, 3 bit, Block-AP 5120 -> 5120 380 / 351 (320 and 400
 // tiles: 1.25 and 1.56 rounds), 13824 -> 5120 967 / 905.  Whole rounds of both gain 1 % (8192 tokens, 4096 -> 4096 410 / 407) or lose it (11008 -> 4096
@@ -381,28 +381,29 @@ int bwd_together(const Problem &p, bool block_ap, int cus, const SkScratch &sk)
     const bool cut = dw.cut;
     if (cut && (small_dw || !dw.sk.split)) return -1;
     int alone = 0, best = -1;
-    const double alone_us = dx_us(p, cus, sk, &alone), apart = 3.0 + alone_us + dw_us(p, block_ap), t2 = dw_tile_us(p, block_ap);
+    const double alone_us = dx_us(p, cus, sk, &alone), apart = 3.0 + alone_us + dw_us(p, block_ap, cus), t2 = dw_tile_us(p, block_ap);
     const int64_t n2 = (tiles_of(p.I, p.O, 256, 256) + 7) / 8, small = tiles_of(p.I, p.O, 128, 128);
+    const int64_t per_xcd = cus / 8;
     double least = 1.0;                               // of the estimates with a margin, as shares of that of two launches
     for (const int dx : {64, 96, 128, (int)kBwdBig}) {
         int64_t n1 = dx == kBwdBig ? tiles_of(p.T, p.I, 256, 256) : tiles_of(p.T, p.I, dx, 128);
-        if (dx != kBwdBig && (cut || n1 > 700)) continue;
+        if (dx != kBwdBig && (cut || n1 * 256 > 700 * (int64_t)cus)) continue;
         n1 = (n1 + 7) / 8;
         double est;
-        if (small_dw && small <= 256 && n1 + n2 <= 32) {
-            est = bwd_one_round_us(p, block_ap, dx, n2) / (0.96 * bwd_apart_few_us(p, block_ap, alone_us, small));
+        if (small_dw && small <= cus && n1 + n2 <= per_xcd) {
+            est = bwd_one_round_us(p, block_ap, dx, (double)n2 / (double)per_xcd) / (0.96 * bwd_apart_few_us(p, block_ap, alone_us, (double)small / cus));
         } else {
             const double t1 = dx == kBwdBig ? 4.6 + 1.26 * (double)((p.O + 63) / 64) : 4.0 + (double)((p.O + 127) / 128) * (dx == 64 ? 0.78 : dx == 96 ? 0.83 : 0.98);
-            // n1 tiles on 32 compute units: `late` of them are done after `a`, the others after `b`
-            const int64_t late = n1 % 32;
-            const double b = (double)(n1 / 32) * t1, a = late ? b + t1 : b, even = ((double)n1 * t1 + (double)n2 * t2) / 32.0;
+            // n1 tiles on the compute units of an XCD: `late` of them are done after `a`, the others after `b`
+            const int64_t late = n1 % per_xcd;
+            const double b = (double)(n1 / per_xcd) * t1, a = late ? b + t1 : b, even = ((double)n1 * t1 + (double)n2 * t2) / (double)per_xcd;
             // the end of the last tile of dW: some whole number of them after a or b
             double end = 1e30;
             for (const double from : {a, b}) {
                 const double first = from + t2 * std::max(0.0, (double)(int64_t)((even - from) / t2) - 2.0);
                 for (int i = 0; i < 8; ++i) {
                     const double at = first + t2 * i;
-                    const int64_t done = late * (int64_t)std::max(0.0, (at - a) / t2 + 1e-9) + (32 - late) * (int64_t)std::max(0.0, (at - b) / t2 + 1e-9);
+                    const int64_t done = late * (int64_t)std::max(0.0, (at - a) / t2 + 1e-9) + (per_xcd - late) * (int64_t)std::max(0.0, (at - b) / t2 + 1e-9);
                     if (done >= n2 && at < end) end = at;
                 }
             }

@@ -33,11 +33,11 @@ template <int BITS, int BM> void launch_t(const MidArgs &a, hipStream_t st)
 }  // namespace
 
 // Rounds of workgroups (one per compute unit) at 0.73 (64 tokens), 0.93 (96) or 1.2 us (128) a step, 3 us between rounds.
-double mid_dx_us(const Problem &p, int *tokens)
+double mid_dx_us(const Problem &p, int cus, int *tokens)
 {
     double best = 1e30;
     for (const int bm : {64, 96, 128}) {
-        const int64_t rounds = (((p.T + bm - 1) / bm) * ((p.I + kMidBN - 1) / kMidBN) + 255) / 256;
+        const int64_t rounds = (((p.T + bm - 1) / bm) * ((p.I + kMidBN - 1) / kMidBN) + cus - 1) / cus;
         if (rounds > 2) continue;
         const double us = 2.7 + (double)rounds * (3.0 + (double)((p.O + 127) / 128) * (bm == 64 ? 0.73 : bm == 96 ? 0.93 : 1.2));
         if (us < best) { best = us; *tokens = bm; }

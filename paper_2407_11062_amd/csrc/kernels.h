@@ -116,7 +116,7 @@ void launch_mid(const Problem &p, const void *X, const void *Wpacked, const floa
 void launch_mid_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, hipStream_t st);
 
 // ---- gemm_mid_dx.hip (dX for few output tiles, on codes in the working layout) -------------------------
-double mid_dx_us(const Problem &p, int *tokens);      // what it takes, as the rule of dispatch estimates it, and with which token tiles; 1e30: too many tiles
+double mid_dx_us(const Problem &p, int cus, int *tokens);      // what it takes, as the rule of dispatch estimates it, and with which token tiles; 1e30: too many tiles
 void launch_mid_dx(const Problem &p, int tokens, const void *dY, const void *codes, const void *sz, void *dX, hipStream_t st);
 
 // ---- train_step.hip (Block-AP step glue: reconstruction loss, AdamW over {W, s, z}) --------------------
