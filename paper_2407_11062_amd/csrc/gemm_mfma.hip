@@ -110,6 +110,9 @@ template <typename K> void allow_dynamic_lds(K kern, size_t smem, uint64_t &done
     done |= (uint64_t)1 << dev;
 }
 
+// Tiles beyond whole rounds are split from this many pairs of K tiles on: two for every contributor there may be.
+bool long_enough_to_split(int pairs) { return pairs >= 2 * kSkMaxSplit; }
+
 // How `resident` workgroups share `ntiles` tiles of `tile` outputs and `pairs` K-tile pairs each (see SkPlan).  One workgroup per tile
 // when they all fit; otherwise whole tiles, except that (K long enough)
 //   - between one and two rounds of tiles, with more than half a round beyond the first, every tile is cut along K into
@@ -135,7 +138,7 @@ SkPlan plan_tiles(int ntiles, int tile, int pairs, int resident, const SkScratch
     // gate) 1.5-2.3 %: the partly filled round that the split replaces ran at a higher clock, and the instantiation that
     // can cut is 1-5 % slower in its main loop.  Beyond six whole rounds the promise is smaller than that price.
     const int n_sk_max = per + (ntiles % 8 ? 1 : 0) - full * W;
-    if (may_cut && full <= 6 && n_sk_max >= 1 && 2 * n_sk_max <= W && pairs >= 2 * kSkMaxSplit) { sk.dp_rounds = full; sk.split = 1; sk.slots = 1; }
+    if (may_cut && full <= 6 && n_sk_max >= 1 && 2 * n_sk_max <= W && long_enough_to_split(pairs)) { sk.dp_rounds = full; sk.split = 1; sk.slots = 1; }
     return sk;
 }
 
@@ -278,13 +281,14 @@ DwLaunchPlan plan_dw_of(const Problem &p, int cus, const SkScratch &sk, bool *sm
 // ---- what the launches of a backward take, in us, as the two rules below estimate it (fits to single calls, operands cold) ----------
 int64_t tiles_of(int64_t m, int64_t n, int edge_m, int edge_n) { return ((m + edge_m - 1) / edge_m) * ((n + edge_n - 1) / edge_n); }
 // Rounds that `tiles` one-per-compute-unit workgroups cost (workgroups go round the XCDs): a few beyond whole rounds are
-// split where the contraction is long (plan_tiles); else a partly filled round costs less than its share, the clock rises.
+// split where the contraction is long (plan_tiles; the parts of dW's cost more, its instantiation for them is slower); else a partly filled round costs less than
+// its share, the clock rises.
 double rounds_cost(int64_t tiles, int per_xcd, int k_tiles, bool dx)
 {
     const double rounds = (double)((tiles + 7) / 8) / per_xcd, full = (double)(int64_t)rounds, part = rounds - full;
     if (full < 1.0) return 1.0;
     if (part == 0.0) return full;
-    if (full <= 6.0 && part <= 0.5 && k_tiles >= 32) return full + part + 0.15;
+    if (full <= 6.0 && part <= 0.5 && long_enough_to_split((k_tiles + 1) / 2)) return full + part + (dx ? 0.15 : 0.3);
     if (!dx) return full + std::max(0.8, __builtin_pow(part, 0.25));
     return full == 1.0 && k_tiles >= 8 ? 1.1 + part : full + __builtin_pow(part, 0.35);
 }

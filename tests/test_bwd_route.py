@@ -13,7 +13,10 @@ APART = [(392, 672, 64, 4, 32, BF16W, 17.1, 23.1), (441, 832, 96, 2, 64, BF16W, 
          (426, 2752, 368, 3, 64, E2E, 20.4, 24.3), (278, 1248, 448, 2, 96, BF16W, 22.2, 25.7), (1, 7744, 272, 2, 32, BF16W, 17.6, 22.5)]
 ONE = [(515, 11008, 4096, 3, -1, E2E, 144, 122), (1000, 4096, 11008, 4, 128, F32W, 254, 234),
        (4096, 5120, 5120, 3, 128, BF16W, 380, 351), (7, 896, 1024, 3, 128, F32W, 22.7, 19.4), (910, 256, 1400, 3, 128, E2E, 29.8, 25.3),
-       (118, 2304, 944, 2, 128, F32W, 23.2, 21.1), (2449, 576, 4224, 4, 96, F32W, 79.8, 67.1)]
+       (118, 2304, 944, 2, 128, F32W, 23.2, 21.1), (2449, 576, 4224, 4, 96, F32W, 79.8, 67.1),
+       # contractions of 31 K tiles, 16 pairs: dX (1921 to 1984 out-features) and dW (as many tokens) alone split tiles
+       (1999, 10624, 1968, 2, 32, BF16W, 223.7, 204.2), (1991, 11744, 1952, 2, 32, E2E, 204.5, 196.1),
+       (1953, 12256, 1960, 2, 32, F32W, 263.4, 245.3)]
 
 
 def together(T, I, O, bits, g, weights):
