@@ -15,14 +15,15 @@ pytestmark = pytest.mark.gpu
 BLOCK_AP = [(269, 1280, 1072, 256, 64, False), (515, 4096, 2568, 32, 96, False), (864, 2208, 2384, 96, 128, False),
             (1710, 3328, 2072, 32, 1, False), (620, 8192, 2688, 128, 0, False), (2200, 4384, 4224, 32, 0, True), (2200, 4384, 4232, 32, 1, True)]
 E2E = [(698, 1792, 3328, 128, 64, False), (515, 4096, 4096, -1, 96, False), (459, 4608, 5504, 32, 128, False),
-       (277, 2304, 3464, 256, 64, False), (1090, 8704, 5376, 64, 0, False), (2926, 1536, 4304, 96, 1, False)]
+       (277, 2304, 3464, 256, 64, False), (1090, 8704, 5376, 64, 0, False), (2926, 1536, 4304, 96, 1, False),
+       (2448, 14112, 1392, 32, 1, True), (2200, 4384, 4224, 32, 0, True)]
 
 
 def cuts_dw(T, I, O):
     return any(it[4] > 1 for _, _, it in items_of_launch(T, I, O, 2)[0])
 
 
-@pytest.mark.parametrize("bits,wdt", [(2, torch.bfloat16), (3, torch.float32), (4, torch.bfloat16)])
+@pytest.mark.parametrize("bits,wdt", [(2, torch.bfloat16), (3, torch.float32), (4, torch.bfloat16), (2, torch.float32), (4, torch.float32)])
 @pytest.mark.parametrize("T,I,O,g,dx,cut", BLOCK_AP)
 def test_block_ap(T, I, O, g, dx, cut, bits, wdt):
     assert (dx_route(T, I, O, bits, g, True, eq.F32 if wdt == torch.float32 else eq.BF16)[1], cuts_dw(T, I, O)) == (dx, cut)
