@@ -372,7 +372,8 @@ Shape shape_of(const Problem &p, bool bt)
 // contributors, 2.5 us and 0.045 per part; a part is at least four pairs.  Two or four whole K tiles are too few for two groups: the
 // tile kernel needs no sum of theirs (forward on a prepared layer, us, there / here: 128 inputs, 150 tokens, 3224 rows 9.1 / 9.8, 3546
 // tokens, 880 rows 10.0 / 10.8; 256 inputs, 617 tokens, 3480 rows 10.8 / 11.6; dX, 128 rows, 74 tokens, 24128 inputs 18.5 / 19.2).
-// Lengths that are no multiple of two K tiles take its slower instantiation and stay here (192 inputs: 12.0 and 10.4).
+// Lengths up to four K tiles that are no multiple of two stay here: the forward is level (71 random sizes 32 to 224 inputs, 1 to 4000 tokens, within 2 % but for one), dX 1 %
+// faster with one pair of K tiles and 5 % with two (69 sizes; 477 tokens, 216 -> 5088 7.5 us here, 8.4 there).
 int ksplit_parts(const Problem &p, bool bt, const SkScratch &sk)
 {
     if (!p.act_bf16 || p.T < 1 || !group_by_magic(p)) return 0;

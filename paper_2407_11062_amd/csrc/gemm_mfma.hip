@@ -303,7 +303,7 @@ double dx_us(const Problem &p, int cus, const SkScratch &sk, int *tokens)
         there = (parts == 1 ? 5.8 : 6.5 + 0.03 * groups) + pairs * (0.8 + 0.5 * groups / 256.0 * std::min(1.0, pairs / 32.0));
     } else {
         switch (q_tile(p, true, cus, sk)) {
-        case TileChoice::Small: there = 4.0 + 0.97 * k_tiles; break;
+        case TileChoice::Small: there = 4.0 + 0.97 * k_tiles; break;       // operands cold; q_tile and the forward's rule weigh these tiles at 0.9, in fits of their own
         case TileChoice::Big: there = 5.0 + 1.38 * k_tiles * rounds_cost(big, cus / 8, k_tiles, true); break;
         default: {
             const int64_t c = resident_workgroups(cus, 1) / 8 / ((big + 7) / 8);
