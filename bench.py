@@ -74,8 +74,8 @@ def profile_kernels(torch, eq, fn, steps):
     return eq.eqat_profile_stop()
 
 
-def step_row(torch, eq, fn, flops, tokens, flop_per_launch, args, peaks):
-    """One fwd+bwd step of a block: step time (mean / median / min), TFLOP/s, and the three GEMM kernels per launch."""
+def step_row(torch, eq, fn, flops, tokens, flop, args, peaks):
+    """One fwd+bwd step of a block: step time (mean / median / min), TFLOP/s, and its GEMM launches (`flop`: see gemm_flop)."""
     t = time_steps(torch, fn, args.steps, 2)
     prof = profile_kernels(torch, eq, fn, max(5, args.steps // 2))
     tf = flops / (t["mean_ms"] * 1e-3) / 1e12
@@ -85,7 +85,7 @@ def step_row(torch, eq, fn, flops, tokens, flop_per_launch, args, peaks):
            "pct_of_bf16_mfma_peak": round(100 * tf / PEAK_BF16_TFLOPS, 2),
            "frac_of_measured_mfma_peak": frac_measured(tf, peaks),
            "tokens_per_s_per_layer": round(tokens / (t["mean_ms"] * 1e-3), 1),
-           "kernels": kernel_table(prof, flop_per_launch, peaks)}
+           "kernels": kernel_table(prof, flop, peaks)}
     return row
 
 
@@ -94,23 +94,27 @@ def frac_measured(tflops, peaks):
     return round(tflops / m, 4) if m else None
 
 
-def launch_flop(prof, k, flop_per_launch):
-    """Mean flop of a launch of GEMM class k (flop_per_launch: of one GEMM, mean over the linears); gemm_bwd is dX and dW in one launch.  None where some linears
-    run their backward in one launch and some in two: the mean over all linears is that of neither."""
-    if k == "gemm_fwd":
-        return flop_per_launch
-    if "gemm_bwd" in prof and ("gemm_dx" in prof or "gemm_dw" in prof):
-        return None
-    return 2 * flop_per_launch if k == "gemm_bwd" else flop_per_launch
+def gemm_flop(eq, layers, T, bits, g, block_ap):
+    """Mean flop of a launch of every GEMM class over a step of these linears: the library says which of them run dX and dW in one launch (gemm_bwd)
+    and which in two."""
+    import ctypes
+    flop = {}
+    for L in layers:
+        one, route = 2.0 * T * L["O"] * L["I"], (ctypes.c_int32 * 2)(0, -1)
+        d = eq.make_desc(T, L["I"], L["O"], bits, g, eq._dt(L["X"]), eq._dt(L["W"]))
+        eq.lib().eqat_dx_route(ctypes.byref(d), int(block_ap), route)       # refuses fp32 activations, which have no such launches
+        backward = {"gemm_bwd": 2 * one} if route[1] >= 0 else {"gemm_dx": one, "gemm_dw": one}
+        for k, v in {"gemm_fwd": one, **backward}.items():
+            flop.setdefault(k, []).append(v)
+    return {k: sum(v) / len(v) for k, v in flop.items()}
 
 
-def kernel_table(prof, flop_per_launch, peaks):
+def kernel_table(prof, flop, peaks):
     out = {}
     for k, (ms, n) in prof.items():
         out[k] = {"launches": n, "avg_ms": round(ms / n, 4)}
-        flop = launch_flop(prof, k, flop_per_launch) if k.startswith("gemm_") else None
-        if flop is not None:
-            tf = flop / (ms / n * 1e-3) / 1e12
+        if k in flop:
+            tf = flop[k] / (ms / n * 1e-3) / 1e12
             out[k].update({"tflops": round(tf, 2), "frac": round(tf / PEAK_BF16_TFLOPS, 4),
                            "frac_of_measured_peak": frac_measured(tf, peaks)})
     return out
@@ -226,12 +230,12 @@ def main():
     ms_step = t["mean_ms"]
     tflops = flops_step / (ms_step * 1e-3) / 1e12
 
-    # dominant kernel of the step: the GEMM kernels do 2*T*I*O flop per launch, dX and dW in one launch twice that
-    flop_per_launch = 2.0 * T * sum_io / len(layers)          # mean over the seven shapes
-    gemms = {k: v for k, v in prof.items() if k.startswith("gemm_") and launch_flop(prof, k, flop_per_launch) is not None}
+    # dominant kernel of the step
+    flop = gemm_flop(eq, layers, T, bits, g, True)
+    gemms = {k: v for k, v in prof.items() if k in flop}
     dom = max(gemms, key=lambda k: gemms[k][0])
     dom_ms, dom_n = gemms[dom]
-    flop_per_launch = launch_flop(prof, dom, flop_per_launch)
+    flop_per_launch = flop[dom]
     dom_tflops = flop_per_launch / (dom_ms / dom_n * 1e-3) / 1e12
     traffic = None
     tpath = os.path.join(ROOT, "profiles", "hbm_traffic.json")
@@ -244,7 +248,7 @@ def main():
                 "traffic": traffic, "traffic_source": "profiles/hbm_traffic.json (rocprofv3 --pmc runs of this bench, committed)",
                 "avg_launch_ms": round(dom_ms / dom_n, 4), "launches": dom_n,
                 "flop_per_launch": flop_per_launch}
-    kernels = kernel_table(prof, 2.0 * T * sum_io / len(layers), peaks)
+    kernels = kernel_table(prof, flop, peaks)
     if "quantize" in prof:
         # W and (s, z) in; codes, clamp bit-plane and (s, zbar) pairs out
         # (one launch per step over all linears of the block)
@@ -388,10 +392,10 @@ def config_rows(torch, eq, synth, dev, args, peaks, name, phases=("block_ap", "e
     layers = build_layers(torch, eq, synth, wl, dev)
     T, bits, g = wl.tokens, wl.bits, wl.group
     sum_io = sum(L["O"] * L["I"] for L in layers)
-    fpl = 2.0 * T * sum_io / len(layers)
     out = {"tokens": T, "bits": bits, "group": g, "linears": len(layers)}
     if "block_ap" in phases:
-        out["block_ap"] = step_row(torch, eq, lambda: run_block_ap_step(eq, layers, bits, g), 6.0 * T * sum_io, T, fpl, args, peaks)
+        out["block_ap"] = step_row(torch, eq, lambda: run_block_ap_step(eq, layers, bits, g), 6.0 * T * sum_io, T,
+                                   gemm_flop(eq, layers, T, bits, g, True), args, peaks)
     packed = pack_block(torch, eq, layers, bits, g, T, dev)
     if "eqat_pack" in phases:
         pb = eq.Batch(layers[0]["batch"].descs if "batch" in layers[0] else block_batch(eq, layers, bits, g, T).descs,
@@ -402,7 +406,8 @@ def config_rows(torch, eq, synth, dev, args, peaks, name, phases=("block_ap", "e
             eq.eqat_pack_batched(pb)
         out["eqat_pack"] = hbm_row(torch, eq, pack_all, sum_io * (2 + 8.0 / g + bits / 8.0 + bits / (8.0 * g)), args, peaks)
     if "e2e_qp" in phases:
-        out["e2e_qp"] = step_row(torch, eq, lambda: run_e2e_step(eq, layers, packed, bits, g), 6.0 * T * sum_io, T, fpl, args, peaks)
+        out["e2e_qp"] = step_row(torch, eq, lambda: run_e2e_step(eq, layers, packed, bits, g), 6.0 * T * sum_io, T,
+                                 gemm_flop(eq, layers, T, bits, g, False), args, peaks)
     del layers, packed
     torch.cuda.empty_cache()
     return out
@@ -416,15 +421,15 @@ def measure_other_rows(torch, eq, layers, bits, g, adt, dev, args, peaks):
     packed = pack_block(torch, eq, layers, bits, g, T2, dev)
     sum_io = sum(L["O"] * L["I"] for L in layers)
     fl = 6.0 * T2 * sum_io
-    fpl = 2.0 * T2 * sum_io / len(layers)
+    flop = gemm_flop(eq, layers, T2, bits, g, False)
     # BASELINE configuration 3: E2E-QP on the 7B block, 4096 tokens
-    rows["e2e_qp_fwd_bwd"] = step_row(torch, eq, lambda: run_e2e_step(eq, layers, packed, bits, g), fl, T2, fpl, args, peaks)
+    rows["e2e_qp_fwd_bwd"] = step_row(torch, eq, lambda: run_e2e_step(eq, layers, packed, bits, g), fl, T2, flop, args, peaks)
     # the same step with step sizes AND zero points trained (zero points kept in floating point, dz from the same epilogue)
     zf = [(L["z"].clamp(0, 2 ** bits - 1) + 0.25).contiguous() for L in layers]
     outz = [{"dX": P["out"]["dX"], "ds": P["out"]["ds"], "dz": torch.empty_like(L["s"])} for L, P in zip(layers, packed)]
 
     rows["e2e_qp_fwd_bwd_trained_s_z"] = step_row(torch, eq, lambda: run_e2e_step(eq, layers, packed, bits, g, zf, outz),
-                                                  fl, T2, fpl, args, peaks)
+                                                  fl, T2, flop, args, peaks)
     wbytes = 2 if adt == torch.bfloat16 else 4
 
     descs = block_batch(eq, layers, bits, g, T2).descs
@@ -533,7 +538,7 @@ def master_weight_row(torch, eq, dev, args, peaks, name):
     layers = build_layers(torch, eq, synth, wl, dev, w_dtype=torch.float32)
     sum_io = sum(L["O"] * L["I"] for L in layers)
     row = step_row(torch, eq, lambda: run_block_ap_step(eq, layers, wl.bits, wl.group), 6.0 * wl.tokens * sum_io, wl.tokens,
-                   2.0 * wl.tokens * sum_io / len(layers), args, peaks)
+                   gemm_flop(eq, layers, wl.tokens, wl.bits, wl.group, True), args, peaks)
     del layers
     torch.cuda.empty_cache()
     return row
