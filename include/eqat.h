@@ -202,7 +202,8 @@ eqat_status eqat_qlinear_fwd(const eqat_desc *d, const void *X, const uint8_t *W
 /*
  * E2E-QP backward (Sec. 3.3): dX = dY * What and
  *   ds[o,j] = sum over group of (dY^T X)[o,i] * (w_q[o,i] - z[o,j]).
- * dX or ds may be NULL (skipped).  d->w_dtype is ignored.
+ * dX or ds may be NULL (skipped); as in eqat_fq_linear_bwd, ds does not depend on which is asked for, dX may in the order of its sums (so, too, in the
+ * calls below).  d->w_dtype is ignored.
  */
 eqat_status eqat_qlinear_bwd(const eqat_desc *d, const void *X, const uint8_t *Wpacked, const float *s,
                              const uint8_t *zpacked, const void *dY, void *dX, float *ds,

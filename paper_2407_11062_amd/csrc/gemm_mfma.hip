@@ -357,7 +357,7 @@ double bwd_apart_few_us(const Problem &p, bool block_ap, double dx_alone_us, dou
 // than k_gemm_ksplit or the tiles of k_gemm_q.  196 random sizes, 50 to 2200 tokens, 768 to 12000 in-features, 768 to 16000 out-features: the rule
 // takes no kernel more than 2 % slower than the one it leaves and is within 1 % of the best choice in the mean; 8 % faster in the mean, 25 to 50 %
 // where one or two rounds are well filled.  us, that kernel / here: 515 tokens, 3 bit 4096 -> 4096 37.7 / 31.8, 11008 -> 4096 99 / 74; 1000
-// tokens, 4 bit 11008 -> 4096 128 / 107, 4096 -> 4096 level.
+// tokens, 4 bit 11008 -> 4096 128 / 107, 4096 -> 4096 level.  830 more sizes, 1 to 20000 tokens and down to 64 in- and out-features: 4 % faster in the mean, five 2 to 5 % slower.
 int mid_dx_tokens(const Problem &p, int cus, const SkScratch &sk)
 {
     int tokens = 0;
@@ -373,8 +373,8 @@ int mid_dx_tokens(const Problem &p, int cus, const SkScratch &sk)
 // tiles: 1.25 and 1.56 rounds), 13824 -> 5120 967 / 905.  Whole rounds of both gain 1 % (8192 tokens, 4096 -> 4096 410 / 407) or lose it (11008 -> 4096
 // 1095 / 1101), and a single filled round of each does not care.  Where both together fill one round at most, the one launch takes as long as the longer of the
 // two, and dW in big tiles, an epilogue on a quarter of the compute units, is longer than in small ones: estimates of their own (fits to 1420 random sizes,
-// 1 to 9000 tokens, 200 to 14000 in-features, 64 to 14000 out-features; with the others in their place 157 calls were 5 % slower and up to 36 %, now 13 and 12 %,
-// and the mean gains 2 % more): 426 tokens, E2E-QP, 2752 -> 368 20.4 / 24.3 and 278 tokens, Block-AP, 1248 -> 448 22.2 / 25.7 stay apart.
+// 1 to 9000 tokens, 200 to 14000 in-features, 64 to 14000 out-features; with the others in their place 163 calls were 5 to 39 % slower than two launches, now 19
+// are, 13 % at most, and all are 8 % faster in the mean, 6 % before, 9 % with the best choice at each): 426 tokens, E2E-QP, 2752 -> 368 20.4 / 24.3 and 278 tokens, Block-AP, 1248 -> 448 22.2 / 25.7 stay apart.
 int bwd_together(const Problem &p, bool block_ap, int cus, const SkScratch &sk)
 {
     if (p.T < 1) return -1;

@@ -29,7 +29,8 @@ import json
 import sys
 
 # kernel-name fragment -> name the library's own timers use
-KERNELS = (("k_gemm_q<", None), ("k_gemm_dw", "gemm_dw"), ("k_gemm_bwd", "gemm_bwd"), ("k_quantize", "quantize"), ("k_init_minmax", "init_minmax"),
+KERNELS = (("k_gemm_q<", None), ("k_gemm_dw", "gemm_dw"), ("k_gemm_bwd", "gemm_bwd"), ("k_gemm_mid_dx", "gemm_dx"), ("k_gemm_mid", "gemm_fwd"),
+           ("k_quantize", "quantize"), ("k_init_minmax", "init_minmax"),
            ("k_e2e_prepare", "e2e_prepare"), ("k_gemv", "gemv"), ("k_recon_loss", "recon_loss"), ("k_adamw", "adamw_update"))
 
 
