@@ -45,7 +45,7 @@ def test_host_side_of_the_library_passes_its_abi_and_work_plan_tests_under_asan_
     assert b.returncode == 0, (b.stdout + b.stderr)[-3000:]
     # (all of them but the one that links a plain gcc program against the library: that program has no sanitizer runtime)
     r = subprocess.run([sys.executable, "-m", "pytest", "-x", "-q", "-p", "no:cacheprovider", "-k", "not plain_c",
-                        *(os.path.join(ROOT, "tests", f) for f in ("test_host_abi.py", "test_work_plan.py", "test_shared_tiles_plan.py", "test_workspace_parts.py"))],
+                        *(os.path.join(ROOT, "tests", f) for f in ("test_host_abi.py", "test_work_plan.py", "test_shared_tiles_plan.py", "test_workspace_parts.py", "test_bwd_route.py"))],
                        cwd=ROOT, env=_env(rts[0], EQAT_LIB=str(lib)), capture_output=True, text=True, timeout=900)
     tail = (r.stdout + r.stderr)[-3000:]
     assert r.returncode == 0, tail
