@@ -6,12 +6,15 @@ import torch
 
 import paper_2407_11062_amd as eq
 from paper_2407_11062_amd import synth
+from test_gpu_mid_dx import dx_route
 
 pytestmark = pytest.mark.gpu
 
 
-def test_block_ap_and_e2e_steps_replay_from_a_graph():
-    T, I, O, bits, g = 300, 384, 264, 2, 64
+# two launches in the Block-AP backward; dX and dW in one, dX on 64-token tiles; in one, tiles of dW split along the tokens
+@pytest.mark.parametrize("T,I,O,bits,g,way", [(300, 384, 264, 2, 64, -1), (269, 1280, 1072, 3, 256, 64), (2200, 4384, 4224, 2, 32, 0)])
+def test_block_ap_and_e2e_steps_replay_from_a_graph(T, I, O, bits, g, way):
+    assert dx_route(T, I, O, bits, g, True)[1] == way
     dev = torch.device("cuda:0")
     W = synth.normal((O, I), 0.02, synth.seed_of("graph", "W"), torch.bfloat16).to(dev)
     s, z = eq.eqat_init_minmax(W, bits, g)

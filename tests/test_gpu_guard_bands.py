@@ -61,6 +61,8 @@ CASES = [
     ("mid_64", 100, 1056, 200, 3, 32, torch.bfloat16, torch.bfloat16),              # ... k_gemm_mid, 64- and 96-token tiles
     ("mid_96", 381, 1056, 5480, 4, 32, torch.bfloat16, torch.bfloat16),
     ("mid_relaid", 450, 3520, 8200, 3, 32, torch.bfloat16, torch.bfloat16),         # ... behind a re-layout of the codes
+    ("bwd_64", 7, 160, 1352, 4, 32, torch.bfloat16, torch.float32),                 # dX and dW in one launch, 64- and 96-token tiles of dX, fp32 dW
+    ("bwd_96", 848, 1824, 1472, 4, 32, torch.bfloat16, torch.float32),
     ("fp32_short", 40, 1056, 31, 4, 32, torch.float32, torch.float32),
     ("fp32_tile_per_wave", 20, 2080, 1043, 2, 32, torch.float32, torch.float32),
 ]
