@@ -7,9 +7,9 @@ namespace eqat {
 
 // ---------------------------------------------------------------------------------------------
 // Eq.(1) for one weight.  The code must equal clamp(round_half_even(fl32(w/s)) + zbar, 0, Qmax) exactly.  The exact
-// quotient costs a dozen instructions, so k_quantize first uses w * (1/s), which is within 2^-22 relative of it; only
-// a chunk in which some product lies too close to a rounding tie - where the cheap and the exact quotient could round
-// differently - is redone with this exact division.
+// quotient costs a dozen instructions, so k_quantize first rounds w * r for an r just below and one just above 1/s (2^-21
+// relative, where the reciprocal is within 2^-23 and the quotient's own rounding 2^-24): rounding is monotonic, so where both
+// give the same integer, fl32(w/s) gives it too.  A chunk in which some weight's differ is redone with this exact division.
 __device__ __forceinline__ float quant_exact(float w, float s) { return __builtin_rintf(w / s); }
 
 template <typename WT> struct Chunk8;   // 8 consecutive weights of one lane
@@ -17,6 +17,7 @@ template <> struct Chunk8<bf16_t> {
     static constexpr int kBytes = 16;
     uintx4 v;
     __device__ __forceinline__ void load(const bf16_t *p) { v = *reinterpret_cast<const uintx4 *>(p); }
+    __device__ __forceinline__ void load_once(const bf16_t *p) { v = __builtin_nontemporal_load(reinterpret_cast<const uintx4 *>(p)); }
     __device__ __forceinline__ float get(int k) const
     {
         const uint32_t u = v[k >> 1];
@@ -45,15 +46,30 @@ __device__ __forceinline__ uint32_t quad_bcast(uint32_t v, int k)
     }
 }
 
+// Place of the code k of a lane's eight: bit 3 k of the dense stream (2, 4 k); in the working layout byte k % 4, field k / 4.
+template <bool WORK, int BITS> __host__ __device__ constexpr int code_place(int k) { return WORK ? 8 * (k % 4) + WorkCodes<BITS>::kField * (k / 4) : k * BITS; }
+// the same word at all eight places, added up
+template <bool WORK, int BITS> __host__ __device__ constexpr uint32_t packed_sum(uint32_t v)
+{
+    uint32_t p = 0;
+    for (int k = 0; k < 8; ++k) p += v << code_place<WORK, BITS>(k);
+    return p;
+}
+// From here on floats are integers, and what is added to it is rounded to one, ties to even: the low bits of kIntegers + n are n.
+constexpr float kIntegers = 0x1.8p23f;
+
 // The quantize pass.  One lane owns 8 consecutive weights (a 16- or 32-byte load); the four lanes of a
 // quad own one 32-code segment, i.e. BITS output words, assembled with quad permutes.
 //   codes     [O, I*BITS/32] words      packed stream (same layout as eqat_pack's Wpacked)
 //   clampbits [O, I/8] bytes (CLAMPBITS) bit k of byte e/8: weight e was clamped by Eq.(1)
 //   sz        [O, G] float2 or NULL     (s, zbar) per group, zbar = clamp(round(z), 0, Qmax)
 // Rows are contiguous and g divides I, so weight e belongs to group e / g of the flattened [O*G] arrays.
-// Per weight the common path costs: widen, multiply, round, two ops of tie test, clamp, convert, shift-add.
-// The clamp is applied to round(w/s) against [-zbar, Qmax - zbar] and zbar is added once, as an integer, to
-// all eight packed fields (the per-field sums stay inside [0, Qmax], so no carry crosses a field).
+// Per weight the common path costs six instructions: widen, two fused multiply-adds that round to an integer (kIntegers + zbar is
+// added; a tie, which an odd zbar would turn the other way, is a chunk for the exact path), their comparison, the clamp, a shift-add of the
+// float as it is (the exponents of all eight add up to a constant).  With the clamp plane two more.  With the ten there were before (multiply,
+// round, difference, maximum, clamp, conversion, shift-add, and three for the clamp plane) the pass was bound by its arithmetic: seven matrices of a
+// 4096 / 11008 block, bf16, quantize 99 -> 94 us, and 84 with W, which nobody reads soon again, loaded past the caches (non-temporal); pack 94 -> 86,
+// where the end of W comes from the memory-side cache and such loads lose 1-3 %; fp32 weights do not gain by them either (189 and 192 us).
 // WORK = false: the dense stream of the C ABI (eqat_pack).  WORK = true: the library's working layout (WorkCodes).
 // Zero points at N bits: one thread per output word (tail bits of a row are zero).
 template <int BITS>
@@ -137,7 +153,8 @@ __global__ __launch_bounds__(256) void k_quantize(const QuantizeBatch batch)
         const uint32_t cc = c < a.n_chunks ? c : 0u;             // past the end: recompute chunk 0, store nothing
         const uint32_t e = cc * 8u;
         gi[u] = a.g_shift >= 0 ? (e >> a.g_shift) : (e / a.g);
-        ch[u].load(W + e);
+        if constexpr (WORK && sizeof(WT) == 2) ch[u].load_once(W + e);
+        else ch[u].load(W + e);
         sv[u] = a.s[gi[u]];
         zb[u] = a.z[gi[u]];
     }
@@ -150,36 +167,39 @@ __global__ __launch_bounds__(256) void k_quantize(const QuantizeBatch batch)
         const float zbar = zbar_of(zb[u], qmax);
         if (a.sz != nullptr && e == gi[u] * a.g) { floatx2 o; o[0] = sv[u]; o[1] = zbar; a.sz[gi[u]] = o; }
         const float rinv = __builtin_amdgcn_rcpf(sv[u]);          // 1 ulp; s is a normal number
-        const float lo = -zbar, hi = qmax - zbar;
-        // Far from a rounding tie the cheap quotient w * rcp(s) (within 2^-22 relative of w/s) rounds like the exact one.
-        // Only weights whose code is not clamped matter, and for those |w/s| <= |zbar| + Qmax + 1.
-        const float thr = 0.5f - 0x1p-20f * (__builtin_fabsf(zbar) + qmax + 2.0f);
-        float r[8];
-        float worst = 0.0f;
+        const float below = rinv * (1.0f - 0x1p-21f), above = rinv * (1.0f + 0x1p-21f), base = kIntegers + zbar;
+        float f[8];
+        uint32_t differ = 0;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const float t = ch[u].get(k) * rinv;
-            r[k] = __builtin_rintf(t);
-            worst = __builtin_fmaxf(worst, __builtin_fabsf(t - r[k]));
+            const float w = ch[u].get(k), other = __builtin_fmaf(w, above, base);
+            f[k] = __builtin_fmaf(w, below, base);
+            differ |= __float_as_uint(f[k]) ^ __float_as_uint(other);
+            asm("" : "+v"(differ));                                // one v_bitop3 a weight, not a comparison and two selects
         }
-        if (worst >= thr) {
+        if (differ != 0) {
 #pragma unroll
-            for (int k = 0; k < 8; ++k) r[k] = quant_exact(ch[u].get(k), sv[u]);
+            for (int k = 0; k < 8; ++k) f[k] = quant_exact(ch[u].get(k), sv[u]) + base;
         }
-        uint32_t p = 0, cb = 0;
+        float fc[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) fc[k] = __builtin_amdgcn_fmed3f(f[k], kIntegers, kIntegers + qmax);
+        if constexpr (CLAMPBITS) {
+            uint32_t cb = 0;
+#pragma unroll
+            for (int k = 7; k >= 0; --k)                           // cb = 2 cb + (clamped)
+                asm("v_cmp_ne_u32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(cb) : "v"(fc[k]), "v"(f[k]) : "vcc");
+            a.clampbits[c] = (uint8_t)cb;
+        }
+        // the codes at their places in a word
+        uint32_t p = 0u - packed_sum<WORK, BITS>(__builtin_bit_cast(uint32_t, kIntegers));
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            p += __float_as_uint(fc[k]) << code_place<WORK, BITS>(k);
+            asm("" : "+v"(p));                                     // one v_lshl_add a weight
+        }
         if constexpr (!WORK) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const float qc = __builtin_amdgcn_fmed3f(r[k], lo, hi);      // lo <= hi: the median is the clamp
-                p += (uint32_t)(int)qc << (k * BITS);          // two's complement: fields may be negative until zbar is added
-                if (CLAMPBITS) cb |= (qc != r[k] ? 1u : 0u) << k;
-            }
-            constexpr uint32_t ones = BITS == 2 ? 0x5555u : BITS == 3 ? 0x249249u : 0x11111111u;   // a one in every field
-            p += (uint32_t)(int)zbar * ones;
-            if (CLAMPBITS) a.clampbits[c] = (uint8_t)cb;
-
-            const uint32_t pu = p & (BITS == 4 ? 0xFFFFFFFFu : ((1u << (8 * BITS)) - 1u));
-            const uint32_t p0 = quad_bcast(pu, 0), p1 = quad_bcast(pu, 1), p2 = quad_bcast(pu, 2), p3 = quad_bcast(pu, 3);
+            const uint32_t p0 = quad_bcast(p, 0), p1 = quad_bcast(p, 1), p2 = quad_bcast(p, 2), p3 = quad_bcast(p, 3);
             uint32_t word;
             if constexpr (BITS == 2) {
                 word = (q4 == 0) ? (p0 | (p1 << 16)) : (p2 | (p3 << 16));
@@ -190,23 +210,11 @@ __global__ __launch_bounds__(256) void k_quantize(const QuantizeBatch batch)
             }
             if (q4 < (uint32_t)BITS) a.codes[(c >> 2) * BITS + q4] = word;
         } else {
-            // working layout: this lane's code k goes to byte k % 4, field k / 4 (+ 2 fields for the odd lane of a 2-bit pair)
-            constexpr int F = WorkCodes<BITS>::kField;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const float qc = __builtin_amdgcn_fmed3f(r[k], lo, hi);
-                p += (uint32_t)(int)qc << (8 * (k % 4) + F * (k / 4));
-                if (CLAMPBITS) cb |= (qc != r[k] ? 1u : 0u) << k;
-            }
-            constexpr uint32_t ones = BITS == 2 ? 0x05050505u : 0x11111111u;
-            p += (uint32_t)(int)zbar * ones;
-            if (CLAMPBITS) a.clampbits[c] = (uint8_t)cb;
             if constexpr (BITS == 2) {
-                const uint32_t mine = p & 0x0F0F0F0Fu;
-                const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
-                if ((q4 & 1u) == 0) a.codes[(c >> 2) * 2 + (q4 >> 1)] = mine | (other << 4);
+                const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)p, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
+                if ((q4 & 1u) == 0) a.codes[(c >> 2) * 2 + (q4 >> 1)] = p | (other << 4);
             } else {
-                a.codes[c] = p & WorkCodes<BITS>::kByteMask * 0x11u;
+                a.codes[c] = p;
             }
         }
     }
@@ -320,51 +328,96 @@ __global__ __launch_bounds__(256) void k_unpack_work(const uint32_t *__restrict_
 }
 
 // ---------------------------------------------------------------------------------------------
-// min/max initialisation.  LPG = lanes per group (g/8), a power of two <= 64: one lane reduces its 8
-// weights, an xor butterfly reduces the group.
+// min/max initialisation: one lane reduces a piece of 16 bytes, a butterfly over lanes the pieces of a group.
+template <typename WT> constexpr int kMinmaxPieces = sizeof(WT) == 4 ? 8 : 4;      // pieces per lane: 64 / 128 bytes in flight
 struct InitBatch {
     const void *W[kMaxBatch]; float *s[kMaxBatch], *z[kMaxBatch];
-    uint32_t n[kMaxBatch];                 // chunks of 8 weights (small kernel) / groups (wave kernel)
+    uint32_t n[kMaxBatch];                 // pieces of 16 bytes (small kernel) / groups (wave kernel)
     uint32_t g[kMaxBatch];                 // group size (wave kernel)
     uint32_t first[kMaxBatch + 1];
 };
 
+__device__ __forceinline__ void minmax_to_sz(float lo, float hi, float qmax, float *s, float *z)
+{
+    float step = (hi - lo) / qmax;
+    if (!(step >= 1e-10f)) step = 1e-10f;
+    const float zf = __builtin_rintf((-lo) / step);
+    *s = step;
+    *z = __builtin_fminf(__builtin_fmaxf(zf, 0.0f), qmax);
+}
+
+// One step of a butterfly over the lanes of a row, for four minima and maxima at a time: one instruction each (through LDS two and a
+// wait).  Two wait states lie between the write of a register and its read by another lane.
+#define EQAT_MINMAX_DPP(CTRL)                                                                                                     \
+    asm("s_nop 1\n\tv_min_f32_dpp %0, %0, %0 " CTRL "\n\tv_max_f32_dpp %4, %4, %4 " CTRL "\n\tv_min_f32_dpp %1, %1, %1 " CTRL          \
+        "\n\tv_max_f32_dpp %5, %5, %5 " CTRL "\n\tv_min_f32_dpp %2, %2, %2 " CTRL "\n\tv_max_f32_dpp %6, %6, %6 " CTRL                \
+        "\n\tv_min_f32_dpp %3, %3, %3 " CTRL "\n\tv_max_f32_dpp %7, %7, %7 " CTRL                                                    \
+        : "+v"(lo[0]), "+v"(lo[1]), "+v"(lo[2]), "+v"(lo[3]), "+v"(hi[0]), "+v"(hi[1]), "+v"(hi[2]), "+v"(hi[3]))
+// minima and maxima over LANES neighbouring lanes, in all of them
+template <int U, int LANES> __device__ __forceinline__ void group_minmax(float *lo, float *hi)
+{
+#pragma unroll
+    for (int u = 0; u < U; u += 4, lo += 4, hi += 4) {
+        EQAT_MINMAX_DPP("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf");
+        EQAT_MINMAX_DPP("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf");
+        if constexpr (LANES >= 8) EQAT_MINMAX_DPP("row_half_mirror row_mask:0xf bank_mask:0xf");
+        if constexpr (LANES >= 16) EQAT_MINMAX_DPP("row_mirror row_mask:0xf bank_mask:0xf");
+#pragma unroll
+        for (int m = 16; m < LANES; m <<= 1)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                lo[k] = __builtin_fminf(lo[k], __shfl_xor(lo[k], m));
+                hi[k] = __builtin_fmaxf(hi[k], __shfl_xor(hi[k], m));
+            }
+    }
+}
+#undef EQAT_MINMAX_DPP
+
+// A lane takes pieces of 16 bytes, eight weights (bf16) or four (fp32), neighbouring lanes neighbouring pieces; a wave takes U runs of 64 pieces.
+// LPG = pieces of a group.  The two divisions of a group cost as much as its reduction: the lanes of a group take a run each.
+// (One group at a time through LDS, with the divisions in one lane of the group: 4096 x 4096 bf16, min/max + pack, 20.4 us, so 17.7 with the
+// leaner pack; the block's seven matrices 82 -> 74 alone.  Loads past the caches gain 5 us there, and the pack that follows loses them.)
 template <typename WT, int LPG>
 __global__ __launch_bounds__(256) void k_init_minmax_small(const InitBatch b, float qmax)
 {
-    constexpr int U = kQuantUnroll;
+    constexpr int PIECE = 16 / (int)sizeof(WT), U = kMinmaxPieces<WT>, LANES = LPG < 64 ? LPG : 64;
     const int slot = batch_slot(b.first, blockIdx.x);
     const WT *__restrict__ W = reinterpret_cast<const WT *>(b.W[slot]);
     float *__restrict__ s = b.s[slot], *__restrict__ z = b.z[slot];
-    const uint32_t n_chunks = b.n[slot];
-    const uint32_t c0 = (blockIdx.x - b.first[slot]) * (256u * U) + threadIdx.x;
-    // n_chunks % LPG == 0 and 256 % LPG == 0: a group never straddles the end of the array or of a 256-chunk slice
-    Chunk8<WT> ch[U];
+    const uint32_t n = b.n[slot], lane = threadIdx.x & 63u;
+    // n % LPG == 0: a group never straddles the end of the array.  The runs of a workgroup's waves take turns in memory; where a group is two runs
+    // long, those of a wave follow one another.
+    constexpr uint32_t STRIDE = LPG == 128 ? 64u : 256u;
+    const uint32_t c0 = (blockIdx.x - b.first[slot]) * (256u * U) + (STRIDE == 64u ? (threadIdx.x >> 6) * (64u * U) + lane : threadIdx.x);
+    uintx4 v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const uint32_t c = c0 + u * 256u;
-        ch[u].load(W + (size_t)(c < n_chunks ? c : 0u) * 8);
+        const uint32_t c = c0 + u * STRIDE;
+        v[u] = *reinterpret_cast<const uintx4 *>(W + (size_t)(c < n ? c : 0u) * PIECE);
     }
+    float lo[U], hi[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const uint32_t c = c0 + u * 256u;
-        if (c >= n_chunks) break;
-        float lo = ch[u].get(0), hi = lo;
+        auto get = [&](int k) { return sizeof(WT) == 4 ? __uint_as_float(v[u][k & 3]) : __uint_as_float(k & 1 ? v[u][k >> 1] & 0xFFFF0000u : v[u][k >> 1] << 16); };
+        lo[u] = hi[u] = get(0);
 #pragma unroll
-        for (int k = 1; k < 8; ++k) { lo = __builtin_fminf(lo, ch[u].get(k)); hi = __builtin_fmaxf(hi, ch[u].get(k)); }
+        for (int k = 1; k < PIECE; ++k) { lo[u] = __builtin_fminf(lo[u], get(k)); hi[u] = __builtin_fmaxf(hi[u], get(k)); }
+    }
+    group_minmax<U, LANES>(lo, hi);
+    if constexpr (LPG == 128) {
 #pragma unroll
-        for (int m = 1; m < LPG; m <<= 1) {
-            lo = __builtin_fminf(lo, __shfl_xor(lo, m));
-            hi = __builtin_fmaxf(hi, __shfl_xor(hi, m));
-        }
-        if ((c & (LPG - 1)) == 0) {
-            float step = (hi - lo) / qmax;
-            if (!(step >= 1e-10f)) step = 1e-10f;
-            float zf = __builtin_rintf((-lo) / step);
-            zf = __builtin_fminf(__builtin_fmaxf(zf, 0.0f), qmax);
-            s[c / LPG] = step;
-            z[c / LPG] = zf;
-        }
+        for (int u = 0; u < U; u += 2) { lo[u] = lo[u + 1] = __builtin_fminf(lo[u], lo[u + 1]); hi[u] = hi[u + 1] = __builtin_fmaxf(hi[u], hi[u + 1]); }
+    }
+    // Every lane of a group has its minimum and maximum now: one of them works out the group of each run (four, 16 pieces of four runs, ...).
+    constexpr int TURN = LANES < U ? LANES : U;                // runs that the lanes of a group work out at a time
+#pragma unroll
+    for (int u0 = 0; u0 < U; u0 += TURN) {
+        const uint32_t mine = lane & (LANES - 1u);
+        float l = lo[u0], h = hi[u0];
+#pragma unroll
+        for (int u = 1; u < TURN; ++u) { l = mine == (uint32_t)u ? lo[u0 + u] : l; h = mine == (uint32_t)u ? hi[u0 + u] : h; }
+        const uint32_t c = c0 + (u0 + mine) * STRIDE;
+        if (mine < (uint32_t)TURN && c < n) minmax_to_sz(l, h, qmax, s + c / LPG, z + c / LPG);
     }
 }
 // Any other group size: one wavefront per group.
@@ -391,14 +444,7 @@ __global__ __launch_bounds__(256) void k_init_minmax_wave(const InitBatch b, flo
         lo = __builtin_fminf(lo, __shfl_xor(lo, m));
         hi = __builtin_fmaxf(hi, __shfl_xor(hi, m));
     }
-    if (lane == 0) {
-        float step = (hi - lo) / qmax;
-        if (!(step >= 1e-10f)) step = 1e-10f;
-        float zf = __builtin_rintf((-lo) / step);
-        zf = __builtin_fminf(__builtin_fmaxf(zf, 0.0f), qmax);
-        s[grp] = step;
-        z[grp] = zf;
-    }
+    if (lane == 0) minmax_to_sz(lo, hi, qmax, s + grp, z + grp);
 }
 
 // Groups wider than a dW tile: ds / dz of group t from its n_per consecutive per-32-column partials, in one launch
@@ -544,7 +590,7 @@ template <typename WT>
 static void init_minmax_t(const InitJob *jobs, int n, hipStream_t st)
 {
     const float qmax = (float)((1 << jobs[0].p.bits) - 1);
-    // one lane per 8 weights and an xor butterfly over the lanes of a group when every matrix has the same group size
+    // one lane per 16 bytes and a butterfly over the lanes of a group when every matrix has the same group size
     // of 32 .. 512; one wavefront per group otherwise
     int64_t g = jobs[0].p.g;
     for (int i = 1; i < n; ++i) if (jobs[i].p.g != g) g = 0;
@@ -554,18 +600,18 @@ static void init_minmax_t(const InitJob *jobs, int n, hipStream_t st)
     for (int i = 0; i < n; ++i) {
         const Problem &p = jobs[i].p;
         b.W[i] = jobs[i].W; b.s[i] = jobs[i].s; b.z[i] = jobs[i].z; b.g[i] = (uint32_t)p.g;
-        b.n[i] = small ? (uint32_t)((size_t)p.O * p.I / 8) : (uint32_t)((size_t)p.O * p.G);
+        b.n[i] = small ? (uint32_t)((size_t)p.O * p.I * sizeof(WT) / 16) : (uint32_t)((size_t)p.O * p.G);
         b.first[i] = first;
-        first += small ? blocks_for(b.n[i], 256 * kQuantUnroll) : blocks_for(b.n[i], 4);
+        first += small ? blocks_for(b.n[i], 256 * kMinmaxPieces<WT>) : blocks_for(b.n[i], 4);
     }
     for (int i = n; i <= kMaxBatch; ++i) b.first[i] = first;
     const dim3 grid(first), block(256);
     switch (small ? (int)g : 0) {
-    case 32:  k_init_minmax_small<WT, 4><<<grid, block, 0, st>>>(b, qmax); break;
-    case 64:  k_init_minmax_small<WT, 8><<<grid, block, 0, st>>>(b, qmax); break;
-    case 128: k_init_minmax_small<WT, 16><<<grid, block, 0, st>>>(b, qmax); break;
-    case 256: k_init_minmax_small<WT, 32><<<grid, block, 0, st>>>(b, qmax); break;
-    case 512: k_init_minmax_small<WT, 64><<<grid, block, 0, st>>>(b, qmax); break;
+    case 32:  k_init_minmax_small<WT, 32 * (int)sizeof(WT) / 16><<<grid, block, 0, st>>>(b, qmax); break;
+    case 64:  k_init_minmax_small<WT, 64 * (int)sizeof(WT) / 16><<<grid, block, 0, st>>>(b, qmax); break;
+    case 128: k_init_minmax_small<WT, 128 * (int)sizeof(WT) / 16><<<grid, block, 0, st>>>(b, qmax); break;
+    case 256: k_init_minmax_small<WT, 256 * (int)sizeof(WT) / 16><<<grid, block, 0, st>>>(b, qmax); break;
+    case 512: k_init_minmax_small<WT, 512 * (int)sizeof(WT) / 16><<<grid, block, 0, st>>>(b, qmax); break;
     default:  k_init_minmax_wave<WT><<<grid, block, 0, st>>>(b, qmax);
     }
 }
