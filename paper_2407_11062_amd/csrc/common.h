@@ -215,6 +215,13 @@ __device__ __forceinline__ void load_to_lds16_at(const RawRsrc &r, uint32_t lds_
                  :: "s"(lds_addr_uniform), "v"(voffset), "s"(r.w) : "memory", "m0");
 }
 
+// the same past the caches (non-temporal), for what is read once
+__device__ __forceinline__ void load_to_lds16_once_at(const RawRsrc &r, uint32_t lds_addr_uniform, uint32_t voffset)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+                 :: "s"(lds_addr_uniform), "v"(voffset), "s"(r.w) : "memory", "m0");
+}
+
 // the same with 4 bytes per lane: lane j's word lands at lds_wave_base + 4 j
 __device__ __forceinline__ void load_to_lds4_at(const RawRsrc &r, uint32_t lds_addr_uniform, uint32_t voffset)
 {

@@ -54,6 +54,7 @@ __device__ __forceinline__ bf16x8 frag_kc_swz(const bf16_t *tile, int row0, int 
     return *reinterpret_cast<const bf16x8 *>(tile + r * 64 + kc_swz(r, kk * 2 + (lane >> 5)) * 8);
 }
 
+constexpr int kAuxOnce = 2;              // "nt": past the caches
 constexpr int kAuxDeviceScope = 16;      // "sc1" of the raw buffer intrinsics on gfx940 and later
 
 }  // namespace eqat
