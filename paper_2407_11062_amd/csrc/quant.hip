@@ -16,8 +16,11 @@ template <typename WT> struct Chunk8;   // 8 consecutive weights of one lane
 template <> struct Chunk8<bf16_t> {
     static constexpr int kBytes = 16;
     uintx4 v;
-    __device__ __forceinline__ void load(const bf16_t *p) { v = *reinterpret_cast<const uintx4 *>(p); }
-    __device__ __forceinline__ void load_once(const bf16_t *p) { v = __builtin_nontemporal_load(reinterpret_cast<const uintx4 *>(p)); }
+    template <bool ONCE = false> __device__ __forceinline__ void load(const bf16_t *p)          // ONCE: past the caches
+    {
+        const uintx4 *const q = reinterpret_cast<const uintx4 *>(p);
+        v = ONCE ? __builtin_nontemporal_load(q) : *q;
+    }
     __device__ __forceinline__ float get(int k) const
     {
         const uint32_t u = v[k >> 1];
@@ -27,10 +30,28 @@ template <> struct Chunk8<bf16_t> {
 template <> struct Chunk8<float> {
     static constexpr int kBytes = 32;
     floatx4 a, b;
-    __device__ __forceinline__ void load(const float *p)
+    template <bool ONCE = false> __device__ __forceinline__ void load(const float *p)            // (32 bytes a lane: never past the caches)
     {
         a = *reinterpret_cast<const floatx4 *>(p);
         b = *reinterpret_cast<const floatx4 *>(p + 4);
+    }
+    // Neighbouring lanes read neighbouring 16 bytes, twice: lanes 2 i and 2 i + 1 the halves of chunk i and those of chunk 32 + i of the wave, of which
+    // the even lane then keeps the first and the odd one the second.
+    template <bool ONCE> __device__ __forceinline__ void load_halves(const float *p, const float *q)
+    {
+        const floatx4 *const v = reinterpret_cast<const floatx4 *>(p), *const w = reinterpret_cast<const floatx4 *>(q);
+        a = ONCE ? __builtin_nontemporal_load(v) : *v;
+        b = ONCE ? __builtin_nontemporal_load(w) : *w;
+    }
+    __device__ __forceinline__ void exchange(bool odd)
+    {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int mine = __float_as_int(odd ? a[k] : b[k]);
+            const float theirs = __int_as_float(__builtin_amdgcn_update_dpp(0, mine, 0xB1, 0xF, 0xF, false));      // quad_perm [1,0,3,2]
+            a[k] = odd ? theirs : a[k];
+            b[k] = odd ? b[k] : theirs;
+        }
     }
     __device__ __forceinline__ float get(int k) const { return k < 4 ? a[k] : b[k - 4]; }
 };
@@ -68,8 +89,9 @@ constexpr float kIntegers = 0x1.8p23f;
 // added; a tie, which an odd zbar would turn the other way, is a chunk for the exact path), their comparison, the clamp, a shift-add of the
 // float as it is (the exponents of all eight add up to a constant).  With the clamp plane two more.  With the ten there were before (multiply,
 // round, difference, maximum, clamp, conversion, shift-add, and three for the clamp plane) the pass was bound by its arithmetic: seven matrices of a
-// 4096 / 11008 block, bf16, quantize 99 -> 94 us, and 84 with W, which nobody reads soon again, loaded past the caches (non-temporal); pack 94 -> 86,
-// where the end of W comes from the memory-side cache and such loads lose 1-3 %; fp32 weights do not gain by them either (189 and 192 us).
+// 4096 / 11008 block, bf16, quantize 99 -> 94 us, and 84 with W loaded past the caches (see kQuantizeOnceBytes); pack 94 -> 86, where the end of W
+// comes from the memory-side cache and such loads lose 1-3 %.  fp32 weights gain by them only where neighbouring lanes read neighbouring 16 bytes
+// (load_halves; 810 MB, 4 bit: 187 -> 158 us, without that 192).
 // WORK = false: the dense stream of the C ABI (eqat_pack).  WORK = true: the library's working layout (WorkCodes).
 // Zero points at N bits: one thread per output word (tail bits of a row are zero).
 template <int BITS>
@@ -108,7 +130,7 @@ __device__ __forceinline__ void clear_words(uint32_t *__restrict__ w, uint32_t n
 // Up to kMaxBatch matrices in one launch (the linears of a decoder block are 34-90 MB each at 7B size: alone, each would
 // be a 10-25 us launch that spends a good part of its time filling and draining the chip).  Workgroups
 // [first[i], first[i + 1]) work on matrix i.
-struct QuantizeBatch { QuantizeArgs a[kMaxBatch]; uint32_t first[kMaxBatch + 1]; };
+struct QuantizeBatch { QuantizeArgs a[kMaxBatch]; uint32_t first[kMaxBatch + 1]; uint32_t once; };      // once: W is loaded past the caches
 __device__ __forceinline__ int batch_slot(const uint32_t (&first)[kMaxBatch + 1], uint32_t block)
 {
     int i = 0;
@@ -142,23 +164,38 @@ __global__ __launch_bounds__(256) void k_quantize(const QuantizeBatch batch)
     }
     const WT *__restrict__ W = reinterpret_cast<const WT *>(a.W);
     constexpr float qmax = (float)((1 << BITS) - 1);
-    const uint32_t c0 = block * (256u * U) + threadIdx.x;   // chunk index; n_chunks % 4 == 0 so quads stay whole
+    constexpr bool SPREAD = WORK && sizeof(WT) == 4;
+    const uint32_t first = block * (256u * U) + (threadIdx.x & ~63u), lane = threadIdx.x & 63u;
+    // chunk index; n_chunks % 4 == 0 so quads stay whole
+    const uint32_t c0 = first + (SPREAD ? (lane >> 1) + 32u * (lane & 1u) : lane);
     // all loads of the thread's U chunks first: the pass lives on bytes in flight
     Chunk8<WT> ch[U];
     uint32_t gi[U];
     float sv[U], zb[U];
+    auto fetch = [&](auto once_) {
+        constexpr bool ONCE = decltype(once_)::value != 0;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const uint32_t c = c0 + u * 256u;
-        const uint32_t cc = c < a.n_chunks ? c : 0u;             // past the end: recompute chunk 0, store nothing
-        const uint32_t e = cc * 8u;
-        gi[u] = a.g_shift >= 0 ? (e >> a.g_shift) : (e / a.g);
-        if constexpr (WORK && sizeof(WT) == 2) ch[u].load_once(W + e);
-        else ch[u].load(W + e);
-        sv[u] = a.s[gi[u]];
-        zb[u] = a.z[gi[u]];
+        for (int u = 0; u < U; ++u) {
+            const uint32_t c = c0 + u * 256u;
+            const uint32_t cc = c < a.n_chunks ? c : 0u;             // past the end: recompute chunk 0, store nothing
+            const uint32_t e = cc * 8u;
+            gi[u] = a.g_shift >= 0 ? (e >> a.g_shift) : (e / a.g);
+            if constexpr (SPREAD) {
+                const uint32_t p0 = (first + u * 256u) * 2u + lane, p1 = p0 + 64u, n = a.n_chunks * 2u;     // pieces of four weights
+                ch[u].template load_halves<ONCE>(W + (size_t)(p0 < n ? p0 : 0u) * 4, W + (size_t)(p1 < n ? p1 : 0u) * 4);
+            } else ch[u].template load<ONCE>(W + e);
+            sv[u] = a.s[gi[u]];
+            zb[u] = a.z[gi[u]];
+        }
+    };
+    if constexpr (WORK) {
+        if (batch.once) fetch(IC<1>{}); else fetch(IC<0>{});
+    } else fetch(IC<0>{});
+    if constexpr (SPREAD) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) ch[u].exchange((lane & 1u) != 0);
     }
-    const uint32_t q4 = threadIdx.x & 3u;
+    const uint32_t q4 = c0 & 3u;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const uint32_t c = c0 + u * 256u;
@@ -211,7 +248,7 @@ __global__ __launch_bounds__(256) void k_quantize(const QuantizeBatch batch)
             if (q4 < (uint32_t)BITS) a.codes[(c >> 2) * BITS + q4] = word;
         } else {
             if constexpr (BITS == 2) {
-                const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)p, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
+                const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)p, SPREAD ? 0x4E : 0xB1, 0xF, 0xF, false);   // the chunk beside this one: quad_perm [2,3,0,1] or [1,0,3,2]
                 if ((q4 & 1u) == 0) a.codes[(c >> 2) * 2 + (q4 >> 1)] = p | (other << 4);
             } else {
                 a.codes[c] = p;
@@ -502,6 +539,10 @@ static QuantizeArgs quantize_args(const QuantizeJob &j, int unroll)
     return a;
 }
 
+// More weights than the memory-side cache holds: the backward, which reads W again, finds nothing of it there whatever the quantize pass does.  A step of
+// 1000 tokens, seven matrices of 810 MB in all: 1731 us, loaded past the caches 1708; 4096 x 11008, 90 MB, 300 tokens: 165 and 172.
+constexpr size_t kQuantizeOnceBytes = (size_t)256 << 20;
+
 template <typename WT, int BITS>
 static void quantize_t(const QuantizeJob *jobs, int n, bool for_pack, hipStream_t st)
 {
@@ -514,6 +555,9 @@ static void quantize_t(const QuantizeJob *jobs, int n, bool for_pack, hipStream_
         first += b.a[i].n_quant_blocks + blocks_for(b.a[i].n_zwords);
     }
     for (int i = n; i <= kMaxBatch; ++i) b.first[i] = first;
+    size_t w_bytes = 0;
+    for (int i = 0; i < n; ++i) w_bytes += (size_t)jobs[i].p.O * jobs[i].p.I * sizeof(WT);
+    b.once = w_bytes > kQuantizeOnceBytes;
     const dim3 grid(first), block(256);
     // eqat_pack: dense stream, no clamp plane;
     // the quantize pass of the Block-AP calls: working layout, clamp plane for the backward
