@@ -108,12 +108,14 @@ void launch_ksplit(const Problem &p, bool bt, const void *A, const void *codes, 
 // ---- gemm_mid.hip (forward for few output tiles) --------------------------------------------
 bool mid_applies(const Problem &p);
 FwdRoute mid_route(const Problem &p, bool from_packed);
-double mid_us(const Problem &p);                  // what it takes, as the rules of dispatch estimate it
+double mid_us(const Problem &p);                  // what it takes, as the rules of dispatch estimate it, with one workgroup to a tile
 // from the caller's dense stream (exactly one of zpacked / zfloat is not NULL), or from the working layout and (s, z) pairs:
 // bitwise the same results
 void launch_mid(const Problem &p, const void *X, const void *Wpacked, const float *s, const void *zpacked, const float *zfloat,
-                void *Y, hipStream_t st);
-void launch_mid_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, hipStream_t st);
+                void *Y, const SkScratch &sk, hipStream_t st);
+void launch_mid_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, const SkScratch &sk, hipStream_t st);
+// Bytes of sk.partials (of `room` that there are) that the launch of a problem which comes here writes; in less its workgroups share no tiles.
+size_t mid_parts_bytes(const Problem &p, size_t room);
 
 // ---- gemm_mid_dx.hip (dX for few output tiles, on codes in the working layout) -------------------------
 double mid_dx_us(const Problem &p, int cus, int *tokens);      // what it takes, as the rule of dispatch estimates it, and with which token tiles; 1e30: too many tiles
