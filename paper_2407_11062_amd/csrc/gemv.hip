@@ -321,7 +321,7 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
 
 // More tokens (up to 64) than the kernels above stage at once.  The tokens a wave needs are those of its own run only, so
 // nothing is shared between the waves of a workgroup: each streams its piece of the token rows through a small patch of
-// LDS of its own, SUB segments of every lane group at a time (the whole run with up to 8 tokens), with the next piece already
+// LDS of its own, SUB segments of every lane group at a time, with the next piece already
 // on its way into registers, and the main loop has no barrier.  Runs are half as long as above (RS = 4 segments, 512 inputs per wave and trip): the waves
 // of a long row spread more evenly, and the tokens weigh more per run.  LDS rows are 16 bytes longer than
 // their data (the 8 lanes served together read 8 rows) and the four 16-byte chunks of a segment are XOR-permuted with the
@@ -338,28 +338,55 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
 // the slower for it, but not slower than what they replace: 32 tokens, 28672 x 8192, 2 bit: g = 128 105 -> 53 us, g = 32
 // 128 -> 89; 8192 x 8192, 4 bit: 96 -> 21, 100 -> 34.
 constexpr int kWideRS = 4;              // segments per lane and run
-template <int TR> constexpr int kWideSub = TR >= 64 ? 1 : TR >= 16 ? 2 : 4;              // TR: token rows of the patch
+template <int TR> constexpr int kWideSub = TR >= 64 ? 1 : 2;              // TR: token rows of the patch
 template <int TR> constexpr int kWideRowBytes = 4 * kWideSub<TR> * 64 + 16;
-template <int TR> constexpr int kWideWaveBytes = TR * kWideRowBytes<TR>;
+// What a wave fetches of the weights per run and 16-row block, straight into LDS: row pieces of 16 segments of codes, then the step sizes and
+// zero points of their groups.  The chunk c (16 bytes) of a row lies where the 16 rows that a read serves together meet different banks.
+template <int BITS, int SRC, int NG> struct WideRun {
+    static constexpr int WPS = SRC == kWorking ? WorkCodes<BITS>::kWords : BITS;                  // words per segment (the working layout is read by the lanes)
+    static constexpr int CPR = 4 * WPS;                                                           // chunks of a row piece
+    static constexpr int CODES = 16 * CPR * 16, S = NG * 256, Z = SRC == kPackedZ ? 256 : NG * 256, BYTES = CODES + S + Z;
+    static __device__ __forceinline__ int place(int row, int c)
+    {
+        if constexpr (CPR == 8) return c ^ ((row >> 1) & 7);
+        else if constexpr (CPR == 16) return c ^ (row & 15);
+        else { const int t = c + 3 * ((row >> 2) & 3); return t >= 12 ? t - 12 : t; }             // a lane's three chunks stay side by side
+    }
+    static __device__ __forceinline__ int chunk_at(int row, int at)                               // the chunk that lies there
+    {
+        if constexpr (CPR != 12) return place(row, at);
+        else { const int t = at - 3 * ((row >> 2) & 3); return t < 0 ? t + 12 : t; }
+    }
+};
+// Where a wave fetches them so, and the next run's under the arithmetic of this one's last piece: up to 8 tokens.  The lanes
+// that use them read 8 to 16 bytes of 16 rows x 4 places per instruction otherwise, every line several times: with many waves in flight it has left the
+// first cache in between (such loads marked non-temporal cost 10-25 %).  What decides beside that is how many waves the LDS leaves room for: a patch of two
+// segments a lane group, 8 KB a wave in all.  us, by the lanes / so: 8 tokens, 3 bit, 5120 / 13824 block 98 / 86 (with a patch of four segments 102, of one 92),
+// 2 bit, 28672 x 8192 29.4 / 26.6, 4 bit, 4096 x 11008 12.0 / 11.7.  More tokens leave no such room: 16 tokens, 2 bit, 4096 / 11008 50 / 55, 13 tokens, 3 bit, 3200 /
+// 10880 54 / 60 (though 5120 / 13824 118 / 111), 24 tokens, 3 bit, g = 32 88 / 90.
+template <int BITS, int SRC, int NG, int TR, int RB> constexpr bool kWideDirect = SRC != kWorking && TR == 8;
+template <int BITS, int SRC, int NG, int TR, int RB>
+constexpr int kWideWaveBytes = TR * kWideRowBytes<TR> + (kWideDirect<BITS, SRC, NG, TR, RB> ? RB * WideRun<BITS, SRC, NG>::BYTES : 0);
 
 // KEEP: masked 4-bit words stay words, see wide_keeps_words below (then two codes are converted at a time, but for groups of 32 in the largest form, which has no
 // registers for it: 24 tokens, 7168 x 12288 45 us, 48 in pairs)
 template <int BITS, int SRC, int NG, int TR, int RB, bool KEEP>
 __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs a)
 {
-    constexpr int RS = kWideRS, SUB = kWideSub<TR>, ROWB = kWideRowBytes<TR>, NB = (TR + 15) / 16, WPS = SRC == kWorking ? WorkCodes<BITS>::kWords : BITS, CW = RS * WPS / 4, XC = TR * SUB / 4;
+    typedef WideRun<BITS, SRC, NG> L;
+    constexpr int RS = kWideRS, SUB = kWideSub<TR>, ROWB = kWideRowBytes<TR>, NB = (TR + 15) / 16, WPS = L::WPS, XC = TR * SUB / 4;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_waves = (int)(blockDim.x >> 6);
     const int r = lane & 15, kq = lane >> 4;
     const int n_segs = a.I >> 5, n_runs = (n_segs + 4 * RS - 1) / (4 * RS);
-    const int o0 = blockIdx.x * (RB * kGemvRows) + r;                        // this lane's row of block 0
-    unsigned char *const patch = smem_raw + wave * kWideWaveBytes<TR>;
+    const int o0 = blockIdx.x * (RB * kGemvRows);                            // first row of block 0
+    unsigned char *const patch = smem_raw + wave * kWideWaveBytes<BITS, SRC, NG, TR, RB>;
+    unsigned char *const stage = patch + TR * ROWB;
 
     const __amdgpu_buffer_rsrc_t rX = make_rsrc(a.X, a.x_bytes);
-    const __amdgpu_buffer_rsrc_t rW = make_rsrc(a.Wp, a.w_bytes);
-    const __amdgpu_buffer_rsrc_t rS = make_rsrc(a.s, a.s_bytes);
-    const __amdgpu_buffer_rsrc_t rZ = make_rsrc(SRC == kFloatZ ? (const void *)a.zf : (const void *)a.zp, a.z_bytes);
+    const RawRsrc rW = make_raw_rsrc(a.Wp, a.w_bytes), rS = make_raw_rsrc(a.s, a.s_bytes);
+    const RawRsrc rZ = make_raw_rsrc(SRC == kFloatZ ? (const void *)a.zf : (const void *)a.zp, a.z_bytes);
 
     // Piece `sub` of run `sc`: 16-byte chunk i of this lane is number (lane + 64 i) of [token][lane group][SUB][4], so that
     // neighbouring lanes read neighbouring chunks; tokens and segments past the end come as zeros.
@@ -392,19 +419,53 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[rb][b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 
-    // codes, step sizes and zero points of run `sc`; past the last run all out of range
-    struct Run { uintx4 cq[RB][CW]; float sq[RB][NG], zq[RB][NG]; uint32_t zw[RB][2]; };
-    auto fetch_run = [&](int sc, Run &into) {
-        const int seg0 = (sc * 4 + kq) * RS;
-        const uint32_t j0 = NG > 1 ? (uint32_t)(seg0 / RS) * NG : __umulhi((uint32_t)seg0, a.spg_magic);
+    auto group_of = [&](int seg) { return NG > 1 ? (uint32_t)(seg / RS) * NG : __umulhi((uint32_t)seg, a.spg_magic); };      // of a lane's first segment
+    // Codes, step sizes and zero points of run `sc`.  Neighbouring lanes fetch neighbouring chunks of a row.  Rows past O are out of range (zeros); past the
+    // end of a row comes what follows it: the weights there are forced to zero.
+    const uint32_t stage_lds = lds_addr_of(stage);
+    uint32_t coff[RB][WPS];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int i = 0; i < WPS; ++i) {
+            const int e = lane + 64 * i, row = e / L::CPR, o = o0 + rb * kGemvRows + row;
+            coff[rb][i] = o < a.O ? (uint32_t)o * a.w_row_bytes + (uint32_t)(L::chunk_at(row, e % L::CPR) * 16) : kOobOffset;
+        }
+    [[maybe_unused]] auto issue_run = [&](int sc) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            const int o = o0 + rb * kGemvRows;
+            const uint32_t at = stage_lds + (uint32_t)(rb * L::BYTES);
+#pragma unroll
+            for (int i = 0; i < WPS; ++i) load_to_lds16_at(rW, at + (uint32_t)(i * 1024), coff[rb][i] + (uint32_t)sc * (uint32_t)(L::CPR * 16));
+#pragma unroll
+            for (int i = 0; i < NG; ++i) {
+                const int e = lane + 64 * i, o = o0 + rb * kGemvRows + e / (4 * NG), k = e % (4 * NG);
+                const uint32_t gi = (uint32_t)o * (uint32_t)a.G + (NG > 1 ? (uint32_t)(sc * 4 * NG + k) : group_of((sc * 4 + k) * RS));
+                const bool ok = o < a.O;
+                load_to_lds4_at(rS, at + (uint32_t)(L::CODES + i * 256), ok ? gi * 4u : kOobOffset);
+                if constexpr (SRC == kFloatZ) load_to_lds4_at(rZ, at + (uint32_t)(L::CODES + L::S + i * 256), ok ? gi * 4u : kOobOffset);
+            }
+            if constexpr (SRC == kPackedZ) {          // four words of a row hold the zero points of a run wherever they begin
+                const int o = o0 + rb * kGemvRows + (lane >> 2);
+                const uint32_t w0 = (group_of(sc * 4 * RS) * BITS) >> 5;
+                load_to_lds4_at(rZ, at + (uint32_t)(L::CODES + L::S), o < a.O ? ((uint32_t)o * a.z_row_words + w0 + (uint32_t)(lane & 3)) * 4u : kOobOffset);
+            }
+        }
+    };
+    struct Run { uintx4 cq[RB][WPS]; float sq[RB][NG], zq[RB][NG]; uint32_t zw[RB][2]; };
+    // the same by the lanes that use them
+    [[maybe_unused]] const __amdgpu_buffer_rsrc_t bW = make_rsrc(a.Wp, a.w_bytes), bS = make_rsrc(a.s, a.s_bytes), bZ = make_rsrc(SRC == kFloatZ ? (const void *)a.zf : (const void *)a.zp, a.z_bytes);
+    auto fetch_run = [&](int sc, Run &into) {
+        const int seg0 = (sc * 4 + kq) * RS;
+        const uint32_t j0 = group_of(seg0);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const int o = o0 + rb * kGemvRows + r;
             const bool ok = o < a.O && seg0 < n_segs;
             const uint32_t base = (uint32_t)o * a.w_row_bytes + (uint32_t)seg0 * (4u * WPS);
 #pragma unroll
-            for (int q = 0; q < CW; ++q) {
-                const intx4 v = buf_load16(rW, ok ? base + 16u * q : kOobOffset);
+            for (int q = 0; q < WPS; ++q) {
+                const intx4 v = buf_load16(bW, ok ? base + 16u * q : kOobOffset);
                 into.cq[rb][q] = uintx4{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
             }
             const uint32_t gi = ok ? ((uint32_t)o * (uint32_t)a.G + j0) * 4u : kOobOffset;
@@ -423,39 +484,77 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
             if constexpr (SRC == kWorking) {
 #pragma unroll
                 for (int k = 0; k < NG; ++k) {
-                    const intx2 v = buf_load8(rS, ok ? ((uint32_t)o * (uint32_t)a.G + j0 + k) * 8u : kOobOffset);
+                    const intx2 v = buf_load8(bS, ok ? ((uint32_t)o * (uint32_t)a.G + j0 + k) * 8u : kOobOffset);
                     into.sq[rb][k] = __int_as_float(v[0]); into.zq[rb][k] = __int_as_float(v[1]);
                 }
             } else {
-                wide(rS, into.sq[rb]);
+                wide(bS, into.sq[rb]);
             }
             if constexpr (SRC == kFloatZ) {
-                wide(rZ, into.zq[rb]);
+                wide(bZ, into.zq[rb]);
             } else if constexpr (SRC == kPackedZ) {
                 const uint32_t wi = (j0 * BITS) >> 5;
-                into.zw[rb][0] = (uint32_t)buf_load4(rZ, ok ? ((uint32_t)o * a.z_row_words + wi) * 4u : kOobOffset);
-                into.zw[rb][1] = (BITS == 3) ? (uint32_t)buf_load4(rZ, ok ? ((uint32_t)o * a.z_row_words + wi + 1u) * 4u : kOobOffset) : 0u;
+                into.zw[rb][0] = (uint32_t)buf_load4(bZ, ok ? ((uint32_t)o * a.z_row_words + wi) * 4u : kOobOffset);
+                into.zw[rb][1] = (BITS == 3) ? (uint32_t)buf_load4(bZ, ok ? ((uint32_t)o * a.z_row_words + wi + 1u) * 4u : kOobOffset) : 0u;
+            }
+        }
+    };
+    [[maybe_unused]] auto read_run = [&](int sc, Run &into) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const unsigned char *const at = stage + rb * L::BYTES;
+#pragma unroll
+            for (int q = 0; q < WPS; ++q) into.cq[rb][q] = *reinterpret_cast<const uintx4 *>(at + r * (L::CPR * 16) + L::place(r, kq * WPS + q) * 16);
+            const float *const sp = reinterpret_cast<const float *>(at + L::CODES) + (r * 4 + kq) * NG, *const zp = sp + L::S / 4;
+#pragma unroll
+            for (int k = 0; k < NG; ++k) {
+                into.sq[rb][k] = sp[k];
+                if constexpr (SRC == kFloatZ) into.zq[rb][k] = zp[k];
+            }
+            if constexpr (SRC == kPackedZ) {
+                const uint32_t w0 = (group_of(sc * 4 * RS) * BITS) >> 5, wi = ((group_of((sc * 4 + kq) * RS) * BITS) >> 5) - w0;
+                const uint32_t *const zw = reinterpret_cast<const uint32_t *>(at + L::CODES + L::S) + r * 4 + wi;
+                into.zw[rb][0] = zw[0];
+                into.zw[rb][1] = BITS == 3 ? zw[1] : 0u;
             }
         }
     };
 
-    // Fetched a run ahead where that costs no waves: 2-bit codes and few tokens (13824 x 5120, 8 tokens 17 -> 12 us; 4 bit or 16
-    // tokens 5-15 % slower).
     constexpr int kCodes = !KEEP ? kFields : NG == 4 && TR >= 32 && RB == 2 ? kWords : kTwoCodes;
-    constexpr bool AHEAD = TR == 8 && BITS == 2;
-    Run run, next;
-    if constexpr (AHEAD) fetch_run(wave, next);
-    if (wave < n_runs) fetch_tokens(wave, 0);
+    Run run;
+    constexpr bool DIRECT = kWideDirect<BITS, SRC, NG, TR, RB>;
+    // Past the last run the tokens' loads are all out of range.  Without them, but with a branch: 24 tokens, 4 bit, g = 32, 4096 / 11008 block 114 -> 95 us, 16 tokens,
+    // 2 bit 51 -> 48, 60 tokens, 2 bit, 8192 x 8192 27.3 -> 25.2; where the order of the instructions suffers more from the branch they are issued (24 tokens, 3 bit,
+    // g = 32 88 / 90 without, 4 bit, g = 64 93 / 94.5; 10 tokens, 4 bit, 1792 / 5760 34.1 / 34.9).
+    constexpr bool kLastRunAsks = !(DIRECT || BITS == 2 || (TR == 16 && BITS == 3) || (BITS == 4 && NG == 4));
+    if (wave < n_runs) {
+        if constexpr (DIRECT) issue_run(wave);
+        fetch_tokens(wave, 0);
+    }
     for (int sc = wave; sc < n_runs; sc += n_waves) {
         const int seg0 = (sc * 4 + kq) * RS;
-        const uint32_t j0 = NG > 1 ? (uint32_t)(seg0 / RS) * NG : __umulhi((uint32_t)seg0, a.spg_magic);
-        if constexpr (AHEAD) { run = next; fetch_run(sc + n_waves, next); } else fetch_run(sc, run);
+        const uint32_t j0 = group_of(seg0);
+        if constexpr (!DIRECT) fetch_run(sc, run);
         WhatTable<BITS> tab[RB];
 #pragma unroll
         for (int sub = 0; sub < RS / SUB; ++sub) {
             stage_tokens();
-            if (sub + 1 < RS / SUB) fetch_tokens(sc, sub + 1);
-            else fetch_tokens(sc + n_waves, 0);       // past the last run: all out of range
+            if (DIRECT && sub == 0) {
+                __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));      // the run's weights were asked for before these tokens
+                asm volatile("" ::: "memory");
+                read_run(sc, run);
+            }
+            if (sub + 1 < RS / SUB) {
+                fetch_tokens(sc, sub + 1);
+            } else if (kLastRunAsks ? true : sc + n_waves < n_runs) {
+                if constexpr (DIRECT) {
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_s_waitcnt(0xC07F);               // lgkmcnt(0): this run's weights have left LDS
+                    asm volatile("" ::: "memory");
+                    issue_run(sc + n_waves);
+                }
+                fetch_tokens(sc + n_waves, 0);
+            }
 #pragma unroll
             for (int k = 0; k < SUB; ++k) {
                 const int u = sub * SUB + k;
@@ -623,14 +722,15 @@ static void launch_wide_t(const GemvArgs &a, hipStream_t st)
     auto kern = k_gemv_wide<BITS, SRC, NG, TR, RB, KEEP>;
     const int n_runs = wide_runs(a.I), trips = (n_runs + kGemvMaxWaves - 1) / kGemvMaxWaves;
     const int waves = (n_runs + trips - 1) / trips;
-    const size_t smem = (size_t)waves * kWideWaveBytes<TR>;      // at least the 1 KB per wave and token block of the final sum
-    static_assert(kWideWaveBytes<TR> >= (TR + 15) / 16 * RB * 1024 && kGemvMaxWaves * kWideWaveBytes<TR> <= 160 * 1024, "LDS of the final sum, of one CU");
+    constexpr int kWaveBytes = kWideWaveBytes<BITS, SRC, NG, TR, RB>;
+    const size_t smem = (size_t)waves * kWaveBytes;      // at least the 1 KB per wave and token block of the final sum
+    static_assert(kWaveBytes >= (TR + 15) / 16 * RB * 1024 && kGemvMaxWaves * kWaveBytes <= 160 * 1024, "LDS of the final sum, of one CU");
     // more dynamic LDS than the default limit: allowed once per instantiation and device
     static std::atomic<uint64_t> allowed{0};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev > 63) dev = 0;
     if (!((allowed.load(std::memory_order_relaxed) >> dev) & 1u)) {
-        (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kGemvMaxWaves * kWideWaveBytes<TR>);
+        (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kGemvMaxWaves * kWaveBytes);
         allowed.fetch_or((uint64_t)1 << dev, std::memory_order_relaxed);
     }
     kern<<<dim3((unsigned)((a.O + RB * kGemvRows - 1) / (RB * kGemvRows))), dim3(64 * waves), smem, st>>>(a);

@@ -1,0 +1,52 @@
+"""k_gemv_wide where a wave fetches its weights as row pieces straight into LDS (up to 8 tokens), and beside it
+where the lanes fetch them.
+
+Rows of a run less, a piece more, several runs a wave; the last run cut anywhere; row blocks cut; every number of groups in a run; zero points packed and as
+floats, in words that begin in the middle of a run's.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2407_11062_amd as eq
+from paper_2407_11062_amd import synth
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-2          # bf16 activations, as max|got - ref| / max|ref|
+
+
+def npf(t):
+    return t.detach().float().cpu().numpy()
+
+
+# in-features: 512 a run; eight waves at most: 4608 is nine runs, two of them a wave's second
+@pytest.mark.parametrize("T,bits", [(7, 2), (8, 2), (7, 3), (8, 4), (12, 3), (16, 3), (27, 3)])
+@pytest.mark.parametrize("I,O,g", [(512, 16, 32), (480, 24, 32), (544, 40, 32), (576, 8, 64), (4608, 72, 64), (5120, 104, 128), (4736, 56, 128), (4864, 56, 256),
+                                   (4608, 72, -1), (10752, 16, 384)])
+def test_against_the_oracle(T, bits, I, O, g):
+    W = synth.normal((O, I), 0.02, synth.seed_of("lds", I, O, g), torch.bfloat16)
+    X = synth.normal((T, I), 1.0, synth.seed_of("lds", T, I), torch.bfloat16)
+    s, z = oracle.init_minmax(npf(W), bits, g)
+    Wp, zp = eq.eqat_pack(W.cuda(), torch.from_numpy(s).cuda(), torch.from_numpy(z).cuda(), bits, g)
+    Xd, sd = X.cuda(), torch.from_numpy(s).cuda()
+    Y = eq.eqat_qlinear_fwd(Xd, Wp, sd, zp, bits, g)
+    ref = oracle.qlinear_fwd(npf(X), Wp.cpu().numpy(), s, zp.cpu().numpy(), bits, g)
+    assert np.abs(npf(Y) - ref).max() <= TOL * np.abs(ref).max()
+    assert torch.equal(Y, eq.eqat_qlinear_fwd(Xd, Wp, sd, zp, bits, g))
+    assert torch.equal(Y, eq.eqat_qlinear_fwd_z(Xd, Wp, sd, torch.from_numpy(z).cuda(), bits, g))
+
+
+def test_what_follows_a_row_never_counts():
+    """infinite step sizes and zero points in the rows behind, which the last run of a row reaches into"""
+    T, I, O, bits, g = 8, 544, 48, 3, 32
+    W = synth.normal((O, I), 0.02, 3, torch.bfloat16)
+    X = synth.normal((T, I), 1.0, 4, torch.bfloat16).cuda()
+    s, z = oracle.init_minmax(npf(W), bits, g)
+    Wp, _ = eq.eqat_pack(W.cuda(), torch.from_numpy(s).cuda(), torch.from_numpy(z).cuda(), bits, g)
+    clean = eq.eqat_qlinear_fwd_z(X, Wp, torch.from_numpy(s).cuda(), torch.from_numpy(z).cuda(), bits, g)
+    for bad in (np.inf, -np.inf, np.nan):
+        s2, z2 = s.copy(), z.copy()
+        s2[1::2], z2[1::2] = bad, bad
+        Y = eq.eqat_qlinear_fwd_z(X, Wp, torch.from_numpy(s2).cuda(), torch.from_numpy(z2).cuda(), bits, g)
+        assert torch.equal(Y[:, 0::2], clean[:, 0::2])
