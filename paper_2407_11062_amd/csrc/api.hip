@@ -401,7 +401,7 @@ static eqat_status fq_bwd_any(const eqat_desc *d, const void *X, const void *W, 
 
 // What the E2E-QP GEMMs read: codes (working layout; fp32 activations: the dense stream), the (s, z) pairs, the
 // scratch of launches that cut tiles, the array of per-32-column partials of dW, the fp32 dWhat of the fp32 path.
-struct QOperands { const void *codes; const void *sz; eqat::SkScratch sk; float *part; float *dwhat, *what; };
+struct QOperands { const void *codes; const void *sz; eqat::SkScratch sk; float *part; float *dwhat, *what; const float *z; };       // z: of a prepared layer
 
 static eqat_status qlinear_fwd_run(const Problem &p, const void *X, const float *s, const QOperands &q, void *Y, hipStream_t st)
 {
@@ -468,7 +468,7 @@ static eqat_status qlinear_fwd_any(const eqat_desc *d, const void *X, const uint
     }
     const eqat::SkScratch sk = sk_of(l, w8, ws_bytes);
     qlinear_prepare_into(p, Wpacked, s, zpacked, zfloat, w8 + l.codes, w8 + l.sz, sk.counters, l.sk_ctr_bytes, st);
-    const QOperands q{p.act_bf16 ? (const void *)(w8 + l.codes) : (const void *)Wpacked, w8 + l.sz, sk, nullptr, nullptr, nullptr};
+    const QOperands q{p.act_bf16 ? (const void *)(w8 + l.codes) : (const void *)Wpacked, w8 + l.sz, sk, nullptr, nullptr, nullptr, nullptr};
     return qlinear_fwd_run(p, X, s, q, Y, st);
 }
 
@@ -492,7 +492,7 @@ static eqat_status qlinear_bwd_any(const eqat_desc *d, const void *X, const uint
     const eqat::SkScratch sk = sk_of(l, w8, ws_bytes);
     if (!kept) qlinear_prepare_into(p, Wpacked, s, zpacked, zfloat, w8 + l.codes, w8 + l.sz, sk.counters, l.sk_ctr_bytes, st);
     const QOperands q{p.act_bf16 ? (const void *)(w8 + l.codes) : (const void *)Wpacked, w8 + l.sz, sk,
-                      (float *)(w8 + l.part), (float *)(w8 + l.dwhat), what_of(l, w8, ws_bytes)};
+                      (float *)(w8 + l.part), (float *)(w8 + l.dwhat), what_of(l, w8, ws_bytes), nullptr};
     return qlinear_bwd_run(p, X, s, q, dY, dX, ds, dz, st);
 }
 
@@ -528,9 +528,9 @@ eqat_status eqat_qlinear_prepare(const eqat_desc *d, const uint8_t *Wpacked, con
 
 // Operands of a call on a prepared layer; enqueues the small launch that pairs the current step sizes with the zero
 // points (`z` NULL: those the layer was prepared with; else trained zero points, as floats) unless the workspace still
-// holds the pairs of a forward call that kept them.
+// holds the pairs of a forward call that kept them, or the call makes them itself.
 static eqat_status prepared_operands(const Problem &p, const void *prepared, const float *s, const float *z, int op, void *ws,
-                                     size_t ws_bytes, hipStream_t st, QOperands *q, bool make_pairs = true)
+                                     size_t ws_bytes, hipStream_t st, QOperands *q, bool make_pairs)
 {
     EQAT_REQUIRE(prepared);
     if (!aligned(prepared, 256)) return EQAT_ERR_ALIGN;
@@ -544,8 +544,8 @@ static eqat_status prepared_operands(const Problem &p, const void *prepared, con
     q->part = (float *)(w8 + l.part);
     q->dwhat = (float *)(w8 + l.dwhat);
     q->what = what_of(l, w8, ws_bytes);
-    if (make_pairs)
-        qlinear_prepare_into(p, nullptr, s, nullptr, z != nullptr ? z : (const float *)(p8 + pl.zb), nullptr, w8 + l.sz, nullptr, 0, st);
+    q->z = z != nullptr ? z : (const float *)(p8 + pl.zb);
+    if (make_pairs) qlinear_prepare_into(p, nullptr, s, nullptr, q->z, nullptr, w8 + l.sz, nullptr, 0, st);
     return EQAT_OK;
 }
 
@@ -560,8 +560,16 @@ static eqat_status fwd_prepared_any(const eqat_desc *d, const void *X, const voi
     EQAT_ALIGNED(X); EQAT_ALIGNED(s); EQAT_ALIGNED(z); EQAT_ALIGNED(Y);
     if (p.T == 0 && !keep) return prepared == nullptr ? EQAT_ERR_NULL : EQAT_OK;
     QOperands q{};
-    if (eqat_status e = prepared_operands(p, prepared, s, z, keep ? EQAT_OP_QP_BWD : EQAT_OP_QP_FWD, ws, ws_bytes, (hipStream_t)stream, &q)) return e;
-    return qlinear_fwd_run(p, X, s, q, Y, (hipStream_t)stream);
+    // few tiles: one launch reads the step sizes and zero points as they are and leaves the pairs of a call that keeps them.  Graph replays of a
+    // prepared layer's forward and backward, us, with the small launch / without: 1000 tokens, 4096 -> 4096 110.4 / 107.6; 300 tokens, 8192 -> 1024 47.5 / 43.9;
+    // the seven linears of a 1024-wide block, 300 tokens 200 / 188; of the 4096-wide one, 515 tokens (five of them come here) 961 / 949.
+    const bool one_launch = p.act_bf16 && p.T > 0 && fwd_route(p, false, false).kernel == eqat::FWD_MID;
+    hipStream_t st = (hipStream_t)stream;
+    if (eqat_status e = prepared_operands(p, prepared, s, z, keep ? EQAT_OP_QP_BWD : EQAT_OP_QP_FWD, ws, ws_bytes, st, &q, !one_launch)) return e;
+    if (!one_launch) return qlinear_fwd_run(p, X, s, q, Y, st);
+    ProfScope ps(eqat::PK_GEMM_FWD, st);
+    eqat::launch_mid_prepared(p, X, q.codes, s, q.z, keep ? const_cast<void *>(q.sz) : nullptr, Y, q.sk, st);
+    return launch_status();
 }
 
 eqat_status eqat_qlinear_fwd_prepared(const eqat_desc *d, const void *X, const void *prepared, const float *s, const float *z,

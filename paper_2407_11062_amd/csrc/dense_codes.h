@@ -92,9 +92,11 @@ __device__ __forceinline__ bf16x8 eight_of(const WhatTable<BITS> &tab, const Cod
 }
 
 // Where the weights come from: the caller's dense stream with packed or with float zero points, or the working layout with
-// (s, z) pairs that a kept workspace or a prepared layer holds.  The contraction runs in the same order for all three, so
-// the forward of a layer is bitwise the same whichever of them a call has.
-constexpr int kPackedZ = 0, kFloatZ = 1, kWorking = 2;
+// (s, z) pairs that a workspace holds, or (a prepared layer) with step sizes and zero points as two arrays.  The contraction
+// runs in the same order for all four, so the forward of a layer is bitwise the same whichever of them a call has.
+constexpr int kPackedZ = 0, kFloatZ = 1, kWorking = 2, kPrepared = 3;
+template <int SRC> constexpr bool kRelaid = SRC == kWorking || SRC == kPrepared;          // codes in the working layout
+template <int SRC> constexpr bool kTwoFloats = SRC == kFloatZ || SRC == kPrepared;        // step sizes and zero points: an array of floats each
 
 // eight consecutive values in slot order
 template <int BITS> __device__ __forceinline__ bf16x8 slots_of(bf16x8 v)

@@ -38,10 +38,33 @@ namespace {
 
 constexpr int kMidBK = 256;
 
+// A prepared layer's forward reads the step sizes as the caller has them and the zero points as the layer holds them.  The backward wants them as pairs: where
+// it follows, this launch leaves them as well, a share per workgroup, read before the sums meet and written behind the tile.
+struct PairsShare {
+    uint32_t at;
+    intx4 s, z;
+    static __device__ __forceinline__ uint32_t fours(const MidArgs &a) { return a.pairs != nullptr ? a.s_bytes / 16 : 0u; }      // the rows are a multiple of 8
+    __device__ __forceinline__ void read(const MidArgs &a)
+    {
+        at = blockIdx.x * (uint32_t)kMidNT + threadIdx.x;
+        if (at < fours(a)) { s = reinterpret_cast<const intx4 *>(a.s)[at]; z = reinterpret_cast<const intx4 *>(a.zf)[at]; }
+    }
+    __device__ __forceinline__ void write(const MidArgs &a)
+    {
+        while (at < fours(a)) {
+            intx4 *const to = reinterpret_cast<intx4 *>(a.pairs) + 2 * (size_t)at;
+            to[0] = intx4{s[0], z[0], s[1], z[1]};
+            to[1] = intx4{s[2], z[2], s[3], z[3]};
+            at += gridDim.x * (uint32_t)kMidNT;
+            if (at < fours(a)) { s = reinterpret_cast<const intx4 *>(a.s)[at]; z = reinterpret_cast<const intx4 *>(a.zf)[at]; }
+        }
+    }
+};
+
 // LDS of one K step: token tile, codes, and per weight row and segment a word with the step size and one (3-bit packed zero
 // points: two) with the zero point.
 template <int BITS, int SRC, int BM> struct MidLds {
-    static constexpr int WPS = SRC == kWorking ? WorkCodes<BITS>::kWords : BITS;      // words per segment
+    static constexpr int WPS = kRelaid<SRC> ? WorkCodes<BITS>::kWords : BITS;      // words per segment
     static constexpr int NCH = 2 * WPS;                                               // 16-byte chunks of a row's codes
     static constexpr int ZW = SRC == kPackedZ && BITS == 3 ? 2 : 1;
     static constexpr uint32_t WAVE_CODES = NCH == 4 ? 1024 : 2048;                    // the 16 rows that a wave fetches
@@ -111,7 +134,8 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
     Moving bX(a.X, a.x_bytes), bW(a.codes, a.codes_bytes);
     if constexpr (SHARED) { bX.by((uint32_t)first * (kMidBK * 2u)); bW.by((uint32_t)first * (NCH * 16u)); }
     RawRsrc rX, rW;
-    uint32_t s_left = 0, z_left = 0;
+    uint32_t s_left = 0;
+    [[maybe_unused]] uint32_t z_left = 0;            // floats: as many as step sizes
     uint32_t sgroup = 0;                 // of this lane's segment
     uint32_t soff = 0;                   // 0, or out of range where the segment lies past the end of the rows
     int to_aim = steps;                  // counters of their own: a step number that lanes compute with ends up in a vector register, and
@@ -120,7 +144,8 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
         const bool live = to_aim-- > 0;
         rX = bX.at(live); rW = bW.at(live);
         bX.by(kMidBK * 2); bW.by(NCH * 16);
-        s_left = live ? a.s_bytes : 0u; z_left = live ? a.z_bytes : 0u;
+        s_left = live ? a.s_bytes : 0u;
+        if constexpr (!kTwoFloats<SRC>) z_left = live ? a.z_bytes : 0u;
         sgroup = group_of(seg);
         soff = (int)seg < n_segs ? 0u : kOobOffset;
         seg += 8;
@@ -139,7 +164,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
     constexpr int S_LOADS = 2 * (1 + L::ZW), LOADS = C_LOADS + S_LOADS + A_LOADS;
     auto load = [&](int d, int buf) {
         const uint32_t base = lds0 + (uint32_t)buf * L::STEP;
-        const RawRsrc rS = make_raw_rsrc(a.s, s_left), rZ = make_raw_rsrc(SRC == kFloatZ ? (const void *)a.zf : (const void *)a.zp, z_left);
+        const RawRsrc rS = make_raw_rsrc(a.s, s_left), rZ = make_raw_rsrc(kTwoFloats<SRC> ? (const void *)a.zf : (const void *)a.zp, kTwoFloats<SRC> ? s_left : z_left);
         if (d < C_LOADS) {
             load_to_lds16_at(rW, base + L::TOK + (uint32_t)wave * L::WAVE_CODES + (uint32_t)(d * 1024), coff[d]);
         } else if (d < C_LOADS + S_LOADS) {
@@ -148,7 +173,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
             const uint32_t at = base + L::TOK + L::CODES + (uint32_t)((wave * 2 + it) * 256) + (uint32_t)what * L::ROWW;
             if constexpr (SRC == kWorking) load_to_lds4_at(rS, at, (gi * 8u + 4u * what) | soff);
             else if (what == 0) load_to_lds4_at(rS, at, (gi * 4u) | soff);
-            else if constexpr (SRC == kFloatZ) load_to_lds4_at(rZ, at, (gi * 4u) | soff);
+            else if constexpr (kTwoFloats<SRC>) load_to_lds4_at(rZ, at, (gi * 4u) | soff);
             else load_to_lds4_at(rZ, at, ((srow + 8 * it) * a.z_row_words + ((sgroup * BITS) >> 5)) * 4u + 4u * (what - 1));
         } else {
             const int it = d - C_LOADS - S_LOADS;
@@ -178,7 +203,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
     Raw raw;
     uint32_t cur[2][WPS];
     WhatTable<BITS> tab[2];
-    constexpr bool kShared = BITS == 2 && SRC != kWorking;     // 2-bit codes as packed: the lookups of a word serve two slices
+    constexpr bool kShared = BITS == 2 && !kRelaid<SRC>;     // 2-bit codes as packed: the lookups of a word serve two slices
     uint32_t lo[2][4], hi[2][4];
     bf16x8 x[4][MI], w[2][2];
     uint32_t raw_seg = (uint32_t)(first * 8 + 2 * kg);        // of the lanes h = 0
@@ -238,7 +263,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
 #pragma unroll
             for (int k = 0; k < 4; ++k) u[k] = __builtin_amdgcn_perm(hi[b][k], lo[b][k], T4 % 2 ? 0x07030602u : 0x05010400u);
             return unslot_of<BITS>(__builtin_bit_cast(bf16x8, u));
-        } else if constexpr (SRC == kWorking) {
+        } else if constexpr (kRelaid<SRC>) {
             WorkCodes<BITS> c;
 #pragma unroll
             for (int k = 0; k < WPS; ++k) c.w[k] = cur[b][k];
@@ -289,7 +314,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
         __builtin_amdgcn_sched_barrier(0);
     };
     auto end = [&](int slot) { asm volatile("" : "+v"(w[slot][0]), "+v"(w[slot][1])); };
-    constexpr int kRebuild = BITS == 2 ? (kShared ? 16 : 24) : BITS == 3 ? (SRC == kWorking ? 24 : 40) : 46;      // of one slice
+    constexpr int kRebuild = BITS == 2 ? (kShared ? 16 : 24) : BITS == 3 ? (kRelaid<SRC> ? 24 : 40) : 46;      // of one slice
     constexpr int kTables = BITS == 2 ? 26 : BITS == 3 ? 42 : 12, kLook = kShared ? 30 : 0;
 
     mask_last(0); aim();
@@ -335,10 +360,14 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
     }
     wait_all_and_barrier();
 
+    [[maybe_unused]] PairsShare pairs;
+    if constexpr (SRC == kPrepared) pairs.read(a);
+    bool stored = false;
     if constexpr (SHARED) {
-        if (part >= 0) return share_sums<BM, L::TOTAL>(a, acc, smem_raw, m0, n0, wave, lane, shared_tile, part, s_last);
+        if (part >= 0) { share_sums<BM, L::TOTAL>(a, acc, smem_raw, m0, n0, wave, lane, shared_tile, part, s_last); stored = true; }
     }
-    store_sums<BM, L::TOTAL>(a, acc, smem_raw, m0, n0, wave, lane);
+    if (!stored) store_sums<BM, L::TOTAL>(a, acc, smem_raw, m0, n0, wave, lane);
+    if constexpr (SRC == kPrepared) pairs.write(a);
 }
 
 // ---- 128 tokens per tile -----------------------------------------------------------------------------------
@@ -354,7 +383,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
 // products need 1056, the arithmetic beside them 1290; without the loads of a step 1500.
 constexpr int kTallBM = 128;
 template <int BITS, int SRC> struct TallLds {
-    static constexpr int WPS = SRC == kWorking ? WorkCodes<BITS>::kWords : BITS;
+    static constexpr int WPS = kRelaid<SRC> ? WorkCodes<BITS>::kWords : BITS;
     static constexpr int NCH = WPS;
     static constexpr int ZW = SRC == kPackedZ && BITS == 3 ? 2 : 1;
     // tokens: three stages; codes: four, 1 KB per wave and its 16 rows; step sizes and zero points of four steps: two
@@ -397,7 +426,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
         if constexpr (SRC == kWorking) {
             const int row = wave * 16 + e * 8 + (lane >> 3), c = (lane & 7) ^ (row & 7);
             soff[e] = c < (8 >> dshift) ? (uint32_t)(n0 + row) * (uint32_t)a.G * 8u + (uint32_t)c * 16u : kOobOffset;
-        } else if (SRC == kFloatZ || e == 0) {
+        } else if (kTwoFloats<SRC> || e == 0) {
             const int row = wave * 16 + (lane >> 2), c = (lane & 3) ^ ((row >> 1) & 3);
             soff[e] = c < (4 >> dshift) ? (uint32_t)(n0 + row) * (uint32_t)a.G * 4u + (uint32_t)c * 16u : kOobOffset;
         } else {
@@ -421,8 +450,8 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
             load_to_lds16_at(rS, to + (uint32_t)(wave * 2048 + 1024), soff[1]);
         } else {
             load_to_lds16_at(rS, to + (uint32_t)(wave * 1024), soff[0]);
-            const uint32_t zat = SRC == kFloatZ ? j * 4u : ((j * BITS) >> 5) * 4u;
-            const RawRsrc rZ = make_raw_rsrc((SRC == kFloatZ ? (const char *)a.zf : (const char *)a.zp) + zat, live ? a.z_bytes - zat : 0u);
+            const uint32_t zat = kTwoFloats<SRC> ? j * 4u : ((j * BITS) >> 5) * 4u;
+            const RawRsrc rZ = make_raw_rsrc((kTwoFloats<SRC> ? (const char *)a.zf : (const char *)a.zp) + zat, live ? a.z_bytes - zat : 0u);
             load_to_lds16_at(rZ, to + 8192u + (uint32_t)(wave * 1024), soff[1]);
         }
     };
@@ -461,7 +490,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
     // A wave multiplies the segment kg of a step; the lanes h = 0 and 1 of a row take 16 of its codes each, eight per product.
     // Codes, step size and zero point of a step are read from LDS a slice before they are rebuilt.
     constexpr int HW = WPS == 2 ? 1 : 2;
-    constexpr bool kShared = BITS == 2 && SRC != kWorking;     // 2-bit codes as packed: the lookups of a word serve both products
+    constexpr bool kShared = BITS == 2 && !kRelaid<SRC>;     // 2-bit codes as packed: the lookups of a word serve both products
     struct Raw { uint32_t c[2][HW], s[2], z[2][L::ZW], zshift, keep; };
     Raw raw;
     uint32_t cur[2][HW], lo[2][4], hi[2][4];
@@ -494,7 +523,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
             } else {
                 const uint32_t at = (uint32_t)(b * 2048 + row * 64 + (((slot >> 2) ^ ((row >> 1) & 3)) * 16) + (slot & 3) * 4);
                 raw.s[b] = *reinterpret_cast<const uint32_t *>(sup + at);
-                if constexpr (SRC == kFloatZ) {
+                if constexpr (kTwoFloats<SRC>) {
                     raw.z[b][0] = *reinterpret_cast<const uint32_t *>(sup + 8192 + at);
                 } else {
                     const uint32_t *const p = reinterpret_cast<const uint32_t *>(sup + 8192 + b * 2048 + (row >> 4) * 1024 + (row & 15) * 16) + (zbit >> 5);
@@ -548,7 +577,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
 #pragma unroll
             for (int k = 0; k < 4; ++k) u[k] = __builtin_amdgcn_perm(hi[b][k], lo[b][k], T4 ? 0x07030602u : 0x05010400u);
             return unslot_of<BITS>(__builtin_bit_cast(bf16x8, u));
-        } else if constexpr (SRC == kWorking) {
+        } else if constexpr (kRelaid<SRC>) {
             WorkCodes<BITS> c;
 #pragma unroll
             for (int k = 0; k < HW; ++k) c.w[k] = cur[b][k];
@@ -583,8 +612,8 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
         __builtin_amdgcn_sched_barrier(0);
     };
     // instructions of arithmetic in the two slices of a step
-    constexpr int kV0 = (BITS == 2 ? (kShared ? 52 : 54) : BITS == 3 ? (SRC == kWorking ? 70 : 88) : 68) / (2 * MI) + 1;
-    constexpr int kV1 = (BITS == 2 ? (kShared ? 60 : 44) : BITS == 3 ? (SRC == kWorking ? 48 : 60) : 60) / (2 * MI) + 1;
+    constexpr int kV0 = (BITS == 2 ? (kShared ? 52 : 54) : BITS == 3 ? (kRelaid<SRC> ? 70 : 88) : 68) / (2 * MI) + 1;
+    constexpr int kV1 = (BITS == 2 ? (kShared ? 60 : 44) : BITS == 3 ? (kRelaid<SRC> ? 48 : 60) : 60) / (2 * MI) + 1;
     auto wait_and_barrier = [&](auto left) {
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(decltype(left)::value));
@@ -660,7 +689,10 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
     }
     wait_and_barrier(IC<0>{});
 
+    [[maybe_unused]] PairsShare pairs;
+    if constexpr (SRC == kPrepared) pairs.read(a);
     store_sums<BM, L::TOTAL>(a, acc, smem_raw, m0, n0, wave, lane);
+    if constexpr (SRC == kPrepared) pairs.write(a);
 }
 
 template <int BITS, int SRC, int BM, bool SHARED = false> void launch_t(MidArgs a, hipStream_t st)
@@ -849,6 +881,17 @@ void launch_mid_work(const Problem &p, const void *X, const void *codes, const v
     a.codes_bytes = (uint32_t)work_code_bytes(p);
     a.s_bytes = (uint32_t)(p.O * p.G * 8);
     launch_src<kWorking>(p, a, sk, st);
+}
+
+void launch_mid_prepared(const Problem &p, const void *X, const void *codes, const float *s, const float *z, void *pairs, void *Y, const SkScratch &sk, hipStream_t st)
+{
+    MidArgs a = mid_args(p, X, codes, s, Y);
+    a.zf = z;
+    a.code_row_bytes = (uint32_t)(work_code_bytes(p) / p.O);
+    a.codes_bytes = (uint32_t)work_code_bytes(p);
+    a.s_bytes = a.z_bytes = (uint32_t)(p.O * p.G * 4);
+    a.pairs = (float *)pairs;
+    launch_src<kPrepared>(p, a, sk, st);
 }
 
 }  // namespace eqat

@@ -20,6 +20,7 @@ struct MidArgs {
     // The tiles from number `whole` on, `shared` of them, are computed by `parts` workgroups each, a part of the contraction apiece (see share_sums).
     int whole, shared, parts;
     float *part_sums; unsigned long long *arrivals, launch;
+    float *pairs;                        // the launch of a prepared layer leaves the (s, z) pairs here; NULL: does not
 };
 
 constexpr int kMidBN = 128, kMidKG = 4, kMidNT = 512;
