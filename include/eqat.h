@@ -227,7 +227,8 @@ eqat_status eqat_qlinear_bwd_kept(const eqat_desc *d, const void *X, const uint8
 /*
  * E2E-QP on a layer prepared once (Sec. 3.3: W_q is frozen in this phase and only s, or s and z, train).  The codes are
  * brought into the layout the GEMM kernels read and the packed zero points become floats, one time; a call then runs its
- * GEMMs behind one small launch that pairs the current step sizes with the zero points (O*G pairs: s changes every step).
+ * GEMMs behind one small launch that pairs the current step sizes with the zero points (O*G pairs: s changes every step;
+ * the forward of a short batch makes the pairs itself).
  *   eqat_prepared_bytes    size of the prepared layer for this descriptor (tokens ignored; act_dtype matters:
  *                          with fp32 activations the prepared layer holds the dense stream); 0 for a bad descriptor.
  *   eqat_qlinear_prepare   Wpacked, zpacked (as eqat_pack wrote them) -> prepared (device, 256-byte aligned, owned by
