@@ -824,6 +824,11 @@ static double shared_us(const Problem &p)
     return bm == kTallBM ? launch_us(p, bm) : low_us(p, bm, kAnyRoom);
 }
 
+// Step sizes and zero points from two arrays take twice the cache lines of pairs, 2 to 6 % of a long launch; the launch that pairs them takes 5 us.  Forward and backward, us,
+// with that launch / without: 515 tokens, 2 bit, 4096 -> 4096 79.8 / 77.9, 16384 -> 4096 238.2 / 237.6, 22016 -> 4096 336.3 / 337.2; two long rounds, 836 tokens, 19776 -> 7072
+// 714 / 727, 315 tokens, 12672 -> 14368 478 / 485.
+bool mid_pairs_itself(const Problem &p) { return shared_us(p) <= 120.0; }
+
 // as if no tile were shared
 double mid_us(const Problem &p)
 {

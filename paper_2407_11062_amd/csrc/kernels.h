@@ -114,7 +114,8 @@ double mid_us(const Problem &p);                  // what it takes, as the rules
 void launch_mid(const Problem &p, const void *X, const void *Wpacked, const float *s, const void *zpacked, const float *zfloat,
                 void *Y, const SkScratch &sk, hipStream_t st);
 void launch_mid_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, const SkScratch &sk, hipStream_t st);
-// the same from the working layout, step sizes and zero points (O * G floats each); leaves them as pairs for a backward (`pairs` NULL: does not)
+// the same from the working layout, step sizes and zero points (O * G floats each); leaves them as pairs for a backward (`pairs` NULL: does not).  Short launches gain by it
+bool mid_pairs_itself(const Problem &p);
 void launch_mid_prepared(const Problem &p, const void *X, const void *codes, const float *s, const float *z, void *pairs, void *Y, const SkScratch &sk, hipStream_t st);
 // Bytes of sk.partials (of `room` that there are) that the launch of a problem which comes here writes; in less its workgroups share no tiles.
 size_t mid_parts_bytes(const Problem &p, size_t room);
