@@ -338,8 +338,8 @@ __global__ __launch_bounds__(64 * (MW ? kGemvMaxWaves : kGemvWaves)) void k_gemv
 // the slower for it, but not slower than what they replace: 32 tokens, 28672 x 8192, 2 bit: g = 128 105 -> 53 us, g = 32
 // 128 -> 89; 8192 x 8192, 4 bit: 96 -> 21, 100 -> 34.
 constexpr int kWideRS = 4;              // segments per lane and run
-template <int TR> constexpr int kWideSub = TR >= 64 ? 1 : 2;              // TR: token rows of the patch
-template <int TR> constexpr int kWideRowBytes = 4 * kWideSub<TR> * 64 + 16;
+template <int TR, bool DIRECT> constexpr int kWideSub = TR >= 64 ? 1 : TR >= 16 || DIRECT ? 2 : 4;              // TR: token rows of the patch
+template <int TR, bool DIRECT> constexpr int kWideRowBytes = 4 * kWideSub<TR, DIRECT> * 64 + 16;
 // What a wave fetches of the weights per run and 16-row block, straight into LDS: row pieces of 16 segments of codes, then the step sizes and
 // zero points of their groups.  The chunk c (16 bytes) of a row lies where the 16 rows that a read serves together meet different banks.
 template <int BITS, int SRC, int NG> struct WideRun {
@@ -364,24 +364,28 @@ template <int BITS, int SRC, int NG> struct WideRun {
 // segments a lane group, 8 KB a wave in all.  us, by the lanes / so: 8 tokens, 3 bit, 5120 / 13824 block 98 / 86 (with a patch of four segments 102, of one 92),
 // 2 bit, 28672 x 8192 29.4 / 26.6, 4 bit, 4096 x 11008 12.0 / 11.7.  More tokens leave no such room: 16 tokens, 2 bit, 4096 / 11008 50 / 55, 13 tokens, 3 bit, 3200 /
 // 10880 54 / 60 (though 5120 / 13824 118 / 111), 24 tokens, 3 bit, g = 32 88 / 90.
-template <int BITS, int SRC, int NG, int TR, int RB> constexpr bool kWideDirect = SRC != kWorking && TR == 8;
-template <int BITS, int SRC, int NG, int TR, int RB>
-constexpr int kWideWaveBytes = TR * kWideRowBytes<TR> + (kWideDirect<BITS, SRC, NG, TR, RB> ? RB * WideRun<BITS, SRC, NG>::BYTES : 0);
+template <int SRC, int TR> constexpr bool kWideDirect = SRC != kWorking && TR == 8;
+template <int BITS, int SRC, int NG, int TR, int RB, bool DIRECT>
+constexpr int kWideWaveBytes = TR * kWideRowBytes<TR, DIRECT> + (DIRECT ? RB * WideRun<BITS, SRC, NG>::BYTES : 0);
+// 4-bit codes, whose 16 bytes a lane and segment are as wide as the pieces, gain by it only in long rows of large matrices, 8192 inputs and more than
+// 2^26 weights.  5 to 8 tokens, us, by the lanes (the whole run's tokens in the patch) / so: 28672 x 8192, the longer side the inputs 42.6 / 36.8, the rows 41.1 / 39.1;
+// 13824 -> 5120 17.8 / 16.4; 11008 -> 4096 9.0 / 9.8, 14336 -> 4096 10.7 / 11.7, 8192 -> 8192, one group per row 12.1 / 13.0, 5120 -> 13824 13.8 / 14.5.
+static bool wide_pieces_gain(int I, int O) { return I >= 8192 && (int64_t)I * O > (int64_t)1 << 26; }
 
 // KEEP: masked 4-bit words stay words, see wide_keeps_words below (then two codes are converted at a time, but for groups of 32 in the largest form, which has no
 // registers for it: 24 tokens, 7168 x 12288 45 us, 48 in pairs)
-template <int BITS, int SRC, int NG, int TR, int RB, bool KEEP>
+template <int BITS, int SRC, int NG, int TR, int RB, bool KEEP, bool DIRECT>
 __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs a)
 {
     typedef WideRun<BITS, SRC, NG> L;
-    constexpr int RS = kWideRS, SUB = kWideSub<TR>, ROWB = kWideRowBytes<TR>, NB = (TR + 15) / 16, WPS = L::WPS, XC = TR * SUB / 4;
+    constexpr int RS = kWideRS, SUB = kWideSub<TR, DIRECT>, ROWB = kWideRowBytes<TR, DIRECT>, NB = (TR + 15) / 16, WPS = L::WPS, XC = TR * SUB / 4;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_waves = (int)(blockDim.x >> 6);
     const int r = lane & 15, kq = lane >> 4;
     const int n_segs = a.I >> 5, n_runs = (n_segs + 4 * RS - 1) / (4 * RS);
     const int o0 = blockIdx.x * (RB * kGemvRows);                            // first row of block 0
-    unsigned char *const patch = smem_raw + wave * kWideWaveBytes<BITS, SRC, NG, TR, RB>;
+    unsigned char *const patch = smem_raw + wave * kWideWaveBytes<BITS, SRC, NG, TR, RB, DIRECT>;
     unsigned char *const stage = patch + TR * ROWB;
 
     const __amdgpu_buffer_rsrc_t rX = make_rsrc(a.X, a.x_bytes);
@@ -522,11 +526,10 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
 
     constexpr int kCodes = !KEEP ? kFields : NG == 4 && TR >= 32 && RB == 2 ? kWords : kTwoCodes;
     Run run;
-    constexpr bool DIRECT = kWideDirect<BITS, SRC, NG, TR, RB>;
     // Past the last run the tokens' loads are all out of range.  Without them, but with a branch: 24 tokens, 4 bit, g = 32, 4096 / 11008 block 114 -> 95 us, 16 tokens,
     // 2 bit 51 -> 48, 60 tokens, 2 bit, 8192 x 8192 27.3 -> 25.2; where the order of the instructions suffers more from the branch they are issued (24 tokens, 3 bit,
     // g = 32 88 / 90 without, 4 bit, g = 64 93 / 94.5; 10 tokens, 4 bit, 1792 / 5760 34.1 / 34.9).
-    constexpr bool kLastRunAsks = !(DIRECT || BITS == 2 || (TR == 16 && BITS == 3) || (BITS == 4 && NG == 4));
+    constexpr bool kLastRunAsks = !(DIRECT || BITS == 2 || (TR == 16 && BITS == 3) || (BITS == 4 && NG == 4 && TR > 8));
     if (wave < n_runs) {
         if constexpr (DIRECT) issue_run(wave);
         fetch_tokens(wave, 0);
@@ -713,16 +716,19 @@ static bool wide_keeps_words(int I, int O, int rows)
     const int runs = wide_runs(I), blocks = (O + rows - 1) / rows;
     return !((runs % kGemvMaxWaves == 0 && (rows == kGemvRows || runs <= 2 * kGemvMaxWaves)) || (runs == 4 && blocks > 256));
 }
-template <int BITS, int SRC, int NG, int TR, int RB, bool KEEP = true>
+template <int BITS, int SRC, int NG, int TR, int RB, bool KEEP = true, bool DIRECT = kWideDirect<SRC, TR>>
 static void launch_wide_t(const GemvArgs &a, hipStream_t st)
 {
     if constexpr (KEEP && BITS == 4 && SRC != kWorking && NG == 2 && TR == 32) {
         if (!wide_keeps_words(a.I, a.O, RB * kGemvRows)) return launch_wide_t<BITS, SRC, NG, TR, RB, false>(a, st);
     }
-    auto kern = k_gemv_wide<BITS, SRC, NG, TR, RB, KEEP>;
+    if constexpr (DIRECT && BITS == 4) {
+        if (!wide_pieces_gain(a.I, a.O)) return launch_wide_t<BITS, SRC, NG, TR, RB, KEEP, false>(a, st);
+    }
+    auto kern = k_gemv_wide<BITS, SRC, NG, TR, RB, KEEP, DIRECT>;
     const int n_runs = wide_runs(a.I), trips = (n_runs + kGemvMaxWaves - 1) / kGemvMaxWaves;
     const int waves = (n_runs + trips - 1) / trips;
-    constexpr int kWaveBytes = kWideWaveBytes<BITS, SRC, NG, TR, RB>;
+    constexpr int kWaveBytes = kWideWaveBytes<BITS, SRC, NG, TR, RB, DIRECT>;
     const size_t smem = (size_t)waves * kWaveBytes;      // at least the 1 KB per wave and token block of the final sum
     static_assert(kWaveBytes >= (TR + 15) / 16 * RB * 1024 && kGemvMaxWaves * kWaveBytes <= 160 * 1024, "LDS of the final sum, of one CU");
     // more dynamic LDS than the default limit: allowed once per instantiation and device

@@ -50,3 +50,18 @@ def test_what_follows_a_row_never_counts():
         s2[1::2], z2[1::2] = bad, bad
         Y = eq.eqat_qlinear_fwd_z(X, Wp, torch.from_numpy(s2).cuda(), torch.from_numpy(z2).cuda(), bits, g)
         assert torch.equal(Y[:, 0::2], clean[:, 0::2])
+
+
+@pytest.mark.parametrize("I,g", [(8192, 32), (8192, 64), (8192 + 128, 128), (9216, -1)])
+def test_large_matrices_of_4_bit_codes_as_their_parts(I, g):
+    """codes as row pieces in the whole (more than 2^26 weights), by the lanes in the parts: the same sums"""
+    T, O, bits = 8, (1 << 26) // I // 8 * 8 + 24, 4
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    W = (torch.randn((O, I), generator=gen, device="cuda") * 0.02).bfloat16()
+    X = torch.randn((T, I), generator=gen, device="cuda").bfloat16()
+    s, z = eq.eqat_init_minmax(W, bits, g)
+    Wp, zp = eq.eqat_pack(W, s, z, bits, g)
+    Y = eq.eqat_qlinear_fwd(X, Wp, s, zp, bits, g)
+    for a, b in ((0, 40), (O - 24, O)):
+        assert torch.equal(Y[:, a:b], eq.eqat_qlinear_fwd(X, Wp[a:b].contiguous(), s[a:b].contiguous(), zp[a:b].contiguous(), bits, g))
+    assert torch.equal(Y, eq.eqat_qlinear_fwd_z(X, Wp, s, z, bits, g))
