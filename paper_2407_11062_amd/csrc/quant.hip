@@ -79,6 +79,34 @@ template <bool WORK, int BITS> __host__ __device__ constexpr uint32_t packed_sum
 // From here on floats are integers, and what is added to it is rounded to one, ties to even: the low bits of kIntegers + n are n.
 constexpr float kIntegers = 0x1.8p23f;
 
+// Bit k: a[k] is not b[k], as words.  A compare and an add with carry (bits = 2 bits + carry) each; two wait states lie between a vector instruction that writes
+// a scalar register and one that reads it, which the compiler does not put into assembly: three carries take turns, so that other compares and sums lie there.
+__device__ __forceinline__ uint32_t differ_bits(const float (&a)[8], const float (&b)[8])
+{
+    uint32_t bits = 0;
+    uint64_t c0, c1, c2;
+    asm("v_cmp_ne_u32_e64 %1, %11, %19\n\t"
+        "v_cmp_ne_u32_e64 %2, %10, %18\n\t"
+        "v_cmp_ne_u32_e64 %3, %9, %17\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %1\n\t"
+        "v_cmp_ne_u32_e64 %1, %8, %16\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\t"
+        "v_cmp_ne_u32_e64 %2, %7, %15\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %3\n\t"
+        "v_cmp_ne_u32_e64 %3, %6, %14\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %1\n\t"
+        "v_cmp_ne_u32_e64 %1, %5, %13\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\t"
+        "v_cmp_ne_u32_e64 %2, %4, %12\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %3\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %1\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %2"
+        : "+&v"(bits), "=&s"(c0), "=&s"(c1), "=&s"(c2)
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]),
+          "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]), "v"(b[6]), "v"(b[7]) : "vcc");
+    return bits;
+}
+
 // The quantize pass.  One lane owns 8 consecutive weights (a 16- or 32-byte load); the four lanes of a
 // quad own one 32-code segment, i.e. BITS output words, assembled with quad permutes.
 //   codes     [O, I*BITS/32] words      packed stream (same layout as eqat_pack's Wpacked)
@@ -222,11 +250,7 @@ __global__ __launch_bounds__(256) void k_quantize(const QuantizeBatch batch)
 #pragma unroll
         for (int k = 0; k < 8; ++k) fc[k] = __builtin_amdgcn_fmed3f(f[k], kIntegers, kIntegers + qmax);
         if constexpr (CLAMPBITS) {
-            uint32_t cb = 0;
-#pragma unroll
-            for (int k = 7; k >= 0; --k)                           // cb = 2 cb + (clamped)
-                asm("v_cmp_ne_u32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(cb) : "v"(fc[k]), "v"(f[k]) : "vcc");
-            a.clampbits[c] = (uint8_t)cb;
+            a.clampbits[c] = (uint8_t)differ_bits(f, fc);
         }
         // the codes at their places in a word
         uint32_t p = 0u - packed_sum<WORK, BITS>(__builtin_bit_cast(uint32_t, kIntegers));
