@@ -215,10 +215,12 @@ __device__ __forceinline__ void load_to_lds16_at(const RawRsrc &r, uint32_t lds_
                  :: "s"(lds_addr_uniform), "v"(voffset), "s"(r.w) : "memory", "m0");
 }
 
-// the same past the caches (non-temporal), for what is read once
+// the same past the caches (non-temporal), for what is read once.  A buffer load may use scalar registers that a vector instruction wrote five wait states later at the
+// earliest, and the compiler, which keeps that distance for its own loads, sees none in assembly.  In dW of cut tiles, 2 bit, it brings this descriptor back from the
+// lanes of a vector register right in front of the first load: the wait is here.  (None of the loads above and below has such a neighbour.)
 __device__ __forceinline__ void load_to_lds16_once_at(const RawRsrc &r, uint32_t lds_addr_uniform, uint32_t voffset)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
                  :: "s"(lds_addr_uniform), "v"(voffset), "s"(r.w) : "memory", "m0");
 }
 

@@ -88,3 +88,8 @@ def found(tmp_path_factory):
 def test_vector_instructions_wait_for_carries_and_masks(found):
     found = [f for f in found if f[2].startswith("v_")]
     assert found == [], f"{len(found)}: {found[:4]}"
+
+
+def test_buffer_loads_wait_for_their_descriptors(found):
+    found = [f for f in found if f[2].startswith("buffer_")]
+    assert found == [], f"{len(found)}: {found[:4]}"
