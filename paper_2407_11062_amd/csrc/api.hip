@@ -91,8 +91,6 @@ eqat::FwdRoute fwd_route(const Problem &p, bool from_packed, bool floatz)
     return eqat::FwdRoute{eqat::FWD_TILES, 0, 0};
 }
 
-inline bool fwd_is_mid(eqat::FwdKernel k) { return k == eqat::FWD_MID || k == eqat::FWD_RELAY_MID; }
-
 struct WsLayout { size_t codes, clamp, sz, part, dwhat, what, what_bytes, sk_ctr, sk_ctr_bytes, sk_part, sk_part_bytes, total, needed; };
 
 inline bool op_is_bwd(int op) { return op == EQAT_OP_FQ_BWD || op == EQAT_OP_Q_BWD || op == EQAT_OP_QP_BWD; }
@@ -136,9 +134,8 @@ WsLayout ws_layout(const Problem &p, int op)
         // Parts of launches that would share tiles only to fill the chip may be missing: a workspace that was sized for
         // another token count is taken, and those launches give every tile one workgroup.
         size_t needed = 0;
-        const eqat::FwdKernel fwd = p.T > 0 ? fwd_route(p, op == EQAT_OP_Q_FWD, false).kernel : eqat::FWD_GEMV_ANY;
-        eqat::sk_scratch_bytes(p, fwd == eqat::FWD_TILES, bwd, &l.sk_part_bytes, &needed, &l.sk_ctr_bytes);
-        if (fwd_is_mid(fwd)) l.sk_part_bytes = std::max(l.sk_part_bytes, eqat::mid_parts_bytes(p, ~(size_t)0));
+        const bool tiles = p.T > 0 && fwd_route(p, op == EQAT_OP_Q_FWD, false).kernel == eqat::FWD_TILES;
+        eqat::sk_scratch_bytes(p, tiles, bwd, &l.sk_part_bytes, &needed, &l.sk_ctr_bytes);
         if (prepared) l.sk_ctr_bytes = 0;
         l.sk_ctr = take(l.sk_ctr_bytes);
         l.sk_part = take(l.sk_part_bytes);
@@ -302,7 +299,7 @@ static void fwd_on_work(const Problem &p, const void *X, const void *codes, cons
 {
     const eqat::FwdKernel kernel = fwd_route(p, false, false).kernel;
     if (kernel == eqat::FWD_GEMV_WIDE) { ProfScope ps(eqat::PK_GEMV, st); eqat::launch_gemv_work(p, X, codes, sz, Y, st); }
-    else if (kernel == eqat::FWD_MID) { ProfScope ps(eqat::PK_GEMM_FWD, st); eqat::launch_mid_work(p, X, codes, sz, Y, sk, st); }
+    else if (kernel == eqat::FWD_MID) { ProfScope ps(eqat::PK_GEMM_FWD, st); eqat::launch_mid_work(p, X, codes, sz, Y, st); }
     else { ProfScope ps(eqat::PK_GEMM_FWD, st); eqat::launch_mfma_fwd(p, X, codes, sz, Y, sk, st); }
 }
 
@@ -458,7 +455,7 @@ static eqat_status qlinear_fwd_any(const eqat_desc *d, const void *X, const uint
     const eqat::FwdKernel kernel = !keep && p.act_bf16 ? fwd_route(p, true, zfloat != nullptr).kernel : eqat::FWD_TILES;
     if (kernel == eqat::FWD_MID) {
         ProfScope ps(eqat::PK_GEMM_FWD, st);
-        eqat::launch_mid(p, X, Wpacked, s, zpacked, zfloat, Y, sk_of(l, w8, ws_bytes), st);
+        eqat::launch_mid(p, X, Wpacked, s, zpacked, zfloat, Y, st);
         return launch_status();
     }
     if (kernel != eqat::FWD_TILES && kernel != eqat::FWD_RELAY_MID) {
@@ -568,7 +565,7 @@ static eqat_status fwd_prepared_any(const eqat_desc *d, const void *X, const voi
     if (eqat_status e = prepared_operands(p, prepared, s, z, keep ? EQAT_OP_QP_BWD : EQAT_OP_QP_FWD, ws, ws_bytes, st, &q, !one_launch)) return e;
     if (!one_launch) return qlinear_fwd_run(p, X, s, q, Y, st);
     ProfScope ps(eqat::PK_GEMM_FWD, st);
-    eqat::launch_mid_prepared(p, X, q.codes, s, q.z, keep ? const_cast<void *>(q.sz) : nullptr, Y, q.sk, st);
+    eqat::launch_mid_prepared(p, X, q.codes, s, q.z, keep ? const_cast<void *>(q.sz) : nullptr, Y, st);
     return launch_status();
 }
 
@@ -653,9 +650,9 @@ eqat_status eqat_plan_scratch(const eqat_desc *d, int op, int gemm, int cus, siz
     char *const some = reinterpret_cast<char *>(256);                // an address to plan with, nothing is done with it
     if (eqat_status e = check_ws(l, some, ws_bytes)) return e;
     const eqat::SkScratch sk = sk_of(l, some, ws_bytes, op_is_prepared(op) ? reinterpret_cast<uint32_t *>(some) : nullptr);
-    const eqat::FwdKernel fwd = fwd_route(p, op == EQAT_OP_Q_FWD, false).kernel;
+    const bool parts = gemm != 0 || fwd_route(p, op == EQAT_OP_Q_FWD, false).kernel == eqat::FWD_TILES;
     *first = l.sk_part;
-    *end = l.sk_part + (gemm != 0 || fwd == eqat::FWD_TILES ? eqat::parts_written_for_test(p, gemm, cus, sk) : fwd_is_mid(fwd) ? eqat::mid_parts_bytes(p, sk.bytes) : 0);
+    *end = l.sk_part + (parts ? eqat::parts_written_for_test(p, gemm, cus, sk) : 0);
     return EQAT_OK;
 }
 

@@ -78,8 +78,7 @@ template <int NCH> __device__ __forceinline__ int code_chunk_swz(int row, int c)
     return NCH == 2 ? c ^ ((row >> 2) & 1) : NCH == 4 ? c ^ ((row >> 1) & 3) : NCH == 8 ? c ^ (row & 7) : c;            // rows of 96 bytes spread by themselves
 }
 
-// SHARED: the last tiles of the launch are computed by several workgroups each, which take a part of the K steps apiece
-template <int BITS, int SRC, int BM, bool SHARED>
+template <int BITS, int SRC, int BM>
 __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
 {
     typedef MidLds<BITS, SRC, BM> L;
@@ -90,27 +89,10 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 1, kg = wave >> 1, r = lane & 31, h = lane >> 5;
 
-    const int n_segs = a.I >> 5, all_steps = (a.I + kMidBK - 1) / kMidBK;
-    int m0, n0, steps = all_steps, first = 0;               // K steps of this workgroup
-    [[maybe_unused]] int shared_tile = 0, part = -1;
-    [[maybe_unused]] __shared__ uint32_t s_last;
-    if constexpr (SHARED) {
-        if (blockIdx.x < (uint32_t)a.whole) {
-            tile_of(a, BM, blockIdx.x, (uint32_t)a.whole, m0, n0);
-        } else {      // one part after another: the workgroups of an XCD read the same columns of the tokens and rows of the codes
-            const uint32_t pid = in_xcd_order(blockIdx.x - (uint32_t)a.whole, (uint32_t)(a.shared * a.parts));
-            part = __builtin_amdgcn_readfirstlane((int)(pid / (uint32_t)a.shared));
-            shared_tile = __builtin_amdgcn_readfirstlane((int)(pid % (uint32_t)a.shared));
-            place_of(a, BM, (uint32_t)(a.whole + shared_tile), m0, n0);
-            const int base = all_steps / a.parts, extra = all_steps % a.parts;
-            first = __builtin_amdgcn_readfirstlane(part * base + (part < extra ? part : extra));
-            steps = __builtin_amdgcn_readfirstlane(base + (part < extra ? 1 : 0));
-            if (tid == 0) s_last = arrive(a, shared_tile) ? 1u : 0u;
-        }
-    } else {
-        tile_of(a, BM, blockIdx.x, gridDim.x, m0, n0);
-    }
-    const int last_step = all_steps - 1 - first;            // the one that the rows end in, if it is one of these
+    int m0, n0;
+    tile_of(a, BM, blockIdx.x, gridDim.x, m0, n0);
+
+    const int n_segs = a.I >> 5, steps = (a.I + kMidBK - 1) / kMidBK;
     const uint32_t lds0 = lds_addr_of(smem_raw);
 
     // ---- loads of one K step.  Rows past T or O are out of range of their buffers (zeros); columns past I: tokens and
@@ -132,14 +114,13 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
     const uint32_t each = a.spg_magic == 0u ? ~0u : 0u;                    // groups of 32: every segment is one
     auto group_of = [&](uint32_t seg) { return __umulhi(seg, a.spg_magic) + (seg & each); };
     Moving bX(a.X, a.x_bytes), bW(a.codes, a.codes_bytes);
-    if constexpr (SHARED) { bX.by((uint32_t)first * (kMidBK * 2u)); bW.by((uint32_t)first * (NCH * 16u)); }
     RawRsrc rX, rW;
     uint32_t s_left = 0;
     [[maybe_unused]] uint32_t z_left = 0;            // floats: as many as step sizes
     uint32_t sgroup = 0;                 // of this lane's segment
     uint32_t soff = 0;                   // 0, or out of range where the segment lies past the end of the rows
     int to_aim = steps;                  // counters of their own: a step number that lanes compute with ends up in a vector register, and
-    uint32_t seg = (uint32_t)(first * 8 + (lane & 7)); // with it the descriptors
+    uint32_t seg = (uint32_t)(lane & 7); // with it the descriptors
     auto aim = [&]() {                   // at the next step; past the last one nothing is in range (zeros)
         const bool live = to_aim-- > 0;
         rX = bX.at(live); rW = bW.at(live);
@@ -152,7 +133,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
     };
     // in front of the loads of every step
     auto mask_last = [&](int step) {
-        if (step == last_step && a.I % kMidBK != 0) {
+        if (step == steps - 1 && a.I % kMidBK != 0) {
 #pragma unroll
             for (int it = 0; it < A_LOADS; ++it) {
                 const int row = (wave * A_LOADS + it) * 2 + h;
@@ -206,7 +187,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
     constexpr bool kShared = BITS == 2 && !kRelaid<SRC>;     // 2-bit codes as packed: the lookups of a word serve two slices
     uint32_t lo[2][4], hi[2][4];
     bf16x8 x[4][MI], w[2][2];
-    uint32_t raw_seg = (uint32_t)(first * 8 + 2 * kg);        // of the lanes h = 0
+    uint32_t raw_seg = (uint32_t)(2 * kg);        // of the lanes h = 0
     auto read_raw = [&](int buf) {        // the steps in order
         const unsigned char *const here = smem_raw + (uint32_t)buf * L::STEP;
         if constexpr (SRC == kPackedZ) raw.zshift = ((h ? group_of(raw_seg + 1) : group_of(raw_seg)) * BITS) & 31u;
@@ -362,11 +343,7 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid(const MidArgs a)
 
     [[maybe_unused]] PairsShare pairs;
     if constexpr (SRC == kPrepared) pairs.read(a);
-    bool stored = false;
-    if constexpr (SHARED) {
-        if (part >= 0) { share_sums<BM, L::TOTAL>(a, acc, smem_raw, m0, n0, wave, lane, shared_tile, part, s_last); stored = true; }
-    }
-    if (!stored) store_sums<BM, L::TOTAL>(a, acc, smem_raw, m0, n0, wave, lane);
+    store_sums<BM, L::TOTAL>(a, acc, smem_raw, m0, n0, wave, lane);
     if constexpr (SRC == kPrepared) pairs.write(a);
 }
 
@@ -695,12 +672,12 @@ __global__ __launch_bounds__(kMidNT) void k_gemm_mid_tall(const MidArgs a)
     if constexpr (SRC == kPrepared) pairs.write(a);
 }
 
-template <int BITS, int SRC, int BM, bool SHARED = false> void launch_t(MidArgs a, hipStream_t st)
+template <int BITS, int SRC, int BM> void launch_t(MidArgs a, hipStream_t st)
 {
     int smem;
     void (*kern)(MidArgs);
     if constexpr (BM == kTallBM) { kern = k_gemm_mid_tall<BITS, SRC>; smem = (int)TallLds<BITS, SRC>::TOTAL; }
-    else { kern = k_gemm_mid<BITS, SRC, BM, SHARED>; smem = (int)MidLds<BITS, SRC, BM>::TOTAL; }
+    else { kern = k_gemm_mid<BITS, SRC, BM>; smem = (int)MidLds<BITS, SRC, BM>::TOTAL; }
     static std::atomic<uint64_t> allowed{0};          // more dynamic LDS than the default limit: once per device
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev > 63) dev = 0;
@@ -711,7 +688,7 @@ template <int BITS, int SRC, int BM, bool SHARED = false> void launch_t(MidArgs 
     a.tiles_m = (a.T + BM - 1) / BM;
     a.tiles_n = (a.O + kMidBN - 1) / kMidBN;
     a.band = band_of(a.tiles_m, BM);
-    kern<<<dim3((unsigned)(SHARED ? a.whole + a.shared * a.parts : a.tiles_m * a.tiles_n)), dim3(kMidNT), smem, st>>>(a);
+    kern<<<dim3((unsigned)(a.tiles_m * a.tiles_n)), dim3(kMidNT), smem, st>>>(a);
 }
 
 // What a launch with token tiles of `bm` takes, in us: rounds of workgroups (one per compute unit), each 6 us and 1.2 (64
@@ -727,70 +704,16 @@ double launch_us(const Problem &p, int bm)
 // the 96-token tiles (or the tile kernels) are faster (2000 tokens, 4096 x 4096, 2 bit: 82 us, the tile kernel 75).
 bool tall_applies(const Problem &p) { return (p.g == 32 || p.g == 64 || p.g % 128 == 0) && rounds_of(p, 128) == 1; }
 
-// Long contractions of few tiles: the tiles beyond whole rounds, where they are at most half a round, are computed by two to four workgroups each
-// (`parts`, at least two K steps apiece).  Estimates, us: a workgroup 6 (96 tokens: 7.5) and, with n of them at work, 0.95 + 0.3 n / 256 (1.06 + 0.36 n / 256) a
-// step; meeting in memory 4.2, 5.0, 7.2 (1.3 more) with two, three, four parts.  Graph replays, us, alone / shared: 333 tokens, 4 bit, 11008 -> 4096 52 / 46
-// (96 tokens a tile, two parts; 64 alone), 4096 -> 11008 54 / 49 (the last 88 tiles of 344); 256 tokens, 11008 -> 4096 50 / 38; 100 tokens, 4096 -> 4096 22.6 / 17.5
-// (three parts; two 18.5, four 18.2), 11008 -> 4096 50 / 27 (four; two 33); 150 tokens, 8192 -> 1024 37 / 20.  Eight steps gain nothing: 200 tokens, 2048 -> 2048
-// 13.8 / 15.0.
-struct Sharing { int whole, shared, parts; };          // parts == 1: no tile is
-constexpr size_t kArrivalBytes = 256 * 8;              // in front of the parts
-size_t sharing_bytes(const Sharing &s, int bm) { return s.parts > 1 ? kArrivalBytes + (size_t)s.shared * s.parts * bm * kMidBN * 4 : 0; }
-double sharing_us(const Problem &p, int bm, const Sharing &s)
+int token_tile(const Problem &p)
 {
-    static const double meet[kMidMaxParts + 1] = {0.0, 0.0, 4.2, 5.0, 7.2};
-    const int steps = (int)((p.I + kMidBK - 1) / kMidBK);
-    auto round = [&](int n, int k) { return bm == 64 ? 6.0 + (0.95 + 0.3 * n / 256.0) * k : 7.5 + (1.06 + 0.36 * n / 256.0) * k; };
-    double us = s.whole / 256 * round(256, steps);
-    if (s.shared != 0) us += round(s.shared * s.parts, (steps + s.parts - 1) / s.parts) + (s.parts > 1 ? meet[s.parts] + (bm == 96 ? 1.3 : 0.0) : 0.0);
-    return us;
-}
-Sharing sharing_of(const Problem &p, int bm, size_t room)
-{
-    const int64_t tiles = ((p.T + bm - 1) / bm) * ((p.O + kMidBN - 1) / kMidBN), steps = (p.I + kMidBK - 1) / kMidBK;
-    Sharing s{(int)std::min<int64_t>(tiles / 256 * 256, 1 << 24), (int)(tiles % 256), 1};
-    if (bm == kTallBM || tiles > 512) return s;
-    Sharing best = s;
-    double least = 0.97 * sharing_us(p, bm, s);
-    for (s.parts = 2; s.parts <= kMidMaxParts && s.parts * s.shared <= 256 && 2 * s.parts <= steps; ++s.parts) {
-        const double us = sharing_us(p, bm, s);
-        if (s.shared != 0 && sharing_bytes(s, bm) <= room && us < least) { least = us; best = s; }
-    }
-    return best;
-}
-constexpr size_t kAnyRoom = ~(size_t)0;
-bool shares(const Problem &p, int bm, size_t room) { return sharing_of(p, bm, room).parts > 1; }
-double low_us(const Problem &p, int bm, size_t room) { return shares(p, bm, room) ? sharing_us(p, bm, sharing_of(p, bm, room)) : launch_us(p, bm); }
-
-// with `room` for parts
-int token_tile(const Problem &p, size_t room)
-{
-    int low = launch_us(p, 96) < launch_us(p, 64) ? 96 : 64;
-    if (shares(p, 64, room) || shares(p, 96, room))
-        low = rounds_of(p, 96) <= 2 && sharing_us(p, 96, sharing_of(p, 96, room)) < sharing_us(p, 64, sharing_of(p, 64, room)) ? 96 : 64;
-    return tall_applies(p) && launch_us(p, 128) < low_us(p, low, room) ? 128 : low;
+    const int low = launch_us(p, 96) < launch_us(p, 64) ? 96 : 64;
+    return tall_applies(p) && launch_us(p, 128) < launch_us(p, low) ? 128 : low;
 }
 
-// A number for every launch that shares tiles, spread over 56 bits (a bijection of the count: no two launches of a process have the same).
-unsigned long long launch_number()
+template <int SRC> void launch_src(const Problem &p, const MidArgs &a, hipStream_t st)
 {
-    static std::atomic<unsigned long long> count{1};
-    return count.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull << 8;
-}
-
-template <int SRC> void launch_src(const Problem &p, MidArgs a, const SkScratch &sk, hipStream_t st)
-{
-    const size_t room = sk.partials != nullptr ? sk.bytes : 0;
-    const int bm = token_tile(p, room);
-    const Sharing s = sharing_of(p, bm, room);
-    const bool shared = s.parts > 1;
-    if (shared) {
-        a.whole = s.whole; a.shared = s.shared; a.parts = s.parts;
-        a.arrivals = (unsigned long long *)sk.partials; a.part_sums = sk.partials + kArrivalBytes / 4; a.launch = launch_number();
-    }
-#define EQAT_MID(B) do { if (bm == 128) launch_t<B, SRC, 128>(a, st); \
-        else if (bm == 96) { if (shared) launch_t<B, SRC, 96, true>(a, st); else launch_t<B, SRC, 96>(a, st); } \
-        else if (shared) launch_t<B, SRC, 64, true>(a, st); else launch_t<B, SRC, 64>(a, st); } while (0)
+    const int bm = token_tile(p);
+#define EQAT_MID(B) do { if (bm == 128) launch_t<B, SRC, 128>(a, st); else if (bm == 96) launch_t<B, SRC, 96>(a, st); else launch_t<B, SRC, 64>(a, st); } while (0)
     if (p.bits == 2) EQAT_MID(2); else if (p.bits == 3) EQAT_MID(3); else EQAT_MID(4);
 #undef EQAT_MID
 }
@@ -814,27 +737,16 @@ MidArgs mid_args(const Problem &p, const void *X, const void *codes, const void 
 // rebuilt twice only: 160 tokens, 28672 x 4096 76 as packed, 81 re-laid.
 FwdRoute mid_route(const Problem &p, bool from_packed)
 {
-    const int tokens = token_tile(p, kAnyRoom);
+    const int tokens = token_tile(p);
     return FwdRoute{from_packed && p.bits == 3 && p.T > 2 * tokens && rounds_of(p, tokens) > 1 ? FWD_RELAY_MID : FWD_MID, tokens, kMidBN};
 }
 
-static double shared_us(const Problem &p)
-{
-    const int bm = token_tile(p, kAnyRoom);
-    return bm == kTallBM ? launch_us(p, bm) : low_us(p, bm, kAnyRoom);
-}
+double mid_us(const Problem &p) { return launch_us(p, token_tile(p)); }
 
 // Step sizes and zero points from two arrays take twice the cache lines of pairs, 2 to 6 % of a long launch; the launch that pairs them takes 5 us.  Forward and backward, us,
 // with that launch / without: 515 tokens, 2 bit, 4096 -> 4096 79.8 / 77.9, 16384 -> 4096 238.2 / 237.6, 22016 -> 4096 336.3 / 337.2; two long rounds, 836 tokens, 19776 -> 7072
 // 714 / 727, 315 tokens, 12672 -> 14368 478 / 485.
-bool mid_pairs_itself(const Problem &p) { return shared_us(p) <= 120.0; }
-
-// as if no tile were shared
-double mid_us(const Problem &p)
-{
-    const double low = std::min(launch_us(p, 64), launch_us(p, 96));
-    return tall_applies(p) ? std::min(low, launch_us(p, 128)) : low;
-}
+bool mid_pairs_itself(const Problem &p) { return mid_us(p) <= 120.0; }
 
 // Against k_gemm_ksplit while there are at most 256 tiles of 128 x 128 (with one workgroup per tile 4.8 us and 0.8 to 1.1, with
 // the fill, a pair of 64-wide K tiles; 1024 inputs, 2000 tokens, 2048 rows: 12 us there, 14 here).  With more than 640 inputs one
@@ -853,15 +765,15 @@ bool mid_applies(const Problem &p)
     if (!p.act_bf16 || !group_by_magic(p) || p.T <= 32) return false;
     if (p.T <= 64) return !gemv_work_applies(p);
     const int64_t tiles = ((p.T + 127) / 128) * ((p.O + 127) / 128);
-    const int bm = token_tile(p, kAnyRoom);
+    const int bm = token_tile(p);
     if (tiles <= 256 && p.I > 640 && bm < 128 && rounds_of(p, bm) == 1) return true;
     const double other = tiles <= 256 ? 4.8 + (double)((p.I + 127) / 128) * (0.8 + 0.3 * (double)tiles / 256.0)
                                       : 4.0 + (double)((p.I + 63) / 64) * 0.9;
-    return tiles <= 512 && shared_us(p) < other;
+    return tiles <= 512 && mid_us(p) < other;
 }
 
 void launch_mid(const Problem &p, const void *X, const void *Wpacked, const float *s, const void *zpacked, const float *zfloat,
-                void *Y, const SkScratch &sk, hipStream_t st)
+                void *Y, hipStream_t st)
 {
     MidArgs a = mid_args(p, X, Wpacked, s, Y);
     a.zp = (const uint32_t *)zpacked; a.zf = zfloat;
@@ -870,25 +782,19 @@ void launch_mid(const Problem &p, const void *X, const void *Wpacked, const floa
     a.codes_bytes = (uint32_t)(p.O * p.I * p.bits / 8);
     a.s_bytes = (uint32_t)(p.O * p.G * 4);
     a.z_bytes = zfloat != nullptr ? a.s_bytes : (uint32_t)(p.O * a.z_row_words * 4);
-    if (zfloat != nullptr) launch_src<kFloatZ>(p, a, sk, st); else launch_src<kPackedZ>(p, a, sk, st);
+    if (zfloat != nullptr) launch_src<kFloatZ>(p, a, st); else launch_src<kPackedZ>(p, a, st);
 }
 
-size_t mid_parts_bytes(const Problem &p, size_t room)
-{
-    const int bm = token_tile(p, room);
-    return sharing_bytes(sharing_of(p, bm, room), bm);
-}
-
-void launch_mid_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, const SkScratch &sk, hipStream_t st)
+void launch_mid_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, hipStream_t st)
 {
     MidArgs a = mid_args(p, X, codes, sz, Y);
     a.code_row_bytes = (uint32_t)(work_code_bytes(p) / p.O);
     a.codes_bytes = (uint32_t)work_code_bytes(p);
     a.s_bytes = (uint32_t)(p.O * p.G * 8);
-    launch_src<kWorking>(p, a, sk, st);
+    launch_src<kWorking>(p, a, st);
 }
 
-void launch_mid_prepared(const Problem &p, const void *X, const void *codes, const float *s, const float *z, void *pairs, void *Y, const SkScratch &sk, hipStream_t st)
+void launch_mid_prepared(const Problem &p, const void *X, const void *codes, const float *s, const float *z, void *pairs, void *Y, hipStream_t st)
 {
     MidArgs a = mid_args(p, X, codes, s, Y);
     a.zf = z;
@@ -896,7 +802,7 @@ void launch_mid_prepared(const Problem &p, const void *X, const void *codes, con
     a.codes_bytes = (uint32_t)work_code_bytes(p);
     a.s_bytes = a.z_bytes = (uint32_t)(p.O * p.G * 4);
     a.pairs = (float *)pairs;
-    launch_src<kPrepared>(p, a, sk, st);
+    launch_src<kPrepared>(p, a, st);
 }
 
 }  // namespace eqat

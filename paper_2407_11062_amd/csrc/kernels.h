@@ -108,17 +108,15 @@ void launch_ksplit(const Problem &p, bool bt, const void *A, const void *codes, 
 // ---- gemm_mid.hip (forward for few output tiles) --------------------------------------------
 bool mid_applies(const Problem &p);
 FwdRoute mid_route(const Problem &p, bool from_packed);
-double mid_us(const Problem &p);                  // what it takes, as the rules of dispatch estimate it, with one workgroup to a tile
+double mid_us(const Problem &p);                  // what it takes, as the rules of dispatch estimate it
 // from the caller's dense stream (exactly one of zpacked / zfloat is not NULL), or from the working layout and (s, z) pairs:
 // bitwise the same results
 void launch_mid(const Problem &p, const void *X, const void *Wpacked, const float *s, const void *zpacked, const float *zfloat,
-                void *Y, const SkScratch &sk, hipStream_t st);
-void launch_mid_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, const SkScratch &sk, hipStream_t st);
+                void *Y, hipStream_t st);
+void launch_mid_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, hipStream_t st);
 // the same from the working layout, step sizes and zero points (O * G floats each); leaves them as pairs for a backward (`pairs` NULL: does not).  Short launches gain by it
 bool mid_pairs_itself(const Problem &p);
-void launch_mid_prepared(const Problem &p, const void *X, const void *codes, const float *s, const float *z, void *pairs, void *Y, const SkScratch &sk, hipStream_t st);
-// Bytes of sk.partials (of `room` that there are) that the launch of a problem which comes here writes; in less its workgroups share no tiles.
-size_t mid_parts_bytes(const Problem &p, size_t room);
+void launch_mid_prepared(const Problem &p, const void *X, const void *codes, const float *s, const float *z, void *pairs, void *Y, hipStream_t st);
 
 // ---- gemm_mid_dx.hip (dX for few output tiles, on codes in the working layout) -------------------------
 double mid_dx_us(const Problem &p, int cus, int *tokens);      // what it takes, as the rule of dispatch estimates it, and with which token tiles; 1e30: too many tiles
