@@ -158,6 +158,7 @@ __device__ __forceinline__ void adam_one(float &p, float g, float &m, float &v, 
 }
 
 // Workgroup `block` of a parameter tensor: 4 elements per lane and access, neighbouring lanes neighbouring 16 bytes of each fp32 array.
+// The last workgroup keeps to that: element by element, eight trips of it, small tensors took up to 1.1 us more (4352 -> 120, 2 bit, 6.2 -> 4.8 us; 1152 -> 104, 4 bit, 4.3 -> 3.4).
 constexpr int kAdamUnroll = 2;
 template <typename T, bool ONCE>
 __device__ __forceinline__ void adam_block(const AdamSeg &sg, const AdamArgs &a, int64_t first)
@@ -179,10 +180,23 @@ __device__ __forceinline__ void adam_block(const AdamSeg &sg, const AdamArgs &a,
             store4<ONCE>(P + e0, p[u]); store4<ONCE>(sg.m + e0, m[u]); store4<ONCE>(sg.v + e0, v[u]);
         }
     } else {
-        for (int64_t e = first + threadIdx.x; e < sg.n; e += kThreads) {
-            float p = to_float(P[e]), m = sg.m[e], v = sg.v[e];
-            adam_one(p, to_float(G[e]), m, v, sg, a);
-            store1(P + e, p); sg.m[e] = m; sg.v[e] = v;
+        // the last workgroup of a tensor: whole accesses, then what is left of four elements
+#pragma unroll
+        for (int u = 0; u < kAdamUnroll; ++u) {
+            const int64_t e0 = first + 4 * (u * kThreads + (int)threadIdx.x);
+            if (e0 + 4 <= sg.n) {
+                float p[4], g[4], m[4], v[4];
+                load4<ONCE>(P + e0, p); load4<ONCE>(G + e0, g); load4<ONCE>(sg.m + e0, m); load4<ONCE>(sg.v + e0, v);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) adam_one(p[k], g[k], m[k], v[k], sg, a);
+                store4<ONCE>(P + e0, p); store4<ONCE>(sg.m + e0, m); store4<ONCE>(sg.v + e0, v);
+            } else {
+                for (int64_t e = e0; e < sg.n; ++e) {
+                    float p = to_float(P[e]), m = sg.m[e], v = sg.v[e];
+                    adam_one(p, to_float(G[e]), m, v, sg, a);
+                    store1(P + e, p); sg.m[e] = m; sg.v[e] = v;
+                }
+            }
         }
     }
 }

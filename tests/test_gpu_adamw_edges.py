@@ -1,4 +1,4 @@
-"""AdamW at the edges of its workgroups: 2048 elements each, the last one element by element."""
+"""AdamW at the edges of its workgroups, 2048 elements each, four to an access."""
 import numpy as np
 import pytest
 import torch
@@ -27,3 +27,18 @@ def test_adamw_where_workgroups_end(O, I, wdt):
     eq.eqat_block_ap_update(eq.AdamW(1e-3, 1e-4, 0.9, 0.999, 1e-8, 0.1, 0.0, 3), 2, g, W=Wd, dW=dW.cuda(), mW=md, vW=vd)
     for got, want, tol in ((Wd, ref[0], 1e-5 if wdt == torch.float32 else 2 ** -8), (md, ref[1], 1e-5), (vd, ref[2], 1e-5)):
         assert np.abs(npf(got) - want).max() <= tol * np.abs(want).max()
+
+
+# one group to a row: as many step sizes as rows.  Less than four; the last four cut; a workgroup less, exactly and more than one; the last access of a workgroup alone
+@pytest.mark.parametrize("O", [1, 3, 5, 1023, 1024, 1025, 1030, 2047, 2048, 2051, 3073])
+def test_step_sizes_and_zero_points_where_workgroups_end(O):
+    t = {k: synth.normal((O, 1), std, synth.seed_of("adam groups", O, k)) for k, std in (("ds", 1e-2), ("ms", 1e-3), ("dz", 1e-2), ("mz", 1e-3))}
+    p = {"s": synth.uniform((O, 1), 0.01, 0.05, synth.seed_of("adam groups", O, "s")), "z": synth.uniform((O, 1), 0.0, 3.0, synth.seed_of("adam groups", O, "z"))}
+    f = lambda x: float(np.float32(x))
+    d = {k: v.cuda() for k, v in {**t, **p, "vs": t["ms"].square() + 1e-8, "vz": t["mz"].square() + 1e-8}.items()}
+    eq.eqat_block_ap_update(eq.AdamW(1e-3, 1e-4, 0.9, 0.999, 1e-8, 0.1, 0.0, 3), 2, -1, shape=(O, 32), **d)
+    for k in "sz":
+        m = t["m" + k]
+        ref = oracle.adamw(npf(p[k]), npf(t["d" + k]), npf(m), npf(m.square() + 1e-8), f(1e-4), f(0.9), f(0.999), f(1e-8), f(0.0), 3, f(1e-10) if k == "s" else -np.inf)
+        for got, want in zip((d[k], d["m" + k], d["v" + k]), ref):
+            assert np.abs(npf(got) - want).max() <= 1e-5 * np.abs(want).max()
