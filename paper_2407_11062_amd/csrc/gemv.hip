@@ -360,17 +360,29 @@ template <int BITS, int SRC, int NG> struct WideRun {
 };
 // Where a wave fetches them so, and the next run's under the arithmetic of this one's last piece: up to 8 tokens.  The lanes
 // that use them read 8 to 16 bytes of 16 rows x 4 places per instruction otherwise, every line several times: with many waves in flight it has left the
-// first cache in between (such loads marked non-temporal cost 10-25 %).  What decides beside that is how many waves the LDS leaves room for: a patch of two
-// segments a lane group, 8 KB a wave in all.  us, by the lanes / so: 8 tokens, 3 bit, 5120 / 13824 block 98 / 86 (with a patch of four segments 102, of one 92),
-// 2 bit, 28672 x 8192 29.4 / 26.6, 4 bit, 4096 x 11008 12.0 / 11.7.  More tokens leave no such room: 16 tokens, 2 bit, 4096 / 11008 50 / 55, 13 tokens, 3 bit, 3200 /
+// first cache in between (such loads marked non-temporal cost 10-25 %).  What decides beside that, with many row blocks, is how many waves the LDS leaves room for: a patch
+// of two segments a lane group, 8 KB a wave in all.  us, by the lanes / so: 8 tokens, 3 bit, 5120 / 13824 block 98 / 86 (with a patch of four segments 102, of one 92),
+// 2 bit, 28672 x 8192 29.4 / 26.6.  More tokens leave no such room: 16 tokens, 2 bit, 4096 / 11008 50 / 55, 13 tokens, 3 bit, 3200 /
 // 10880 54 / 60 (though 5120 / 13824 118 / 111), 24 tokens, 3 bit, g = 32 88 / 90.
 template <int SRC, int TR> constexpr bool kWideDirect = SRC != kWorking && TR == 8;
 template <int BITS, int SRC, int NG, int TR, int RB, bool DIRECT>
 constexpr int kWideWaveBytes = TR * kWideRowBytes<TR, DIRECT> + (DIRECT ? RB * WideRun<BITS, SRC, NG>::BYTES : 0);
-// 4-bit codes, whose 16 bytes a lane and segment are as wide as the pieces, gain by it only in long rows of large matrices, 8192 inputs and more than
-// 2^26 weights.  5 to 8 tokens, us, by the lanes (the whole run's tokens in the patch) / so: 28672 x 8192, the longer side the inputs 42.6 / 36.8, the rows 41.1 / 39.1;
-// 13824 -> 5120 17.8 / 16.4; 11008 -> 4096 9.0 / 9.8, 14336 -> 4096 10.7 / 11.7, 8192 -> 8192, one group per row 12.1 / 13.0, 5120 -> 13824 13.8 / 14.5.
-static bool wide_pieces_gain(int I, int O) { return I >= 8192 && (int64_t)I * O > (int64_t)1 << 26; }
+// Where the pieces are the faster way.  A wave with little to fetch ahead waits the longer for its first run: 1024 inputs, 0.2 to 0.5 us of 3 to 4.  8 tokens, us, by the
+// lanes (the whole run's tokens in the patch, 2-bit codes a run ahead in registers) / so, over 1024 to 28672 inputs and 256 to 28672 rows:
+// - 2 bit, and 3 bit with packed zero points: from 2048 inputs on (four runs).  2 bit, g = 128: 1024 -> 1024 3.02 / 3.23, 2048 -> 1024 3.53 / 3.42, 4096 -> 4096 4.90 / 4.60, 4096 -> 11008
+//   10.1 / 8.5; 3 bit 2048 -> 1024 4.17 / 3.76, 8192 -> 4096 9.1 / 7.7, 28672 -> 1024 21.0 / 16.9.  (Rows that end just behind a run in few rows: 2816 -> 352 3.79 / 3.91.)
+// - groups of 32, whose four step sizes and zero points a lane reads one by one (2 bit with float z, two loads of 16 bytes by the lanes, as above): from 4096 inputs and 8192 rows on.
+//   2 bit: 1024 -> 256 3.01 / 3.46, 5120 -> 256 5.40 / 5.80, 4096 -> 11008 11.1 / 10.1; 3 bit 3072 -> 11008 11.6 / 11.6, 11008 -> 1024 9.2 / 9.8, 8192 -> 28672 46.6 / 43.0.
+// - 3 bit, float z: from 4096 inputs and 8192 rows on, or 8192 inputs.  1024 -> 4096 3.75 / 3.82, 2048 -> 4096 4.16 / 4.29, 3072 -> 11008 9.8 / 9.9, 4096 -> 11008 11.3 / 10.9, 8192 -> 4096 9.0 / 8.0.
+// - 4 bit, 16 bytes a lane and segment, as wide as the pieces: from 8192 inputs and more than 2^26 weights on.  28672 x 8192, the longer side the inputs 42.6 / 36.8, the rows
+//   41.1 / 39.1; 13824 -> 5120 17.8 / 16.4; 11008 -> 4096 9.0 / 9.8, 8192 -> 8192, one group per row 12.1 / 13.0, 5120 -> 13824 13.8 / 14.5.
+static bool wide_pieces_gain(int bits, int groups, bool floatz, int I, int O)
+{
+    if (bits == 4) return I >= 8192 && (int64_t)I * O > (int64_t)1 << 26;
+    const bool few_words = groups < 4;
+    if (bits == 2 ? few_words || floatz : few_words && !floatz) return I >= 2048;
+    return (I >= 4096 && O >= 8192) || (few_words && I >= 8192);
+}
 
 // KEEP: masked 4-bit words stay words, see wide_keeps_words below (then two codes are converted at a time, but for groups of 32 in the largest form, which has no
 // registers for it: 24 tokens, 7168 x 12288 45 us, 48 in pairs)
@@ -384,7 +396,7 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
     const int n_waves = (int)(blockDim.x >> 6);
     const int r = lane & 15, kq = lane >> 4;
     const int n_segs = a.I >> 5, n_runs = (n_segs + 4 * RS - 1) / (4 * RS);
-    const int o0 = blockIdx.x * (RB * kGemvRows);                            // first row of block 0
+    const int o0 = blockIdx.x * (RB * kGemvRows), my0 = o0 + r;              // first row of block 0, this lane's
     unsigned char *const patch = smem_raw + wave * kWideWaveBytes<BITS, SRC, NG, TR, RB, DIRECT>;
     unsigned char *const stage = patch + TR * ROWB;
 
@@ -464,7 +476,7 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
         const uint32_t j0 = group_of(seg0);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            const int o = o0 + rb * kGemvRows + r;
+            const int o = my0 + rb * kGemvRows;
             const bool ok = o < a.O && seg0 < n_segs;
             const uint32_t base = (uint32_t)o * a.w_row_bytes + (uint32_t)seg0 * (4u * WPS);
 #pragma unroll
@@ -525,11 +537,15 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
     };
 
     constexpr int kCodes = !KEEP ? kFields : NG == 4 && TR >= 32 && RB == 2 ? kWords : kTwoCodes;
+    // By the lanes a run ahead where that costs no waves: 2-bit codes and few tokens (13824 x 5120, 8 tokens 17 -> 12 us; 4 bit or 16 tokens 5-15 % slower).
+    constexpr bool AHEAD = !DIRECT && TR == 8 && BITS == 2;
     Run run;
+    [[maybe_unused]] Run next;
     // Past the last run the tokens' loads are all out of range.  Without them, but with a branch: 24 tokens, 4 bit, g = 32, 4096 / 11008 block 114 -> 95 us, 16 tokens,
     // 2 bit 51 -> 48, 60 tokens, 2 bit, 8192 x 8192 27.3 -> 25.2; where the order of the instructions suffers more from the branch they are issued (24 tokens, 3 bit,
     // g = 32 88 / 90 without, 4 bit, g = 64 93 / 94.5; 10 tokens, 4 bit, 1792 / 5760 34.1 / 34.9).
-    constexpr bool kLastRunAsks = !(DIRECT || BITS == 2 || (TR == 16 && BITS == 3) || (BITS == 4 && NG == 4 && TR > 8));
+    constexpr bool kLastRunAsks = TR == 8 ? !DIRECT : !(BITS == 2 || (TR == 16 && BITS == 3) || (BITS == 4 && NG == 4));
+    if constexpr (AHEAD) fetch_run(wave, next);
     if (wave < n_runs) {
         if constexpr (DIRECT) issue_run(wave);
         fetch_tokens(wave, 0);
@@ -537,7 +553,8 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
     for (int sc = wave; sc < n_runs; sc += n_waves) {
         const int seg0 = (sc * 4 + kq) * RS;
         const uint32_t j0 = group_of(seg0);
-        if constexpr (!DIRECT) fetch_run(sc, run);
+        if constexpr (AHEAD) { run = next; fetch_run(sc + n_waves, next); }
+        else if constexpr (!DIRECT) fetch_run(sc, run);
         WhatTable<BITS> tab[RB];
 #pragma unroll
         for (int sub = 0; sub < RS / SUB; ++sub) {
@@ -722,8 +739,8 @@ static void launch_wide_t(const GemvArgs &a, hipStream_t st)
     if constexpr (KEEP && BITS == 4 && SRC != kWorking && NG == 2 && TR == 32) {
         if (!wide_keeps_words(a.I, a.O, RB * kGemvRows)) return launch_wide_t<BITS, SRC, NG, TR, RB, false>(a, st);
     }
-    if constexpr (DIRECT && BITS == 4) {
-        if (!wide_pieces_gain(a.I, a.O)) return launch_wide_t<BITS, SRC, NG, TR, RB, KEEP, false>(a, st);
+    if constexpr (DIRECT) {
+        if (!wide_pieces_gain(BITS, NG, SRC == kFloatZ, a.I, a.O)) return launch_wide_t<BITS, SRC, NG, TR, RB, KEEP, false>(a, st);
     }
     auto kern = k_gemv_wide<BITS, SRC, NG, TR, RB, KEEP, DIRECT>;
     const int n_runs = wide_runs(a.I), trips = (n_runs + kGemvMaxWaves - 1) / kGemvMaxWaves;

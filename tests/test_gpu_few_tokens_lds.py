@@ -1,4 +1,4 @@
-"""k_gemv_wide where a wave fetches its weights as row pieces straight into LDS (up to 8 tokens), and beside it
+"""k_gemv_wide where a wave fetches its weights as row pieces straight into LDS (up to 8 tokens, long rows), and beside it
 where the lanes fetch them.
 
 Rows of a run less, a piece more, several runs a wave; the last run cut anywhere; row blocks cut; every number of groups in a run; zero points packed and as
@@ -65,3 +65,12 @@ def test_large_matrices_of_4_bit_codes_as_their_parts(I, g):
     for a, b in ((0, 40), (O - 24, O)):
         assert torch.equal(Y[:, a:b], eq.eqat_qlinear_fwd(X, Wp[a:b].contiguous(), s[a:b].contiguous(), zp[a:b].contiguous(), bits, g))
     assert torch.equal(Y, eq.eqat_qlinear_fwd_z(X, Wp, s, z, bits, g))
+
+
+# where 2- and 3-bit codes go through LDS: four runs or more, groups of 32 and 3 bit with float zero points in large matrices only.  Rows of whole runs and a segment, two, a piece more;
+# row blocks cut; eight waves at most: 4608 is nine runs
+@pytest.mark.parametrize("T,bits", [(7, 2), (8, 2), (7, 3), (8, 3)])
+@pytest.mark.parametrize("I,O,g", [(2016, 24, 32), (2048, 16, 64), (2080, 24, 32), (2112, 40, 64), (2176, 8, -1), (2560, 56, 128), (4608, 72, 256), (8192, 24, 128), (8320, 40, 64),
+                                   (10752, 16, 384), (4096, 8184, 32), (4096, 8200, 32), (4128, 8216, 32), (5120, 8200, 128)])
+def test_both_ways_against_the_oracle(T, bits, I, O, g):
+    test_against_the_oracle(T, bits, I, O, g)
