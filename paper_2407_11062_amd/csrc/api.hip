@@ -560,7 +560,7 @@ static eqat_status fwd_prepared_any(const eqat_desc *d, const void *X, const voi
     // few tiles: one launch reads the step sizes and zero points as they are and leaves the pairs of a call that keeps them.  Graph replays of a
     // prepared layer's forward and backward, us, with the small launch / without: 1000 tokens, 4096 -> 4096 110.4 / 107.6; 300 tokens, 8192 -> 1024 47.5 / 43.9;
     // the seven linears of a 1024-wide block, 300 tokens 200 / 188; of the 4096-wide one, 515 tokens (five of them come here) 961 / 949.
-    const bool one_launch = p.act_bf16 && p.T > 0 && fwd_route(p, false, false).kernel == eqat::FWD_MID && eqat::mid_pairs_itself(p);
+    const bool one_launch = p.act_bf16 && p.T > 0 && fwd_route(p, false, false).kernel == eqat::FWD_MID && eqat::mid_pairs_itself(p, keep);
     hipStream_t st = (hipStream_t)stream;
     if (eqat_status e = prepared_operands(p, prepared, s, z, keep ? EQAT_OP_QP_BWD : EQAT_OP_QP_FWD, ws, ws_bytes, st, &q, !one_launch)) return e;
     if (!one_launch) return qlinear_fwd_run(p, X, s, q, Y, st);

@@ -743,10 +743,18 @@ FwdRoute mid_route(const Problem &p, bool from_packed)
 
 double mid_us(const Problem &p) { return launch_us(p, token_tile(p)); }
 
-// Step sizes and zero points from two arrays take twice the cache lines of pairs, 2 to 6 % of a long launch; the launch that pairs them takes 5 us.  Forward and backward, us,
-// with that launch / without: 515 tokens, 2 bit, 4096 -> 4096 79.8 / 77.9, 16384 -> 4096 238.2 / 237.6, 22016 -> 4096 336.3 / 337.2; two long rounds, 836 tokens, 19776 -> 7072
-// 714 / 727, 315 tokens, 12672 -> 14368 478 / 485.
-bool mid_pairs_itself(const Problem &p) { return mid_us(p) <= 120.0; }
+// The small launch that pairs step sizes and zero points takes 2 us beside the forward.  Without it the forward fetches twice the cache lines of them a K step, with groups of 64 and
+// more: 200 random sizes of 256 to 16000 inputs, 65 to 2000 tokens, us, with that launch / without:
+// - one group to a row: 288 -> 544 8.6 / 6.6, 7360 -> 1144 38.1 / 36.1, 14624 -> 1880 91.5 / 89.7; with the backward, 14880 -> 1408 193.9 / 191.9;
+// - groups of 32: 8160 -> 1856 54.8 / 46.7, 13856 -> 3640 97.8 / 95.2.  A forward that leaves many pairs for few workgroups to write loses, though: with the backward 4928 -> 7368
+//   107.5 / 104.3, 14016 -> 1272, 82 tokens 117.9 / 126.4;
+// - others gain up to 24 steps of 256 inputs, counted over the rounds of workgroups: 3200 -> 2360 19.4 / 17.7, 4992 -> 4096 37.5 / 36.1, 6592 -> 208 32.0 / 32.4, 9216 -> 1096 40.5 / 41.2, 14464 -> 544
+//   70.2 / 77.9; two rounds, 7424 -> 3672 with the backward 218.6 / 222.3.
+bool mid_pairs_itself(const Problem &p, bool keep)
+{
+    if (mid_us(p) > 120.0) return false;
+    return p.G == 1 || (p.g == 32 && !keep) || rounds_of(p, token_tile(p)) * ((p.I + kMidBK - 1) / kMidBK) <= 24;
+}
 
 // Against k_gemm_ksplit while there are at most 256 tiles of 128 x 128 (with one workgroup per tile 4.8 us and 0.8 to 1.1, with
 // the fill, a pair of 64-wide K tiles; 1024 inputs, 2000 tokens, 2048 rows: 12 us there, 14 here).  With more than 640 inputs one

@@ -114,8 +114,8 @@ double mid_us(const Problem &p);                  // what it takes, as the rules
 void launch_mid(const Problem &p, const void *X, const void *Wpacked, const float *s, const void *zpacked, const float *zfloat,
                 void *Y, hipStream_t st);
 void launch_mid_work(const Problem &p, const void *X, const void *codes, const void *sz, void *Y, hipStream_t st);
-// the same from the working layout, step sizes and zero points (O * G floats each); leaves them as pairs for a backward (`pairs` NULL: does not).  Short launches gain by it
-bool mid_pairs_itself(const Problem &p);
+// the same from the working layout, step sizes and zero points (O * G floats each); leaves them as pairs for a backward (`pairs` NULL: does not)
+bool mid_pairs_itself(const Problem &p, bool keep);       // where that is faster than a small launch that makes the pairs in front
 void launch_mid_prepared(const Problem &p, const void *X, const void *codes, const float *s, const float *z, void *pairs, void *Y, hipStream_t st);
 
 // ---- gemm_mid_dx.hip (dX for few output tiles, on codes in the working layout) -------------------------

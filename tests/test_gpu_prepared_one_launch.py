@@ -1,6 +1,8 @@
-"""Prepared layers where k_gemm_mid computes the forward: it reads step sizes and zero points as they are and leaves the pairs that a backward wants.
+"""Prepared layers where k_gemm_mid computes the forward: it reads step sizes and zero points as they are and leaves the pairs that a backward wants, or
+reads the pairs of a small launch in front of it (long contractions).
 
-Sizes: every token tile, shared tiles, more pairs than one round of the launch's lanes, fewer than its lanes, one group to a row, ragged rows and columns.
+Sizes: every token tile, more pairs than one round of the launch's lanes, fewer than its lanes, one group to a row, ragged rows and columns; both sides of
+the lines between the two.
 """
 import ctypes
 
@@ -18,8 +20,11 @@ TOL = 2e-2          # bf16 activations, as max|got - ref| / max|ref|
 # (tokens, in, out, bits, group, token tile)
 SIZES = [
     (65, 896, 392, 3, 32, 64),
-    (66, 28672, 128, 2, 32, 64),              # shared tiles; 28672 quads of pairs, 4096 lanes
-    (300, 4096, 2048, 4, 64, 64),             # shared
+    (66, 28672, 128, 2, 32, 64),              # groups of 32: the pairs by themselves where a backward follows, else not
+    (66, 6144, 1024, 2, 32, 64),              # 49152 quads of pairs, 8192 lanes
+    (70, 6400, 264, 4, 128, 64),              # a step more than the forward without the small launch takes
+    (400, 8192, 520, 3, -1, 64),              # one group to a row, at any length
+    (300, 4096, 2048, 4, 64, 64),
     (515, 4096, 4096, 3, -1, 96),             # one pair to a row
     (1000, 4096, 4096, 2, 128, 128),
     (700, 1056, 1016, 3, 32, 64),
@@ -52,7 +57,7 @@ def test_forward_and_what_it_leaves(T, I, O, bits, g, bm, trained):
     alone = eq.eqat_qlinear_bwd_prepared(X, prepared, sd, dY, I, bits, g, z=zt, want=("dX", "ds", "dz"))
     assert all(torch.equal(kept[k], alone[k]) for k in alone)
     packed = eq.eqat_qlinear_fwd_z(X, Wp, sd, zt, bits, g) if trained else eq.eqat_qlinear_fwd(X, Wp, sd, zp, bits, g)
-    assert torch.equal(Y, packed)
+    assert torch.equal(Y, packed) and torch.equal(Y, eq.eqat_qlinear_fwd_prepared(X, prepared, sd, O, bits, g, z=zt))
     if not trained:
         ref = oracle.qlinear_fwd(npf(X), Wp.cpu().numpy(), s, zp.cpu().numpy(), bits, g)
         assert np.abs(npf(Y) - ref).max() <= TOL * np.abs(ref).max()
