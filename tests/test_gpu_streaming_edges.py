@@ -1,7 +1,7 @@
 """The streaming passes at the edges of what a lane, a wave and a workgroup take.
 
 min/max: a piece of 16 bytes per lane (8 bf16, 4 fp32 weights), 4 or 8 runs of 64 pieces a wave, groups of 4 to 128 pieces; codes:
-8 weights a lane, 8192 a workgroup.
+8 weights a lane, 8192 a workgroup; loss and quantize pass: the sizes from which accesses pass the caches by.
 """
 import numpy as np
 import pytest
@@ -45,3 +45,48 @@ def test_codes_of_quotients_beyond_every_code(zbar):
     Wp, zp = eq.eqat_pack(torch.from_numpy(w[None]).cuda(), torch.from_numpy(s).cuda(), torch.from_numpy(z).cuda(), 2, -1)
     codes = eq.eqat_unpack(Wp, zp, len(w), 2, -1)[0].cpu().numpy()[0]
     assert np.array_equal(codes, np.clip(np.rint(w) + zbar, 0, 3).astype(np.int32))
+
+
+# bf16 loss: Y and Yref of 48 MB in all are where loads begin to pass the caches by (fp32 never does)
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("more", [-5, 0, 3, 8])
+def test_loss_on_both_sides_of_the_size_that_passes_the_caches_by(more, dt):
+    n = (48 << 20) // 4 + more
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    Y = torch.randn(n, generator=gen, device="cuda").to(dt)
+    R = (Y.float() + 0.3 * torch.randn(n, generator=gen, device="cuda")).to(dt)
+    loss, dY = eq.eqat_recon_loss(Y, R)
+    assert torch.equal(dY, ((Y.float() - R.float()) * torch.tensor(2.0 / n, dtype=torch.float32, device="cuda")).to(dt))
+    want = float((Y.double() - R.double()).square().mean())
+    assert abs(loss.item() - want) <= 1e-5 * want
+
+
+# 256 MB of weights are where the quantize pass begins to load them past the caches
+@pytest.mark.parametrize("bits,g", [(2, 64), (3, 128), (4, 32), (2, -1)])
+@pytest.mark.parametrize("wdt", [torch.float32, torch.bfloat16])
+def test_quantize_on_both_sides_of_the_size_that_passes_the_caches_by(wdt, bits, g):
+    I = 8192 + max(g, 32)
+    each = 4 if wdt == torch.float32 else 2
+    below = (256 << 20) // (I * each) // 8 * 8
+    above = below + 8
+    assert below * I * each <= 256 << 20 < above * I * each
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    W = (torch.randn((above, I), generator=gen, device="cuda") * 0.02).to(wdt)
+    s, z = eq.eqat_init_minmax(W, bits, g)
+    s = s * 0.8                                      # some weights are clamped
+    z = (z + 0.3).contiguous()
+
+    def state(rows):
+        Wr, sr, zr = W[rows].contiguous(), s[rows].contiguous(), z[rows].contiguous()
+        d = eq.make_desc(8, I, Wr.shape[0], bits, g, eq.BF16, eq._dt(W))
+        ws = eq.workspace(d, eq.OP_FQ_BWD, W.device)
+        eq.eqat_fq_quantize_batched(eq.Batch([d], W=[Wr], s=[sr], z=[zr], ws=[ws]))
+        return eq.eqat_unpack_state(eq.STATE_FQ_KEPT, ws, Wr.shape[0], I, bits, g, want_clamped=True)
+    whole = state(slice(0, above))
+    for rows in (slice(0, below), slice(above - 24, above)):
+        for a, b in zip(whole, state(rows)):
+            assert torch.equal(a[rows], b)
+    rows = slice(above - 24, above)
+    codes, side = oracle.quantize(npf(W[rows]), npf(s[rows]), npf(z[rows]), bits, g)
+    assert np.array_equal(whole[0][rows].cpu().numpy(), codes) and np.array_equal(whole[1][rows].cpu().numpy(), (side != 0).astype(np.uint8))
+    assert 0.001 < whole[1].float().mean().item() < 0.5
