@@ -215,13 +215,16 @@ __device__ __forceinline__ void load_to_lds16_at(const RawRsrc &r, uint32_t lds_
                  :: "s"(lds_addr_uniform), "v"(voffset), "s"(r.w) : "memory", "m0");
 }
 
-// the same past the caches (non-temporal), for what is read once.  A buffer load may use scalar registers that a vector instruction wrote five wait states later at the
-// earliest, and the compiler, which keeps that distance for its own loads, sees none in assembly.  In dW of cut tiles, 2 bit, it brings this descriptor back from the
-// lanes of a vector register right in front of the first load: the wait is here.  (None of the loads above and below has such a neighbour.)
-__device__ __forceinline__ void load_to_lds16_once_at(const RawRsrc &r, uint32_t lds_addr_uniform, uint32_t voffset)
+// The same for the W rows of dW, past the caches (non-temporal) where there are more than `once_from` bytes of them.  A branch of the compiler's own around these loads
+// costs dW its last registers (a dozen instantiations with some in scratch), so it stands in the assembly.  A buffer load may use scalar registers that a vector instruction
+// wrote five wait states later at the earliest, and the compiler, which keeps that distance for its own loads, sees none in assembly.  In dW of cut tiles, 2 bit, it brings
+// this descriptor back from the lanes of a vector register right in front of the first load: the wait is here.  (None of the loads above and below has such a neighbour.)
+__device__ __forceinline__ void load_row_to_lds16_at(const RawRsrc &r, uint32_t lds_addr_uniform, uint32_t voffset, uint32_t once_from)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
-                 :: "s"(lds_addr_uniform), "v"(voffset), "s"(r.w) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_cmp_gt_u32 %3, %4\n\ts_nop 1\n\ts_cbranch_scc1 .Lonce%=\n\t"
+                 "buffer_load_dwordx4 %1, %2, 0 offen lds\n\ts_branch .Ldone%=\n.Lonce%=:\n\t"
+                 "buffer_load_dwordx4 %1, %2, 0 offen nt lds\n.Ldone%=:"
+                 :: "s"(lds_addr_uniform), "v"(voffset), "s"(r.w), "s"(r.w[2]), "i"(once_from) : "memory", "m0", "scc");
 }
 
 // the same with 4 bytes per lane: lane j's word lands at lds_wave_base + 4 j

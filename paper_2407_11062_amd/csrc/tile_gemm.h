@@ -613,9 +613,11 @@ struct GemmDwArgs {
 // store instruction would touch 32 different rows, 8 or 16 bytes of each.  Instead a wave moves the W rows it needs as
 // whole 128- or 256-byte row pieces (16 bytes per lane, straight into LDS), picks its quads out of LDS, puts the dW
 // quads back in their place and writes the rows out the way they came in.
-// Both streams go past the caches (non-temporal): neither is touched again before the update, and in the L2s they drove out the X and dY panels that
-// the tiles still to come share.  Block-AP steps, us: 1000 tokens, fp32 W, 4096 / 11008 1684 -> 1660; 4096 tokens, 5120 / 13824 6633 -> 6557; 8192 tokens,
-// 4096 / 11008 7682 -> 7630.  (Y and dX, which the next call reads, lose 0.2-0.7 % that way.)
+// dW goes past the caches (non-temporal): it is not touched again before the update, and in the L2s it drives out the X and dY panels that the tiles still to come
+// share.  So does W where there is more of it than they keep from the pass that read it last.  Backward, us, neither past them / dW / both: 300 tokens, 768 -> 4568, bf16 (7 MB of W)
+// 29.2 / 28.6 / 28.6; 276 tokens, 1536 -> 1208, fp32 (7 MB) 25.9 / 25.3 / 27.8; 409 tokens, 5120 -> 752, fp32 (15 MB) 35.0 / 30.4 / 35.0; 78 tokens, 6240 -> 1648, bf16 (21 MB) 30.1 / 25.8 / 27.0;
+// 514 tokens, 6016 -> 1248, fp32 (30 MB) 49.9 / 47.0 / 44.3; 748 tokens, 4224 -> 3952, fp32 (67 MB) 86.0 / 85.2 / 82.6.  (Y and dX, which the next call reads, lose 0.2-0.7 % that way.)
+constexpr uint32_t kRowsOnceBytes = 24u << 20;
 // A unit = 32 rows x UB blocks of 32 in-features, RBY bytes per row; a wave owns two unit-sized LDS slots.  The 16-byte
 // chunks of a row are XOR-swizzled with (row >> 1) so that the 32 lanes of a quad read (32 rows, same chunk) spread
 // over all banks (two rows share a chunk position: the 2-way conflict of an 8-byte access by 32 lanes is the minimum).
@@ -990,7 +992,7 @@ __device__ __forceinline__ void gemm_dw_body(const GemmDwArgs &a, const int bid,
     auto slot_bytes = [&](int slot) { return (uint32_t)((wave * 2 + slot) * SG::UNIT_BYTES); };
     auto issue_unit = [&](int slot, const uint32_t (&off)[SG::NIU]) {
 #pragma unroll
-        for (int k = 0; k < SG::NIU; ++k) load_to_lds16_once_at(rWraw, stage_lds + slot_bytes(slot) + (uint32_t)(k * 1024), off[k]);
+        for (int k = 0; k < SG::NIU; ++k) load_row_to_lds16_at(rWraw, stage_lds + slot_bytes(slot) + (uint32_t)(k * 1024), off[k], kRowsOnceBytes);
     };
 
     constexpr int NU = BLOCK_AP ? NI * SG::UPJ : 0;

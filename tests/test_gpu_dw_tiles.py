@@ -19,6 +19,11 @@ CASES = [  # tokens, in, out, group, tile
     (576, 2816, 3000, 256, 128),       # 132
     (577, 2816, 3000, 256, 256),
     (2049, 2784, 3064, 96, 128),       # 132, long; 16 small ones are split
+    # W rows past the caches from more than 24 MB on: bf16, then fp32
+    (90, 3072, 4096, 64, 256),
+    (90, 3072, 4104, 64, 256),
+    (90, 2048, 3072, 64, 128),
+    (90, 2048, 3080, 64, 128),
 ]
 
 
