@@ -35,13 +35,12 @@ template <> struct Chunk8<float> {
         a = *reinterpret_cast<const floatx4 *>(p);
         b = *reinterpret_cast<const floatx4 *>(p + 4);
     }
-    // Neighbouring lanes read neighbouring 16 bytes, twice: lanes 2 i and 2 i + 1 the halves of chunk i and those of chunk 32 + i of the wave, of which
+    // Past the caches, neighbouring lanes neighbouring 16 bytes, twice: lanes 2 i and 2 i + 1 the halves of chunk i and those of chunk 32 + i of the wave, of which
     // the even lane then keeps the first and the odd one the second.
-    template <bool ONCE> __device__ __forceinline__ void load_halves(const float *p, const float *q)
+    __device__ __forceinline__ void load_halves(const float *p, const float *q)
     {
-        const floatx4 *const v = reinterpret_cast<const floatx4 *>(p), *const w = reinterpret_cast<const floatx4 *>(q);
-        a = ONCE ? __builtin_nontemporal_load(v) : *v;
-        b = ONCE ? __builtin_nontemporal_load(w) : *w;
+        a = __builtin_nontemporal_load(reinterpret_cast<const floatx4 *>(p));
+        b = __builtin_nontemporal_load(reinterpret_cast<const floatx4 *>(q));
     }
     __device__ __forceinline__ void exchange(bool odd)
     {
@@ -119,7 +118,8 @@ __device__ __forceinline__ uint32_t differ_bits(const float (&a)[8], const float
 // round, difference, maximum, clamp, conversion, shift-add, and three for the clamp plane) the pass was bound by its arithmetic: seven matrices of a
 // 4096 / 11008 block, bf16, quantize 99 -> 94 us, and 84 with W loaded past the caches (see kQuantizeOnceBytes); pack 94 -> 86, where the end of W
 // comes from the memory-side cache and such loads lose 1-3 %.  fp32 weights gain by them only where neighbouring lanes read neighbouring 16 bytes
-// (load_halves; 810 MB, 4 bit: 187 -> 158 us, without that 192).
+// (load_halves; 810 MB, 4 bit: 187 -> 158 us, without that 192); through the caches the exchange behind that costs 0.2 to 0.7 us of a launch (quantize and forward, 238 tokens, 352 -> 7000
+// 14.1 / 14.6, 136 tokens, 4608 -> 1936 30.8 / 31.5; level from 100 MB on).
 // WORK = false: the dense stream of the C ABI (eqat_pack).  WORK = true: the library's working layout (WorkCodes).
 // Zero points at N bits: one thread per output word (tail bits of a row are zero).
 template <int BITS>
@@ -158,7 +158,7 @@ __device__ __forceinline__ void clear_words(uint32_t *__restrict__ w, uint32_t n
 // Up to kMaxBatch matrices in one launch (the linears of a decoder block are 34-90 MB each at 7B size: alone, each would
 // be a 10-25 us launch that spends a good part of its time filling and draining the chip).  Workgroups
 // [first[i], first[i + 1]) work on matrix i.
-struct QuantizeBatch { QuantizeArgs a[kMaxBatch]; uint32_t first[kMaxBatch + 1]; uint32_t once; };      // once: W is loaded past the caches
+struct QuantizeBatch { QuantizeArgs a[kMaxBatch]; uint32_t first[kMaxBatch + 1]; };
 __device__ __forceinline__ int batch_slot(const uint32_t (&first)[kMaxBatch + 1], uint32_t block)
 {
     int i = 0;
@@ -173,7 +173,8 @@ constexpr int kQuantUnroll = 4;     // chunks per thread: 64 B (bf16) / 128 B (f
 constexpr int kPackUnrollLarge = 8;
 constexpr size_t kPackLargeChunks = (size_t)1 << 24;     // 8-weight chunks: 134 M weights
 
-template <typename WT, int BITS, bool CLAMPBITS, bool WORK, int U = kQuantUnroll>
+// ONCE: W is loaded past the caches
+template <typename WT, int BITS, bool CLAMPBITS, bool WORK, bool ONCE = false, int U = kQuantUnroll>
 __global__ __launch_bounds__(256) void k_quantize(const QuantizeBatch batch)
 {
     // Packing walks its matrices from the last weight to the first: the pass that comes before it (min/max, an optimizer
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(256) void k_quantize(const QuantizeBatch batch)
     }
     const WT *__restrict__ W = reinterpret_cast<const WT *>(a.W);
     constexpr float qmax = (float)((1 << BITS) - 1);
-    constexpr bool SPREAD = WORK && sizeof(WT) == 4;
+    constexpr bool SPREAD = ONCE && sizeof(WT) == 4;
     const uint32_t first = block * (256u * U) + (threadIdx.x & ~63u), lane = threadIdx.x & 63u;
     // chunk index; n_chunks % 4 == 0 so quads stay whole
     const uint32_t c0 = first + (SPREAD ? (lane >> 1) + 32u * (lane & 1u) : lane);
@@ -200,25 +201,19 @@ __global__ __launch_bounds__(256) void k_quantize(const QuantizeBatch batch)
     Chunk8<WT> ch[U];
     uint32_t gi[U];
     float sv[U], zb[U];
-    auto fetch = [&](auto once_) {
-        constexpr bool ONCE = decltype(once_)::value != 0;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t c = c0 + u * 256u;
-            const uint32_t cc = c < a.n_chunks ? c : 0u;             // past the end: recompute chunk 0, store nothing
-            const uint32_t e = cc * 8u;
-            gi[u] = a.g_shift >= 0 ? (e >> a.g_shift) : (e / a.g);
-            if constexpr (SPREAD) {
-                const uint32_t p0 = (first + u * 256u) * 2u + lane, p1 = p0 + 64u, n = a.n_chunks * 2u;     // pieces of four weights
-                ch[u].template load_halves<ONCE>(W + (size_t)(p0 < n ? p0 : 0u) * 4, W + (size_t)(p1 < n ? p1 : 0u) * 4);
-            } else ch[u].template load<ONCE>(W + e);
-            sv[u] = a.s[gi[u]];
-            zb[u] = a.z[gi[u]];
-        }
-    };
-    if constexpr (WORK) {
-        if (batch.once) fetch(IC<1>{}); else fetch(IC<0>{});
-    } else fetch(IC<0>{});
+    for (int u = 0; u < U; ++u) {
+        const uint32_t c = c0 + u * 256u;
+        const uint32_t cc = c < a.n_chunks ? c : 0u;             // past the end: recompute chunk 0, store nothing
+        const uint32_t e = cc * 8u;
+        gi[u] = a.g_shift >= 0 ? (e >> a.g_shift) : (e / a.g);
+        if constexpr (SPREAD) {
+            const uint32_t p0 = (first + u * 256u) * 2u + lane, p1 = p0 + 64u, n = a.n_chunks * 2u;     // pieces of four weights
+            ch[u].load_halves(W + (size_t)(p0 < n ? p0 : 0u) * 4, W + (size_t)(p1 < n ? p1 : 0u) * 4);
+        } else ch[u].template load<ONCE>(W + e);
+        sv[u] = a.s[gi[u]];
+        zb[u] = a.z[gi[u]];
+    }
     if constexpr (SPREAD) {
 #pragma unroll
         for (int u = 0; u < U; ++u) ch[u].exchange((lane & 1u) != 0);
@@ -581,15 +576,17 @@ static void quantize_t(const QuantizeJob *jobs, int n, bool for_pack, hipStream_
     for (int i = n; i <= kMaxBatch; ++i) b.first[i] = first;
     size_t w_bytes = 0;
     for (int i = 0; i < n; ++i) w_bytes += (size_t)jobs[i].p.O * jobs[i].p.I * sizeof(WT);
-    b.once = w_bytes > kQuantizeOnceBytes;
+    const bool once = w_bytes > kQuantizeOnceBytes;
     const dim3 grid(first), block(256);
     // eqat_pack: dense stream, no clamp plane;
     // the quantize pass of the Block-AP calls: working layout, clamp plane for the backward
     if constexpr (sizeof(WT) == 2) {
-        if (large_pack) { k_quantize<WT, BITS, false, false, kPackUnrollLarge><<<grid, block, 0, st>>>(b); return; }
+        if (large_pack) { k_quantize<WT, BITS, false, false, false, kPackUnrollLarge><<<grid, block, 0, st>>>(b); return; }
     }
     if (for_pack) k_quantize<WT, BITS, false, false><<<grid, block, 0, st>>>(b);
+    else if (jobs[0].clampbits != nullptr && once) k_quantize<WT, BITS, true, true, true><<<grid, block, 0, st>>>(b);
     else if (jobs[0].clampbits != nullptr) k_quantize<WT, BITS, true, true><<<grid, block, 0, st>>>(b);
+    else if (once) k_quantize<WT, BITS, false, true, true><<<grid, block, 0, st>>>(b);
     else k_quantize<WT, BITS, false, true><<<grid, block, 0, st>>>(b);
 }
 
