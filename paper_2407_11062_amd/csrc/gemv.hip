@@ -541,9 +541,10 @@ __global__ __launch_bounds__(64 * kGemvMaxWaves) void k_gemv_wide(const GemvArgs
     constexpr bool AHEAD = !DIRECT && TR == 8 && BITS == 2;
     Run run;
     [[maybe_unused]] Run next;
-    // Past the last run the tokens' loads are all out of range.  Without them, but with a branch: 24 tokens, 4 bit, g = 32, 4096 / 11008 block 114 -> 95 us, 16 tokens,
-    // 2 bit 51 -> 48, 60 tokens, 2 bit, 8192 x 8192 27.3 -> 25.2; where the order of the instructions suffers more from the branch they are issued (24 tokens, 3 bit,
-    // g = 32 88 / 90 without, 4 bit, g = 64 93 / 94.5; 10 tokens, 4 bit, 1792 / 5760 34.1 / 34.9).
+    // Past the last run the tokens' loads are all out of range.  Leaving them out takes a branch, which the compiler moves no instruction across.  Without them: 24 tokens, 4 bit, g = 32,
+    // 4096 / 11008 block 114 -> 95 us, 16 tokens, 2 bit 51 -> 48, 60 tokens, 2 bit, 8192 x 8192 27.3 -> 25.2; over 90 random sizes each, 2 bit 9 to 16 and 33 to 64 tokens 1 to 22 % faster but for a few of 2 %, 17 to
+    // 32 tokens 1 to 4 % faster from 20 runs on and as much slower in short rows.  Elsewhere the branch costs as often as it gains (24 tokens, 3 bit, g = 32 88 / 90 us
+    // without the loads, 4 bit, g = 64 93 / 94.5; 10 tokens, 4 bit, 1792 / 5760 34.1 / 34.9) and the loads are issued.
     constexpr bool kLastRunAsks = TR == 8 ? !DIRECT : !(BITS == 2 || (TR == 16 && BITS == 3) || (BITS == 4 && NG == 4));
     if constexpr (AHEAD) fetch_run(wave, next);
     if (wave < n_runs) {
